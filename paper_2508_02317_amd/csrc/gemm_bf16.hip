@@ -3,13 +3,13 @@
 //
 // One kernel skeleton serves all nine matrix products of the layer (and the three of the router):
 //   * a BM x BN output tile per workgroup, a grid of WGM x WGN wavefronts over it, each owning a
-//     WM x WN sub-tile made of 32x32 MFMA tiles (v_mfma_f32_32x32x16_bf16, fp32 accumulators kept in
+//     WM x WN sub-tile made of 16x16 MFMA tiles (v_mfma_f32_16x16x32_bf16, fp32 accumulators kept in
 //     registers for the whole reduction); the default is 256 x 256 with 2 x 4 wavefronts of 128 x 64;
-//   * the reduction dimension is walked in BK-wide slabs through an S-stage LDS ring that is
-//     filled by direct global->LDS loads (no staging registers); S-1 slabs are in flight behind the
-//     one being multiplied, the MFMA operands are double-buffered in registers one reduction step
-//     ahead, and one barrier per slab separates writers from readers; a partial last slab reads
-//     zeros for the reduction indices it does not have;
+//   * the reduction dimension is walked in BK-wide slabs through two LDS rings (one per operand) that are
+//     filled by direct global->LDS loads (no staging registers); one to two slabs are in flight behind the
+//     one being multiplied, every MFMA operand is read from LDS most of a reduction step before its use,
+//     and one barrier per slab separates writers from readers; what does not exist (rows, columns, the end
+//     of a partial last slab) is out of the loads' range and reads as zero;
 //   * results leave through LDS as well, so that all global stores (and the loads of the
 //     saved pre-activations in the fused SwiGLU derivative) are 16 bytes per lane and
 //     contiguous along rows;
@@ -40,6 +40,7 @@ namespace moe {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kXcds = 8;
 
@@ -50,7 +51,8 @@ struct Tile {
   static constexpr int WGM = WGM_, WGN = WGN_;            // grid of wavefronts over the tile
   static constexpr int kWaves = WGM * WGN, kThreads = 64 * kWaves;
   static constexpr int WM = BM / WGM, WN = BN / WGN;      // sub-tile of one wavefront
-  static constexpr int MI = WM / 32, NI = WN / 32;        // MFMA tiles per wave
+  static constexpr int MI = WM / 32, NI = WN / 32;        // 32-row strips and 32-column stretches per wave
+  static constexpr int FM = WM / 16, FN = WN / 16;        // bf16 MFMA fragments per wave (16 x 16 outputs each)
   static constexpr int kABytes = BM * BK * 2, kBBytes = BN * BK * 2;
   // LDS ring: each operand has its own ring of slab buffers (SA for the row side, SB for the column side); slab kt
   // lives in buffer kt % SA and kt % SB.  One slab is being multiplied, the others are in flight.  With 64 KiB per
@@ -93,30 +95,38 @@ __device__ __forceinline__ int kc_off(int row, int piece) {
   constexpr int RPL = 256 / (BK * 2);            // rows per 256-byte line
   return row * (BK * 2) + ((piece ^ ((row / RPL) & (PPR - 1))) << 4);
 }
-// k-strided operand: [BK][ROWS]; the 64-byte chunks of a k-row are XORed with k & 3, so the four
-// k-rows a transposing read touches lie in different banks.
+// k-strided operand: [BK][ROWS]; the 32-byte chunks of a k-row (16 columns, what one group of 16 lanes of a transposing
+// read takes from it) are XORed with bits 0, 1 and 3 of k, so the eight k-rows that 32 lanes touch together -- four
+// consecutive ones from k = 8 g and four from 8 (g + 1) -- lie in different banks.
+__device__ __forceinline__ int ks_swizzle(int k) { return ((k & 3) << 1) | ((k >> 3) & 1); }
 template <int ROWS>
 __device__ __forceinline__ int ks_off(int k, int piece) {
-  return k * (ROWS * 2) + (((((piece >> 2) ^ (k & 3)) << 2) | (piece & 3)) << 4);
+  static_assert(ROWS >= 128, "the swizzle moves a piece by up to 14 pieces of its k-row");
+  return k * (ROWS * 2) + ((piece ^ (ks_swizzle(k) << 1)) << 4);
 }
 
 // ---- MFMA operand fragments ----------------------------------------------------------------------------
-// Fragment = 32 rows x 16 k: lane l holds row l%32, k = 8*(l/32) .. +7 of the 16-wide step kk.
-// frag_off: this lane's byte offset inside the operand tile, computed once per kernel for step 0; the main
-// loop derives the other steps with one XOR (or a constant) and adds compile-time stage offsets.
+// bf16 fragment = 16 rows x 32 k: lane l holds row l%16, k = 8*(l/16) .. +7 of the 32-wide step kk.
+// frag_off: this lane's byte offset inside the operand tile, computed once per kernel; the main loop derives the
+// other steps and fragments with compile-time offsets.
 template <bool KS, int ROWS, int BK>
 __device__ __forceinline__ int frag_off(int row_base, int kk, int lane) {
   if constexpr (!KS) {
-    return kc_off<BK>(row_base + (lane & 31), 2 * kk + (lane >> 5));
+    return kc_off<BK>(row_base + (lane & 15), 4 * kk + (lane >> 4));
   } else {
     // Transposing read: within each group of 16 lanes, lane i receives element i%4 of the 8-byte
     // rows addressed by lanes i/4, i/4+4, i/4+8, i/4+12.  Lane s therefore addresses k-row s/4 at
-    // columns 4*(s%4)..+3 of its group's 16 columns, and ends up with 4 consecutive k of column s.
+    // columns 4*(s%4)..+3 of the fragment's 16 columns, and ends up with 4 consecutive k of column s.
     const int s = lane & 15;
-    const int col = row_base + 16 * ((lane >> 4) & 1) + 4 * (s & 3);     // multiple of 4
-    const int k = kk * 16 + 8 * (lane >> 5) + (s >> 2);
+    const int col = row_base + 4 * (s & 3);                               // multiple of 4
+    const int k = kk * 32 + 8 * (lane >> 4) + (s >> 2);
     return ks_off<ROWS>(k, col >> 3) + (col & 4) * 2;                     // 8-byte half of the piece
   }
+}
+// the fragment of the 8-bit products: 32 rows, lane l holds row l%32, 16-byte piece 2*kk + l/32 (k-contiguous tiles only)
+template <int BK>
+__device__ __forceinline__ int frag_off_32(int row_base, int kk, int lane) {
+  return kc_off<BK>(row_base + (lane & 31), 2 * kk + (lane >> 5));
 }
 // One fragment: 16 bytes per lane at LDS address `addr` + IMM (a compile-time constant: buffer, reduction step or
 // fragment).  Both kinds of read are assembly statements on purpose.
@@ -136,7 +146,7 @@ __device__ __forceinline__ bf16x8 lds_read_frag(uint32_t addr) {
     asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "n"(IMM));
     return v;
   } else {
-    // k + 4 has the same swizzle (k & 3 unchanged): a constant 4 k-rows further
+    // k + 4 has the same swizzle (bits 0, 1 and 3 of k unchanged): a constant 4 k-rows further
     bf16x4 lo, hi;
     asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(lo) : "v"(addr), "n"(IMM));
     asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(hi) : "v"(addr), "n"(IMM + 4 * ROWS * 2));
@@ -145,25 +155,32 @@ __device__ __forceinline__ bf16x8 lds_read_frag(uint32_t addr) {
 }
 
 // ---- global -> LDS without passing through registers -----------------------------------------------
-// One wave instruction (global_load_lds_dwordx4) moves 64 x 16 bytes into 1 KiB of consecutive LDS;
+// One wave instruction (buffer_load_dwordx4 ... lds) moves 64 x 16 bytes into 1 KiB of consecutive LDS;
 // the swizzles above are applied on the global side: each lane fetches the piece that belongs in its
-// LDS slot.  Addresses are a wave-uniform base (advanced per slab with scalar arithmetic) plus a
-// 32-bit per-lane offset.  Rows that do not exist are redirected to the tile's first row: they only
-// feed output rows / columns that are never stored.  Reduction indices beyond K (last, partial
-// slab only) are redirected to a block of zeros, so they contribute nothing.
-template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false> struct Dma {
+// LDS slot.  Addresses are a wave-uniform base in a buffer descriptor (moved on per slab with scalar arithmetic) plus a
+// 32-bit per-lane offset.  The descriptor's range check replaces branches and selects: a load beyond it touches no
+// memory and writes zeros, so
+//   * rows (k-contiguous) or columns (k-strided) that do not exist carry an offset beyond every range,
+//   * reduction rows beyond K of a k-strided operand lie beyond the range of the last slab's descriptor, and
+//   * slabs beyond the end of the reduction get an empty descriptor,
+// and every wave enqueues the same number of loads per slab whatever is left: all waits are immediates and the slab
+// loop has a single path.  Only a partial last slab of a k-contiguous operand needs a select (issue_tail).
+constexpr uint32_t kRangeAll = 0xFFFF0000u;     // in-range offsets stay below 4 GiB - 64 KiB
+constexpr uint32_t kOffNone = 0xFFFFFFF0u;      // beyond every range
+template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false, bool TWO_SEG = false> struct Dma {
   static constexpr int CHUNKS = ROWS * BK * 2 / 1024;
   static constexpr int N = CHUNKS / WAVES;                   // chunks per wave
   static_assert(N >= 1 && CHUNKS % WAVES == 0, "tile too small for this many waves");
+  static_assert(WAVES % 2 == 0, "a wave's chunks must lie in one half of the tile");
   static constexpr int KPC = KS ? 1024 / (ROWS * 2) : 1;      // k-strided: reduction rows per chunk
   static constexpr int NR = N * KPC;                         // k-strided: reduction rows per wave and slab (consecutive)
-  const char* base[N];       // wave-uniform
-  uint32_t voff[N];          // per lane, bytes
-  uint32_t kpack[(N + 3) / 4];   // per lane: reduction index inside the slab of this lane's piece of chunk i, 8 bits each
-                                 // (only the partial last slab needs it: packed to keep registers for the main loop)
-  __device__ __forceinline__ void set_kidx(int i, int k) { kpack[i / 4] |= static_cast<uint32_t>(k) << (8 * (i % 4)); }
-  __device__ __forceinline__ int kidx(int i) const { return static_cast<int>((kpack[i / 4] >> (8 * (i % 4))) & 255u); }
+  const char* base;          // wave-uniform: slab 0
   long step;                 // bytes per slab (uniform)
+  uint32_t voff[N];          // per lane, bytes
+  int K, nslabs;             // reduction length (k-strided: limits the last slab) and slabs that exist
+  int seg_slabs;             // TWO_SEG: slabs seg_slabs.. come from a second matrix ...
+  long seg_delta;            // ... whose bytes lie this much further
+  __amdgpu_buffer_rsrc_t rsrc;   // the slab being enqueued
   // gathered k-strided operand: the memory rows of the wave's NR reduction rows of the next slab to be
   // issued, fetched with scalar loads one slab ahead (they do not touch the vector-memory counter
   // that orders the ring)
@@ -173,6 +190,7 @@ template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false> struct Dma 
   RowVec next_row;
   uint32_t ld2;              // bytes per memory row
   int lq;                    // per lane: which of the KPC rows of a chunk this lane loads
+  int k_first;               // k-strided: first reduction row of this wave inside a slab
   __device__ __forceinline__ void fetch_rows(int slab) {
     if constexpr (KS && GATHER) {
       RowList r = rows + slab * BK;
@@ -180,107 +198,114 @@ template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false> struct Dma 
       for (int j = 0; j < NR; ++j) next_row[j] = r[j];
     }
   }
-  __device__ __forceinline__ void init(const Operand& op, int wave, int lane) {
-    const bf16_t* const h0 = op.half[0];                     // scalars, so that the selects below stay selects
-    const bf16_t* const h1 = op.half[1];
-    const int v0 = op.valid[0], v1 = op.valid[1];
-    static_assert(BK <= 256, "reduction indices are packed in 8 bits");
+  // K_: reduction length, nslabs_: slabs the main loop may read
+  __device__ __forceinline__ void init(const Operand& op, int K_, int nslabs_, int wave, int lane) {
+    K = K_; nslabs = nslabs_;
+    const bf16_t* b = op.half[0];
+    if constexpr (!KS) {
+      constexpr int PPR = BK / 8, RPC = 1024 / (BK * 2), RPL = 256 / (BK * 2);
+      const bool upper = wave >= WAVES / 2;                    // uniform
+      const int valid = upper ? op.valid[1] : op.valid[0];
+      if (!GATHER && upper) b = op.half[1];
 #pragma unroll
-    for (int i = 0; i < (N + 3) / 4; ++i) kpack[i] = 0u;
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const int c = wave * N + i;                            // wave-uniform
-      if constexpr (!KS) {
-        constexpr int PPR = BK / 8, RPC = 1024 / (BK * 2), RPL = 256 / (BK * 2);
-        static_assert((ROWS / 2) % RPC == 0, "a chunk must not straddle the two halves");
-        const int row = c * RPC + lane / PPR;
+      for (int i = 0; i < N; ++i) {
+        const int row = (wave * N + i) * RPC + lane / PPR;
         const int piece = (lane % PPR) ^ ((row / RPL) & (PPR - 1));
-        const bool upper = c * RPC >= ROWS / 2;              // uniform
         const int rh = row - (upper ? ROWS / 2 : 0);
-        const int valid = upper ? v1 : v0;
+        const bool exists = rh < valid;
         if constexpr (GATHER) {
-          // rows that do not exist read the tile's first row (it exists)
-          const int mrow = op.gather[op.grow + (rh < valid ? row : 0)];
-          base[i] = reinterpret_cast<const char*>(h0);
-          voff[i] = static_cast<uint32_t>(mrow) * static_cast<uint32_t>(op.ld * 2) + piece * 16;
+          const int mrow = op.gather[op.grow + (exists ? row : 0)];
+          voff[i] = exists ? static_cast<uint32_t>(mrow) * static_cast<uint32_t>(op.ld * 2) + piece * 16 : kOffNone;
         } else {
-          // the chunk's base stays the upper half only if the chunk holds at least one row that exists
-          // (uniform); single missing rows are redirected through the per-lane offset
-          const bool chunk_any = (c * RPC - (upper ? ROWS / 2 : 0)) < valid;
-          const bool own_base = !upper || chunk_any;
-          base[i] = reinterpret_cast<const char*>((own_base && upper) ? h1 : h0);
-          const bool own_row = own_base && rh < valid;
-          voff[i] = static_cast<uint32_t>((own_row ? static_cast<long>(rh) * op.ld : 0) * 2 + piece * 16);
+          voff[i] = exists ? static_cast<uint32_t>(static_cast<long>(rh) * op.ld * 2 + piece * 16) : kOffNone;
         }
-        set_kidx(i, piece * 8);
-      } else {
-        constexpr int PPK = ROWS / 8;
-        const int k = c * KPC + lane / PPK;
-        const int phys = lane % PPK;
-        const int piece = ((((phys >> 2) ^ (k & 3)) << 2) | (phys & 3));
+      }
+    } else {
+      constexpr int PPK = ROWS / 8;
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const int k = (wave * N + i) * KPC + lane / PPK;
+        const int piece = (lane % PPK) ^ (ks_swizzle(k) << 1);
         const int col = piece * 8;
-        const bool upper = col >= ROWS / 2;
-        const int ch = col - (upper ? ROWS / 2 : 0);
-        const bool ok = ch < (upper ? v1 : v0);
-        // k-strided operands are never dual: half[1] is half[0] shifted by ROWS/2 columns
-        base[i] = reinterpret_cast<const char*>(h0);
-        if constexpr (GATHER) voff[i] = static_cast<uint32_t>((ok ? col : 0) * 2);
-        else voff[i] = static_cast<uint32_t>(((ok ? col : 0) + static_cast<long>(k) * op.ld) * 2);
-        set_kidx(i, k);
+        const bool exists = col < op.valid[0] + op.valid[1];   // k-strided operands are never dual
+        // (gathered: a column that does not exist reads the row's first one, so that row offset + column offset cannot wrap)
+        if constexpr (GATHER) voff[i] = static_cast<uint32_t>((exists ? col : 0) * 2);
+        else voff[i] = exists ? static_cast<uint32_t>((static_cast<long>(k) * op.ld + col) * 2) : kOffNone;
       }
     }
     step = (KS ? (GATHER ? 0L : static_cast<long>(BK) * op.ld) : BK) * 2;
-    // the bases are the same in every lane: say so, to get scalar base + 32-bit lane offset addressing
-    // (no 64-bit per-lane address arithmetic, fewer registers held across the main loop)
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      const uint64_t b64 = reinterpret_cast<uint64_t>(base[i]);
-      const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64));
-      const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64 >> 32));
-      base[i] = reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
-    }
+    ld2 = static_cast<uint32_t>(op.ld * 2);
+    // the base is the same in every lane: say so
+    const uint64_t b64 = reinterpret_cast<uint64_t>(b);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64));
+    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64 >> 32));
+    base = reinterpret_cast<const char*>((static_cast<uint64_t>(hi) << 32) | lo);
     if constexpr (KS && GATHER) {
       rows = reinterpret_cast<RowList>(reinterpret_cast<uintptr_t>(op.gather + op.grow + wave * NR));
-      ld2 = static_cast<uint32_t>(op.ld * 2);
       lq = lane / (ROWS / 8);
+      k_first = wave * NR;
       fetch_rows(0);
     }
   }
-  // byte offset of this lane's piece of chunk i from the wave-uniform base
+  // descriptor of slab `slab`; every part of it scalar (a clamp on the vector unit would make the loads a loop over lanes)
+  __device__ __forceinline__ void point(int slab) {
+    long off = slab * step;
+    if constexpr (TWO_SEG) off += slab >= seg_slabs ? seg_delta : 0L;
+    uint32_t range = slab < nslabs ? kRangeAll : 0u;
+    if constexpr (KS && !GATHER) {
+      int first = slab * BK;
+      if constexpr (TWO_SEG) first -= slab >= seg_slabs ? seg_slabs * BK : 0;
+      int left = min(BK, K - first);
+      asm("" : "+s"(left));
+      left = max(left, 0);
+      if constexpr (TWO_SEG) left = slab < nslabs ? left : 0;
+      range = static_cast<uint32_t>(left) * ld2;
+    }
+    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base + off), 0, static_cast<int>(range), 0x00020000);
+    if constexpr (KS && GATHER) {
+      // byte offsets of the wave's rows; rows beyond K are beyond the range
+#pragma unroll
+      for (int j = 0; j < NR; ++j) next_row[j] = slab * BK + k_first + j < K ? static_cast<int32_t>(static_cast<uint32_t>(next_row[j]) * ld2) : static_cast<int32_t>(kRangeAll);
+    }
+  }
+  // byte offset of this lane's piece of chunk i
   __device__ __forceinline__ uint32_t lane_off(int i) const {
     if constexpr (KS && GATHER) {
-      int32_t mrow = next_row[i * KPC];
+      int32_t moff = next_row[i * KPC];
 #pragma unroll
-      for (int q = 1; q < KPC; ++q) mrow = lq == q ? next_row[i * KPC + q] : mrow;
-      return static_cast<uint32_t>(mrow) * ld2 + voff[i];
+      for (int q = 1; q < KPC; ++q) moff = lq == q ? next_row[i * KPC + q] : moff;
+      return static_cast<uint32_t>(moff) + voff[i];
     } else {
       return voff[i];
     }
   }
-  // enqueue this wave's share of slab `slab` into the operand tile at `tile` (LDS); slabs are issued in order
+  // one of the N loads of the slab that point() described, into the operand tile at `tile` (LDS); slabs are issued in order
+  __device__ __forceinline__ void issue_at(int i, uint32_t off, char* tile, int wave) const {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(tile + (wave * N + i) * 1024), 16, static_cast<int>(off), 0, 0, 0);
+  }
+  __device__ __forceinline__ void issue_one(int i, char* tile, int wave) const { issue_at(i, lane_off(i), tile, wave); }
+  // a whole slab, then the row list of the one after it
   __device__ __forceinline__ void issue(int slab, char* tile, int wave) {
+    point(slab);
 #pragma unroll
-    for (int i = 0; i < N; ++i) issue_one(i, slab, tile, wave);
+    for (int i = 0; i < N; ++i) issue_one(i, tile, wave);
     fetch_rows(slab + 1);
   }
-  // one of the N loads of a full slab (the caller enqueues all N, in order, then fetch_rows(slab + 1))
-  __device__ __forceinline__ void issue_one(int i, int slab, char* tile, int wave) {
-    const char* g = base[i] + slab * step + lane_off(i);
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
-                                     (__attribute__((address_space(3))) void*)(tile + (wave * N + i) * 1024), 16, 0, 0);
-  }
-  // the same for the last, partial slab: pieces whose reduction index is >= K read zeros
-  __device__ __forceinline__ void issue_tail(int slab, int K, const char* zeros, char* tile, int wave) {
+  // the partial last slab of a k-contiguous operand: pieces whose reduction index is >= K read zeros
+  __device__ __forceinline__ void issue_tail(int slab, char* tile, int wave, int lane) {
+    nslabs = slab + 1;
+    point(slab);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-      const bool in_range = slab * BK + kidx(i) < K;
-      uint32_t off = lane_off(i);
-      asm volatile("" : "+v"(off));                          // the 64-bit per-lane address is formed here, not kept in registers across the slab loop
-      const char* g = in_range ? base[i] + slab * step + off : zeros;
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
-                                       (__attribute__((address_space(3))) void*)(tile + (wave * N + i) * 1024), 16, 0, 0);
+      if constexpr (KS) {
+        issue_one(i, tile, wave);
+      } else {
+        constexpr int PPR = BK / 8, RPC = 1024 / (BK * 2), RPL = 256 / (BK * 2);
+        const int row = (wave * N + i) * RPC + lane / PPR;
+        const int piece = (lane % PPR) ^ ((row / RPL) & (PPR - 1));
+        issue_at(i, slab * BK + piece * 8 < K ? voff[i] : kOffNone, tile, wave);
+      }
     }
-    fetch_rows(slab + 1);
   }
 };
 
@@ -292,374 +317,365 @@ template <int n> __device__ __forceinline__ void wait_vmcnt() {
 // s_waitcnt that waits only for the LDS / scalar-memory counter to reach zero
 __device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14)); }
 
-// wait until at most n of this wave's direct loads are still in flight; n is a multiple of STEP and at most MAX
-// (the hardware wait takes an immediate: one comparison per candidate, the steady-state value first)
-template <int MAX, int STEP>
-__device__ __forceinline__ void wait_loads_in_flight(int n) {
-  if constexpr (MAX <= 0) {
-    wait_vmcnt<0>();
-  } else {
-    if (n >= MAX) wait_vmcnt<MAX>();
-    else wait_loads_in_flight<MAX - STEP, STEP>(n);
-  }
-}
-
-// the MFMA operands of one 16-wide reduction step for this wave's sub-tile
-template <class T> struct Frags {
-  bf16x8 a[T::MI];
-  bf16x8 b[T::NI];
-};
-// Per-lane LDS addresses of the fragments, set up once per tile.  The wave's fragments of one side lie a constant
-// number of tile rows apart (FR rows, normally 32), and
-//   * in a k-contiguous tile a fragment FR rows further is a constant number of bytes further (the swizzle of a row
-//     repeats every 16 rows), while the reduction step moves the piece index by 2*KK, which the swizzle turns into
-//     an XOR of the address: one register per step, the fragment in the immediate;
-//   * in a k-strided tile the step is a constant number of bytes (16 reduction rows; the swizzle k & 3 is unchanged)
-//     but a fragment 32 columns further is not (its 64-byte chunk index is XORed with k & 3): one register per
-//     fragment, the step in the immediate.
-// A buffer that starts 64 KiB or more into its side's ring is out of reach of the immediate: `far` holds the same
-// addresses 64 KiB further (only the third buffer of a three-deep ring needs them).
-template <class T, bool A_KS, bool B_KS> struct FragAddrs {
-  static constexpr int STEPS = T::BK / 16;
-  static constexpr int NA = A_KS ? T::MI : STEPS, NB = B_KS ? T::NI : STEPS;
-  static constexpr bool A_FAR = (T::SA - 1) * T::kABytes >= 65536, B_FAR = (T::SB - 1) * T::kBBytes >= 65536;
-  uint32_t a[NA], b[NB];
-  uint32_t a_far[A_FAR ? NA : 1], b_far[B_FAR ? NB : 1];
-};
-// Fragment I of one side at reduction step KK, from the buffer that starts OFF bytes into the side's ring; FR: tile
-// rows between the wave's fragments; near / far: the side's address registers.
-template <bool KS, int ROWS, int BK, int FR, int OFF, int KK, int I, int N>
-__device__ __forceinline__ bf16x8 read_side(const uint32_t (&near)[N], const uint32_t* far) {
-  constexpr int FAR = OFF >= 65536 ? 65536 : 0;
-  if constexpr (KS) return lds_read_frag<true, ROWS, OFF - FAR + KK * 16 * ROWS * 2>(FAR ? far[I] : near[I]);
-  else return lds_read_frag<false, ROWS, OFF - FAR + I * FR * BK * 2>(FAR ? far[KK] : near[KK]);
-}
-template <class T, bool A_KS, bool B_KS, int FRA, int FRB, int OFF_A, int OFF_B, int KK, int... IA, int... IB>
-__device__ __forceinline__ void load_frags_seq(Frags<T>& f, const FragAddrs<T, A_KS, B_KS>& fa, std::integer_sequence<int, IA...>,
-                                               std::integer_sequence<int, IB...>) {
-  ((f.a[IA] = read_side<A_KS, T::BM, T::BK, FRA, OFF_A, KK, IA>(fa.a, fa.a_far)), ...);
-  ((f.b[IB] = read_side<B_KS, T::BN, T::BK, FRB, OFF_B, KK, IB>(fa.b, fa.b_far)), ...);
-}
-// OFF_A / OFF_B: where the slab's buffers start in their side's ring; FRA / FRB: tile rows between the wave's fragments.
-template <class T, bool A_KS, bool B_KS, int FRA, int FRB, int OFF_A, int OFF_B, int KK>
-__device__ __forceinline__ void load_frags(Frags<T>& f, const FragAddrs<T, A_KS, B_KS>& fa) {
-  static_assert((T::BK / 16 - 1) * 32 < T::BK * 2, "the step bits must lie inside a row");
-  load_frags_seq<T, A_KS, B_KS, FRA, FRB, OFF_A, OFF_B, KK>(f, fa, std::make_integer_sequence<int, T::MI>{}, std::make_integer_sequence<int, T::NI>{});
-}
-// Wait until this wave's LDS reads have delivered, with the fragments as operands of the wait: the registers a
-// transposing read (an assembly statement, see read_frag) is filling stay reserved until here on every path --
-// the compiler must neither reuse them earlier nor move a consumer above the wait.
-template <class T>
-__device__ __forceinline__ void settle(Frags<T>& f) {
-  static_assert(T::MI + T::NI <= 8, "one operand per fragment");
-  if constexpr (T::MI == 4 && T::NI == 2) {
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.a[2]), "+v"(f.a[3]), "+v"(f.b[0]), "+v"(f.b[1]));
-  } else if constexpr (T::MI == 2 && T::NI == 2) {
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.a[0]), "+v"(f.a[1]), "+v"(f.b[0]), "+v"(f.b[1]));
-  } else {
-    static_assert(T::MI == 1 && T::NI == 2, "add the operand list of this wave shape");
-    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.a[0]), "+v"(f.b[0]), "+v"(f.b[1]));
-  }
-}
-
-// MFMAs number FROM .. TO-1 (row-major over the wave's MI x NI fragments) of one reduction step
-template <class T, int FROM, int TO>
-__device__ __forceinline__ void mma(const Frags<T>& f, f32x16 (&acc)[T::MI][T::NI]) {
-#pragma unroll
-  for (int mi = 0; mi < T::MI; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < T::NI; ++ni)
-      if (mi * T::NI + ni >= FROM && mi * T::NI + ni < TO)
-        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.b[ni], f.a[mi], acc[mi][ni], 0, 0, 0);   // transposed tile, see Strip
-}
+// a wave's accumulators
+template <class T> using Acc = f32x4[T::FM][T::FN];
 
 // acc += sum over segments of A_s(BM x K) * B_s(BN x K)^T for this wave's sub-tile (segments differ
-// only in their base pointers).  a_row[mi] / b_row[ni]: first tile row of the wave's mi-th / ni-th
-// 32-row fragment.
+// only in their base pointers).
 //
-// Slabs stream through the two LDS rings (SA buffers for the A side, SB <= SA for the B side) filled by direct
-// global->LDS loads, and the MFMA operands are double-buffered in registers, so that every LDS read is issued
-// one reduction step ahead of the MFMAs that consume it.  Per slab kt:
-//     read step 1.. of slab kt (into the other register set) | MFMAs of the steps already loaded
-//     wait: own LDS reads of slab kt complete, own loads of slab kt+1 landed (later slabs stay in flight)
-//     barrier: slab kt+1 is visible to all, and nobody reads the buffers of slab kt any more
-//     refill them with B of slab kt+SB, then A of slab kt+SA; read step 0 of slab kt+1 | MFMAs of the last step
-// Loads complete in the order they were enqueued, and the refill enqueues the slab that is needed first first, so
-// "slab kt+1 has landed" is a wait for all but the loads enqueued after it -- an immediate count.  The loop over
-// slabs is unrolled lcm(SA, SB) times so that every LDS address is "register + constant" and no address arithmetic
-// competes with the MFMAs for issue slots.  What limits the stream is the number of L2 requests a CU can have
-// outstanding (about 128 lines, whatever is in flight in the rings): 64-byte row pieces (BK = 32) give about
-// 30 bytes per clock and CU on L2 hits, 128-byte pieces (BK = 64) about 60; the rings only have to keep that
-// window full, which a ring that drains at every slab (SA = SB = 2) does not.
-template <class T, bool A_KS, bool B_KS, bool A_GATHER = false, bool B_GATHER = false, int FRB = 32>
+// The MFMA is the 16 x 16 x 32 one: at the chip's power limit, where these products run, it does 13-17 % more
+// arithmetic per second on random operands than the 32 x 32 x 16 one (256 CUs, operands in registers: 1974-2128
+// against 1713-1880 TFLOP/s; with the LDS reads of a 128 x 64 sub-tile 1768-1851 against 1680-1694).
+//
+// Slabs stream through the two LDS rings (SA buffers for the A side, SB for the B side) filled by direct
+// global->LDS loads.  A slab is two reduction steps (S0, S1) of FM rows of FN MFMAs.  A row-side fragment is read again
+// for the next step right after the last MFMA that consumes it, so it has the FM - 1 other rows to arrive; the
+// column-side fragments, which every row uses, are double-buffered in registers.  Per slab kt:
+//     S0: row i | read a_i of S1, then b_j of S1 | (spread) refill B of slab kt+SB-1, whose buffer slab kt-1 has left
+//     S1: rows 0 .. R0-1
+//         wait: own LDS reads of slab kt complete, own loads of slab kt+1 landed (later slabs stay in flight)
+//         barrier: slab kt+1 is visible to all, and nobody reads the buffers of slab kt any more
+//         read b, a_0 .. a_R0-1 of S0 of slab kt+1
+//         rows R0 .. | read a_i of S0 of slab kt+1 | (spread) refill A of slab kt+SA
+// LDS reads of a wave complete in order, so "fragment X has arrived" is a wait for all but the reads issued after it;
+// loads complete in the order they were enqueued, so "slab kt+1 has landed" is a wait for all but the loads enqueued
+// after it -- immediates, both: slabs beyond the end of the reduction are enqueued too (see Dma) and touch no memory.
+// The loop is a plain loop over one slab body with run-time ring positions, a single path: with a body chosen per slab
+// the compiler keeps fragments and accumulators in scratch memory.  The address registers of the fragments are
+// advanced once per slab (4 to 12 vector additions against 64 MFMAs).
+template <class T, bool A_KS, bool B_KS, bool A_GATHER = false, bool B_GATHER = false, int B_HALF = T::WN / 2, bool TWO_SEG = false>
 struct MainLoop {
-  static constexpr int FRA = 32;                       // tile rows between the wave's fragments, A side and B side
   typedef Dma<A_KS, T::BM, T::BK, T::kWaves, A_GATHER> DmaA;
-  typedef Dma<B_KS, T::BN, T::BK, T::kWaves, B_GATHER> DmaB;
+  typedef Dma<B_KS, T::BN, T::BK, T::kWaves, B_GATHER, TWO_SEG> DmaB;
   static constexpr int NA = DmaA::N, NB = DmaB::N;     // loads per thread per slab and side
   static constexpr int SA = T::SA, SB = T::SB;
-  static_assert(SA >= 2 && SB >= 2, "one slab being multiplied, at least one in flight");
-  static constexpr int U = (SA % SB == 0) ? SA : SA * SB;   // slabs per unrolled trip: buffer indices are compile-time
-  static constexpr int STEPS = T::BK / 16;             // reduction steps per slab (even)
-  static constexpr int kMaxAhead = (SA - 1) * NA + (SB - 1) * NB;   // most loads ever in flight behind slab 0
-  static constexpr int kStep = NA == NB ? NA : 1;
-  static_assert(kMaxAhead < 64, "vmcnt is a 6-bit counter");
+  static constexpr int FM = T::FM, FN = T::FN;
+  static_assert(SA >= 2 && SB >= 3, "one slab being multiplied, at least one in flight");
+  static constexpr int STEPS = T::BK / 32;
+  static_assert(STEPS == 2, "a slab is two reduction steps");
+  static constexpr int R0 = FM >= 8 ? 2 : 1;           // rows of S1 before the barrier
+  static_assert(FM > R0, "rows of S1 after the barrier");
+  static constexpr int kMaxAhead = (SA - 1) * NA + (SB - 2) * NB;   // loads in flight behind slab 0 when the stream starts
+  static constexpr int kBeyond = (SA - 2) * NA + (SB - 2) * NB;     // loads enqueued after those of slab kt+1 at the end of slab kt
+  static_assert((SA - 1) * NA + (SB - 1) * NB < 64, "vmcnt is a 6-bit counter");
+  static constexpr int RA = A_KS ? 2 : 1, RB = B_KS ? 2 : 1;   // LDS instructions per fragment
+  static constexpr bool KS_ONLY = A_KS && B_KS;        // a partial last slab needs no pass of its own
 
   DmaA da;
   DmaB db;
-  FragAddrs<T, A_KS, B_KS> fa;
-  Frags<T> f0, f1;                                     // even / odd reduction steps
+  // Per-lane LDS addresses of the fragments.  k-contiguous side: a fragment 16 rows further is a constant number of
+  // bytes further (the swizzle of a row repeats every 16 rows), while the step moves the piece index by 4, an XOR of
+  // the address: one register per step, [0] in the buffer of the NEXT slab (its S0 is what is read ahead), [1] in that of
+  // the slab being multiplied.  k-strided side: the step is a constant number of bytes (32 reduction rows; their
+  // swizzle is the same) but a fragment 16 columns further is not: one register per fragment, moved on to the next
+  // slab's buffer after its S1 read.
+  static constexpr int NAA = A_KS ? FM : STEPS, NAB = B_KS ? FN : STEPS;
+  uint32_t aa[NAA], ab[NAB];
+  // Column-side fragments: two sets (S0, S1), or with four waves per SIMD -- 128 registers each, and three other waves to
+  // cover an LDS latency -- one, each fragment read again right after its last MFMA, in the last row of the step.
+  static constexpr bool B_ROLL = T::kWavesPerSimd >= 4;
+  bf16x8 a[FM];
+  bf16x8 b[B_ROLL ? 1 : 2][FN];
+  static constexpr int b_set(int kk) { return B_ROLL ? 0 : kk; }
   char* lds;
   uint32_t lds32;                                      // the ring's start as an LDS address
-  const char* zeros;
-  int nslabs, nfull, K, wave;
+  int stage_a, stage_b;                                // ring positions of the slab being multiplied
+  int nslabs, K, wave;
 
+  // tile rows between the wave's first fragment of a side and fragment i (the second half of the column side may lie apart)
+  static constexpr int a_frag_row(int i) { return 16 * i; }
+  static constexpr int b_frag_row(int i) { return (i >= FN / 2 ? B_HALF : 0) + 16 * (i % (FN / 2)); }
+  static __device__ __forceinline__ int next_stage(int s, int n) { return s + 1 == n ? 0 : s + 1; }
   __device__ __forceinline__ char* buf_a(int stage) const { return lds + stage * T::kABytes; }
   __device__ __forceinline__ char* buf_b(int stage) const { return lds + T::kBBase + stage * T::kBBytes; }
-  // LDS reads: the B side's fragment offsets already contain kBBase, so that every buffer but the last of a
-  // three-deep ring is reached with the 16-bit immediate offset of the LDS instruction
-  __device__ __forceinline__ void issue_a(int slab, int stage) {
-    if (slab < nfull) da.issue(slab, buf_a(stage), wave);
-    else da.issue_tail(slab, K, zeros, buf_a(stage), wave);
-  }
-  __device__ __forceinline__ void issue_b(int slab, int stage) {
-    if (slab < nfull) db.issue(slab, buf_b(stage), wave);
-    else db.issue_tail(slab, K, zeros, buf_b(stage), wave);
-  }
-  // loads enqueued so far for slabs beyond kt + 1 (they may stay in flight when slab kt + 1 is needed)
-  __device__ __forceinline__ int loads_beyond(int kt) const {
-    const int rest = nslabs - 2 - kt;                  // slabs that exist beyond kt + 1
-    return max(0, min(SA - 2, rest)) * NA + max(0, min(SB - 2, rest)) * NB;
-  }
 
-  // Steps KK .. STEPS-2 of the slab in buffers SGA / SGB.  Every step first waits for its own operands, then issues
-  // the LDS reads of the next step and only then its MFMAs, so each read has a whole step of MFMAs (plus the other
-  // wave on the SIMD) to complete.  Even steps multiply f0, odd steps f1.
-  template <int SGA, int SGB, int KK>
-  __device__ __forceinline__ void steps(f32x16 (&acc)[T::MI][T::NI]) {
-    if constexpr (KK + 1 < STEPS) {
-      settle<T>((KK & 1) ? f1 : f0);
+  // ---- LDS reads of reduction step KK ----
+  template <int KK, int I> __device__ __forceinline__ void read_a() {
+    if constexpr (A_KS) a[I] = lds_read_frag<true, T::BM, KK * 32 * T::BM * 2>(aa[I]);
+    else a[I] = lds_read_frag<false, T::BM, a_frag_row(I) * T::BK * 2>(aa[KK]);
+  }
+  template <int KK, int J> __device__ __forceinline__ void read_b() {
+    if constexpr (B_KS) b[b_set(KK)][J] = lds_read_frag<true, T::BN, KK * 32 * T::BN * 2>(ab[J]);
+    else b[b_set(KK)][J] = lds_read_frag<false, T::BN, b_frag_row(J) * T::BK * 2>(ab[KK]);
+  }
+  template <int KK, int J, int JEND> __device__ __forceinline__ void read_range_b() {
+    if constexpr (J < JEND) { read_b<KK, J>(); read_range_b<KK, J + 1, JEND>(); }
+  }
+  template <int KK, int I, int IEND> __device__ __forceinline__ void read_range_a() {
+    if constexpr (I < IEND) { read_a<KK, I>(); read_range_a<KK, I + 1, IEND>(); }
+  }
+  // Wait until at most N of this wave's LDS reads are outstanding (the counter has 4 bits: more is the same as 15), with
+  // the fragments that have arrived by then as operands of the wait: the registers an asynchronous read is filling stay
+  // reserved until here on every path -- the compiler must neither reuse them earlier nor move a consumer above the wait.
+  template <int N> static __device__ __forceinline__ void arrived(bf16x8& x) {
+    asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(x) : "n"(N < 15 ? N : 15));
+  }
+  template <int N, int KK> __device__ __forceinline__ void arrived_with_b(bf16x8& x) {
+    static_assert(FN == 4, "add the operand list of this wave shape");
+    constexpr int Q = b_set(KK);
+    asm volatile("s_waitcnt lgkmcnt(%5)" : "+v"(x), "+v"(b[Q][0]), "+v"(b[Q][1]), "+v"(b[Q][2]), "+v"(b[Q][3]) : "n"(N < 15 ? N : 15));
+  }
+  __device__ __forceinline__ void all_arrived() {      // every row-side fragment
+    static_assert(FM == 2 || FM == 4 || FM == 8, "add the operand list of this wave shape");
+    if constexpr (FM == 8)
+      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]), "+v"(a[4]), "+v"(a[5]), "+v"(a[6]), "+v"(a[7]));
+    else if constexpr (FM == 4)
+      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3]));
+    else
+      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]));
+  }
+  // the MFMAs of one row of a step
+  template <int KK, int I> __device__ __forceinline__ void mma_row(Acc<T>& acc) {
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+      acc[I][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[b_set(KK)][j], a[I], acc[I][j], 0, 0, 0);   // transposed tile, see Strip
+  }
+  // the same for the last row of a step with B_ROLL: each column-side fragment is read for step NKK once it is free
+  template <int KK, int NKK, int J = 0> __device__ __forceinline__ void mma_row_roll(int adv_b, Acc<T>& acc) {
+    if constexpr (J < FN) {
+      acc[FM - 1][J] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[0][J], a[FM - 1], acc[FM - 1][J], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
-      load_frags<T, A_KS, B_KS, FRA, FRB, SGA * T::kABytes, SGB * T::kBBytes, KK + 1>((KK & 1) ? f0 : f1, fa);
+      read_b<NKK, J>();
+      if constexpr (B_KS && NKK == 1) ab[J] += adv_b;
       __builtin_amdgcn_sched_barrier(0);
-      mma<T, 0, T::MI * T::NI>((KK & 1) ? f1 : f0, acc);
-      __builtin_amdgcn_sched_barrier(0);
-      steps<SGA, SGB, KK + 1>(acc);
+      mma_row_roll<KK, NKK, J + 1>(adv_b, acc);
     }
   }
 
-  // ACTIVE = false: a wave whose sub-tile holds no row of the expert (the tile sticks out of the
-  // row segment) only takes part in the loads and barriers; its SIMD time goes to the other waves.
-  template <int STG, bool ACTIVE>
-  __device__ __forceinline__ void slab_body(int kt, f32x16 (&acc)[T::MI][T::NI]) {
-    constexpr int SGA = STG % SA, SGB = STG % SB, NXA = (STG + 1) % SA, NXB = (STG + 1) % SB;
-    constexpr int ALL = T::MI * T::NI;
-    if constexpr (ACTIVE) {
-      steps<SGA, SGB, 0>(acc);                         // every step but the last: fetch the next step, multiply this one
-      settle<T>(f1);                                   // last step is in f1; this wave no longer needs the buffers of slab kt
+  // ---- refill ----
+  // The B side has nearly two slab periods from its refill to its use: its loads are spread over the rows of S0.  The A
+  // side has one: it is enqueued right after the barrier, where it is not held up by MFMAs that a wave of the lower priority
+  // on its SIMD has to wait for (spread over the rows of S1 instead, at 2560 rows per expert: gate/up 1946 us against 1861,
+  // down 1074 against 1038, dX 1850 against 1781).
+  static constexpr int load_at(int n, int row) { return n * row / FM; }
+  template <int J, int JEND> __device__ __forceinline__ void refill_a(char* tile) {
+    if constexpr (J < JEND) { da.issue_one(J, tile, wave); refill_a<J + 1, JEND>(tile); }
+  }
+  template <int J, int JEND> __device__ __forceinline__ void refill_b(char* tile) {
+    if constexpr (J < JEND) { db.issue_one(J, tile, wave); refill_b<J + 1, JEND>(tile); }
+  }
+
+  // column-side fragments of S1 read before row `row` of S0 (as early as the rows allow)
+  static constexpr int kBPerRow = 2 * FN > FM ? 2 * FN / FM : 1;
+  static constexpr int b_at(int row) { return B_ROLL ? 0 : row * kBPerRow < FN ? row * kBPerRow : FN; }
+  static constexpr int last_b_row() { int r = 0; while (!B_ROLL && b_at(r + 1) < FN) ++r; return r; }
+  // rows I .. of S0
+  template <int I>
+  __device__ __forceinline__ void step0(char* new_b, int adv_a, int adv_b, Acc<T>& acc) {
+    if constexpr (I < FM) {
+      // B_ROLL: the last row-side read follows those of the column side; row 0 has waited for all but it
+      constexpr int YOUNGER = B_ROLL ? (I == FM - 1 ? FM - 1 : I + 1) * RA : (FM - 1 - I) * RA + I * RA + b_at(I) * RB;
+      if constexpr (I == 0) arrived_with_b<YOUNGER, 0>(a[0]);
+      else arrived<YOUNGER>(a[I]);
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (B_ROLL && I == FM - 1) mma_row_roll<0, 1>(adv_b, acc);
+      else mma_row<0, I>(acc);
+      __builtin_amdgcn_sched_barrier(0);
+      read_a<1, I>();
+      if constexpr (A_KS) aa[I] += adv_a;
+      read_range_b<1, b_at(I), b_at(I + 1)>();
+      if constexpr (B_KS) {
+#pragma unroll
+        for (int j = b_at(I); j < b_at(I + 1); ++j) ab[j] += adv_b;
+      }
+      refill_b<load_at(NB, I), load_at(NB, I + 1)>(new_b);
+      __builtin_amdgcn_sched_barrier(0);
+      step0<I + 1>(new_b, adv_a, adv_b, acc);
     }
-    if (kt + 1 < nslabs) wait_loads_in_flight<(SA - 2) * NA + (SB - 2) * NB, kStep>(loads_beyond(kt));   // slab kt+1 has landed
+  }
+  // rows I .. R0-1 of S1, before the barrier
+  template <int I>
+  __device__ __forceinline__ void step1_head(Acc<T>& acc) {
+    if constexpr (I < R0) {
+      // younger than a_I and every b of S1: the row-side reads issued after the later of them
+      constexpr int FROM = I > last_b_row() ? I : last_b_row(), YOUNGER = B_ROLL ? RA : (FM - 1 - FROM) * RA;
+      if constexpr (I == 0) arrived_with_b<YOUNGER, 1>(a[0]);
+      else arrived<YOUNGER>(a[I]);
+      __builtin_amdgcn_sched_barrier(0);
+      mma_row<1, I>(acc);
+      __builtin_amdgcn_sched_barrier(0);
+      step1_head<I + 1>(acc);
+    }
+  }
+  // the other rows of S1; the first step of the next slab is read between them
+  template <int I>
+  __device__ __forceinline__ void step1_tail(Acc<T>& acc) {
+    if constexpr (I < FM) {
+      if constexpr (B_ROLL && I == FM - 1) mma_row_roll<1, 0>(0, acc);
+      else mma_row<1, I>(acc);
+      __builtin_amdgcn_sched_barrier(0);
+      read_a<0, I>();
+      __builtin_amdgcn_sched_barrier(0);
+      step1_tail<I + 1>(acc);
+    }
+  }
+  // A slab of a wave with rows.  On entry the reads of its S0 are in flight, on exit those of the next slab's -- after the
+  // last one, of a buffer that holds nothing: a body of its own for the last slab costs registers across the loop.
+  __device__ __forceinline__ void slab(int kt, Acc<T>& acc) {
+    const int na = next_stage(stage_a, SA), nb = next_stage(stage_b, SB);
+    const int adv_a = (na - stage_a) * T::kABytes, adv_b = (nb - stage_b) * T::kBBytes;
+    db.point(kt + SB - 1);
+    step0<0>(buf_b(stage_b == 0 ? SB - 1 : stage_b - 1), adv_a, adv_b, acc);
+    db.fetch_rows(kt + SB);
+    step1_head<0>(acc);
+    all_arrived();                                     // this wave no longer needs the buffers of slab kt
+    wait_vmcnt<kBeyond>();                             // slab kt+1 has landed
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    // Products that read an operand transposed start with the last step's MFMAs (their LDS reads and the refill then
-    // issue under those MFMAs); the others first fetch and refill (measured: 1-3 % either way).
-    constexpr bool MMA_FIRST = A_KS || B_KS;
-    if constexpr (ACTIVE && MMA_FIRST) {
-      mma<T, 0, ALL>(f1, acc);
-      __builtin_amdgcn_sched_barrier(0);
+    da.point(kt + SA);
+    if constexpr (!B_ROLL) read_range_b<0, 0, FN>();
+    read_range_a<0, 0, R0>();
+    __builtin_amdgcn_sched_barrier(0);
+    refill_a<0, NA>(buf_a(stage_a));
+    __builtin_amdgcn_sched_barrier(0);
+    step1_tail<R0>(acc);
+    da.fetch_rows(kt + SA + 1);
+    if constexpr (!A_KS) {
+      aa[0] += (next_stage(na, SA) - na) * T::kABytes;
+      aa[1] += adv_a;
     }
-    if constexpr (ACTIVE) {
-      if (kt + 1 < nslabs) load_frags<T, A_KS, B_KS, FRA, FRB, NXA * T::kABytes, NXB * T::kBBytes, 0>(f0, fa);
-      __builtin_amdgcn_sched_barrier(0);
+    if constexpr (!B_KS) {
+      ab[0] += (next_stage(nb, SB) - nb) * T::kBBytes;
+      ab[1] += adv_b;
     }
-    if constexpr (SB <= SA) {                          // the side whose slab is needed sooner goes first
-      if (kt + SB < nslabs) issue_b(kt + SB, SGB);
-      if (kt + SA < nslabs) issue_a(kt + SA, SGA);
+    stage_a = na; stage_b = nb;
+    __builtin_amdgcn_sched_barrier(0);
+  }
+
+  // first slab's S0 from the first buffers of the rings
+  __device__ __forceinline__ void read_first() {
+    if constexpr (B_ROLL) {                            // in the order of the slab body
+      read_range_a<0, 0, FM - 1>();
+      read_range_b<0, 0, FN>();
+      read_range_a<0, FM - 1, FM>();
     } else {
-      if (kt + SA < nslabs) issue_a(kt + SA, SGA);
-      if (kt + SB < nslabs) issue_b(kt + SB, SGB);
+      read_range_b<0, 0, FN>();
+      read_range_a<0, 0, FM>();
     }
-    if constexpr (ACTIVE && !MMA_FIRST) {
-      __builtin_amdgcn_sched_barrier(0);
-      mma<T, 0, ALL>(f1, acc);
-    }
+    if constexpr (!A_KS) aa[0] += T::kABytes;          // from here on [0] addresses the buffer of the next slab
+    if constexpr (!B_KS) ab[0] += T::kBBytes;
+    __builtin_amdgcn_sched_barrier(0);
   }
 
-  // The same for a wave with rows, when every slab the body touches is a full one that exists (slabs kt + 1, kt + SA and
-  // kt + SB below nfull): nothing branches, and the refill and the first LDS reads of the next slab are spread between
-  // the MFMAs of the last step, one group per MFMA -- they issue while the matrix pipe is busy with the MFMA before
-  // them instead of holding it up after the barrier.
-  template <int STG>
-  __device__ __forceinline__ void slab_interior(int kt, f32x16 (&acc)[T::MI][T::NI]) {
-    constexpr int SGA = STG % SA, SGB = STG % SB, NXA = (STG + 1) % SA, NXB = (STG + 1) % SB;
-    constexpr int ALL = T::MI * T::NI;
-    constexpr int LOADS = NA + NB;
-    constexpr int GAPS = ALL - 1;                      // the first gap takes the LDS reads, the others the loads
-    constexpr int PER = (LOADS + GAPS - 1) / GAPS;
-    static_assert(GAPS >= 1, "a wave has at least two MFMA tiles");
-    steps<SGA, SGB, 0>(acc);
-    settle<T>(f1);
-    __builtin_amdgcn_sched_barrier(0);
-    wait_vmcnt<(SA - 2) * NA + (SB - 2) * NB>();       // slab kt+1 has landed
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    mma_one<0>(acc);
-    __builtin_amdgcn_sched_barrier(0);
-    load_frags<T, A_KS, B_KS, FRA, FRB, NXA * T::kABytes, NXB * T::kBBytes, 0>(f0, fa);
-    __builtin_amdgcn_sched_barrier(0);
-    interior_gaps<SGA, SGB, 1, PER>(kt, acc);
-  }
-  // MFMA number M of the last step (operands in f1)
-  template <int M>
-  __device__ __forceinline__ void mma_one(f32x16 (&acc)[T::MI][T::NI]) { mma<T, M, M + 1>(f1, acc); }
-  // load number J of the refill: the side whose slab is needed sooner comes first
-  template <int SGA, int SGB, int J>
-  __device__ __forceinline__ void refill_one(int kt) {
-    constexpr bool B_FIRST = SB <= SA;
-    constexpr int N1 = B_FIRST ? NB : NA;
-    if constexpr (J < N1) {
-      if constexpr (B_FIRST) db.issue_one(J, kt + SB, buf_b(SGB), wave); else da.issue_one(J, kt + SA, buf_a(SGA), wave);
-      if constexpr (J == N1 - 1) { if constexpr (B_FIRST) db.fetch_rows(kt + SB + 1); else da.fetch_rows(kt + SA + 1); }
-    } else if constexpr (J < NA + NB) {
-      if constexpr (B_FIRST) da.issue_one(J - N1, kt + SA, buf_a(SGA), wave); else db.issue_one(J - N1, kt + SB, buf_b(SGB), wave);
-      if constexpr (J == NA + NB - 1) { if constexpr (B_FIRST) da.fetch_rows(kt + SA + 1); else db.fetch_rows(kt + SB + 1); }
-    }
-  }
-  template <int SGA, int SGB, int J, int JEND>
-  __device__ __forceinline__ void refill_range(int kt) {
-    if constexpr (J < JEND) { refill_one<SGA, SGB, J>(kt); refill_range<SGA, SGB, J + 1, JEND>(kt); }
-  }
-  template <int SGA, int SGB, int M, int PER>
-  __device__ __forceinline__ void interior_gaps(int kt, f32x16 (&acc)[T::MI][T::NI]) {
-    if constexpr (M < T::MI * T::NI) {
-      mma_one<M>(acc);
-      __builtin_amdgcn_sched_barrier(0);
-      refill_range<SGA, SGB, (M - 1) * PER, M * PER>(kt);
-      __builtin_amdgcn_sched_barrier(0);
-      interior_gaps<SGA, SGB, M + 1, PER>(kt, acc);
-    }
-  }
-  template <int STG>
-  __device__ __forceinline__ void interior_trip(int& kt, f32x16 (&acc)[T::MI][T::NI]) {
-    if constexpr (STG < U) {
-      slab_interior<STG>(kt, acc);
-      ++kt;
-      interior_trip<STG + 1>(kt, acc);
-    }
-  }
-
-  template <int STG, bool ACTIVE>
-  __device__ __forceinline__ void run_from(int& kt, f32x16 (&acc)[T::MI][T::NI]) {
-    if constexpr (STG < U) {
-      if (kt < nslabs) {
-        slab_body<STG, ACTIVE>(kt, acc);
-        ++kt;
-        run_from<STG + 1, ACTIVE>(kt, acc);
-      }
-    }
-  }
-
-  template <bool ACTIVE>
-  __device__ __forceinline__ void stream(f32x16 (&acc)[T::MI][T::NI]) {
-    if constexpr (ACTIVE) load_frags<T, A_KS, B_KS, FRA, FRB, 0, 0, 0>(f0, fa);
-    int kt = 0;
-    if constexpr (ACTIVE) {
-#pragma nounroll
-      while (kt + U + (SA > SB ? SA : SB) <= nfull) {  // trips that only touch full slabs: the branch-free bodies
-        interior_trip<0>(kt, acc);
-      }
-    }
-#pragma nounroll
-    while (kt + U <= nslabs) {                         // U slabs per trip: buffers are compile-time
-      run_from<0, ACTIVE>(kt, acc);
-    }
-    run_from<0, ACTIVE>(kt, acc);                      // the remaining < U slabs
-    if constexpr (ACTIVE) settle<T>(f0);               // nothing is in flight into a register when the epilogue starts
-  }
-
-  // reduction length, LDS ring and the per-lane fragment offsets of this wave's sub-tile
-  __device__ __forceinline__ void prepare(int K_, char* lds_, const bf16_t* zeros_, const int (&a_row)[T::MI],
-                                          const int (&b_row)[T::NI]) {
-    const int tid = threadIdx.x, lane = tid & 63;
-    wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: LDS destinations stay scalar
-    lds = lds_; zeros = reinterpret_cast<const char*>(zeros_); K = K_;
+  __device__ __forceinline__ void prepare(int K_, char* lds_) {
+    wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: LDS destinations stay scalar
+    lds = lds_; K = K_;
     lds32 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)lds_));
-    nfull = K > 0 ? K / T::BK : 0;
-    nslabs = K > 0 ? (K + T::BK - 1) / T::BK : 0;
-    typedef FragAddrs<T, A_KS, B_KS> FA;
+    nslabs = K > 0 ? (KS_ONLY ? (K + T::BK - 1) / T::BK : K / T::BK) : 0;
+  }
+  // fragment addresses in the first buffers of the rings (first tile rows of this wave's sub-tile: a_row / b_row)
+  __device__ __forceinline__ void place(int a_row, int b_row, int lane) {
 #pragma unroll
-    for (int i = 0; i < FA::NA; ++i) {                 // k-strided: fragment i at step 0; k-contiguous: fragment 0 at step i
-      if constexpr (A_KS) fa.a[i] = lds32 + frag_off<true, T::BM, T::BK>(a_row[i], 0, lane);
-      else fa.a[i] = lds32 + frag_off<false, T::BM, T::BK>(a_row[0], i, lane);
-      if constexpr (FA::A_FAR) fa.a_far[i] = fa.a[i] + 65536;
+    for (int i = 0; i < NAA; ++i) {                    // k-strided: fragment i at step 0; k-contiguous: fragment 0 at step i
+      if constexpr (A_KS) aa[i] = lds32 + frag_off<true, T::BM, T::BK>(a_row + a_frag_row(i), 0, lane);
+      else aa[i] = lds32 + frag_off<false, T::BM, T::BK>(a_row, i, lane);
     }
 #pragma unroll
-    for (int i = 0; i < FA::NB; ++i) {
-      if constexpr (B_KS) fa.b[i] = lds32 + T::kBBase + frag_off<true, T::BN, T::BK>(b_row[i], 0, lane);
-      else fa.b[i] = lds32 + T::kBBase + frag_off<false, T::BN, T::BK>(b_row[0], i, lane);
-      if constexpr (FA::B_FAR) fa.b_far[i] = fa.b[i] + 65536;
+    for (int i = 0; i < NAB; ++i) {
+      if constexpr (B_KS) ab[i] = lds32 + T::kBBase + frag_off<true, T::BN, T::BK>(b_row + b_frag_row(i), 0, lane);
+      else ab[i] = lds32 + T::kBBase + frag_off<false, T::BN, T::BK>(b_row, i, lane);
     }
   }
-  // point the loads at the operands of a segment and fill both rings, slab by slab (A before B), as far as they go.
-  // The rings must be idle.
-  __device__ __forceinline__ void start(const Operand& oa, const Operand& ob) {
+  // point the loads at the operands and fill both rings, slab by slab (A before B).  The rings must be idle.
+  __device__ __forceinline__ void start(const Operand& oa, const Operand& ob, int a_row, int b_row) {
     const int lane = threadIdx.x & 63;
-    da.init(oa, wave, lane);
-    db.init(ob, wave, lane);
+    place(a_row, b_row, lane);
+    da.init(oa, K, nslabs, wave, lane);
+    db.init(ob, K, nslabs, wave, lane);
+    fill();
+  }
+  __device__ __forceinline__ void fill() {
+    stage_a = 0; stage_b = 0;
+    if (nslabs <= 0) return;
 #pragma unroll
     for (int s0 = 0; s0 < (SA > SB ? SA : SB); ++s0) {
-      if (s0 < SA && s0 < nslabs) issue_a(s0, s0);
-      if (s0 < SB && s0 < nslabs) issue_b(s0, s0);
+      if (s0 < SA) da.issue(s0, buf_a(s0), wave);
+      if (s0 < SB - 1) db.issue(s0, buf_b(s0), wave);
     }
   }
+  // Slabs k0 .. k1-1, the first of which has landed in the first buffers of the rings and is visible to all.
+  // `active` is false for a wave whose sub-tile holds no row of the expert (the tile sticks out of the row segment): it
+  // only takes part in the loads and barriers; its SIMD time goes to the other waves.
+  __device__ __forceinline__ void multiply(int k0, int k1, bool active, Acc<T>& acc) {
+    if (active) {
+      read_first();
+#pragma nounroll
+      for (int kt = k0; kt < k1; ++kt) slab(kt, acc);
+      all_arrived();                                   // nothing is in flight into a register when the epilogue starts
+      arrived_with_b<0, 0>(a[0]);
+    } else {
+#pragma nounroll
+      for (int kt = k0; kt < k1; ++kt) {
+        db.issue(kt + SB - 1, buf_b(stage_b == 0 ? SB - 1 : stage_b - 1), wave);
+        wait_vmcnt<kBeyond>();
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        da.issue(kt + SA, buf_a(stage_a), wave);
+        stage_a = next_stage(stage_a, SA); stage_b = next_stage(stage_b, SB);
+      }
+    }
+    wait_vmcnt<0>();                                   // the loads for slabs beyond the end write (zeros) into the rings too
+    __syncthreads();                                   // all reads and loads done before anything else uses the rings
+  }
   // multiply the segment whose first slabs have been enqueued by start()
-  __device__ __forceinline__ void go(bool active, f32x16 (&acc)[T::MI][T::NI]) {
+  __device__ __forceinline__ void go(bool active, Acc<T>& acc) {
     if (nslabs <= 0) return;
-    const int rest = nslabs - 1;                       // slabs beyond slab 0 that start() enqueued
-    wait_loads_in_flight<kMaxAhead, kStep>(min(SA - 1, rest) * NA + min(SB - 1, rest) * NB);   // slab 0 has landed
+    wait_vmcnt<kMaxAhead>();                           // slab 0 has landed
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    if (active) stream<true>(acc); else stream<false>(acc);
-    __syncthreads();                                   // all reads done before anything refills the rings
+    multiply(0, nslabs, active, acc);
+  }
+  // the reduction indices that do not fill a slab, where a side is k-contiguous: one slab on its own
+  __device__ __forceinline__ void tail(int a_row, int b_row, bool active, Acc<T>& acc) {
+    if constexpr (!KS_ONLY) {
+      if (K <= 0 || K % T::BK == 0) return;
+      const int lane = threadIdx.x & 63;
+      stage_a = 0; stage_b = 0;
+      da.issue_tail(nslabs, buf_a(0), wave, lane);
+      db.issue_tail(nslabs, buf_b(0), wave, lane);
+      place(a_row, b_row, lane);
+      wait_vmcnt<0>();
+      __syncthreads();
+      multiply(nslabs, nslabs + 1, active, acc);
+    }
   }
 
-  __device__ __forceinline__ void run(const Operand* opA, const Operand* opB, int nseg, int K_, char* lds_,
-                                      const bf16_t* zeros_, const int (&a_row)[T::MI], const int (&b_row)[T::NI],
-                                      bool active, f32x16 (&acc)[T::MI][T::NI]) {
-    prepare(K_, lds_, zeros_, a_row, b_row);
-    if (K <= 0) return;
+  __device__ __forceinline__ void run(const Operand& opA, const Operand& opB, int K_, char* lds_, int a_row, int b_row, bool active, Acc<T>& acc) {
+    prepare(K_, lds_);
+    start(opA, opB, a_row, b_row);
+    go(active, acc);
+    tail(a_row, b_row, active, acc);
+  }
+  // Two segments of K reduction indices each: columns 0 .. K-1 and K .. 2K-1 of the A side, opB and then opB2.  Whole
+  // slabs stream through as one reduction of 2K (the rings never drain); otherwise one segment follows the other.
+  __device__ __forceinline__ void run2(const Operand& opA, const Operand& opB, const Operand& opB2, int K_, char* lds_, int a_row, int b_row,
+                                       bool active, Acc<T>& acc) {
+    static_assert(TWO_SEG && !A_KS && B_KS && !A_GATHER, "");
+    const bool whole = K_ % T::BK == 0;
 #pragma nounroll
-    for (int seg = 0; seg < nseg; ++seg) {
-      Operand oa, ob;                                  // picked field by field: no dynamically indexed copies
-      oa.half[0] = seg ? opA[1].half[0] : opA[0].half[0];
-      oa.half[1] = seg ? opA[1].half[1] : opA[0].half[1];
-      oa.ld = opA[0].ld;
-      oa.valid[0] = opA[0].valid[0];
-      oa.valid[1] = opA[0].valid[1];
-      oa.gather = opA[0].gather;
-      oa.grow = opA[0].grow;
-      ob.half[0] = seg ? opB[1].half[0] : opB[0].half[0];
-      ob.half[1] = seg ? opB[1].half[1] : opB[0].half[1];
-      ob.ld = opB[0].ld;
-      ob.valid[0] = opB[0].valid[0];
-      ob.valid[1] = opB[0].valid[1];
-      ob.gather = opB[0].gather;
-      ob.grow = opB[0].grow;
-      start(oa, ob);
+    for (int seg = 0; seg < (whole ? 1 : 2); ++seg) {
+      Operand oa = opA, ob = opB;
+      if (seg) { oa.half[0] += K_; oa.half[1] += K_; ob.half[0] = opB2.half[0]; ob.half[1] = opB2.half[1]; }
+      prepare(whole ? 2 * K_ : K_, lds_);
+      const int lane = threadIdx.x & 63;
+      place(a_row, b_row, lane);
+      da.init(oa, K, nslabs, wave, lane);
+      db.init(ob, K_, nslabs, wave, lane);
+      db.seg_slabs = whole ? K_ / T::BK : 0x7FFFFFFF;
+      db.seg_delta = whole ? reinterpret_cast<const char*>(opB2.half[0]) - reinterpret_cast<const char*>(opB.half[0]) - db.seg_slabs * db.step : 0L;
+      fill();
       go(active, acc);
+      tail(a_row, b_row, active, acc);
     }
   }
 };
 
 // ---- epilogue: accumulators -> LDS (fp32) -> 16-byte row-contiguous global accesses -----------------
-// The products are accumulated transposed (mma() hands the MFMA the weight-side fragment as its first
-// operand): of the 32x32 tile (mi, ni) a lane then holds tile row lane%32 and, for g = 0..3, the four
-// consecutive columns 8g + 4*(lane/32) .. +3 in elements 4g .. 4g+3.  Each wave parks a 32-row strip of its
-// sub-tile in its own quarter of the (now idle) LDS ring with 16-byte writes -- 4 per MFMA tile instead of
-// 16 four-byte ones; a wave can have only 15 LDS operations outstanding and the other workgroup of the CU
-// keeps the LDS busy, so the number of operations is what the epilogue costs -- and reads it back
-// row-major, 8 consecutive columns per lane.
+// The products are accumulated transposed (the MFMA is handed the weight-side fragment as its first operand): of the
+// 16x16 tile (i, j) a lane then holds tile row lane%16 and the four consecutive columns 4*(lane/16) .. +3.  Each wave
+// parks a 32-row strip of its sub-tile in its own part of the (now idle) LDS ring with 16-byte writes and reads it
+// back row-major, 8 consecutive columns per lane.  (The 8-bit products use 32x32 tiles: a lane holds row lane%32 and,
+// for g = 0..3, the four consecutive columns 8g + 4*(lane/32) .. +3 in elements 4g .. 4g+3.)
 template <class T> struct Strip {
   static constexpr int LD = T::WN + 4;                 // floats per staged row: consecutive rows shift the banks by 4, so the 16 lanes
                                                        // the LDS serves per cycle (16 rows, 16 bytes each) cover all 64 banks
@@ -668,6 +684,18 @@ template <class T> struct Strip {
   static_assert(LD % 64 == 4, "bank rotation of the parked rows");
 };
 
+// strip number `mi`: rows 32 mi .. +31 of the wave's sub-tile
+template <class T>
+__device__ __forceinline__ void park_strip(const Acc<T>& acc, int mi, float* strip, int lane) {
+  float* row = strip + (lane & 15) * Strip<T>::LD + 4 * (lane >> 4);
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int j = 0; j < T::FN; ++j) {
+      const f32x4 v = acc[2 * mi + h][j];
+      *reinterpret_cast<float4*>(row + h * 16 * Strip<T>::LD + j * 16) = make_float4(v[0], v[1], v[2], v[3]);
+    }
+}
 template <class T>
 __device__ __forceinline__ void park_strip(const f32x16 (&acc_mi)[T::NI], float* strip, int lane) {
   float* row = strip + (lane & 31) * Strip<T>::LD + 4 * (lane >> 5);
@@ -684,6 +712,20 @@ __device__ __forceinline__ void park_strip(const f32x16 (&acc_mi)[T::NI], float*
 // no padding; the 16-byte pieces of a row are XORed with the row index, which keeps the row-major 16-byte reads
 // free of bank conflicts (16 lanes = 256 consecutive bytes) and spreads the 32 rows of a parking write over
 // 16 different pieces.
+template <class T>
+__device__ __forceinline__ void park_strip_bf16(const Acc<T>& acc, int mi, char* strip, int lane) {
+  constexpr int PPR = T::WN / 8;                       // 16-byte pieces per staged row
+  const int r = lane & 15;                             // rows r and r + 16 have the same swizzle
+  char* row = strip + r * (T::WN * 2) + 8 * ((lane >> 4) & 1);
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int j = 0; j < T::FN; ++j) {
+      const f32x4 v = acc[2 * mi + h][j];
+      *reinterpret_cast<uint2*>(row + h * 16 * (T::WN * 2) + (((2 * j + (lane >> 5)) ^ (r & (PPR - 1))) << 4)) =
+          make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+    }
+}
 template <class T>
 __device__ __forceinline__ void park_strip_bf16(const f32x16 (&acc_mi)[T::NI], char* strip, int lane) {
   constexpr int PPR = T::WN / 8;                       // 16-byte pieces per staged row
@@ -748,14 +790,12 @@ struct RowTiles {
   int32_t* expert;       // [max_tiles]
   int32_t* row0;         // [max_tiles]
   int max_tiles;
-  uint32_t* zeros;       // [64] block of zeros the GEMM kernels read for out-of-range reduction indices
 };
 
 __device__ __forceinline__ void build_row_tiles(const int32_t* __restrict__ offsets, int E, int P, int bm, RowTiles rt) {
   __shared__ int32_t scan[kMaxExperts];     // inclusive scan of the row tiles per expert
   __shared__ int32_t first_row[kMaxExperts];
   const int e = threadIdx.x;
-  if (e < 64) rt.zeros[e] = 0u;
   int begin = 0, end = 0, nt = 0;
   if (e < E) {                                       // offsets == null: one segment holding all P rows
     begin = offsets ? min(max(offsets[e], 0), P) : 0;
@@ -799,13 +839,13 @@ __device__ __forceinline__ int xcd_remap(int b, int total) {
 }
 
 template <class T>
-__device__ __forceinline__ void zero_acc(f32x16 (&acc)[T::MI][T::NI]) {
+__device__ __forceinline__ void zero_acc(Acc<T>& acc) {
 #pragma unroll
-  for (int i = 0; i < T::MI; ++i)
+  for (int i = 0; i < T::FM; ++i)
 #pragma unroll
-    for (int j = 0; j < T::NI; ++j)
+    for (int j = 0; j < T::FN; ++j)
 #pragma unroll
-      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.0f;
+      for (int q = 0; q < 4; ++q) acc[i][j][q] = 0.0f;
 }
 
 // Hands back its argument through an empty asm: values derived from the result cannot be computed before
@@ -838,7 +878,6 @@ struct RowArgs {
   int accumulate;          // kRouterDx: add to what out0 holds
   const bf16_t* g;         // kDAct: saved pre-activations
   const bf16_t* u;
-  const bf16_t* zeros;     // at least 16 zero bytes (source of out-of-range reduction indices)
   // FUSED kernels: `a` is the token-major matrix [T, lda] and row r of the product reads a[row_token[r]]
   const int32_t* row_token;    // [P (+ padding)]
   const float* row_w;          // kDAct: combine weight of each row; the product's rows are scaled by it
@@ -857,7 +896,7 @@ template <int KIND, class T, bool FUSED = false>
 __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::kWavesPerSimd, T::kWavesPerSimd))) void row_grouped_kernel(RowArgs p) {
   static_assert(!FUSED || KIND == kGateUp || KIND == kDAct, "only the two products that read activations by token are fused");
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  constexpr int BM = T::BM, BN = T::BN, WM = T::WM, WN = T::WN, MI = T::MI, NI = T::NI;
+  constexpr int BM = T::BM, BN = T::BN, WM = T::WM, WN = T::WN, MI = T::MI;
   const int n_row_tiles = p.rt.count[0];
   const int v = xcd_remap(blockIdx.x, n_row_tiles * p.n_tiles_n);
   if (v < 0) return;
@@ -869,18 +908,14 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / T::WGN, wn = wave % T::WGN;
 
-  f32x16 acc[MI][NI];
+  Acc<T> acc;
   zero_acc<T>(acc);
 
-  int a_row[MI];
-#pragma unroll
-  for (int i = 0; i < MI; ++i) a_row[i] = wm * WM + i * 32;
-  // 32-row fragments of this wave that hold rows of the expert (wave-uniform); a wave without any
+  const int a_row = wm * WM;                           // first tile row of this wave
+  // 32-row strips of this wave that hold rows of the expert (wave-uniform); a wave without any
   // skips the arithmetic, and the epilogue skips strips without rows
   const int mi_n = __builtin_amdgcn_readfirstlane(min(MI, max(0, (rows - wm * WM + 31) / 32)));
-  Operand opsA[2], opsB[2];
-  Operand& opA = opsA[0];
-  Operand& opB = opsB[0];
+  Operand opA, opB;
   opA.ld = p.lda;
   opA.valid[0] = min(rows, BM / 2);
   opA.valid[1] = max(rows - BM / 2, 0);
@@ -895,17 +930,14 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   if constexpr (KIND == kGateUp) {
     // tile columns: BN/2 gate columns n0.. and the matching BN/2 up columns; each wave gets the
     // same gate and up columns so the SwiGLU product needs no exchange between lanes
-    constexpr int HN = BN / 2, HW = WN / 2, HI = NI / 2;
+    constexpr int HN = BN / 2, HW = WN / 2;
     const int n0 = nt * HN;
     const int ncols = min(HN, p.N - n0);
-    int b_row[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) b_row[i] = (i < HI ? 0 : HN) + wn * HW + (i % HI) * 32;
+    const int b_row = wn * HW;                         // the up fragments lie HN tile rows further
     opB.half[0] = p.w0 + e * p.w_expert_stride + static_cast<long>(n0) * p.ldw;
     opB.half[1] = p.w1 + e * p.w_expert_stride + static_cast<long>(n0) * p.ldw;
     opB.valid[0] = opB.valid[1] = ncols;
-    static_assert(HI == 1, "the wave's gate fragment and its up fragment: two fragments BN/2 tile rows apart");
-    { MainLoop<T, false, false, FUSED, false, HN> ml; ml.run(opsA, opsB, 1, p.K, lds, p.zeros, a_row, b_row, mi_n > 0, acc); }
+    { MainLoop<T, false, false, FUSED, false, HN> ml; ml.run(opA, opB, p.K, lds, a_row, b_row, mi_n > 0, acc); }
     // strip columns: [0, HW) gate, [WN/2 + 0, ...) up -- both halves hold the same output columns
     float* strip = reinterpret_cast<float*>(lds + T::kStripBase + wave * Strip<T>::kBytes);
     const int el = not_before_here(lane);             // this lane, for the epilogue
@@ -918,7 +950,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
       if (mi >= mi_n) break;
-      park_strip<T>(acc[mi], strip, el);
+      park_strip<T>(acc, mi, strip, el);
       float g[NP][8], u[NP][8], wr[NP];
 #pragma unroll
       for (int pass = 0; pass < NP; ++pass) {           // the rows' combine weights, if the activation is to carry them
@@ -949,32 +981,27 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   } else {
     const int n0 = nt * BN;
     const int ncols = min(BN, p.N - n0);
-    int b_row[NI];
-#pragma unroll
-    for (int i = 0; i < NI; ++i) b_row[i] = wn * WN + i * 32;
+    const int b_row = wn * WN;
     opB.valid[0] = min(ncols, BN / 2);
     opB.valid[1] = max(ncols - BN / 2, 0);
     if constexpr (KIND == kDown || KIND == kRouterFwd) {
       // yp = act * Wd[e]^T (logits = x * Wr^T): weight rows are output columns, reduction contiguous
       opB.half[0] = p.w0 + e * p.w_expert_stride + static_cast<long>(n0) * p.ldw;
       opB.half[1] = opB.half[0] + (BN / 2) * p.ldw;
-      { MainLoop<T, false, false> ml; ml.run(opsA, opsB, 1, p.K, lds, p.zeros, a_row, b_row, mi_n > 0, acc); }
+      { MainLoop<T, false, false> ml; ml.run(opA, opB, p.K, lds, a_row, b_row, mi_n > 0, acc); }
     } else if constexpr (KIND == kDAct || KIND == kRouterDx) {
       // dA = dyp * Wd[e] (dx = dz * Wr): weight is [K, N], reduction strided
       opB.half[0] = p.w0 + e * p.w_expert_stride + n0;
       opB.half[1] = opB.half[0] + BN / 2;
-      { MainLoop<T, false, true, FUSED, false> ml; ml.run(opsA, opsB, 1, p.K, lds, p.zeros, a_row, b_row, mi_n > 0, acc); }
+      { MainLoop<T, false, true, FUSED, false> ml; ml.run(opA, opB, p.K, lds, a_row, b_row, mi_n > 0, acc); }
     } else {
       // dxp = dG * Wg[e] + dU * Wu[e] : two reduction segments over the columns of [dG | dU]
       opB.half[0] = p.w0 + e * p.w_expert_stride + n0;
       opB.half[1] = opB.half[0] + BN / 2;
-      opsA[1] = opA;
-      opsA[1].half[0] += p.K;
-      opsA[1].half[1] += p.K;
-      opsB[1] = opB;
-      opsB[1].half[0] = p.w1 + e * p.w_expert_stride + n0;
-      opsB[1].half[1] = opsB[1].half[0] + BN / 2;
-      { MainLoop<T, false, true> ml; ml.run(opsA, opsB, 2, p.K, lds, p.zeros, a_row, b_row, mi_n > 0, acc); }
+      Operand opB2 = opB;
+      opB2.half[0] = p.w1 + e * p.w_expert_stride + n0;
+      opB2.half[1] = opB2.half[0] + BN / 2;
+      { MainLoop<T, false, true, false, false, T::WN / 2, true> ml; ml.run2(opA, opB, opB2, p.K, lds, a_row, b_row, mi_n > 0, acc); }
     }
 
     float* strip = reinterpret_cast<float*>(lds + T::kStripBase + wave * Strip<T>::kBytes);
@@ -990,7 +1017,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
 #pragma unroll
       for (int mi = 0; mi < MI; ++mi) {
         if (mi >= mi_n) break;
-        park_strip<T>(acc[mi], strip, el);
+        park_strip<T>(acc, mi, strip, el);
 #pragma unroll
         for (int p0 = 0; p0 < NP; p0 += CH) {
           uint4 gq[CH], uq[CH];
@@ -1058,7 +1085,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
 #pragma unroll
       for (int mi = 0; mi < MI; ++mi) {
         if (mi >= mi_n) break;
-        park_strip_bf16<T>(acc[mi], reinterpret_cast<char*>(strip), el);
+        park_strip_bf16<T>(acc, mi, reinterpret_cast<char*>(strip), el);
         uint4 v[NP];
 #pragma unroll
         for (int pass = 0; pass < NP; ++pass)
@@ -1074,7 +1101,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
       if (mi >= mi_n) break;
-      park_strip<T>(acc[mi], strip, el);
+      park_strip<T>(acc, mi, strip, el);
       float v[NP][8];
 #pragma unroll
       for (int pass = 0; pass < NP; ++pass)
@@ -1232,17 +1259,11 @@ struct WgradArgs {
   int tiles_m, tiles_n;
   bf16_t* out0; bf16_t* out1; int m_split;     // out1 rows are (m - m_split)
   float* partial;                              // [max_slots][M][N]
-  const bf16_t* zeros;     // at least 16 zero bytes
   const int32_t* row_token;    // GATHER kernels: [P + padding], token of each expert-ordered row
   // a side job of the reduction launch that follows dW_down in the gathered backward (null: none): the partial dot
   // products of the combine-weight gradient, one per (column slot, row), are added in slot order and scattered to [T, k]
   const float* dw_partial; int dw_slots; const int32_t* pair_of_row; float* dtopk_w;
 };
-
-// Column tiles one workgroup of a weight-gradient product takes in turn (see the kernel).  Measured in the layer
-// step: two for [dW_gate; dW_up] (7 % faster at 512 rows per expert, no change at 2560), one for dW_down (with two
-// or all three of its column tiles per workgroup it is 15-40 % slower).
-template <class T, int WHICH> constexpr int kWgradSpan = (T::kWaves == 8 && T::BM == 256 && WHICH == 1) ? 2 : 1;
 
 // WHICH 0: dW_down, 1: [dW_gate; dW_up], 2: router (separate symbols so profiles tell them apart).
 // GATHER: the operand that holds one row per token -- lhs for WHICH 0 (the output gradient), rhs for WHICH 1
@@ -1252,22 +1273,17 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   static_assert(!GATHER || WHICH < 2, "the router's operands are token-major already");
   constexpr bool GA = GATHER && WHICH == 0, GB = GATHER && WHICH == 1;
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  constexpr int BM = T::BM, BN = T::BN, WM = T::WM, WN = T::WN, MI = T::MI, NI = T::NI;
-  // A workgroup takes kWgradSpan<T, WHICH> column tiles of one (work item, row tile) in turn: they share the lhs
-  // panel, and where the staging strips sit behind the first stage the first slab of the next tile is
-  // already on its way while the epilogue of the current one runs.
-  constexpr int SPAN = kWgradSpan<T, WHICH>;
-  const int spans_n = (p.tiles_n + SPAN - 1) / SPAN;
-  const int per_e = p.tiles_m * spans_n;
+  constexpr int BM = T::BM, BN = T::BN, WM = T::WM, WN = T::WN, MI = T::MI;
+  const int per_e = p.tiles_m * p.tiles_n;
   const int n_items = p.items.count[0];
   // order of a work item's tiles: row tile fastest for [dW_gate; dW_up] (neighbouring workgroups share the rhs panel;
-  // measured 6 % faster at 512 rows per expert), column span fastest for the others
+  // measured 6 % faster at 512 rows per expert), column tile fastest for the others
   constexpr bool MT_FASTEST = WHICH == 1;
   // Work items come sorted by length, so consecutive stretches of the list differ in work: they are dealt to the
   // XCDs (workgroup b runs on XCD b % 8) in turn, in units of 1/g of an item's tiles -- whole items while there
   // are at least 8 per XCD, otherwise g runs of the slow tile index, so that under skewed routing every XCD still
   // gets several units of the few long items.  A unit's workgroups are consecutive on their XCD (shared panels).
-  const int slow = MT_FASTEST ? spans_n : p.tiles_m;
+  const int slow = MT_FASTEST ? p.tiles_n : p.tiles_m;
   int g = 1;
   while (g < slow && (n_items * g < 8 * kXcds || slow % g != 0)) ++g;
   const int per_u = per_e / g;                          // g divides slow, so it divides per_e
@@ -1275,8 +1291,8 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   if (unit >= n_items * g) return;
   const int item = unit / g;
   const int vi = (unit % g) * per_u + (blockIdx.x / kXcds) % per_u;   // position among the item's tiles
-  const int mt = MT_FASTEST ? vi % p.tiles_m : vi / spans_n;
-  const int nt0 = (MT_FASTEST ? vi / p.tiles_m : vi % spans_n) * SPAN;
+  const int mt = MT_FASTEST ? vi % p.tiles_m : vi / p.tiles_n;
+  const int nt = MT_FASTEST ? vi / p.tiles_m : vi % p.tiles_n;
   const int e = p.items.expert[item];
   const int slot = p.items.slot[item];
   if (slot == -2) return;
@@ -1286,12 +1302,8 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / T::WGN, wn = wave % T::WGN;
 
-  f32x16 acc[MI][NI];
-  int a_row[MI], b_row[NI];
-#pragma unroll
-  for (int i = 0; i < MI; ++i) a_row[i] = wm * WM + i * 32;
-#pragma unroll
-  for (int i = 0; i < NI; ++i) b_row[i] = wn * WN + i * 32;
+  Acc<T> acc;
+  const int a_row = wm * WM, b_row = wn * WN;
   Operand opA, opB;
   opA.ld = p.ld_lhs;
   opA.half[0] = p.lhs + (GA ? 0L : static_cast<long>(begin) * p.ld_lhs) + m0;
@@ -1303,75 +1315,57 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   opB.ld = p.ld_rhs;
   opB.gather = GB ? p.row_token : nullptr;
   opB.grow = begin;
-  auto point_b = [&](int nt) {                         // rhs columns of column tile nt
-    const int n0 = nt * BN, ncols = min(BN, p.N - n0);
-    opB.half[0] = p.rhs + (GB ? 0L : static_cast<long>(begin) * p.ld_rhs) + n0;
-    opB.half[1] = opB.half[0] + BN / 2;
-    opB.valid[0] = min(ncols, BN / 2);
-    opB.valid[1] = max(ncols - BN / 2, 0);
-  };
-  MainLoop<T, true, true, GA, GB> ml;
-  ml.prepare(end - begin, lds, p.zeros, a_row, b_row);
-  point_b(nt0);
-  ml.start(opA, opB);
+  const int n0 = nt * BN, ncols = min(BN, p.N - n0);
+  opB.half[0] = p.rhs + (GB ? 0L : static_cast<long>(begin) * p.ld_rhs) + n0;
+  opB.half[1] = opB.half[0] + BN / 2;
+  opB.valid[0] = min(ncols, BN / 2);
+  opB.valid[1] = max(ncols - BN / 2, 0);
+  zero_acc<T>(acc);
+  { MainLoop<T, true, true, GA, GB> ml; ml.run(opA, opB, end - begin, lds, a_row, b_row, true, acc); }
 
   float* strip = reinterpret_cast<float*>(lds + T::kStripBase + wave * Strip<T>::kBytes);
   constexpr int LPR = WN / 8;
   constexpr int RPP = 64 / LPR;
-  float* part = slot >= 0 ? p.partial + static_cast<long>(slot) * p.M * p.N : nullptr;
   constexpr int NP = 32 / RPP;                         // passes per strip; all their LDS reads are issued before the first is used
-#pragma nounroll
-  for (int t = 0; t < SPAN; ++t) {
-    const int nt = nt0 + t;
-    if (nt >= p.tiles_n) break;
-    const int n0 = nt * BN, ncols = min(BN, p.N - n0);
-    zero_acc<T>(acc);
-    ml.go(true, acc);
-    const bool more = t + 1 < SPAN && nt + 1 < p.tiles_n;
-    if (more) point_b(nt + 1);
-    const int el = not_before_here(lane);             // this lane, for the epilogue
-    const int cl = wn * WN + (el % LPR) * 8;
-    if (part) {                                        // chunk of a split expert: fp32 partial tile
+  float* part = slot >= 0 ? p.partial + static_cast<long>(slot) * p.M * p.N : nullptr;
+  const int el = not_before_here(lane);                // this lane, for the epilogue
+  const int cl = wn * WN + (el % LPR) * 8;
+  if (part) {                                        // chunk of a split expert: fp32 partial tile
 #pragma unroll
-      for (int mi = 0; mi < MI; ++mi) {
-        park_strip<T>(acc[mi], strip, el);
-        float v[NP][8];
+    for (int mi = 0; mi < MI; ++mi) {
+      park_strip<T>(acc, mi, strip, el);
+      float v[NP][8];
 #pragma unroll
-        for (int pass = 0; pass < NP; ++pass)
-          read8(strip + (pass * RPP + el / LPR) * Strip<T>::LD + (el % LPR) * 8, v[pass]);
+      for (int pass = 0; pass < NP; ++pass)
+        read8(strip + (pass * RPP + el / LPR) * Strip<T>::LD + (el % LPR) * 8, v[pass]);
 #pragma unroll
-        for (int pass = 0; pass < NP; ++pass) {
-          const int rl = wm * WM + mi * 32 + pass * RPP + el / LPR;
-          if (cl < ncols && rl < mrows) {
-            float* o = part + static_cast<long>(m0 + rl) * p.N + n0 + cl;
-            store16(o, v[pass][0], v[pass][1], v[pass][2], v[pass][3]);
-            store16(o + 4, v[pass][4], v[pass][5], v[pass][6], v[pass][7]);
-          }
-        }
-      }
-    } else {                                           // whole expert: rounded once, staged as bf16
-#pragma unroll
-      for (int mi = 0; mi < MI; ++mi) {
-        park_strip_bf16<T>(acc[mi], reinterpret_cast<char*>(strip), el);
-        uint4 v[NP];
-#pragma unroll
-        for (int pass = 0; pass < NP; ++pass)
-          v[pass] = read_strip_bf16<T>(reinterpret_cast<const char*>(strip), pass * RPP + el / LPR, el % LPR);
-#pragma unroll
-        for (int pass = 0; pass < NP; ++pass) {
-          const int rl = wm * WM + mi * 32 + pass * RPP + el / LPR;
-          if (cl < ncols && rl < mrows) {
-            const int m = m0 + rl;
-            bf16_t* out = m < p.m_split ? p.out0 + (static_cast<long>(e) * p.m_split + m) * p.N
-                                        : p.out1 + (static_cast<long>(e) * (p.M - p.m_split) + (m - p.m_split)) * p.N;
-            store16(out + n0 + cl, v[pass]);
-          }
+      for (int pass = 0; pass < NP; ++pass) {
+        const int rl = wm * WM + mi * 32 + pass * RPP + el / LPR;
+        if (cl < ncols && rl < mrows) {
+          float* o = part + static_cast<long>(m0 + rl) * p.N + n0 + cl;
+          store16(o, v[pass][0], v[pass][1], v[pass][2], v[pass][3]);
+          store16(o + 4, v[pass][4], v[pass][5], v[pass][6], v[pass][7]);
         }
       }
     }
-    if (more) {
-      __syncthreads();                                 // every wave is done with its strip: the rings may be refilled
-      ml.start(opA, opB);
+  } else {                                           // whole expert: rounded once, staged as bf16
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) {
+      park_strip_bf16<T>(acc, mi, reinterpret_cast<char*>(strip), el);
+      uint4 v[NP];
+#pragma unroll
+      for (int pass = 0; pass < NP; ++pass)
+        v[pass] = read_strip_bf16<T>(reinterpret_cast<const char*>(strip), pass * RPP + el / LPR, el % LPR);
+#pragma unroll
+      for (int pass = 0; pass < NP; ++pass) {
+        const int rl = wm * WM + mi * 32 + pass * RPP + el / LPR;
+        if (cl < ncols && rl < mrows) {
+          const int m = m0 + rl;
+          bf16_t* out = m < p.m_split ? p.out0 + (static_cast<long>(e) * p.m_split + m) * p.N
+                                      : p.out1 + (static_cast<long>(e) * (p.M - p.m_split) + (m - p.m_split)) * p.N;
+          store16(out + n0 + cl, v[pass]);
+        }
+      }
     }
   }
 }
@@ -1419,12 +1413,12 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradArgs p) {
 // Host side
 // ============================================================================================
 // Tile shapes in use.
-//   TileBig: 256 x 256 outputs, 64-wide slabs, one 8-wave workgroup per CU (2 x 4 wavefronts of 128 x 64), two
-//     stages of 64 KiB.  A slab row is a whole 128-byte line: the fewest L2 requests per flop that fit the CU.
-//   TileBigW16: the TileBig ring under 16 waves (4 x 4 of 64 x 64, four per SIMD, 128 VGPRs) for the weight
-//     gradients: both their operands are read transposed (twice the LDS read instructions per MFMA), and four
-//     waves per SIMD cover that better -- 3-5 % faster on dW_down at every size and on [dW_gate; dW_up] from
-//     about 1000 rows per expert; the row products are 2-5 % slower with it and keep 8 waves.
+//   TileBig: 256 x 256 outputs, 64-wide slabs, one 8-wave workgroup per CU (2 x 4 wavefronts of 128 x 64), rings of
+//     2 + 3 slab buffers of 32 KiB.  A slab row is a whole 128-byte line: the fewest L2 requests per flop that fit the CU.
+//   TileBigW16: the same tile and rings under 16 waves (4 x 4 of 64 x 64, four per SIMD, 128 VGPRs) for the weight
+//     gradients: both their operands are read transposed (twice the LDS instructions per fragment), and four
+//     waves per SIMD cover that better: [dW_gate; dW_up] 510-516 us against 529-532 with 8 waves at 512 rows per expert,
+//     1837 against 1940 at 2560; dW_down 259 against 261 and 911 against 967.  The row products keep 8 waves.
 //   TileRouter: 64 x 128 x 64 for the skinny products with N = E, two workgroups per CU.
 typedef Tile<256, 256, 64, 2, 4, 2, 3> TileBig;
 typedef Tile<256, 256, 64, 4, 4, 2, 3> TileBigW16;
@@ -1452,13 +1446,12 @@ static int wgrad_max_slots(int P) { return wgrad_max_slots(P, wgrad_chunk_rows(P
 static int router_chunk_rows(int T) { return std::max(256, static_cast<int>(align_up(static_cast<size_t>(ceil_div(T, 64)), 256))); }
 
 struct WsLayout {
-  size_t tiles_count, zeros, tiles_expert, tiles_row0, dgu, g, u, items, partial, total;
+  size_t tiles_count, tiles_expert, tiles_row0, dgu, g, u, items, partial, total;
 };
 static WsLayout ws_layout(int P, int d, int f, int E, bool need_dgu, bool need_gu) {
   WsLayout w{};
   size_t off = 0;
   w.tiles_count = off; off += 256;
-  w.zeros = off; off += 256;
   const size_t t = align_up(static_cast<size_t>(max_row_tiles(P, E)) * sizeof(int32_t), 256);
   w.tiles_expert = off; off += t;
   w.tiles_row0 = off; off += t;
@@ -1488,7 +1481,6 @@ static RowTiles row_tiles_at(void* ws, const WsLayout& w, int P, int E) {
   RowTiles rt;
   rt.max_tiles = max_row_tiles(P, E);
   rt.count = reinterpret_cast<int32_t*>(b + w.tiles_count);
-  rt.zeros = reinterpret_cast<uint32_t*>(b + w.zeros);
   rt.expert = reinterpret_cast<int32_t*>(b + w.tiles_expert);
   rt.row0 = reinterpret_cast<int32_t*>(b + w.tiles_row0);
   return rt;
@@ -1547,14 +1539,15 @@ static void launch_row(const RowArgs& p, int P, int E, hipStream_t s) {
   launch_row_t<KIND, TileBig, FUSED>(p, P, E, s);
 }
 
-template <int WHICH, class T, bool GATHER = false>
-static void launch_wgrad_t(WgradArgs p, hipStream_t s) {
+template <int WHICH, bool GATHER = false>
+static void launch_wgrad(WgradArgs p, hipStream_t s) {
+  typedef TileBigW16 T;
   static LdsGrant grant;
   if (!allow_lds(grant, reinterpret_cast<const void*>(&wgrad_kernel<WHICH, T, GATHER>), T::kLdsAlloc, "wgrad")) return;
   p.tiles_m = ceil_div(p.M, T::BM);
   p.tiles_n = ceil_div(p.N, T::BN);
   // units are dealt to the XCDs in groups of 8, the last group may be partial: up to 8 more units than items
-  const unsigned grid = padded_grid(p.tiles_m * ceil_div(p.tiles_n, kWgradSpan<T, WHICH>) * (p.items.max_items + kXcds));
+  const unsigned grid = padded_grid(p.tiles_m * p.tiles_n * (p.items.max_items + kXcds));
   MOE_LAUNCH(WHICH == 0 ? "wgrad_down" : WHICH == 1 ? "wgrad_gate_up" : "wgrad_router", (wgrad_kernel<WHICH, T, GATHER>), dim3(grid),
              dim3(T::kThreads), T::kLdsAlloc, s, p);
   // the reduction loops are grid-strided: a launch with nothing to reduce (balanced routing) should cost as little as a launch can
@@ -1563,16 +1556,6 @@ static void launch_wgrad_t(WgradArgs p, hipStream_t s) {
   const dim3 rgrid(static_cast<unsigned>(std::min(rblocks, 2048L)));
   MOE_LAUNCH(WHICH == 0 ? "wgrad_down_reduce" : WHICH == 1 ? "wgrad_gate_up_reduce" : "wgrad_router_reduce", wgrad_reduce_kernel, rgrid,
              dim3(256), 0, s, p);
-}
-
-template <int WHICH, bool GATHER = false>
-static void launch_wgrad(const WgradArgs& p, hipStream_t s) {
-  // [dW_gate; dW_up] with short reductions is faster with TileBig's paired column tiles
-  if (WHICH == 0 || (WHICH == 1 && p.P >= 1536L * p.E)) {
-    if constexpr (WHICH < 2) launch_wgrad_t<WHICH, TileBigW16, GATHER>(p, s);
-  } else {
-    launch_wgrad_t<WHICH, TileBig, GATHER>(p, s);
-  }
 }
 
 // row_token == null: xp is in expert order; else xp is the token-major input and rows are gathered from it
@@ -1585,7 +1568,7 @@ static void launch_gate_up(const void* xp, const void* wg, const void* wu, int P
   p.a = static_cast<const bf16_t*>(xp); p.lda = d;
   p.w0 = static_cast<const bf16_t*>(wg); p.w1 = static_cast<const bf16_t*>(wu);
   p.w_expert_stride = static_cast<long>(f) * d; p.ldw = d;
-  p.K = d; p.N = f; p.offsets = offsets; p.P = P; p.rt = rt; p.zeros = reinterpret_cast<const bf16_t*>(rt.zeros);
+  p.K = d; p.N = f; p.offsets = offsets; p.P = P; p.rt = rt;
   p.out0 = static_cast<bf16_t*>(G); p.out1 = static_cast<bf16_t*>(U); p.out2 = static_cast<bf16_t*>(act); p.ldo = f;
   if (row_token) launch_row<kGateUp, true>(p, P, E, s);
   else launch_row<kGateUp>(p, P, E, s);
@@ -1596,7 +1579,7 @@ static void launch_down(const void* act, const void* wd, int P, int d, int f, in
   RowArgs p{};
   p.a = static_cast<const bf16_t*>(act); p.lda = f;
   p.w0 = static_cast<const bf16_t*>(wd); p.w_expert_stride = static_cast<long>(d) * f; p.ldw = f;
-  p.K = f; p.N = d; p.offsets = offsets; p.P = P; p.rt = rt; p.zeros = reinterpret_cast<const bf16_t*>(rt.zeros);
+  p.K = f; p.N = d; p.offsets = offsets; p.P = P; p.rt = rt;
   p.out0 = static_cast<bf16_t*>(yp); p.ldo = d;
   launch_row<kDown>(p, P, E, s);
 }
@@ -1607,7 +1590,7 @@ static void launch_dx(const bf16_t* dgu, const void* wg, const void* wu, int P, 
   p.a = dgu; p.lda = 2L * f;
   p.w0 = static_cast<const bf16_t*>(wg); p.w1 = static_cast<const bf16_t*>(wu);
   p.w_expert_stride = static_cast<long>(f) * d; p.ldw = d;
-  p.K = f; p.N = d; p.offsets = offsets; p.P = P; p.rt = rt; p.zeros = reinterpret_cast<const bf16_t*>(rt.zeros);
+  p.K = f; p.N = d; p.offsets = offsets; p.P = P; p.rt = rt;
   p.out0 = static_cast<bf16_t*>(dxp); p.ldo = d;
   launch_row<kDX>(p, P, E, s);
 }
@@ -1645,7 +1628,7 @@ void ffn_bwd_bf16(const FfnBwdArgs& a) {
     RowArgs p{};
     p.a = static_cast<const bf16_t*>(a.dyp); p.lda = a.d;
     p.w0 = static_cast<const bf16_t*>(a.w_down); p.w_expert_stride = static_cast<long>(a.d) * a.f; p.ldw = a.f;
-    p.K = a.d; p.N = a.f; p.offsets = a.offsets; p.P = a.P; p.rt = rt; p.zeros = reinterpret_cast<const bf16_t*>(rt.zeros);
+    p.K = a.d; p.N = a.f; p.offsets = a.offsets; p.P = a.P; p.rt = rt;
     p.out0 = dgu; p.ldo = 2L * a.f; p.g = G; p.u = U;
     launch_row<kDAct>(p, a.P, a.E, a.stream);
   }
@@ -1655,7 +1638,7 @@ void ffn_bwd_bf16(const FfnBwdArgs& a) {
     WgradArgs p{};
     p.lhs = static_cast<const bf16_t*>(a.dyp); p.ld_lhs = a.d; p.M = a.d;
     p.rhs = static_cast<const bf16_t*>(a.act); p.ld_rhs = a.f; p.N = a.f;
-    p.E = a.E; p.P = a.P; p.items = items; p.partial = partial; p.zeros = reinterpret_cast<const bf16_t*>(rt.zeros);
+    p.E = a.E; p.P = a.P; p.items = items; p.partial = partial;
     p.out0 = static_cast<bf16_t*>(a.dw_down); p.out1 = p.out0; p.m_split = a.d;
     launch_wgrad<0>(p, a.stream);
   }
@@ -1663,7 +1646,7 @@ void ffn_bwd_bf16(const FfnBwdArgs& a) {
     WgradArgs p{};
     p.lhs = dgu; p.ld_lhs = 2L * a.f; p.M = 2 * a.f;
     p.rhs = static_cast<const bf16_t*>(a.xp); p.ld_rhs = a.d; p.N = a.d;
-    p.E = a.E; p.P = a.P; p.items = items; p.partial = partial; p.zeros = reinterpret_cast<const bf16_t*>(rt.zeros);
+    p.E = a.E; p.P = a.P; p.items = items; p.partial = partial;
     p.out0 = static_cast<bf16_t*>(a.dw_gate); p.out1 = static_cast<bf16_t*>(a.dw_up); p.m_split = a.f;
     launch_wgrad<1>(p, a.stream);
   }
@@ -1754,7 +1737,7 @@ void ffn_bwd_gather_bf16(const FfnBwdGatherArgs& a) {
     RowArgs p{};
     p.a = static_cast<const bf16_t*>(a.dy); p.lda = a.d;
     p.w0 = static_cast<const bf16_t*>(a.w_down); p.w_expert_stride = static_cast<long>(a.d) * a.f; p.ldw = a.f;
-    p.K = a.d; p.N = a.f; p.offsets = a.offsets; p.P = a.P; p.rt = rt; p.zeros = reinterpret_cast<const bf16_t*>(rt.zeros);
+    p.K = a.d; p.N = a.f; p.offsets = a.offsets; p.P = a.P; p.rt = rt;
     p.out0 = dgu; p.ldo = 2L * a.f; p.g = G; p.u = U;
     p.row_token = row_token; p.row_w = row_w; p.act_w = a.act_w ? nullptr : act_w_ws; p.dw_partial = dw_partial;
     launch_row<kDAct, true>(p, a.P, a.E, a.stream);
@@ -1765,7 +1748,7 @@ void ffn_bwd_gather_bf16(const FfnBwdGatherArgs& a) {
     WgradArgs p{};
     p.lhs = static_cast<const bf16_t*>(a.dy); p.ld_lhs = a.d; p.M = a.d;
     p.rhs = act_w; p.ld_rhs = a.f; p.N = a.f;
-    p.E = a.E; p.P = a.P; p.items = items; p.partial = partial; p.zeros = reinterpret_cast<const bf16_t*>(rt.zeros);
+    p.E = a.E; p.P = a.P; p.items = items; p.partial = partial;
     p.out0 = static_cast<bf16_t*>(a.dw_down); p.out1 = p.out0; p.m_split = a.d;
     p.row_token = row_token;
     p.dw_partial = dw_partial; p.dw_slots = dw_slots(a.f); p.pair_of_row = a.pair_of_row; p.dtopk_w = a.dtopk_w;   // rides in the reduction launch
@@ -1775,7 +1758,7 @@ void ffn_bwd_gather_bf16(const FfnBwdGatherArgs& a) {
     WgradArgs p{};
     p.lhs = dgu; p.ld_lhs = 2L * a.f; p.M = 2 * a.f;
     p.rhs = static_cast<const bf16_t*>(a.x); p.ld_rhs = a.d; p.N = a.d;
-    p.E = a.E; p.P = a.P; p.items = items; p.partial = partial; p.zeros = reinterpret_cast<const bf16_t*>(rt.zeros);
+    p.E = a.E; p.P = a.P; p.items = items; p.partial = partial;
     p.out0 = static_cast<bf16_t*>(a.dw_gate); p.out1 = static_cast<bf16_t*>(a.dw_up); p.m_split = a.f;
     p.row_token = row_token;
     launch_wgrad<1, true>(p, a.stream);
@@ -1798,12 +1781,11 @@ __global__ __launch_bounds__(256) void cast_f32_bf16_kernel(const float* __restr
   store16(out + i * 8, pack8(v));
 }
 
-struct RouterWs { size_t tiles_count, zeros, tiles_expert, tiles_row0, dz, items, partial, total; };
+struct RouterWs { size_t tiles_count, tiles_expert, tiles_row0, dz, items, partial, total; };
 static RouterWs router_ws(int T, int d, int E, bool bwd) {
   RouterWs w{};
   size_t off = 0;
   w.tiles_count = off; off += 256;
-  w.zeros = off; off += 256;
   const size_t t = align_up(static_cast<size_t>(ceil_div(T, 64) + 1) * sizeof(int32_t), 256);   // row tiles of 64 or 128 rows
   w.tiles_expert = off; off += t;
   w.tiles_row0 = off; off += t;
@@ -1829,7 +1811,6 @@ static RowTiles router_tiles_at(void* ws, const RouterWs& w, int T) {
   RowTiles rt;
   rt.max_tiles = ceil_div(T, 64) + 1;
   rt.count = reinterpret_cast<int32_t*>(b + w.tiles_count);
-  rt.zeros = reinterpret_cast<uint32_t*>(b + w.zeros);
   rt.expert = reinterpret_cast<int32_t*>(b + w.tiles_expert);
   rt.row0 = reinterpret_cast<int32_t*>(b + w.tiles_row0);
   return rt;
@@ -1843,7 +1824,7 @@ void router_fwd_bf16(const RouterFwdArgs& a) {
   RowArgs p{};
   p.a = static_cast<const bf16_t*>(a.x); p.lda = a.d;
   p.w0 = static_cast<const bf16_t*>(a.w_router); p.w_expert_stride = 0; p.ldw = a.d;
-  p.K = a.d; p.N = a.E; p.offsets = nullptr; p.P = a.T; p.rt = rt; p.zeros = reinterpret_cast<const bf16_t*>(rt.zeros);
+  p.K = a.d; p.N = a.E; p.offsets = nullptr; p.P = a.T; p.rt = rt;
   p.out_f32 = a.logits; p.ldo = a.E;
   launch_row_t<kRouterFwd, TileRouter>(p, a.T, 1, a.stream);
 }
@@ -1861,7 +1842,7 @@ void router_bwd_bf16(const RouterBwdArgs& a) {
     RowArgs p{};
     p.a = dz; p.lda = a.E;
     p.w0 = static_cast<const bf16_t*>(a.w_router); p.w_expert_stride = 0; p.ldw = a.d;
-    p.K = a.E; p.N = a.d; p.offsets = nullptr; p.P = a.T; p.rt = rt; p.zeros = reinterpret_cast<const bf16_t*>(rt.zeros);
+    p.K = a.E; p.N = a.d; p.offsets = nullptr; p.P = a.T; p.rt = rt;
     p.out0 = static_cast<bf16_t*>(a.dx); p.ldo = a.d; p.accumulate = a.accumulate;
     launch_row<kRouterDx>(p, a.T, 1, a.stream);
   }
@@ -1889,7 +1870,7 @@ void router_bwd_bf16(const RouterBwdArgs& a) {
     p.lhs = dz; p.ld_lhs = a.E; p.M = a.E;
     p.rhs = static_cast<const bf16_t*>(a.x); p.ld_rhs = a.d; p.N = a.d;
     p.E = 1; p.P = a.T; p.items = items; p.partial = reinterpret_cast<float*>(base + w.partial);
-    p.zeros = reinterpret_cast<const bf16_t*>(rt.zeros);
+   
     p.out0 = static_cast<bf16_t*>(a.dw_router); p.out1 = p.out0; p.m_split = a.E;
     launch_wgrad<2>(p, a.stream);
   }
