@@ -319,6 +319,15 @@ __device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(15 
 
 // a wave's accumulators
 template <class T> using Acc = f32x4[T::FM][T::FN];
+template <class T>
+__device__ __forceinline__ void zero_acc(Acc<T>& acc) {
+#pragma unroll
+  for (int i = 0; i < T::FM; ++i)
+#pragma unroll
+    for (int j = 0; j < T::FN; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[i][j][q] = 0.0f;
+}
 
 // acc += sum over segments of A_s(BM x K) * B_s(BN x K)^T for this wave's sub-tile (segments differ
 // only in their base pointers).
@@ -355,7 +364,7 @@ struct MainLoop {
   static_assert(STEPS == 2, "a slab is two reduction steps");
   static constexpr int R0 = FM >= 8 ? 2 : 1;           // rows of S1 before the barrier
   static_assert(FM > R0, "rows of S1 after the barrier");
-  static constexpr int kMaxAhead = (SA - 1) * NA + (SB - 2) * NB;   // loads in flight behind slab 0 when the stream starts
+  static constexpr int kMaxAhead = (SA - 1) * NA + (SB - 2) * NB;   // loads in flight behind those of slab 0 when the stream starts
   static constexpr int kBeyond = (SA - 2) * NA + (SB - 2) * NB;     // loads enqueued after those of slab kt+1 at the end of slab kt
   static_assert((SA - 1) * NA + (SB - 1) * NB < 64, "vmcnt is a 6-bit counter");
   static constexpr int RA = A_KS ? 2 : 1, RB = B_KS ? 2 : 1;   // LDS instructions per fragment
@@ -576,21 +585,22 @@ struct MainLoop {
       else ab[i] = lds32 + T::kBBase + frag_off<false, T::BN, T::BK>(b_row, i, lane);
     }
   }
-  // point the loads at the operands and fill both rings, slab by slab (A before B).  The rings must be idle.
+  // point the loads at the operands and fill both rings, slab by slab.  The rings must be idle.  The column side of a slab
+  // goes first: the row side of a gathered product waits for its row list.
   __device__ __forceinline__ void start(const Operand& oa, const Operand& ob, int a_row, int b_row) {
     const int lane = threadIdx.x & 63;
-    place(a_row, b_row, lane);
     da.init(oa, K, nslabs, wave, lane);
     db.init(ob, K, nslabs, wave, lane);
     fill();
+    place(a_row, b_row, lane);
   }
   __device__ __forceinline__ void fill() {
     stage_a = 0; stage_b = 0;
     if (nslabs <= 0) return;
 #pragma unroll
-    for (int s0 = 0; s0 < (SA > SB ? SA : SB); ++s0) {
-      if (s0 < SA) da.issue(s0, buf_a(s0), wave);
+    for (int s0 = 0; s0 < (SA > SB - 1 ? SA : SB - 1); ++s0) {
       if (s0 < SB - 1) db.issue(s0, buf_b(s0), wave);
+      if (s0 < SA) da.issue(s0, buf_a(s0), wave);
     }
   }
   // Slabs k0 .. k1-1, the first of which has landed in the first buffers of the rings and is visible to all.
@@ -658,12 +668,12 @@ struct MainLoop {
       if (seg) { oa.half[0] += K_; oa.half[1] += K_; ob.half[0] = opB2.half[0]; ob.half[1] = opB2.half[1]; }
       prepare(whole ? 2 * K_ : K_, lds_);
       const int lane = threadIdx.x & 63;
-      place(a_row, b_row, lane);
       da.init(oa, K, nslabs, wave, lane);
       db.init(ob, K_, nslabs, wave, lane);
       db.seg_slabs = whole ? K_ / T::BK : 0x7FFFFFFF;
       db.seg_delta = whole ? reinterpret_cast<const char*>(opB2.half[0]) - reinterpret_cast<const char*>(opB.half[0]) - db.seg_slabs * db.step : 0L;
       fill();
+      place(a_row, b_row, lane);
       go(active, acc);
       tail(a_row, b_row, active, acc);
     }
@@ -784,6 +794,31 @@ __device__ __forceinline__ void store16(void* p, float a, float b, float c, floa
   __builtin_nontemporal_store(w, reinterpret_cast<f32x4_t*>(p));
 }
 
+// A 32-row strip (or fewer rows) of a row-major matrix as a buffer: a load of a row or column that does not exist returns
+// zeros and a store to it does nothing, so the epilogues need no branches and no 64-bit address arithmetic per access.
+//   first: the strip's first row at the tile's first column (uniform); rows: how many of its rows exist (any integer);
+//   ld2: bytes per row; skip2: bytes between the start of a row and the tile's first column
+struct StripRows {
+  __amdgpu_buffer_rsrc_t rsrc;
+  static constexpr uint32_t kNone = 0x80000000u;       // offset of a column that does not exist (a strip is shorter than 2 GiB)
+  __device__ __forceinline__ void at(const void* first, int rows, uint32_t ld2, uint32_t skip2) {
+    int n = min(rows, 32);
+    asm("" : "+s"(n));                                 // (as two scalar instructions: a vector clamp would make this per lane)
+    n = max(n, 0);
+    const uint32_t range = n > 0 ? static_cast<uint32_t>(n) * ld2 - skip2 : 0u;
+    rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(first), 0, static_cast<int>(range), 0x00020000);
+  }
+  typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+  __device__ __forceinline__ void store(uint32_t off, const uint4& v) const {          // non-temporal, as store16
+    const u32x4_t w = {v.x, v.y, v.z, v.w};
+    __builtin_amdgcn_raw_buffer_store_b128(w, rsrc, static_cast<int>(off), 0, 2);
+  }
+  __device__ __forceinline__ uint4 load(uint32_t off) const {
+    const u32x4_t w = __builtin_amdgcn_raw_buffer_load_b128(rsrc, static_cast<int>(off), 0, 0);
+    return make_uint4(w.x, w.y, w.z, w.w);
+  }
+};
+
 // ---- device-built schedule of (expert, row tile) for row-grouped products -----------------
 struct RowTiles {
   int32_t* count;        // [1] number of row tiles
@@ -838,23 +873,13 @@ __device__ __forceinline__ int xcd_remap(int b, int total) {
   return (b / kXcds < per && v < total) ? v : -1;
 }
 
-template <class T>
-__device__ __forceinline__ void zero_acc(Acc<T>& acc) {
-#pragma unroll
-  for (int i = 0; i < T::FM; ++i)
-#pragma unroll
-    for (int j = 0; j < T::FN; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) acc[i][j][q] = 0.0f;
-}
-
+// ============================================================================================
+// Row-grouped kernels
+// ============================================================================================
 // Hands back its argument through an empty asm: values derived from the result cannot be computed before
 // this point, so the epilogue's per-lane indices do not occupy registers during the main loop.
 __device__ __forceinline__ int not_before_here(int v) { asm volatile("" : "+v"(v)); return v; }
 
-// ============================================================================================
-// Row-grouped kernels
-// ============================================================================================
 enum { kGateUp = 0, kDown = 1, kDAct = 2, kDX = 3, kRouterFwd = 4, kRouterDx = 5 };
 
 struct RowArgs {
@@ -905,7 +930,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   const int row0 = p.rt.row0[mt];
   const int row_end = p.offsets ? min(p.offsets[e + 1], p.P) : p.P;
   const int rows = min(BM, row_end - row0);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / T::WGN, wn = wave % T::WGN;
 
   Acc<T> acc;
@@ -913,8 +938,9 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
 
   const int a_row = wm * WM;                           // first tile row of this wave
   // 32-row strips of this wave that hold rows of the expert (wave-uniform); a wave without any
-  // skips the arithmetic, and the epilogue skips strips without rows
-  const int mi_n = __builtin_amdgcn_readfirstlane(min(MI, max(0, (rows - wm * WM + 31) / 32)));
+  // skips the arithmetic, and the epilogue skips strips without rows (opaque: a compiler that knows where it comes from
+  // splits the paths behind the main loop by its value and spills the accumulators on them)
+  const int mi_n = __builtin_amdgcn_readfirstlane(not_before_here(min(MI, max(0, (rows - wm * WM + 31) / 32))));
   Operand opA, opB;
   opA.ld = p.lda;
   opA.valid[0] = min(rows, BM / 2);
@@ -944,37 +970,45 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
     constexpr int LPR = HW / 8;                        // lanes per output row (8 columns each)
     constexpr int RPP = 64 / LPR;                      // rows per pass
     const int cl = wn * HW + (el % LPR) * 8;         // first of this lane's 8 columns inside the tile
-    // All LDS reads of a strip are issued before the first is used: one LDS latency per strip, not per pass
-    // (the other workgroup of the CU keeps the LDS busy, so that latency is several hundred cycles).
+    // All LDS reads of a strip are issued before the first is used: one LDS latency per strip, not per pass.
     constexpr int NP = 32 / RPP;                       // passes per strip
+    const uint32_t ld2 = static_cast<uint32_t>(p.ldo) * 2u, skip2 = static_cast<uint32_t>(n0) * 2u;
+    uint32_t off[NP];
+#pragma unroll
+    for (int pass = 0; pass < NP; ++pass) off[pass] = cl < ncols ? (pass * RPP + el / LPR) * ld2 + cl * 2u : StripRows::kNone;
+    float wr[MI][NP];                                  // the rows' combine weights, if the activation is to carry them
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int pass = 0; pass < NP; ++pass) {
+        const int r = wm * WM + mi * 32 + pass * RPP + el / LPR;
+        wr[mi][pass] = p.row_w ? p.row_w[row0 + (r < rows ? r : 0)] : 1.0f;
+      }
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
       if (mi >= mi_n) break;
       park_strip<T>(acc, mi, strip, el);
-      float g[NP][8], u[NP][8], wr[NP];
-#pragma unroll
-      for (int pass = 0; pass < NP; ++pass) {           // the rows' combine weights, if the activation is to carry them
-        const int r = wm * WM + mi * 32 + pass * RPP + el / LPR;
-        wr[pass] = p.row_w ? p.row_w[row0 + (r < rows ? r : 0)] : 1.0f;
-      }
+      float g[NP][8], u[NP][8];
 #pragma unroll
       for (int pass = 0; pass < NP; ++pass) {
         const int rs = pass * RPP + el / LPR;
         read8(strip + rs * Strip<T>::LD + (el % LPR) * 8, g[pass]);
         read8(strip + rs * Strip<T>::LD + WN / 2 + (el % LPR) * 8, u[pass]);
       }
+      const int rs0 = wm * WM + mi * 32;               // first row of the strip inside the tile
+      const long o = static_cast<long>(row0 + rs0) * p.ldo + n0;
+      StripRows sg, su, sa;
+      sg.at(p.out0 + o, p.out0 ? rows - rs0 : 0, ld2, skip2);
+      su.at(p.out1 + o, p.out1 ? rows - rs0 : 0, ld2, skip2);
+      sa.at(p.out2 + o, p.out2 ? rows - rs0 : 0, ld2, skip2);
 #pragma unroll
       for (int pass = 0; pass < NP; ++pass) {
-        const int r = wm * WM + mi * 32 + pass * RPP + el / LPR;
-        if (cl < ncols && r < rows) {
-          float a[8];
+        float a[8];
 #pragma unroll
-          for (int q = 0; q < 8; ++q) a[q] = wr[pass] * (g[pass][q] * sigmoid_fast(g[pass][q]) * u[pass][q]);
-          const long o = static_cast<long>(row0 + r) * p.ldo + n0 + cl;
-          if (p.out0) store16(p.out0 + o, pack8(g[pass]));
-          if (p.out1) store16(p.out1 + o, pack8(u[pass]));
-          if (p.out2) store16(p.out2 + o, pack8(a));
-        }
+        for (int q = 0; q < 8; ++q) a[q] = wr[mi][pass] * (g[pass][q] * sigmoid_fast(g[pass][q]) * u[pass][q]);
+        sg.store(off[pass], pack8(g[pass]));
+        su.store(off[pass], pack8(u[pass]));
+        sa.store(off[pass], pack8(a));
       }
     }
     return;
@@ -1009,73 +1043,93 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
     constexpr int LPR = WN / 8;                        // lanes per output row (8 columns each)
     constexpr int RPP = 64 / LPR;                      // rows per pass
     const int cl = wn * WN + (el % LPR) * 8;         // first of this lane's 8 columns inside the tile
-    // All LDS reads of a strip -- and, for the SwiGLU derivative, the loads of the saved G and U of the
-    // strip -- are issued before the first is used: one latency per batch, not one per pass.
+    // All LDS reads of a strip are issued before the first is used: one latency per strip, not one per pass.
     constexpr int NP = 32 / RPP;                       // passes per strip
+    const uint32_t ld2 = static_cast<uint32_t>(p.ldo) * 2u, skip2 = static_cast<uint32_t>(n0) * 2u;
+    uint32_t off[NP];
+#pragma unroll
+    for (int pass = 0; pass < NP; ++pass) off[pass] = cl < ncols ? (pass * RPP + el / LPR) * ld2 + cl * 2u : StripRows::kNone;
     if constexpr (KIND == kDAct) {
-      constexpr int CH = NP;                           // passes per batch of G / U loads: the whole strip (the fragment registers are free now)
+      // The saved G and U of a strip are requested one strip ahead (the fragment registers are free now).  This epilogue is
+      // bound by the vector unit: 128 derivatives per lane, about 25 issue slots each, two waves per SIMD; it takes 35k of
+      // the 127k clocks of a tile (2560 rows per expert).  With compiled divisions, branches per access and the loads of a
+      // strip awaited on the spot, dA took 1145 us against 1065 there, 274 against 260 at 512 rows per expert.
+      const uint32_t n2 = static_cast<uint32_t>(p.N) * 2u;
+      uint32_t goff[NP];
+#pragma unroll
+      for (int pass = 0; pass < NP; ++pass) goff[pass] = cl < ncols ? (pass * RPP + el / LPR) * n2 + cl * 2u : StripRows::kNone;
+      uint4 gq[2][NP], uq[2][NP];
+      float wr[2][NP];
+      auto request = [&](int mi) {
+        const int rs0 = wm * WM + mi * 32;
+        const long gi = static_cast<long>(row0 + rs0) * p.N + n0;
+        StripRows sg, su;
+        sg.at(p.g + gi, rows - rs0, n2, skip2);
+        su.at(p.u + gi, rows - rs0, n2, skip2);
+#pragma unroll
+        for (int c = 0; c < NP; ++c) {
+          gq[mi & 1][c] = sg.load(goff[c]);
+          uq[mi & 1][c] = su.load(goff[c]);
+          if constexpr (FUSED) {
+            const int r = rs0 + c * RPP + el / LPR;
+            wr[mi & 1][c] = p.row_w[row0 + (r < rows ? r : 0)];
+          }
+        }
+      };
+      request(0);
 #pragma unroll
       for (int mi = 0; mi < MI; ++mi) {
         if (mi >= mi_n) break;
+        if (mi + 1 < MI) request(mi + 1);
         park_strip<T>(acc, mi, strip, el);
+        float v[NP][8];
 #pragma unroll
-        for (int p0 = 0; p0 < NP; p0 += CH) {
-          uint4 gq[CH], uq[CH];
-          float v[CH][8], wr[CH];
+        for (int c = 0; c < NP; ++c)
+          read8(strip + (c * RPP + el / LPR) * Strip<T>::LD + (el % LPR) * 8, v[c]);
+        const int rs0 = wm * WM + mi * 32;
+        StripRows sdg, sdu, saw;
+        const long o = static_cast<long>(row0 + rs0) * p.ldo + n0;
+        sdg.at(p.out0 + o, rows - rs0, ld2, skip2);
+        sdu.at(p.out0 + o + p.N, rows - rs0, ld2, skip2 + n2);
+        if constexpr (FUSED) saw.at(p.act_w + (static_cast<long>(row0 + rs0) * p.N + n0), p.act_w ? rows - rs0 : 0, n2, skip2);
 #pragma unroll
-          for (int c = 0; c < CH; ++c) {               // rows / columns that do not exist read the tile's first element
-            const int r = wm * WM + mi * 32 + (p0 + c) * RPP + el / LPR;
-            const long gi = static_cast<long>(row0 + (r < rows ? r : 0)) * p.N + n0 + (cl < ncols ? cl : 0);
-            gq[c] = *reinterpret_cast<const uint4*>(p.g + gi);
-            uq[c] = *reinterpret_cast<const uint4*>(p.u + gi);
-            if constexpr (FUSED) wr[c] = p.row_w[row0 + (r < rows ? r : 0)];
-          }
+        for (int c = 0; c < NP; ++c) {
+          float g[8], u[8], dg[8], du[8];
+          unpack8(gq[mi & 1][c], g);
+          unpack8(uq[mi & 1][c], u);
+          // silu'(g) = sg (1 + g (1 - sg)) = sg + t (1 - sg) with t = g sg = silu(g)
+          if constexpr (FUSED) {
+            const int r = rs0 + c * RPP + el / LPR;
+            const float w = wr[mi & 1][c];
+            float part = 0.0f, act[8];
 #pragma unroll
-          for (int c = 0; c < CH; ++c)
-            read8(strip + ((p0 + c) * RPP + el / LPR) * Strip<T>::LD + (el % LPR) * 8, v[c]);
-#pragma unroll
-          for (int c = 0; c < CH; ++c) {
-            const int r = wm * WM + mi * 32 + (p0 + c) * RPP + el / LPR;
-            const bool live = cl < ncols && r < rows;
-            float g[8], u[8], dg[8], du[8];
-            unpack8(gq[c], g);
-            unpack8(uq[c], u);
-            const long gi = static_cast<long>(row0 + r) * p.N + n0 + cl;
-            const long o = static_cast<long>(row0 + r) * p.ldo + n0 + cl;
-            if constexpr (FUSED) {
-              float part = 0.0f, aw[8];
-#pragma unroll
-              for (int q = 0; q < 8; ++q) {
-                const float sg = sigmoid_fast(g[q]);
-                const float act = g[q] * sg * u[q];
-                part = fmaf(act, v[c][q], part);
-                const float da = wr[c] * v[c][q];
-                dg[q] = da * u[q] * (sg * (1.0f + g[q] * (1.0f - sg)));
-                du[q] = da * (g[q] * sg);
-                aw[q] = wr[c] * act;
-              }
-              if (live) {
-                store16(p.out0 + o, pack8(dg));
-                store16(p.out0 + o + p.N, pack8(du));
-                if (p.act_w) store16(p.act_w + gi, pack8(aw));
-              } else {
-                part = 0.0f;
-              }
-              // the LPR lanes of a row add up their columns; every (column slot, row) is written exactly once
-              part = row_group_sum<LPR>(part);
-              if (r < rows && el % LPR == 0) p.dw_partial[static_cast<long>(nt * T::WGN + wn) * p.P + row0 + r] = part;
-            } else {
-#pragma unroll
-              for (int q = 0; q < 8; ++q) {
-                const float sg = sigmoid_fast(g[q]);
-                dg[q] = v[c][q] * u[q] * (sg * (1.0f + g[q] * (1.0f - sg)));
-                du[q] = v[c][q] * (g[q] * sg);
-              }
-              if (live) {
-                store16(p.out0 + o, pack8(dg));
-                store16(p.out0 + o + p.N, pack8(du));
-              }
+            for (int q = 0; q < 8; ++q) {
+              const float sg = sigmoid_fast(g[q]), t = g[q] * sg, da = w * v[c][q];
+              act[q] = t * u[q];
+              part = fmaf(act[q], v[c][q], part);
+              dg[q] = (da * u[q]) * fmaf(-t, sg, sg + t);
+              du[q] = da * t;
             }
+            sdg.store(off[c], pack8(dg));
+            sdu.store(off[c], pack8(du));
+            if (p.act_w) {
+#pragma unroll
+              for (int q = 0; q < 8; ++q) act[q] *= w;
+              saw.store(goff[c], pack8(act));
+            }
+            // the LPR lanes of a row add up their columns (those that do not exist have read G = U = 0); every
+            // (column slot, row) is written exactly once
+            part = row_group_sum<LPR>(part);
+            if (r < rows && el % LPR == 0) p.dw_partial[static_cast<long>(nt * T::WGN + wn) * p.P + row0 + r] = part;
+          } else {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+              const float sg = sigmoid_fast(g[q]), t = g[q] * sg;
+              dg[q] = (v[c][q] * u[q]) * fmaf(-t, sg, sg + t);
+              du[q] = v[c][q] * t;
+            }
+            sdg.store(off[c], pack8(dg));
+            sdu.store(off[c], pack8(du));
           }
         }
       }
@@ -1090,11 +1144,11 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
 #pragma unroll
         for (int pass = 0; pass < NP; ++pass)
           v[pass] = read_strip_bf16<T>(reinterpret_cast<const char*>(strip), pass * RPP + el / LPR, el % LPR);
+        const int rs0 = wm * WM + mi * 32;
+        StripRows so;
+        so.at(p.out0 + static_cast<long>(row0 + rs0) * p.ldo + n0, rows - rs0, ld2, skip2);
 #pragma unroll
-        for (int pass = 0; pass < NP; ++pass) {
-          const int r = wm * WM + mi * 32 + pass * RPP + el / LPR;
-          if (cl < ncols && r < rows) store16(p.out0 + static_cast<long>(row0 + r) * p.ldo + n0 + cl, v[pass]);
-        }
+        for (int pass = 0; pass < NP; ++pass) so.store(off[pass], v[pass]);
       }
       return;
     }

@@ -64,8 +64,14 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 __device__ __forceinline__ float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
-// fast variants (bf16 path: the result is rounded to 8 bits of mantissa anyway)
-__device__ __forceinline__ float sigmoid_fast(float g) { return 1.0f / (1.0f + __expf(-g)); }
+// bf16 path: 1 / (1 + exp(-g)) with the hardware's exponential and reciprocal and one Newton step, which brings the
+// reciprocal to the last bit (a compiled division is three times the instructions, and the epilogues that use this are
+// bound by the vector unit).  The sum is capped where it would overflow: the Newton step has no infinities to handle.
+__device__ __forceinline__ float sigmoid_fast(float g) {
+  const float d = fminf(1.0f + __expf(-g), 1.5e38f);
+  const float r = __builtin_amdgcn_rcpf(d);
+  return fmaf(fmaf(-d, r, 1.0f), r, r);
+}
 // accurate variants (fp32 path)
 __device__ __forceinline__ float sigmoid_acc(float g) { return 1.0f / (1.0f + expf(-g)); }
 
