@@ -87,6 +87,47 @@ __device__ __forceinline__ int wave_sum_i(int v) {
   return v;
 }
 
+// ---- row tiles of expert-ordered rows ------------------------------------------------------
+// Inclusive prefix sum over the 64 lanes: shifts inside each row of 16 lanes, then the row totals are passed on.
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);    // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);    // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);    // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);    // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+// Row tile number `tile` of the list in which every expert's segment [offsets[e], offsets[e+1]) is cut into tiles of
+// bm rows, in expert order; rows == 0 beyond its end.  Every lane of the wave must call it; the result is wave-uniform.
+// Offsets are clamped to [0, P], so rows stay in bounds whatever they hold.
+struct RowTile { int expert, row0, rows; };
+__device__ __forceinline__ RowTile find_row_tile(const int32_t* __restrict__ offsets, int E, int P, int bm, int tile) {
+  const int lane = threadIdx.x & 63;
+  int before = 0;                                      // tiles of the experts below `base`
+  for (int base = 0; base < E; base += 64) {
+    const int e = base + lane;
+    int begin = 0, end = 0;
+    if (e < E) {
+      begin = min(max(offsets[e], 0), P);
+      end = min(max(offsets[e + 1], begin), P);
+    }
+    const int nt = (end - begin + bm - 1) / bm, incl = wave_inclusive_sum(nt);
+    const unsigned long long behind = __ballot(before + incl > tile);
+    if (behind) {
+      const int l = __builtin_ctzll(behind);           // the first expert whose last tile is not before `tile`
+      const int first = before + __builtin_amdgcn_readlane(incl - nt, l);
+      RowTile rt;
+      rt.expert = base + l;
+      rt.row0 = __builtin_amdgcn_readlane(begin, l) + (tile - first) * bm;
+      rt.rows = min(bm, __builtin_amdgcn_readlane(end, l) - rt.row0);
+      return rt;
+    }
+    before += __builtin_amdgcn_readlane(incl, 63);
+  }
+  return RowTile{0, 0, 0};
+}
+
 // ---- internal launchers of the grouped expert FFN (one per element type) -------------------
 // All pointers are device pointers; arguments are already validated by the C entry points.
 struct FfnFwdArgs {

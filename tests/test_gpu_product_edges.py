@@ -35,3 +35,35 @@ def test_products_at_tile_and_slab_edges(T, d, f, gather):
     for name, got, ref in (("Y", layer.y, fwd["Y"]), ("dX", layer.dx, bwd["dX"]), ("dWg", layer.dw_gate, bwd["dWg"]),
                            ("dWu", layer.dw_up, bwd["dWu"]), ("dWd", layer.dw_down, bwd["dWd"])):
         assert_close(to_np(got), ref, "bf16", name)
+
+
+# The fp32 products: 32 x 32 outputs per workgroup, reductions in pieces of 16 dealt to four wavefronts, four pieces of each in
+# flight (256 indices per round).  Row counts around one tile and one piece, widths and reduction lengths around one piece, one
+# tile, one deal (64) and one round; experts of E = 5 and 70 (more than one per lane) of which some have no rows.
+F32_SIZES = [(1, 8, 8, 5, 1), (15, 16, 24, 5, 2), (33, 40, 32, 5, 1), (64, 72, 56, 70, 2), (70, 264, 248, 5, 4), (300, 56, 264, 5, 2),
+             (1100, 8, 40, 70, 1)]
+
+
+@pytest.mark.parametrize("gather,save_gu", [(True, True), (True, False), (False, False)])
+@pytest.mark.parametrize("T,d,f,E,k", F32_SIZES)
+def test_f32_products_at_tile_and_piece_edges(T, d, f, E, k, gather, save_gu):
+    """fp32 operands and sums: the library's bound for that type (1e-5 of the largest element)."""
+    import torch
+    from paper_2508_02317_amd.layer import MoELayer
+    r = np.random.default_rng(T * 11 + d)
+    X, dY = (r.standard_normal((T, d)).astype(np.float32) for _ in range(2))
+    Wg, Wu = ((r.standard_normal((E, f, d)) * 0.05).astype(np.float32) for _ in range(2))
+    Wd = (r.standard_normal((E, d, f)) * 0.05).astype(np.float32)
+    logits = r.standard_normal((T, E)).astype(np.float32)
+    logits[:, E // 2] -= 20.0                          # an expert without rows
+    logits[:, 1] += 3.0                                # and one with most of them
+    fwd = O.moe_layer_fwd(X, logits, Wg, Wu, Wd, k)
+    bwd = O.moe_layer_bwd(fwd, dY, logits, Wg, Wu, Wd)
+    layer = MoELayer(T, d, E, k, f, torch.float32, to_dev(Wg), to_dev(Wu), to_dev(Wd), gather=gather, save_gu=save_gu)
+    z = to_dev(logits)
+    layer.forward(to_dev(X), logits=z)
+    layer.backward(to_dev(dY), logits=z)
+    torch.cuda.synchronize()
+    for name, got, ref in (("Y", layer.y, fwd["Y"]), ("dX", layer.dx, bwd["dX"]), ("dWg", layer.dw_gate, bwd["dWg"]),
+                           ("dWu", layer.dw_up, bwd["dWu"]), ("dWd", layer.dw_down, bwd["dWd"]), ("dlogits", layer.dlogits, bwd["dlogits"])):
+        assert_close(to_np(got), ref, "f32", name)
