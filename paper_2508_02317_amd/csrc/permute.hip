@@ -2,14 +2,11 @@
 // forward and backward (the local halves of the dispatch / return of Sec. 3.2.3).
 //
 // The permutation is a stable counting sort of the P = T*k (token, slot) pairs by expert:
-//   1. each workgroup takes a contiguous chunk of pairs, ranks every pair among the
-//      earlier pairs of the same expert inside the chunk and writes the chunk's
-//      per-expert histogram (expert-major, so step 2 reads contiguously);
-//   2. one wavefront per expert prefix-scans its histogram over the chunks and adds the
-//      expert's segment offset;
-//   3. one wavefront per token adds chunk base and in-chunk rank, writes both maps and
-//      copies the token's row to each of its k destination rows (the source row is read
-//      once and kept in registers).
+//   1. (more than kOneLaunchChunks chunks) one workgroup per chunk of 1024 pairs counts the chunk's pairs of every expert;
+//   2. one workgroup per chunk adds up the counts of the earlier chunks and the experts' segment offsets, ranks its own
+//      pairs with wave-wide ballots and writes both maps;
+//   3. (rows given) one wavefront per token copies the token's row to each of its k destination rows (the source row
+//      is read once and kept in registers).
 // Integer work only; no atomics decide an order, so the result is the stable order.
 //
 // The movers are pure HBM traffic: every lane moves 16 bytes per access and rows are
@@ -18,56 +15,94 @@
 
 namespace moe {
 
-constexpr int kChunkPairs = 256;     // pairs ranked by one workgroup
+constexpr int kChunkPairs = 1024;    // pairs ranked by one workgroup, one per thread
+constexpr int kChunkWaves = kChunkPairs / 64;
 constexpr int kMoverThreads = 256;
+// Up to this many chunks a workgroup counts the pairs of the earlier chunks itself instead of reading counts that a launch of
+// its own has left.  Measured: 8.4 us for 8 chunks and 16.6 for 16 in one launch, 11 in two (a launch alone costs 4.7 of a stream's
+// time).  Ranking 256 pairs by comparing ids, scanning and writing the maps in three launches took 17 us at both sizes.
+constexpr int kOneLaunchChunks = 8;
 
-// ---- step 1: in-chunk ranks + chunk histogram ---------------------------------------------
-__global__ __launch_bounds__(kChunkPairs) void permute_rank_kernel(
-    const int32_t* __restrict__ topk_idx, int P, int E, int nchunks,
-    int32_t* __restrict__ rank_in_chunk, int32_t* __restrict__ chunk_hist /* [E][nchunks] */) {
-  __shared__ int32_t idx_s[kChunkPairs];
+// The lanes of this wave that hold the same expert id (lanes with e < 0 match nobody): one ballot per bit of the ids.
+// Unlike LDS atomics, whose lanes of one address take turns, this costs the same under any skew of the routing.
+__device__ __forceinline__ unsigned long long same_expert(int e, int bits) {
+  unsigned long long m = __ballot(e >= 0);
+  for (int b = 0; b < bits; ++b) {
+    const unsigned long long ones = __ballot((e >> b) & 1);
+    m &= ((e >> b) & 1) ? ones : ~ones;
+  }
+  return e >= 0 ? m : 0ull;
+}
+__device__ __forceinline__ int chunk_expert(const int32_t* __restrict__ topk_idx, int p, int P, int E) {
+  return p < P ? min(max(topk_idx[p], 0), E - 1) : -1;               // out-of-range ids cannot leave the counters
+}
+
+// ---- step 1: pairs of every expert in a chunk ----------------------------------------------
+__global__ __launch_bounds__(kChunkPairs) void permute_count_kernel(
+    const int32_t* __restrict__ topk_idx, int P, int E, int bits, int32_t* __restrict__ chunk_hist /* [chunk][E] */) {
   __shared__ int32_t hist[kMaxExperts];
-  const int chunk = blockIdx.x;
-  const int p = chunk * kChunkPairs + threadIdx.x;
   for (int e = threadIdx.x; e < E; e += kChunkPairs) hist[e] = 0;
-  const int my = p < P ? min(max(topk_idx[p], 0), E - 1) : -1;   // out-of-range ids cannot leave the histogram
-  idx_s[threadIdx.x] = my;
+  const int my = chunk_expert(topk_idx, blockIdx.x * kChunkPairs + threadIdx.x, P, E);
+  const unsigned long long same = same_expert(my, bits);
   __syncthreads();
-  if (p < P) {
-    int rank = 0;
-    for (int q = 0; q < static_cast<int>(threadIdx.x); ++q) rank += (idx_s[q] == my);
-    rank_in_chunk[p] = rank;
-    atomicAdd(&hist[my], 1);           // integer count: order-independent
-  }
+  if (same && __builtin_ctzll(same) == static_cast<int>(threadIdx.x & 63)) atomicAdd(&hist[my], __popcll(same));   // integer count: order-independent
   __syncthreads();
-  for (int e = threadIdx.x; e < E; e += kChunkPairs)
-    chunk_hist[static_cast<size_t>(e) * nchunks + chunk] = hist[e];
+  for (int e = threadIdx.x; e < E; e += kChunkPairs) chunk_hist[static_cast<size_t>(blockIdx.x) * E + e] = hist[e];
 }
 
-// ---- step 2: per expert, exclusive scan over chunks, plus the segment offset --------------
-__global__ __launch_bounds__(256) void permute_scan_kernel(
-    int32_t* __restrict__ chunk_hist /* in: counts, out: bases */, int nchunks, int E,
-    const int32_t* __restrict__ offsets) {
-  const int lane = threadIdx.x & 63;
-  const int e = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (e >= E) return;
-  int32_t* col = chunk_hist + static_cast<size_t>(e) * nchunks;
-  int32_t carry = offsets[e];
-  for (int base = 0; base < nchunks; base += 64) {
-    int c = base + lane;
-    int32_t v = c < nchunks ? col[c] : 0;
-    int32_t incl = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      int32_t up = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += up;
+// ---- step 2: both maps -----------------------------------------------------------------------
+// row of a pair = segment offset of its expert + pairs of that expert in earlier chunks, in earlier waves of this chunk and
+// in earlier lanes of this wave.  chunk_hist == null: the earlier pairs are counted here.
+__global__ __launch_bounds__(kChunkPairs) void permute_maps_kernel(
+    const int32_t* __restrict__ topk_idx, int P, int E, int bits, int epad, const int32_t* __restrict__ offsets,
+    const int32_t* __restrict__ chunk_hist, int32_t* __restrict__ row_of_pair, int32_t* __restrict__ pair_of_row) {
+  __shared__ int32_t base[kMaxExperts];
+  __shared__ uint16_t in_wave[kChunkWaves][kMaxExperts];              // pairs of an expert in a wave, then in the waves before it
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, chunk = blockIdx.x;
+  for (int e = tid; e < E; e += kChunkPairs) base[e] = offsets[e];
+  for (int i = tid; i < kChunkWaves * E; i += kChunkPairs) in_wave[i / E][i % E] = 0;
+  const int p = chunk * kChunkPairs + tid;
+  const int my = chunk_expert(topk_idx, p, P, E);
+  const unsigned long long same = same_expert(my, bits);
+  __syncthreads();
+  if (chunk_hist) {
+    const int c = tid % epad;                                         // epad: a power of two, 64 .. 1024, at least E
+    int32_t s = 0;
+    if (c < E) {
+#pragma unroll 8
+      for (int b = tid / epad; b < chunk; b += kChunkPairs / epad) s += chunk_hist[static_cast<size_t>(b) * E + c];
+      if (s) atomicAdd(&base[c], s);
     }
-    if (c < nchunks) col[c] = carry + incl - v;
-    carry += __shfl(incl, 63, 64);
+  } else {
+    int next = chunk_expert(topk_idx, tid, P, E);
+    for (int b = 0; b < chunk; ++b) {
+      const int e = next;
+      next = chunk_expert(topk_idx, (b + 1) * kChunkPairs + tid, P, E);   // (the last one is this chunk's own pair)
+      const unsigned long long m = same_expert(e, bits);
+      if (m && __builtin_ctzll(m) == lane) atomicAdd(&base[e], __popcll(m));
+    }
+  }
+  if (same && __builtin_ctzll(same) == lane) in_wave[wave][my] = static_cast<uint16_t>(__popcll(same));
+  __syncthreads();
+  for (int e = tid; e < E; e += kChunkPairs) {
+    int before = 0;
+#pragma unroll
+    for (int w = 0; w < kChunkWaves; ++w) {
+      const int n = in_wave[w][e];
+      in_wave[w][e] = static_cast<uint16_t>(before);
+      before += n;
+    }
+  }
+  __syncthreads();
+  if (my >= 0) {
+    int row = base[my] + in_wave[wave][my] + __popcll(same & ((1ull << lane) - 1));
+    row = min(max(row, 0), P - 1);                                    // stays in bounds even if offsets are inconsistent
+    row_of_pair[p] = row;
+    pair_of_row[row] = p;
   }
 }
 
-// ---- step 3: maps + row gather ------------------------------------------------------------
+// ---- step 3: row gather ------------------------------------------------------------
 
 // The combine kernels stream their rows: every source piece is read once and every destination piece written
 // once, to be consumed by a later kernel.  Non-temporal accesses keep them from displacing what the neighbouring
@@ -85,22 +120,11 @@ __device__ __forceinline__ void store16_stream(uint4* p, const uint4& v) {
 
 // One wave per token; a row is d*elem bytes = n16 sixteen-byte pieces.
 __global__ __launch_bounds__(kMoverThreads) void permute_gather_kernel(
-    const uint4* __restrict__ x, int T, int k, int E, int n16, const int32_t* __restrict__ topk_idx,
-    const int32_t* __restrict__ rank_in_chunk, const int32_t* __restrict__ chunk_base, int nchunks,
-    uint4* __restrict__ xp, int32_t* __restrict__ row_of_pair, int32_t* __restrict__ pair_of_row) {
+    const uint4* __restrict__ x, int T, int k, int n16, const int32_t* __restrict__ row_of_pair, uint4* __restrict__ xp) {
   const int lane = threadIdx.x & 63;
   const int t = blockIdx.x * (kMoverThreads / 64) + (threadIdx.x >> 6);
   if (t >= T) return;
-  // lanes 0..k-1 resolve the k destination rows of this token
-  int my_row = 0;
-  if (lane < k) {
-    int p = t * k + lane;
-    int e = min(max(topk_idx[p], 0), E - 1);
-    my_row = chunk_base[static_cast<size_t>(e) * nchunks + p / kChunkPairs] + rank_in_chunk[p];
-    my_row = min(max(my_row, 0), T * k - 1);     // stays in bounds even if offsets are inconsistent
-    row_of_pair[p] = my_row;
-    pair_of_row[my_row] = p;
-  }
+  const int my_row = lane < k ? row_of_pair[static_cast<size_t>(t) * k + lane] : 0;   // lanes 0..k-1: the token's destination rows
   const uint4* src = x + static_cast<size_t>(t) * n16;
   for (int c0 = 0; c0 < n16; c0 += 256) {
     uint4 v[4];
@@ -286,12 +310,10 @@ static int32_t check_mover_dims(const char* who, int dtype, int T, int d, int k)
   return MOE_OK;
 }
 
-static size_t permute_ws_layout(int T, int E, int k, size_t* hist_off) {
+// [chunks][E] counters; the published size keeps room for a word per pair and for counters of 256-pair chunks
+static size_t permute_ws_bytes(int T, int E, int k) {
   const size_t P = static_cast<size_t>(T) * k;
-  const size_t nchunks = (P + kChunkPairs - 1) / kChunkPairs;
-  const size_t rank_bytes = align_up(P * sizeof(int32_t), 256);
-  if (hist_off) *hist_off = rank_bytes;
-  return rank_bytes + align_up(nchunks * E * sizeof(int32_t), 256) + 256;
+  return align_up(P * sizeof(int32_t), 256) + align_up((P + 255) / 256 * E * sizeof(int32_t), 256) + 256;
 }
 
 }  // namespace moe
@@ -300,7 +322,7 @@ using namespace moe;
 
 extern "C" size_t moe_permute_workspace_bytes(int T, int E, int k) {
   if (T < 0 || E <= 0 || k <= 0) return 0;
-  return permute_ws_layout(T, E, k, nullptr);
+  return permute_ws_bytes(T, E, k);
 }
 
 extern "C" int32_t moe_permute(const void* x, int dtype, int T, int d, int E, int k,
@@ -314,21 +336,22 @@ extern "C" int32_t moe_permute(const void* x, int dtype, int T, int d, int E, in
   MOE_REQUIRE(topk_idx && offsets && row_of_pair && pair_of_row, MOE_ERR_INVALID_ARG, "permute: null pointer");
   MOE_REQUIRE((x == nullptr) == (xp == nullptr), MOE_ERR_INVALID_ARG, "permute: x and xp must both be given, or both be null for the maps alone");
   MOE_REQUIRE(aligned16(x) && aligned16(xp), MOE_ERR_INVALID_ARG, "permute: x / xp must be 16-byte aligned");
-  size_t hist_off = 0;
-  const size_t need = permute_ws_layout(T, E, k, &hist_off);
+  const size_t need = permute_ws_bytes(T, E, k);
   MOE_REQUIRE(ws && ws_bytes >= need && aligned16(ws), MOE_ERR_WORKSPACE, "permute: workspace null, misaligned or smaller than %zu bytes", need);
   hipStream_t s = static_cast<hipStream_t>(stream);
   begin_call("moe_permute", s);
   const int P = T * k;
-  const int nchunks = ceil_div(P, kChunkPairs);
-  int32_t* rank = static_cast<int32_t*>(ws);
-  int32_t* hist = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + hist_off);
-  const int n16 = x ? d * elem_size(dtype) / 16 : 0;     // no rows to copy: the gather kernel only writes the two maps
-  MOE_LAUNCH("permute_rank", permute_rank_kernel, dim3(nchunks), dim3(kChunkPairs), 0, s, topk_idx, P, E, nchunks, rank, hist);
-  MOE_LAUNCH("permute_scan", permute_scan_kernel, dim3(ceil_div(E, 4)), dim3(256), 0, s, hist, nchunks, E, offsets);
-  MOE_LAUNCH(x ? "permute_gather" : "permute_maps", permute_gather_kernel, dim3(ceil_div(T, kMoverThreads / 64)), dim3(kMoverThreads), 0, s,
-                     static_cast<const uint4*>(x), T, k, E, n16, topk_idx, rank, hist, nchunks,
-                     static_cast<uint4*>(xp), row_of_pair, pair_of_row);
+  const int nchunks = (P - 1) / kChunkPairs + 1;
+  int bits = 0, epad = 64;
+  while ((1 << bits) < E) ++bits;
+  while (epad < E) epad <<= 1;
+  int32_t* hist = nchunks > kOneLaunchChunks ? static_cast<int32_t*>(ws) : nullptr;
+  if (hist) MOE_LAUNCH("permute_count", permute_count_kernel, dim3(nchunks), dim3(kChunkPairs), 0, s, topk_idx, P, E, bits, hist);
+  MOE_LAUNCH("permute_maps", permute_maps_kernel, dim3(nchunks), dim3(kChunkPairs), 0, s, topk_idx, P, E, bits, epad, offsets,
+             static_cast<const int32_t*>(hist), row_of_pair, pair_of_row);
+  if (x)
+    MOE_LAUNCH("permute_gather", permute_gather_kernel, dim3((T - 1) / (kMoverThreads / 64) + 1), dim3(kMoverThreads), 0, s,
+               static_cast<const uint4*>(x), T, k, d * elem_size(dtype) / 16, static_cast<const int32_t*>(row_of_pair), static_cast<uint4*>(xp));
   return end_call();
 }
 
