@@ -1117,9 +1117,9 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
               for (int q = 0; q < 8; ++q) act[q] *= w;
               saw.store(goff[c], pack8(act));
             }
-            // the LPR lanes of a row add up their columns (those that do not exist have read G = U = 0); every
-            // (column slot, row) is written exactly once
-            part = row_group_sum<LPR>(part);
+            // the LPR lanes of a row add up their columns (one that does not exist holds NaN if the row of dy has an
+            // infinity); every (column slot, row) is written exactly once
+            part = row_group_sum<LPR>(cl < ncols ? part : 0.0f);
             if (r < rows && el % LPR == 0) p.dw_partial[static_cast<long>(nt * T::WGN + wn) * p.P + row0 + r] = part;
           } else {
 #pragma unroll
@@ -1272,7 +1272,8 @@ __global__ __launch_bounds__(1024) void build_wgrad_items_kernel(const int32_t* 
   build_wgrad_items(offsets, E, P, chunk_rows, it);
 }
 
-// entries of padding behind the list of row tokens: the scalar loads that run one slab ahead never leave it
+// entries of padding behind the list of row tokens: its scalar loads run up to SA + 1 = SB = 3 slabs past the last whole slab, that
+// is 63 + 2 * 64 + 64 entries past the last row, and never leave it
 constexpr int kRowTokenPad = 256;
 
 // Everything a pass needs before its first product, in one launch: block 0 builds the (expert, row tile)

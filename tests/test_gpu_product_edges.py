@@ -67,3 +67,25 @@ def test_f32_products_at_tile_and_piece_edges(T, d, f, E, k, gather, save_gu):
     for name, got, ref in (("Y", layer.y, fwd["Y"]), ("dX", layer.dx, bwd["dX"]), ("dWg", layer.dw_gate, bwd["dWg"]),
                            ("dWu", layer.dw_up, bwd["dWu"]), ("dWd", layer.dw_down, bwd["dWd"]), ("dlogits", layer.dlogits, bwd["dlogits"])):
         assert_close(to_np(got), ref, "f32", name)
+
+
+@pytest.mark.parametrize("f", [8, 136])
+def test_infinite_gradient_row_keeps_its_sign_in_the_combine_weight_gradient(f):
+    """An infinite element of dY makes <dY, yp> of that row infinite (exact, no tolerance): the columns of the tile that do not
+    exist, where the product is 0 * inf, stay out of the sum.  All operands positive, so that the row's own terms are +inf."""
+    import torch
+    from paper_2508_02317_amd.layer import MoELayer
+    T, d = 5, 8
+    r = np.random.default_rng(f)
+    X = q(r.uniform(0.5, 1.0, (T, d)), "bf16")
+    dY = q(r.uniform(0.5, 1.0, (T, d)), "bf16")
+    dY[2] = np.inf
+    Wg, Wu, Wd = (q(r.uniform(0.1, 0.2, s), "bf16") for s in ((1, f, d), (1, f, d), (1, d, f)))
+    layer = MoELayer(T, d, 1, 1, f, torch_dtype("bf16"), to_dev(Wg, "bf16"), to_dev(Wu, "bf16"), to_dev(Wd, "bf16"), gather=True)
+    z = to_dev(np.zeros((T, 1), dtype=np.float32))
+    layer.forward(to_dev(X, "bf16"), logits=z)
+    layer.backward(to_dev(dY, "bf16"), logits=z)
+    torch.cuda.synchronize()
+    dw = to_np(layer.dw).ravel()
+    assert dw[2] == np.inf
+    assert np.isfinite(np.delete(dw, 2)).all()
