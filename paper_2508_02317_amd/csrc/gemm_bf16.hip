@@ -825,6 +825,7 @@ struct RowTiles {
   int32_t* expert;       // [max_tiles]
   int32_t* row0;         // [max_tiles]
   int max_tiles;
+  int bm;                // rows of a tile: which of the tile shapes the list is for
 };
 
 __device__ __forceinline__ void build_row_tiles(const int32_t* __restrict__ offsets, int E, int P, int bm, RowTiles rt) {
@@ -1479,7 +1480,22 @@ typedef Tile<256, 256, 64, 2, 4, 2, 3> TileBig;
 typedef Tile<256, 256, 64, 4, 4, 2, 3> TileBigW16;
 typedef Tile<64, 128, 64, 2, 2, 3, 3> TileRouter;
 
-static int row_bm() { return TileBig::BM; }
+// Row-grouped products of experts with few rows: a quarter of the tile, two workgroups of four waves per CU.  These products
+// stream the weights once; what they lack with the large tile is workgroups (a row tile per expert) and something to run
+// while a workgroup starts or ends.  The same sums in the same order: results are bit-identical.
+typedef Tile<128, 128, 64, 2, 2, 2, 3> TileFew;
+// Rows of a pass's row tiles.  Measured, forward / forward and backward, large tile -> small:
+//   E = 16, d = 1024, f = 2048 (64 large tiles onto d): 2 rows per expert 65 -> 59 us / 207 -> 183, 64 rows 75 -> 69 / 239 -> 221,
+//     125 rows 88 -> 82 / 282 -> 259;  E = 8, d = 4096, f = 3072 (128): 2 rows 155 -> 134 / 473 -> 413, 64 rows 175 -> 159 / 540 -> 504;
+//   E = 60, d = 1024, f = 1408 (240): 4 rows 125 -> 121 / 369 -> 366, 93 rows 145 -> 144 / 461 -> 459;
+//   E = 128, d = 2048, f = 768 (1024, four rounds of the 256 CUs): 4 rows 244 -> 237, 64 rows 275 -> 273, 96 rows 285 -> 287, 128 rows
+//     305 -> 356 (half of the experts need a second tile, which reads their weights again); with the backward 856 -> 875 at 64 rows
+//     and 926 -> 959 at 96 (its weights are read across the reduction, 256 bytes at a time instead of 512).
+// So: on average at most 128 rows per expert where the large tiles onto d leave CUs without work, and 64 in a forward pass of any size.
+static int row_bm(int P, int E, int d, bool backward) {
+  const bool idle = static_cast<long>(E) * ceil_div(d, TileBig::BN) < 256 && P <= 128L * E;
+  return idle || (!backward && P <= 64L * E) ? TileFew::BM : TileBig::BM;
+}
 // bound used for workspace sizing: the smallest row tile gives the longest list
 static int max_row_tiles(int P, int E) { return ceil_div(P, 128) + E; }
 
@@ -1531,10 +1547,11 @@ size_t ffn_bwd_ws_bytes_bf16(int P, int d, int f, int E, int have_saved) {
   return ws_layout(P, d, f, E, true, !have_saved).total;
 }
 
-static RowTiles row_tiles_at(void* ws, const WsLayout& w, int P, int E) {
+static RowTiles row_tiles_at(void* ws, const WsLayout& w, int P, int E, int bm) {
   char* b = static_cast<char*>(ws);
   RowTiles rt;
   rt.max_tiles = max_row_tiles(P, E);
+  rt.bm = bm;
   rt.count = reinterpret_cast<int32_t*>(b + w.tiles_count);
   rt.expert = reinterpret_cast<int32_t*>(b + w.tiles_expert);
   rt.row0 = reinterpret_cast<int32_t*>(b + w.tiles_row0);
@@ -1591,7 +1608,8 @@ static void launch_row_t(RowArgs p, int P, int E, hipStream_t s) {
 
 template <int KIND, bool FUSED = false>
 static void launch_row(const RowArgs& p, int P, int E, hipStream_t s) {
-  launch_row_t<KIND, TileBig, FUSED>(p, P, E, s);
+  if (p.rt.bm == TileFew::BM) launch_row_t<KIND, TileFew, FUSED>(p, P, E, s);
+  else launch_row_t<KIND, TileBig, FUSED>(p, P, E, s);
 }
 
 template <int WHICH, bool GATHER = false>
@@ -1652,8 +1670,8 @@ static void launch_dx(const bf16_t* dgu, const void* wg, const void* wu, int P, 
 
 void ffn_fwd_bf16(const FfnFwdArgs& a) {
   const WsLayout w = ws_layout(a.P, a.d, a.f, a.E, false, false);
-  const RowTiles rt = row_tiles_at(a.ws, w, a.P, a.E);
-  MOE_LAUNCH("build_row_tiles", build_row_tiles_kernel, dim3(1), dim3(1024), 0, a.stream, a.offsets, a.E, a.P, row_bm(), rt);
+  const RowTiles rt = row_tiles_at(a.ws, w, a.P, a.E, row_bm(a.P, a.E, a.d, false));
+  MOE_LAUNCH("build_row_tiles", build_row_tiles_kernel, dim3(1), dim3(1024), 0, a.stream, a.offsets, a.E, a.P, rt.bm, rt);
   launch_gate_up(a.xp, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, a.offsets, rt, a.g_save, a.u_save, a.act, a.stream);
   launch_down(a.act, a.w_down, a.P, a.d, a.f, a.E, a.offsets, rt, a.yp, a.stream);
 }
@@ -1661,7 +1679,7 @@ void ffn_fwd_bf16(const FfnFwdArgs& a) {
 void ffn_bwd_bf16(const FfnBwdArgs& a) {
   const bool recompute = a.g_save == nullptr;
   const WsLayout w = ws_layout(a.P, a.d, a.f, a.E, true, recompute);
-  const RowTiles rt = row_tiles_at(a.ws, w, a.P, a.E);
+  const RowTiles rt = row_tiles_at(a.ws, w, a.P, a.E, row_bm(a.P, a.E, a.d, true));
   char* base = static_cast<char*>(a.ws);
   bf16_t* dgu = reinterpret_cast<bf16_t*>(base + w.dgu);       // [P, 2f] = [dG | dU]
   const bf16_t* G = static_cast<const bf16_t*>(a.g_save);
@@ -1669,7 +1687,7 @@ void ffn_bwd_bf16(const FfnBwdArgs& a) {
   const WgradItems items = wgrad_items_at(a.ws, w, a.P, a.E);
   {
     ScheduleArgs sa{};
-    sa.offsets = a.offsets; sa.E = a.E; sa.P = a.P; sa.bm = row_bm(); sa.rt = rt;
+    sa.offsets = a.offsets; sa.E = a.E; sa.P = a.P; sa.bm = rt.bm; sa.rt = rt;
     sa.chunk_rows = wgrad_chunk_rows(a.P); sa.items = items;
     launch_schedules(sa, a.stream);
   }
@@ -1719,7 +1737,9 @@ void ffn_bwd_bf16(const FfnBwdArgs& a) {
 // ============================================================================================
 
 // column slots of the partial dot products: one per (column tile, wavefront column) of the dA product
-static int dw_slots(int f) { return ceil_div(f, TileBig::BN) * TileBig::WGN; }
+// column slots (64 columns each) of the combine-weight gradient's partial sums; dw_slots_max sizes the workspace
+static int dw_slots_max(int f) { return ceil_div(f, TileBig::BN) * TileBig::WGN; }
+static int dw_slots(const RowTiles& rt, int f) { return rt.bm == TileFew::BM ? ceil_div(f, TileFew::BN) * TileFew::WGN : dw_slots_max(f); }
 
 struct GatherWs { size_t row_token, row_w, act_w, dw_partial, total; };
 static GatherWs gather_ws(const WsLayout& w, int P, int f, bool bwd) {
@@ -1730,7 +1750,7 @@ static GatherWs gather_ws(const WsLayout& w, int P, int f, bool bwd) {
   g.act_w = off; g.dw_partial = off;
   if (bwd) {
     g.act_w = off; off += align_up(static_cast<size_t>(P) * f * 2, 256);
-    g.dw_partial = off; off += align_up(static_cast<size_t>(dw_slots(f)) * P * sizeof(float), 256);
+    g.dw_partial = off; off += align_up(static_cast<size_t>(dw_slots_max(f)) * P * sizeof(float), 256);
   }
   g.total = off;
   return g;
@@ -1745,12 +1765,12 @@ size_t ffn_bwd_gather_ws_bytes_bf16(int P, int d, int f, int E, int have_saved) 
 void ffn_fwd_gather_bf16(const FfnFwdGatherArgs& a) {
   const WsLayout w = ws_layout(a.P, a.d, a.f, a.E, false, false);
   const GatherWs g = gather_ws(w, a.P, a.f, false);
-  const RowTiles rt = row_tiles_at(a.ws, w, a.P, a.E);
+  const RowTiles rt = row_tiles_at(a.ws, w, a.P, a.E, row_bm(a.P, a.E, a.d, false));
   int32_t* row_token = reinterpret_cast<int32_t*>(static_cast<char*>(a.ws) + g.row_token);
   float* row_w = reinterpret_cast<float*>(static_cast<char*>(a.ws) + g.row_w);
   {
     ScheduleArgs sa{};
-    sa.offsets = a.offsets; sa.E = a.E; sa.P = a.P; sa.bm = row_bm(); sa.rt = rt;
+    sa.offsets = a.offsets; sa.E = a.E; sa.P = a.P; sa.bm = rt.bm; sa.rt = rt;
     sa.pair_of_row = a.pair_of_row; sa.T = a.T; sa.k = a.k; sa.row_token = row_token;
     if (a.topk_w) { sa.topk_w = a.topk_w; sa.row_w = row_w; }
     launch_schedules(sa, a.stream);
@@ -1764,7 +1784,7 @@ void ffn_bwd_gather_bf16(const FfnBwdGatherArgs& a) {
   const bool recompute = a.g_save == nullptr;
   const WsLayout w = ws_layout(a.P, a.d, a.f, a.E, true, recompute);
   const GatherWs gw = gather_ws(w, a.P, a.f, true);
-  const RowTiles rt = row_tiles_at(a.ws, w, a.P, a.E);
+  const RowTiles rt = row_tiles_at(a.ws, w, a.P, a.E, row_bm(a.P, a.E, a.d, true));
   char* base = static_cast<char*>(a.ws);
   bf16_t* dgu = reinterpret_cast<bf16_t*>(base + w.dgu);       // [P, 2f] = [dG | dU]
   int32_t* row_token = reinterpret_cast<int32_t*>(base + gw.row_token);
@@ -1777,7 +1797,7 @@ void ffn_bwd_gather_bf16(const FfnBwdGatherArgs& a) {
   const WgradItems items = wgrad_items_at(a.ws, w, a.P, a.E);
   {
     ScheduleArgs sa{};
-    sa.offsets = a.offsets; sa.E = a.E; sa.P = a.P; sa.bm = row_bm(); sa.rt = rt;
+    sa.offsets = a.offsets; sa.E = a.E; sa.P = a.P; sa.bm = rt.bm; sa.rt = rt;
     sa.chunk_rows = wgrad_chunk_rows(a.P); sa.items = items;
     sa.pair_of_row = a.pair_of_row; sa.topk_w = a.topk_w; sa.T = a.T; sa.k = a.k; sa.row_token = row_token; sa.row_w = row_w;
     launch_schedules(sa, a.stream);
@@ -1806,7 +1826,7 @@ void ffn_bwd_gather_bf16(const FfnBwdGatherArgs& a) {
     p.E = a.E; p.P = a.P; p.items = items; p.partial = partial;
     p.out0 = static_cast<bf16_t*>(a.dw_down); p.out1 = p.out0; p.m_split = a.d;
     p.row_token = row_token;
-    p.dw_partial = dw_partial; p.dw_slots = dw_slots(a.f); p.pair_of_row = a.pair_of_row; p.dtopk_w = a.dtopk_w;   // rides in the reduction launch
+    p.dw_partial = dw_partial; p.dw_slots = dw_slots(rt, a.f); p.pair_of_row = a.pair_of_row; p.dtopk_w = a.dtopk_w;   // rides in the reduction launch
     launch_wgrad<0, true>(p, a.stream);
   }
   {  // [dWg[e]; dWu[e]] = [dG | dU]^T x[token]
@@ -1892,14 +1912,14 @@ void router_bwd_bf16(const RouterBwdArgs& a) {
   const long n8 = static_cast<long>(a.T) * a.E / 8;
   MOE_LAUNCH("router_cast_dz", cast_f32_bf16_kernel, dim3(static_cast<unsigned>((n8 + 255) / 256)), dim3(256), 0, a.stream, a.dlogits, dz, n8);
   MOE_LAUNCH("build_row_tiles", build_row_tiles_kernel, dim3(1), dim3(1024), 0, a.stream, static_cast<const int32_t*>(nullptr), 1, a.T,
-             row_bm(), rt);
+             TileBig::BM, rt);
   {  // dx (+)= dz * Wr
     RowArgs p{};
     p.a = dz; p.lda = a.E;
     p.w0 = static_cast<const bf16_t*>(a.w_router); p.w_expert_stride = 0; p.ldw = a.d;
     p.K = a.E; p.N = a.d; p.offsets = nullptr; p.P = a.T; p.rt = rt;
     p.out0 = static_cast<bf16_t*>(a.dx); p.ldo = a.d; p.accumulate = a.accumulate;
-    launch_row<kRouterDx>(p, a.T, 1, a.stream);
+    launch_row_t<kRouterDx, TileBig>(p, a.T, 1, a.stream);
   }
   {  // dWr = dz^T x
     WgradItems items;

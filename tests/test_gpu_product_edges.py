@@ -89,3 +89,34 @@ def test_infinite_gradient_row_keeps_its_sign_in_the_combine_weight_gradient(f):
     dw = to_np(layer.dw).ravel()
     assert dw[2] == np.inf
     assert np.isfinite(np.delete(dw, 2)).all()
+
+
+# Few rows per expert (at most 128 on average): 128 x 128 tiles.  Row counts at and around the boundary of that rule, experts with
+# none, with one and with more rows than a tile; widths around one tile and one slab; the last size takes them in the forward only.
+FEW_SIZES = [(256, 120, 128, 4, 2), (257, 136, 264, 4, 2), (511, 128, 120, 4, 1), (7, 264, 136, 5, 3), (300, 72, 392, 9, 4),
+             (40, 520, 136, 128, 4)]
+
+
+@pytest.mark.parametrize("gather,save_gu", [(True, True), (True, False), (False, True)])
+@pytest.mark.parametrize("T,d,f,E,k", FEW_SIZES)
+def test_products_of_experts_with_few_rows(T, d, f, E, k, gather, save_gu):
+    import torch
+    from paper_2508_02317_amd.layer import MoELayer
+    r = np.random.default_rng(T * 13 + d)
+    X, dY = q(r.standard_normal((T, d)), "bf16"), q(r.standard_normal((T, d)), "bf16")
+    Wg, Wu = (q(r.standard_normal((E, f, d)) * 0.05, "bf16") for _ in range(2))
+    Wd = q(r.standard_normal((E, d, f)) * 0.05, "bf16")
+    logits = r.standard_normal((T, E)).astype(np.float32)
+    logits[:, 0] -= 20.0                               # an expert without rows
+    logits[:, E - 1] += 3.0                            # and one with most of them
+    fwd = O.moe_layer_fwd(X, logits, Wg, Wu, Wd, k)
+    bwd = O.moe_layer_bwd(fwd, dY, logits, Wg, Wu, Wd)
+    layer = MoELayer(T, d, E, k, f, torch_dtype("bf16"), to_dev(Wg, "bf16"), to_dev(Wu, "bf16"), to_dev(Wd, "bf16"), gather=gather,
+                     save_gu=save_gu)
+    z = to_dev(logits)
+    layer.forward(to_dev(X, "bf16"), logits=z)
+    layer.backward(to_dev(dY, "bf16"), logits=z)
+    torch.cuda.synchronize()
+    for name, got, ref in (("Y", layer.y, fwd["Y"]), ("dX", layer.dx, bwd["dX"]), ("dWg", layer.dw_gate, bwd["dWg"]),
+                           ("dWu", layer.dw_up, bwd["dWu"]), ("dWd", layer.dw_down, bwd["dWd"]), ("dlogits", layer.dlogits, bwd["dlogits"])):
+        assert_close(to_np(got), ref, "bf16", name)
