@@ -273,7 +273,7 @@ __global__ __launch_bounds__(kF32Threads) void f32_dx_kernel(F32Rows R, const fl
 }
 
 // ---- weight gradients: dWd = dy^T act, dWg = dG^T x, dWu = dU^T x over the rows of every expert, in one launch --------
-// Workgroup b < 3 E tiles: product b / (E tiles), expert, 32 x 32 outputs.  Behind them (dw_partial given): the gradient of
+// Workgroup b < 3 E tiles: product b / (E tiles), expert, 32 x 32 outputs.  All behind them (dw_partial given): the gradient of
 // the combine weights, the column tiles' shares added in order and scattered to [T, k].
 struct F32Wgrad {
   const float *dy, *act, *dG, *dU, *x;
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(kF32Threads) void f32_wgrad_kernel(F32Rows R, F32Wg
   __shared__ __attribute__((aligned(16))) float red[kF32Red];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const unsigned tiles = static_cast<unsigned>(p.tiles_d) * p.tiles_f, which = blockIdx.x / (tiles * R.E);
-  if (which == 3) {
+  if (which >= 3) {                                    // (there may be more blocks of these than of one product)
     const long r = static_cast<long>(blockIdx.x - 3 * tiles * R.E) * kF32Threads + threadIdx.x;
     if (r >= R.P) return;
     float s = 0.0f;

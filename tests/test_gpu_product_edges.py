@@ -69,6 +69,31 @@ def test_f32_products_at_tile_and_piece_edges(T, d, f, E, k, gather, save_gu):
         assert_close(to_np(got), ref, "f32", name)
 
 
+# Many rows, few outputs: the weight-gradient launch ends with a workgroup per 256 rows for the combine-weight gradient, here more of
+# them than a product has workgroups (E tiles = 4, 1, 16, 1 against 8, 2, 47, 16).
+@pytest.mark.parametrize("save_gu", [True, False])
+@pytest.mark.parametrize("T,d,f,E,k", [(1024, 32, 32, 4, 2), (257, 8, 8, 1, 1), (3000, 64, 64, 4, 4), (4096, 32, 32, 1, 1)])
+def test_f32_combine_weight_gradient_of_many_rows_and_few_outputs(T, d, f, E, k, save_gu):
+    import torch
+    from paper_2508_02317_amd.layer import MoELayer
+    r = np.random.default_rng(T + E)
+    X, dY = (r.standard_normal((T, d)).astype(np.float32) for _ in range(2))
+    Wg, Wu = ((r.standard_normal((E, f, d)) * 0.05).astype(np.float32) for _ in range(2))
+    Wd = (r.standard_normal((E, d, f)) * 0.05).astype(np.float32)
+    logits = r.standard_normal((T, E)).astype(np.float32)
+    fwd = O.moe_layer_fwd(X, logits, Wg, Wu, Wd, k)
+    bwd = O.moe_layer_bwd(fwd, dY, logits, Wg, Wu, Wd)
+    layer = MoELayer(T, d, E, k, f, torch.float32, to_dev(Wg), to_dev(Wu), to_dev(Wd), gather=True, save_gu=save_gu)
+    layer.dw.fill_(float("nan"))                       # a row that is not written shows
+    z = to_dev(logits)
+    layer.forward(to_dev(X), logits=z)
+    layer.backward(to_dev(dY), logits=z)
+    torch.cuda.synchronize()
+    for name, got, ref in (("dw", layer.dw, bwd["dw"]), ("dX", layer.dx, bwd["dX"]), ("dWg", layer.dw_gate, bwd["dWg"]),
+                           ("dWu", layer.dw_up, bwd["dWu"]), ("dWd", layer.dw_down, bwd["dWd"])):
+        assert_close(to_np(got), ref, "f32", name)
+
+
 @pytest.mark.parametrize("f", [8, 136])
 def test_infinite_gradient_row_keeps_its_sign_in_the_combine_weight_gradient(f):
     """An infinite element of dY makes <dY, yp> of that row infinite (exact, no tolerance): the columns of the tile that do not
