@@ -165,7 +165,13 @@ __device__ __forceinline__ bf16x8 lds_read_frag(uint32_t addr) {
 //   * slabs beyond the end of the reduction get an empty descriptor,
 // and every wave enqueues the same number of loads per slab whatever is left: all waits are immediates and the slab
 // loop has a single path.  Only a partial last slab of a k-contiguous operand needs a select (issue_tail).
-constexpr uint32_t kRangeAll = 0xFFFF0000u;     // in-range offsets stay below 4 GiB - 64 KiB
+//
+// Ranges.  k-contiguous: everything but the offset that stands for "does not exist" (token rows of a gathered operand
+// reach up to 4 GiB - 128 bytes: the 8-bit products' codes).  Gathered k-strided: a row that does not exist is moved to the
+// range's end and a column's offset (below 64 KiB) comes on top, so the range leaves that much room below 4 GiB; its
+// operands, the bf16 token matrices, are smaller than that.
+constexpr uint32_t kRangeAll = 0xFFFFFF80u;
+constexpr uint32_t kRangeRows = 0xFFFF0000u;
 constexpr uint32_t kOffNone = 0xFFFFFFF0u;      // beyond every range
 template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false, bool TWO_SEG = false> struct Dma {
   static constexpr int CHUNKS = ROWS * BK * 2 / 1024;
@@ -251,7 +257,7 @@ template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false, bool TWO_SE
   __device__ __forceinline__ void point(int slab) {
     long off = slab * step;
     if constexpr (TWO_SEG) off += slab >= seg_slabs ? seg_delta : 0L;
-    uint32_t range = slab < nslabs ? kRangeAll : 0u;
+    uint32_t range = slab < nslabs ? (KS ? kRangeRows : kRangeAll) : 0u;
     if constexpr (KS && !GATHER) {
       int first = slab * BK;
       if constexpr (TWO_SEG) first -= slab >= seg_slabs ? seg_slabs * BK : 0;
@@ -265,7 +271,7 @@ template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false, bool TWO_SE
     if constexpr (KS && GATHER) {
       // byte offsets of the wave's rows; rows beyond K are beyond the range
 #pragma unroll
-      for (int j = 0; j < NR; ++j) next_row[j] = slab * BK + k_first + j < K ? static_cast<int32_t>(static_cast<uint32_t>(next_row[j]) * ld2) : static_cast<int32_t>(kRangeAll);
+      for (int j = 0; j < NR; ++j) next_row[j] = slab * BK + k_first + j < K ? static_cast<int32_t>(static_cast<uint32_t>(next_row[j]) * ld2) : static_cast<int32_t>(kRangeRows);
     }
   }
   // byte offset of this lane's piece of chunk i

@@ -321,3 +321,31 @@ def test_full_size_a3b_long_sampled():
     say("  %d rows of %d experts: %d of %d activation codes differ, Yp max error %.2e" % (n_rows, len(experts), flips, n_rows * f, worst_y))
     assert flips <= 5e-3 * n_rows * f
     assert worst_y <= FUSED_YP_MAX
+
+
+@pytest.mark.parametrize("T,d", [((1 << 25) - 1, 128), ((1 << 21) - 1, 2048)])
+def test_rows_read_by_token_up_to_the_size_limit(T, d):
+    """T * d just below 2^32, the largest codes matrix that is read by token: its last rows (and those around 2 GiB) give bit for
+    bit what a call on these rows alone gives."""
+    import torch
+    from paper_2508_02317_amd import libmoe as L
+    assert (1 << 32) - 65536 < T * d < 1 << 32
+    f, n = 128, 600
+    say("mx8 forward T=%d d=%d" % (T, d))
+    gen = torch.Generator(device="cuda").manual_seed(d)
+    wg, wu, wd = (L.moe_mx8_quantise((torch.randn(s, generator=gen, device="cuda") * 0.05).to(torch.bfloat16))
+                  for s in ((1, f, d), (1, f, d), (1, d, f)))
+    rows = torch.cat([torch.arange((1 << 31) // d - n // 2, (1 << 31) // d + n // 2), torch.arange(T - n, T)]).cuda()
+    xq, xs = L.moe_mx8_quantise(torch.randn((2 * n, d), generator=gen, device="cuda").to(torch.bfloat16))
+    i32 = lambda *v: torch.tensor(v, dtype=torch.int32, device="cuda")
+    call = lambda q, s, o: L.moe_grouped_gemm_swiglu_fwd_mx8(q, s, wg[0], wg[1], wu[0], wu[1], wd[0], wd[1], o,
+                                                             pair_of_row=torch.arange(q.shape[0], dtype=torch.int32, device="cuda"))
+    ref = call(xq, xs, i32(0, 2 * n))
+    big_q = torch.zeros((T, d), dtype=torch.uint8, device="cuda")
+    big_s = torch.full((d // 128, T), 0x7F7F7F7F, dtype=torch.int32, device="cuda")
+    big_q[rows] = xq
+    big_s[:, rows] = xs
+    act, scales, yp = call(big_q, big_s, i32(0, T))
+    torch.cuda.synchronize()
+    assert (ref[2] != 0).any(dim=1).all()
+    assert torch.equal(act[rows], ref[0]) and torch.equal(scales[:, rows], ref[1]) and torch.equal(yp[rows], ref[2])
