@@ -1104,7 +1104,8 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
           float g[8], u[8], dg[8], du[8];
           unpack8(gq[mi & 1][c], g);
           unpack8(uq[mi & 1][c], u);
-          // silu'(g) = sg (1 + g (1 - sg)) = sg + t (1 - sg) with t = g sg = silu(g)
+          // silu'(g) = sg (1 + g (1 - sg)) = sg + t (1 - sg) with t = g sg = silu(g); 1 - sg is formed first: where it is zero
+          // the result is sg however large t is (sg + t - t sg would lose sg)
           if constexpr (FUSED) {
             const int r = rs0 + c * RPP + el / LPR;
             const float w = wr[mi & 1][c];
@@ -1114,7 +1115,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
               const float sg = sigmoid_fast(g[q]), t = g[q] * sg, da = w * v[c][q];
               act[q] = t * u[q];
               part = fmaf(act[q], v[c][q], part);
-              dg[q] = (da * u[q]) * fmaf(-t, sg, sg + t);
+              dg[q] = (da * u[q]) * fmaf(t, 1.0f - sg, sg);
               du[q] = da * t;
             }
             sdg.store(off[c], pack8(dg));
@@ -1132,7 +1133,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
               const float sg = sigmoid_fast(g[q]), t = g[q] * sg;
-              dg[q] = (v[c][q] * u[q]) * fmaf(-t, sg, sg + t);
+              dg[q] = (v[c][q] * u[q]) * fmaf(t, 1.0f - sg, sg);
               du[q] = v[c][q] * t;
             }
             sdg.store(off[c], pack8(dg));
