@@ -66,11 +66,14 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 
 // bf16 path: 1 / (1 + exp(-g)) with the hardware's exponential and reciprocal and one Newton step, which brings the
 // reciprocal to the last bit (a compiled division is three times the instructions, and the epilogues that use this are
-// bound by the vector unit).  The sum is capped where it would overflow: the Newton step has no infinities to handle.
+// bound by the vector unit).  The sum is formed 2^-32 times smaller and the result scaled back: the reciprocal's argument and
+// result then lie in 2^-125 .. 2^125 for every g, so nothing depends on how the hardware treats a subnormal one.  Where
+// exp(-g) is not finite the argument is capped (the Newton step has no infinities to handle) and 2^-125 2^-32 is zero, as
+// 1 / inf is; for g from -87.3 to -88.7 the sigmoid is the subnormal number it should be.
 __device__ __forceinline__ float sigmoid_fast(float g) {
-  const float d = fminf(1.0f + __expf(-g), 1.5e38f);
+  const float d = fminf(fmaf(__expf(-g), 0x1p-32f, 0x1p-32f), 0x1p125f);
   const float r = __builtin_amdgcn_rcpf(d);
-  return fmaf(fmaf(-d, r, 1.0f), r, r);
+  return fmaf(fmaf(-d, r, 1.0f), r, r) * 0x1p-32f;
 }
 // accurate variants (fp32 path)
 __device__ __forceinline__ float sigmoid_acc(float g) { return 1.0f / (1.0f + expf(-g)); }

@@ -46,9 +46,10 @@ def _column(g):
     return w
 
 
-# (lowest, highest pre-activation).  Large ones: silu'(G) is 1, also where 1 + G is G in fp32.
+# (lowest, highest pre-activation).  Large ones: silu'(G) is 1, also where 1 + G is G in fp32.  Very negative ones: silu(G) is a
+# normal number although the sigmoid is a subnormal one, and 0, not G times a smallest number, where exp(-G) is not finite.
 @pytest.mark.parametrize("gather", [True, False])
-@pytest.mark.parametrize("lo,hi", [(2.0, np.inf)])
+@pytest.mark.parametrize("lo,hi", [(2.0, np.inf), (-16.0, 2.0), (-np.inf, -16.0)])
 def test_silu_and_its_derivative(lo, hi, gather):
     import torch
     from paper_2508_02317_amd import libmoe as L
