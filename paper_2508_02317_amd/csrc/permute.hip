@@ -3,9 +3,10 @@
 //
 // The permutation is a stable counting sort of the P = T*k (token, slot) pairs by expert:
 //   1. (more than kOneLaunchChunks chunks) one workgroup per chunk of 1024 pairs counts the chunk's pairs of every expert;
-//   2. one workgroup per chunk adds up the counts of the earlier chunks and the experts' segment offsets, ranks its own
-//      pairs with wave-wide ballots and writes both maps;
-//   3. (rows given) one wavefront per token copies the token's row to each of its k destination rows (the source row
+//   2. (more than kScanWords words of counts) the counts become those of the earlier chunks, in place: a scan per expert;
+//   3. one workgroup per chunk adds the counts of the earlier chunks (which it sums itself where step 2 was left out) to the
+//      experts' segment offsets, ranks its own pairs with wave-wide ballots and writes both maps;
+//   4. (rows given) one wavefront per token copies the token's row to each of its k destination rows (the source row
 //      is read once and kept in registers).
 // Integer work only; no atomics decide an order, so the result is the stable order.
 //
@@ -22,6 +23,11 @@ constexpr int kMoverThreads = 256;
 // its own has left.  Measured: 8.4 us for 8 chunks and 16.6 for 16 in one launch, 11 in two (a launch alone costs 4.7 of a stream's
 // time).  Ranking 256 pairs by comparing ids, scanning and writing the maps in three launches took 17 us at both sizes.
 constexpr int kOneLaunchChunks = 8;
+// Above this many counters (chunks times experts, the experts rounded up to a power of two of at least 64) a launch of its own
+// scans them: without it a workgroup sums those of all earlier chunks, all workgroups together chunks^2 E / 2 words.  Measured, summed ->
+// scanned: E = 64, 1024 chunks 24.0 -> 26.8 us, 2048 52.6 -> 46.9; E = 128, 320 chunks 13.8 -> 15.8, 512 17.7 -> 18.5, 768 25.6 -> 24.2,
+// 4096 249 -> 92; E = 256, 256 chunks 14.4 -> 14.1; E = 1024, 64 chunks 16.7 -> 14.1, 4096 1916 -> 130.
+constexpr long kScanWords = 65536;
 
 // The lanes of this wave that hold the same expert id (lanes with e < 0 match nobody): one ballot per bit of the ids.
 // Unlike LDS atomics, whose lanes of one address take turns, this costs the same under any skew of the routing.
@@ -50,22 +56,57 @@ __global__ __launch_bounds__(kChunkPairs) void permute_count_kernel(
   for (int e = threadIdx.x; e < E; e += kChunkPairs) chunk_hist[static_cast<size_t>(blockIdx.x) * E + e] = hist[e];
 }
 
-// ---- step 2: both maps -----------------------------------------------------------------------
+// ---- step 2: counts of a chunk -> counts of all chunks before it -----------------------------
+// A lane per expert, the chunks split over the 16 wavefronts of a workgroup: each sums its stretch, then goes through it again
+// with the sum of the stretches before it.  Eight counters are requested together.
+__global__ __launch_bounds__(1024) void permute_scan_kernel(int32_t* __restrict__ chunk_hist /* [chunk][E] */, int nchunks, int E) {
+  constexpr int B = 8;
+  __shared__ int32_t part[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, e = blockIdx.x * 64 + lane;
+  const int per = (nchunks + 15) / 16, b0 = min(wave * per, nchunks), b1 = min(b0 + per, nchunks);
+  int32_t* col = chunk_hist + (e < E ? e : E - 1);                    // (lanes without an expert read, and do not write)
+  int32_t sum = 0;
+  for (int b = b0; b < b1; b += B) {
+    int32_t v[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) v[u] = col[static_cast<size_t>(min(b + u, b1 - 1)) * E];
+#pragma unroll
+    for (int u = 0; u < B; ++u) sum += b + u < b1 ? v[u] : 0;
+  }
+  part[wave][lane] = sum;
+  __syncthreads();
+  int32_t before = 0;
+  for (int w = 0; w < wave; ++w) before += part[w][lane];
+  for (int b = b0; b < b1; b += B) {
+    int32_t v[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) v[u] = col[static_cast<size_t>(min(b + u, b1 - 1)) * E];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      if (b + u < b1) {
+        if (e < E) col[static_cast<size_t>(b + u) * E] = before;
+        before += v[u];
+      }
+    }
+  }
+}
+
+// ---- step 3: both maps -----------------------------------------------------------------------
 // row of a pair = segment offset of its expert + pairs of that expert in earlier chunks, in earlier waves of this chunk and
-// in earlier lanes of this wave.  chunk_hist == null: the earlier pairs are counted here.
+// in earlier lanes of this wave.  chunk_hist == null: the earlier pairs are counted here; scanned: it holds the earlier chunks' counts.
 __global__ __launch_bounds__(kChunkPairs) void permute_maps_kernel(
     const int32_t* __restrict__ topk_idx, int P, int E, int bits, int epad, const int32_t* __restrict__ offsets,
-    const int32_t* __restrict__ chunk_hist, int32_t* __restrict__ row_of_pair, int32_t* __restrict__ pair_of_row) {
+    const int32_t* __restrict__ chunk_hist, int scanned, int32_t* __restrict__ row_of_pair, int32_t* __restrict__ pair_of_row) {
   __shared__ int32_t base[kMaxExperts];
   __shared__ uint16_t in_wave[kChunkWaves][kMaxExperts];              // pairs of an expert in a wave, then in the waves before it
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, chunk = blockIdx.x;
-  for (int e = tid; e < E; e += kChunkPairs) base[e] = offsets[e];
+  for (int e = tid; e < E; e += kChunkPairs) base[e] = offsets[e] + (scanned ? chunk_hist[static_cast<size_t>(chunk) * E + e] : 0);
   for (int i = tid; i < kChunkWaves * E; i += kChunkPairs) in_wave[i / E][i % E] = 0;
   const int p = chunk * kChunkPairs + tid;
   const int my = chunk_expert(topk_idx, p, P, E);
   const unsigned long long same = same_expert(my, bits);
   __syncthreads();
-  if (chunk_hist) {
+  if (chunk_hist && !scanned) {
     const int c = tid % epad;                                         // epad: a power of two, 64 .. 1024, at least E
     int32_t s = 0;
     if (c < E) {
@@ -73,7 +114,7 @@ __global__ __launch_bounds__(kChunkPairs) void permute_maps_kernel(
       for (int b = tid / epad; b < chunk; b += kChunkPairs / epad) s += chunk_hist[static_cast<size_t>(b) * E + c];
       if (s) atomicAdd(&base[c], s);
     }
-  } else {
+  } else if (!chunk_hist) {
     int next = chunk_expert(topk_idx, tid, P, E);
     for (int b = 0; b < chunk; ++b) {
       const int e = next;
@@ -102,7 +143,7 @@ __global__ __launch_bounds__(kChunkPairs) void permute_maps_kernel(
   }
 }
 
-// ---- step 3: row gather ------------------------------------------------------------
+// ---- step 4: row gather ------------------------------------------------------------
 
 // The combine kernels stream their rows: every source piece is read once and every destination piece written
 // once, to be consumed by a later kernel.  Non-temporal accesses keep them from displacing what the neighbouring
@@ -347,8 +388,10 @@ extern "C" int32_t moe_permute(const void* x, int dtype, int T, int d, int E, in
   while (epad < E) epad <<= 1;
   int32_t* hist = nchunks > kOneLaunchChunks ? static_cast<int32_t*>(ws) : nullptr;
   if (hist) MOE_LAUNCH("permute_count", permute_count_kernel, dim3(nchunks), dim3(kChunkPairs), 0, s, topk_idx, P, E, bits, hist);
+  const bool scan = hist && static_cast<long>(nchunks) * epad > kScanWords;
+  if (scan) MOE_LAUNCH("permute_scan", permute_scan_kernel, dim3(ceil_div(E, 64)), dim3(1024), 0, s, hist, nchunks, E);
   MOE_LAUNCH("permute_maps", permute_maps_kernel, dim3(nchunks), dim3(kChunkPairs), 0, s, topk_idx, P, E, bits, epad, offsets,
-             static_cast<const int32_t*>(hist), row_of_pair, pair_of_row);
+             static_cast<const int32_t*>(hist), static_cast<int>(scan), row_of_pair, pair_of_row);
   if (x)
     MOE_LAUNCH("permute_gather", permute_gather_kernel, dim3((T - 1) / (kMoverThreads / 64) + 1), dim3(kMoverThreads), 0, s,
                static_cast<const uint4*>(x), T, k, d * elem_size(dtype) / 16, static_cast<const int32_t*>(row_of_pair), static_cast<uint4*>(xp));

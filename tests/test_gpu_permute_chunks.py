@@ -1,5 +1,6 @@
 """The two maps of moe_permute where its workgroups end: pairs around one wavefront (64), one chunk (1024) and the number of chunks
-(8) above which the chunks are counted by a launch of their own; expert counts around powers of two (the ids are matched bit by
+(8) above which the chunks are counted by a launch of their own, the number of counters (65536) above which another one scans
+them; expert counts around powers of two (the ids are matched bit by
 bit); every pair on one expert, and experts without pairs.  Whole numbers: the maps equal the oracle's stable counting sort."""
 import numpy as np
 import pytest
@@ -11,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 # (T, k, E)
 SIZES = [(1, 1, 1), (1, 8, 128), (21, 3, 5), (64, 1, 16), (1023, 1, 1), (512, 2, 60), (1025, 1, 1024), (1023, 8, 128), (1024, 8, 128),
-         (1025, 8, 128), (16385, 1, 16), (9001, 4, 1000), (5000, 7, 65)]
+         (1025, 8, 128), (16385, 1, 16), (9001, 4, 1000), (5000, 7, 65),
+         (65536, 1, 1024), (65537, 1, 1024), (32768, 4, 513), (131073, 4, 65), (524289, 2, 5)]
 
 
 @pytest.mark.parametrize("spread", ["even", "one", "skewed"])
