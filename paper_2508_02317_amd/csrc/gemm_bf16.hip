@@ -137,7 +137,8 @@ __device__ __forceinline__ int frag_off_32(int row_base, int kk, int lane) {
 //     barrier that follow its own loads.
 //   * The address register and the 16-bit immediate are chosen here, so no address arithmetic is left in the slab
 //     loop (every vector instruction there takes issue slots from the MFMAs of both waves of the SIMD).
-// The results arrive asynchronously; they are consumed only after settle() below, which names them as operands.
+// The results arrive asynchronously; they are consumed only after a wait that names them as operands (arrived,
+// arrived_with_b, all_arrived in MainLoop).
 template <bool KS, int ROWS, int IMM>
 __device__ __forceinline__ bf16x8 lds_read_frag(uint32_t addr) {
   static_assert(IMM >= 0 && IMM + (KS ? 4 * ROWS * 2 : 0) < 65536, "the immediate offset of an LDS instruction has 16 bits");
@@ -320,8 +321,6 @@ template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false, bool TWO_SE
 template <int n> __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14));
 }
-// s_waitcnt that waits only for the LDS / scalar-memory counter to reach zero
-__device__ __forceinline__ void wait_lgkmcnt0() { __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14)); }
 
 // a wave's accumulators
 template <class T> using Acc = f32x4[T::FM][T::FN];
@@ -1743,8 +1742,8 @@ void ffn_bwd_bf16(const FfnBwdArgs& a) {
 // weight-gradient products never leave it.
 // ============================================================================================
 
-// column slots of the partial dot products: one per (column tile, wavefront column) of the dA product
-// column slots (64 columns each) of the combine-weight gradient's partial sums; dw_slots_max sizes the workspace
+// column slots of the combine-weight gradient's partial dot products: one per (column tile, wavefront column) of the dA product;
+// dw_slots_max sizes the workspace
 static int dw_slots_max(int f) { return ceil_div(f, TileBig::BN) * TileBig::WGN; }
 static int dw_slots(const RowTiles& rt, int f) { return rt.bm == TileFew::BM ? ceil_div(f, TileFew::BN) * TileFew::WGN : dw_slots_max(f); }
 
@@ -1868,7 +1867,7 @@ static RouterWs router_ws(int T, int d, int E, bool bwd) {
   RouterWs w{};
   size_t off = 0;
   w.tiles_count = off; off += 256;
-  const size_t t = align_up(static_cast<size_t>(ceil_div(T, 64) + 1) * sizeof(int32_t), 256);   // row tiles of 64 or 128 rows
+  const size_t t = align_up(static_cast<size_t>(ceil_div(T, 64) + 1) * sizeof(int32_t), 256);   // row tiles of 64 or 256 rows
   w.tiles_expert = off; off += t;
   w.tiles_row0 = off; off += t;
   w.dz = off; w.items = off; w.partial = off;
@@ -1888,10 +1887,11 @@ static RouterWs router_ws(int T, int d, int E, bool bwd) {
 size_t router_fwd_ws_bytes_bf16(int T, int d, int E) { return router_ws(T, d, E, false).total; }
 size_t router_bwd_ws_bytes_bf16(int T, int d, int E) { return router_ws(T, d, E, true).total; }
 
-static RowTiles router_tiles_at(void* ws, const RouterWs& w, int T) {
+static RowTiles router_tiles_at(void* ws, const RouterWs& w, int T, int bm) {
   char* b = static_cast<char*>(ws);
   RowTiles rt;
   rt.max_tiles = ceil_div(T, 64) + 1;
+  rt.bm = bm;
   rt.count = reinterpret_cast<int32_t*>(b + w.tiles_count);
   rt.expert = reinterpret_cast<int32_t*>(b + w.tiles_expert);
   rt.row0 = reinterpret_cast<int32_t*>(b + w.tiles_row0);
@@ -1900,9 +1900,9 @@ static RowTiles router_tiles_at(void* ws, const RouterWs& w, int T) {
 
 void router_fwd_bf16(const RouterFwdArgs& a) {
   const RouterWs w = router_ws(a.T, a.d, a.E, false);
-  const RowTiles rt = router_tiles_at(a.ws, w, a.T);
+  const RowTiles rt = router_tiles_at(a.ws, w, a.T, TileRouter::BM);
   MOE_LAUNCH("build_row_tiles", build_row_tiles_kernel, dim3(1), dim3(1024), 0, a.stream, static_cast<const int32_t*>(nullptr), 1, a.T,
-             TileRouter::BM, rt);
+             rt.bm, rt);
   RowArgs p{};
   p.a = static_cast<const bf16_t*>(a.x); p.lda = a.d;
   p.w0 = static_cast<const bf16_t*>(a.w_router); p.w_expert_stride = 0; p.ldw = a.d;
@@ -1913,13 +1913,13 @@ void router_fwd_bf16(const RouterFwdArgs& a) {
 
 void router_bwd_bf16(const RouterBwdArgs& a) {
   const RouterWs w = router_ws(a.T, a.d, a.E, true);
-  const RowTiles rt = router_tiles_at(a.ws, w, a.T);
+  const RowTiles rt = router_tiles_at(a.ws, w, a.T, TileBig::BM);
   char* base = static_cast<char*>(a.ws);
   bf16_t* dz = reinterpret_cast<bf16_t*>(base + w.dz);
   const long n8 = static_cast<long>(a.T) * a.E / 8;
   MOE_LAUNCH("router_cast_dz", cast_f32_bf16_kernel, dim3(static_cast<unsigned>((n8 + 255) / 256)), dim3(256), 0, a.stream, a.dlogits, dz, n8);
   MOE_LAUNCH("build_row_tiles", build_row_tiles_kernel, dim3(1), dim3(1024), 0, a.stream, static_cast<const int32_t*>(nullptr), 1, a.T,
-             TileBig::BM, rt);
+             rt.bm, rt);
   {  // dx (+)= dz * Wr
     RowArgs p{};
     p.a = dz; p.lda = a.E;
@@ -1952,7 +1952,6 @@ void router_bwd_bf16(const RouterBwdArgs& a) {
     p.lhs = dz; p.ld_lhs = a.E; p.M = a.E;
     p.rhs = static_cast<const bf16_t*>(a.x); p.ld_rhs = a.d; p.N = a.d;
     p.E = 1; p.P = a.T; p.items = items; p.partial = reinterpret_cast<float*>(base + w.partial);
-   
     p.out0 = static_cast<bf16_t*>(a.dw_router); p.out1 = p.out0; p.m_split = a.E;
     launch_wgrad<2>(p, a.stream);
   }

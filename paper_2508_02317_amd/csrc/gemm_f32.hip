@@ -59,7 +59,6 @@ __device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cas
 // piece, the reduction indices 4 (l / 16) .. +3.  Which index an MFMA pairs with which is free as long as both sides agree.
 // Reduction contiguous in memory: one 16-byte load per fragment; fragment h holds rows 16 h + l % 16.
 struct KContig {
-  static constexpr bool kStrided = false;
   const float* row[2];
   struct Piece { f32x4 v[2]; __device__ __forceinline__ float at(int h, int q) const { return v[h][q]; } };
   __device__ __forceinline__ Piece load(int k, int K) const {        // k: this lane's first index; beyond K reads as zero
@@ -72,7 +71,6 @@ struct KContig {
 };
 // Reduction strided: an 8-byte load per index; fragment h holds the columns 2 (l % 16) + h.
 struct KStrided {
-  static constexpr bool kStrided = true;
   const float* col; int ld;
   struct Piece { float2 v[4]; __device__ __forceinline__ float at(int h, int q) const { return h ? v[q].y : v[q].x; } };
   __device__ __forceinline__ Piece load(int k, int K) const {

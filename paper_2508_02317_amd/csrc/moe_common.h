@@ -214,7 +214,7 @@ size_t ffn_bwd_ws_bytes_f32(int P, int d, int f, int E, int have_saved);
 void ffn_fwd_f32(const FfnFwdArgs& a);
 void ffn_bwd_f32(const FfnBwdArgs& a);
 
-// ---- router linear (gemm_bf16.hip: bf16 MFMA; gemm_f32.hip: fp32 reference-speed kernels) --------
+// ---- router linear (gemm_bf16.hip: bf16 MFMA; gemm_f32.hip: fp32, a thread per output) ---------
 struct RouterFwdArgs {
   const void *x, *w_router;    // [T, d], [E, d]
   int T, d, E;

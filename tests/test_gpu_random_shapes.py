@@ -33,7 +33,7 @@ def _draw_cases(n, seed):
         f = 8 * int(r.integers(1, 50))
         skew = float(r.choice([0.0, 1.0, 3.0]))
         dt = "f32" if i % 6 == 5 else "bf16"
-        if dt == "f32":                     # one thread per output: keep the product small
+        if dt == "f32":                     # the small full-precision layers this element type is for
             T, d, f = min(T, 400), min(d, 128), min(f, 96)
         cases.append((i, T, k, d, f, E, dt, skew))
     return cases
