@@ -1,5 +1,6 @@
 """GPU parity of the bf16 products where their tiles and slabs end: reduction lengths around one slab (64), row counts
-around one MFMA fragment (16), one wavefront (128) and one tile (256), and widths around one tile.
+around one MFMA fragment (16), one wavefront (128) and one tile (256), and widths around one tile.  Experts with few rows take a
+smaller tile; LARGE_TILE_ROWS has few and many rows in one call, which takes the large one.
 
 The bound is that of every bf16 product (operands rounded to 8 bits, fp32 accumulation, one rounding of the result)."""
 import numpy as np
@@ -10,7 +11,8 @@ from tests.util import assert_close, q, to_dev, to_np, torch_dtype
 
 pytestmark = pytest.mark.gpu
 
-# (T, d, f): E = 2 experts, k = 1; about half the rows each, except T = 1 (one expert has none)
+# (T, d, f): E = 2 experts, k = 1; about half the rows each, except T = 1 (one expert has none).  The first four are few rows
+# (at most 128 per expert on average): 128 x 128 tiles; the others 256 x 256.
 SIZES = [(1, 8, 8), (31, 56, 64), (33, 64, 72), (130, 72, 128), (258, 128, 136), (509, 136, 56), (515, 264, 248),
          (1030, 192, 320)]
 
@@ -145,3 +147,45 @@ def test_products_of_experts_with_few_rows(T, d, f, E, k, gather, save_gu):
     for name, got, ref in (("Y", layer.y, fwd["Y"]), ("dX", layer.dx, bwd["dX"]), ("dWg", layer.dw_gate, bwd["dWg"]),
                            ("dWu", layer.dw_up, bwd["dWu"]), ("dWd", layer.dw_down, bwd["dWd"]), ("dlogits", layer.dlogits, bwd["dlogits"])):
         assert_close(to_np(got), ref, "bf16", name)
+
+
+# Rows per expert.  With the last expert's the average is above 128 rows: every expert takes the large tile, also those with a row,
+# with one MFMA fragment, with one strip (32) or with half a tile (128) and one row less and more; widths below one slab among them.
+LARGE_TILE_ROWS = [1, 15, 16, 17, 0, 31, 33, 127, 128, 129, 1003]
+
+
+@pytest.mark.parametrize("gather,save_gu", [(True, True), (True, False), (False, True)])
+@pytest.mark.parametrize("d,f", [(56, 40), (72, 136), (264, 56), (136, 264)])
+def test_few_rows_on_the_large_tile(d, f, gather, save_gu):
+    """Against the oracle, and bit for bit against the call without the last expert's rows, which takes the small tile (the same sums
+    in the same order)."""
+    import torch
+    from paper_2508_02317_amd.layer import MoELayer
+    E, T, few = len(LARGE_TILE_ROWS), sum(LARGE_TILE_ROWS), sum(LARGE_TILE_ROWS[:-1])
+    assert T > 128 * E and few <= 128 * E
+    r = np.random.default_rng(d + f)
+    X, dY = q(r.standard_normal((T, d)), "bf16"), q(r.standard_normal((T, d)), "bf16")
+    Wg, Wu = (q(r.standard_normal((E, f, d)) * 0.05, "bf16") for _ in range(2))
+    Wd = q(r.standard_normal((E, d, f)) * 0.05, "bf16")
+    idx = np.repeat(np.arange(E, dtype=np.int32), LARGE_TILE_ROWS)
+    idx[:few] = r.permutation(idx[:few])               # the last expert's rows come last
+    idx, w = idx[:, None], r.uniform(0.2, 1.0, (T, 1)).astype(np.float32)
+    weights = [to_dev(m, "bf16") for m in (Wg, Wu, Wd)]
+
+    def run(n):
+        layer = MoELayer(n, d, E, 1, f, torch_dtype("bf16"), *weights, prerouted=True, gather=gather, save_gu=save_gu)
+        layer.forward(to_dev(X[:n], "bf16"), topk_idx=to_dev(idx[:n]), topk_w=to_dev(w[:n]))
+        layer.backward(to_dev(dY[:n], "bf16"))
+        torch.cuda.synchronize()
+        return layer
+
+    large, small = run(T), run(few)
+    fwd = O.moe_layer_fwd(X, None, Wg, Wu, Wd, 1, routing=(idx, w))
+    bwd = O.moe_layer_bwd(fwd, dY, None, Wg, Wu, Wd)
+    for name, got, ref in (("Y", large.y, fwd["Y"]), ("dX", large.dx, bwd["dX"]), ("dWg", large.dw_gate, bwd["dWg"]),
+                           ("dWu", large.dw_up, bwd["dWu"]), ("dWd", large.dw_down, bwd["dWd"]), ("dw", large.dw, bwd["dw"])):
+        assert_close(to_np(got), ref, "bf16", name)
+    for name in ("y", "dx", "dw"):
+        assert torch.equal(getattr(large, name)[:few], getattr(small, name)), name
+    for name in ("dw_gate", "dw_up", "dw_down"):
+        assert torch.equal(getattr(large, name)[:-1], getattr(small, name)[:-1]), name
