@@ -337,9 +337,14 @@ __device__ __forceinline__ void zero_acc(Acc<T>& acc) {
 // acc += sum over segments of A_s(BM x K) * B_s(BN x K)^T for this wave's sub-tile (segments differ
 // only in their base pointers).
 //
-// The MFMA is the 16 x 16 x 32 one: at the chip's power limit, where these products run, it does 13-17 % more
-// arithmetic per second on random operands than the 32 x 32 x 16 one (256 CUs, operands in registers: 1974-2128
-// against 1713-1880 TFLOP/s; with the LDS reads of a 128 x 64 sub-tile 1768-1851 against 1680-1694).
+// The MFMA is the 16 x 16 x 32 one: kept busy, it does 13-17 % more arithmetic per second on random operands than the
+// 32 x 32 x 16 one (256 CUs, operands in registers: 1974-2128 against 1713-1880 TFLOP/s; with the LDS reads of a
+// 128 x 64 sub-tile 1768-1851 against 1680-1694: in both the clock falls below its 2.4 GHz).
+//
+// What bounds the loop: a slab of the gate/up product at 2560 rows per expert takes 2.62 k clocks at 1.86 GHz = 1.41 us
+// (64 MFMAs per wave, two waves per SIMD: 2.05 k clocks).  The loads and barriers alone take 1.36 us (at 2.39 GHz), the
+// MFMAs and LDS reads alone 1.10 us (at 2.06 GHz): the row products run at the rate the slabs arrive, 64 KiB per CU.  The
+// weight gradients' loads alone take 1.12-1.21 us, their MFMAs and LDS reads 1.25 us, together 1.60 us at 1.70-1.76 GHz.
 //
 // Slabs stream through the two LDS rings (SA buffers for the A side, SB for the B side) filled by direct
 // global->LDS loads.  A slab is two reduction steps (S0, S1) of FM rows of FN MFMAs.  A row-side fragment is read again
@@ -459,8 +464,8 @@ struct MainLoop {
   // ---- refill ----
   // The B side has nearly two slab periods from its refill to its use: its loads are spread over the rows of S0.  The A
   // side has one: it is enqueued right after the barrier, where it is not held up by MFMAs that a wave of the lower priority
-  // on its SIMD has to wait for (spread over the rows of S1 instead, at 2560 rows per expert: gate/up 1946 us against 1861,
-  // down 1074 against 1038, dX 1850 against 1781).
+  // on its SIMD has to wait for (spread over the rows of S1 instead, at 2560 rows per expert: gate/up 4.6 % slower, down
+  // 3.5 %, dX 3.9 %).
   static constexpr int load_at(int n, int row) { return n * row / FM; }
   template <int J, int JEND> __device__ __forceinline__ void refill_a(char* tile) {
     if constexpr (J < JEND) { da.issue_one(J, tile, wave); refill_a<J + 1, JEND>(tile); }
@@ -1057,8 +1062,8 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
     for (int pass = 0; pass < NP; ++pass) off[pass] = cl < ncols ? (pass * RPP + el / LPR) * ld2 + cl * 2u : StripRows::kNone;
     if constexpr (KIND == kDAct) {
       // The saved G and U of a strip are requested one strip ahead (the fragment registers are free now).  This epilogue is
-      // bound by the vector unit: 128 derivatives per lane, about 25 issue slots each, two waves per SIMD; it takes 35k of
-      // the 127k clocks of a tile (2560 rows per expert).  With compiled divisions, branches per access and the loads of a
+      // bound by the vector unit: 128 derivatives per lane, about 25 issue slots each, two waves per SIMD; it takes 24k of
+      // the 111k clocks of a tile (2560 rows per expert).  With compiled divisions, branches per access and the loads of a
       // strip awaited on the spot, dA took 1145 us against 1065 there, 274 against 260 at 512 rows per expert.
       const uint32_t n2 = static_cast<uint32_t>(p.N) * 2u;
       uint32_t goff[NP];
@@ -1498,6 +1503,11 @@ typedef Tile<128, 128, 64, 2, 2, 2, 3> TileFew;
 //     305 -> 356 (half of the experts need a second tile, which reads their weights again); with the backward 856 -> 875 at 64 rows
 //     and 926 -> 959 at 96 (its weights are read across the reduction, 256 bytes at a time instead of 512).
 // So: on average at most 128 rows per expert where the large tiles onto d leave CUs without work, and 64 in a forward pass of any size.
+// The average stands for uneven routing too (Zipf with exponent 1.2; half of the rows on one expert): E = 16, d = 1024, f = 2048, 125 rows
+// 120 -> 93 us / 315 -> 258 and 106 -> 90 / 312 -> 265; E = 63, d = 1024, f = 3072, 128 rows 475 -> 413 / 1547 -> 1449 and 428 -> 362 / 1471 ->
+// 1307; E = 128, d = 2048, f = 768, 64 rows 358 -> 317 and 339 -> 292 forward.  It loses where wide experts spill into a second round of
+// workgroups (E = 8, d = 4096, f = 3072, 128 rows: 190 -> 224 / 651 -> 682, 191 -> 209 / 632 -> 638; at 64 rows 188 -> 169 / 602 -> 558) and in the
+// forward of large calls with every row on one expert (E = 63 above 204 -> 235 / 952 -> 943; E = 512, d = 2048, f = 768, 64 rows 325 -> 386).
 static int row_bm(int P, int E, int d, bool backward) {
   const bool idle = static_cast<long>(E) * ceil_div(d, TileBig::BN) < 256 && P <= 128L * E;
   return idle || (!backward && P <= 64L * E) ? TileFew::BM : TileBig::BM;
