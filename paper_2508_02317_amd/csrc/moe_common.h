@@ -69,7 +69,8 @@ __device__ __forceinline__ float bf16_hi(uint32_t w) { return __uint_as_float(w 
 // bound by the vector unit).  The sum is formed 2^-32 times smaller and the result scaled back: the reciprocal's argument and
 // result then lie in 2^-125 .. 2^125 for every g, so nothing depends on how the hardware treats a subnormal one.  Where
 // exp(-g) is not finite the argument is capped (the Newton step has no infinities to handle) and 2^-125 2^-32 is zero, as
-// 1 / inf is; for g from -87.3 to -88.7 the sigmoid is the subnormal number it should be.
+// 1 / inf is; for g from -87.3 to -88.7 the sigmoid is the subnormal number it should be.  The two scalings cost one more
+// multiplication than the plain sum: 8192 tokens, d = 2048, 128 experts, step 2210 -> 2213 us (runs of one side differ by 0.3 %).
 __device__ __forceinline__ float sigmoid_fast(float g) {
   const float d = fminf(fmaf(__expf(-g), 0x1p-32f, 0x1p-32f), 0x1p125f);
   const float r = __builtin_amdgcn_rcpf(d);
