@@ -10,9 +10,11 @@
 //     one being multiplied, every MFMA operand is read from LDS most of a reduction step before its use,
 //     and one barrier per slab separates writers from readers; what does not exist (rows, columns, the end
 //     of a partial last slab) is out of the loads' range and reads as zero;
-//   * results leave through LDS as well, so that all global stores (and the loads of the
-//     saved pre-activations in the fused SwiGLU derivative) are 16 bytes per lane and
-//     contiguous along rows;
+//   * a workgroup stays on its CU and takes tile after tile; the rings never drain: the first two slabs of the
+//     next tile are enqueued behind the last of this one and land while the epilogue runs;
+//   * results leave through LDS as well -- 16 rows of a wave at a time, in the one ring buffer that is free
+//     between two tiles -- so that all global stores (and the loads of the saved pre-activations in the fused
+//     SwiGLU derivative) are 16 bytes per lane and contiguous along rows;
 //   * an operand whose reduction index is contiguous in memory is staged as
 //     [rows][BK] and read with 16-byte LDS loads; an operand whose reduction index is the
 //     slow axis in memory (the weight in the two backward-data products, both operands of
@@ -41,6 +43,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kXcds = 8;
 
@@ -63,14 +67,23 @@ struct Tile {
   static constexpr int SA = STAGES_A_, SB = STAGES_B_;
   static constexpr int kBBase = SA * kABytes;             // the column side's buffers follow the row side's
   static constexpr int kLdsBytes = SA * kABytes + SB * kBBytes;
-  // Epilogue staging strips (one per wave, 32 rows x (WN + 4) floats) reuse the ring from its start once it is idle.
-  static constexpr int kStripBytes = 32 * (WN + 4) * 4;
-  static constexpr int kStripBase = 0;
-  static constexpr int kLdsAlloc = kWaves * kStripBytes > kLdsBytes ? kWaves * kStripBytes : kLdsBytes;
-  static_assert(kLdsAlloc <= 160 * 1024, "a CU has 160 KiB of LDS");
-  static constexpr int kBlocksPerCu = 2 * kLdsAlloc <= 160 * 1024 ? 2 : 1;   // by LDS capacity
+  static_assert(kLdsBytes <= 160 * 1024, "a CU has 160 KiB of LDS");
+  static constexpr int kBlocksPerCu = 2 * kLdsBytes <= 160 * 1024 ? 2 : 1;   // by LDS capacity
   static constexpr int kWavesPerSimd = kBlocksPerCu * kWaves / 4;
 };
+
+// Hands back its argument through an empty asm: values derived from the result cannot be computed before
+// this point, so per-lane indices of the epilogue and of the next tile's loads do not occupy registers during the main loop.
+__device__ __forceinline__ int not_before_here(int v) { asm volatile("" : "+v"(v)); return v; }
+// A wave-uniform value in a scalar register (integer divisions and clamps are done on the vector unit, and everything derived
+// from their results would stay there).
+__device__ __forceinline__ int scalar(int v) { return __builtin_amdgcn_readfirstlane(not_before_here(v)); }
+// min of two wave-uniform values, as a scalar instruction (a minimum and a maximum in a row would become one vector instruction)
+__device__ __forceinline__ int scalar_min(int a, int b) {
+  int v = min(a, b);
+  asm("" : "+s"(v));
+  return v;
+}
 
 // One operand tile of ROWS rows: element (row, k).  Two halves of ROWS/2 rows with their own
 // base so that the gate and the up projection can share one tile.
@@ -165,12 +178,19 @@ __device__ __forceinline__ bf16x8 lds_read_frag(uint32_t addr) {
 //   * reduction rows beyond K of a k-strided operand lie beyond the range of the last slab's descriptor, and
 //   * slabs beyond the end of the reduction get an empty descriptor,
 // and every wave enqueues the same number of loads per slab whatever is left: all waits are immediates and the slab
-// loop has a single path.  Only a partial last slab of a k-contiguous operand needs a select (issue_tail).
+// loop has a single path.  Only a partial last slab of a k-contiguous operand needs a select (mask_beyond).
 //
 // Ranges.  k-contiguous: everything but the offset that stands for "does not exist" (token rows of a gathered operand
 // reach up to 4 GiB - 128 bytes: the 8-bit products' codes).  Gathered k-strided: a row that does not exist is moved to the
 // range's end and a column's offset (below 64 KiB) comes on top, so the range leaves that much room below 4 GiB; its
 // operands, the bf16 token matrices, are smaller than that.
+// Everything per lane is selected, never branched over: around a divergent branch the compiler rewrites the tile loop's own
+// (uniform) branches as lane masks, the parts of the descriptors end up in vector registers, and every load of the slab loop
+// becomes a loop over lanes.
+__device__ __forceinline__ uint32_t off_if(bool exists, uint32_t off, uint32_t none) {
+  asm("" : "+v"(off));                                 // (formed on every path)
+  return exists ? off : none;
+}
 constexpr uint32_t kRangeAll = 0xFFFFFF80u;
 constexpr uint32_t kRangeRows = 0xFFFF0000u;
 constexpr uint32_t kOffNone = 0xFFFFFFF0u;      // beyond every range
@@ -184,13 +204,14 @@ template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false, bool TWO_SE
   const char* base;          // wave-uniform: slab 0
   long step;                 // bytes per slab (uniform)
   uint32_t voff[N];          // per lane, bytes
-  int K, nslabs;             // reduction length (k-strided: limits the last slab) and slabs that exist
-  int seg_slabs;             // TWO_SEG: slabs seg_slabs.. come from a second matrix ...
+  int K, nslabs;             // reduction length of a segment (k-strided: limits its last slab) and slabs that exist
+  int seg_slabs;             // TWO_SEG: slabs seg_slabs.. belong to a second segment ...
   long seg_delta;            // ... whose bytes lie this much further
+  int valid;                 // k-contiguous: rows of this wave's half of the tile that exist
   __amdgpu_buffer_rsrc_t rsrc;   // the slab being enqueued
-  // gathered k-strided operand: the memory rows of the wave's NR reduction rows of the next slab to be
-  // issued, fetched with scalar loads one slab ahead (they do not touch the vector-memory counter
-  // that orders the ring)
+  // The row list of a gathered operand is read with scalar loads: they do not touch the vector-memory counter that orders
+  // the ring.  k-strided: the memory rows of the wave's NR reduction rows of the next slab to be issued, fetched one slab
+  // ahead.  k-contiguous: the memory rows of the wave's tile rows, once per tile.
   typedef __attribute__((address_space(4))) const int32_t* RowList;
   typedef int32_t RowVec __attribute__((ext_vector_type(KS && GATHER ? NR : 1)));   // a value, not an array: stays in scalar registers
   RowList rows;              // wave-uniform: gather + grow + wave * NR
@@ -205,27 +226,46 @@ template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false, bool TWO_SE
       for (int j = 0; j < NR; ++j) next_row[j] = r[j];
     }
   }
-  // K_: reduction length, nslabs_: slabs the main loop may read
+  // k-contiguous: this lane's 16-byte piece of chunk i
+  static __device__ __forceinline__ void place_of(int i, int wave, int lane, int& row, int& piece) {
+    constexpr int PPR = BK / 8, RPC = 1024 / (BK * 2), RPL = 256 / (BK * 2);
+    row = (wave * N + i) * RPC + lane / PPR;
+    piece = (lane % PPR) ^ ((row / RPL) & (PPR - 1));
+  }
+  // k-contiguous, in row order: the offsets of every chunk
+  __device__ __forceinline__ void place_rows(int wave, int lane) {
+    static_assert(!KS && !GATHER, "");
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      int row, piece;
+      place_of(i, wave, lane, row, piece);
+      const int rh = row - (wave >= WAVES / 2 ? ROWS / 2 : 0);
+      voff[i] = off_if(rh < valid, static_cast<uint32_t>(rh) * ld2 + piece * 16, kOffNone);
+    }
+  }
+  // point at an operand of another tile.  K_: reduction length (of a segment), nslabs_: slabs that exist
   __device__ __forceinline__ void init(const Operand& op, int K_, int nslabs_, int wave, int lane) {
     K = K_; nslabs = nslabs_;
+    asm("" : "+s"(K), "+s"(nslabs));                          // scalar registers on every path: the descriptors are made of them
+    ld2 = static_cast<uint32_t>(op.ld * 2);
     const bf16_t* b = op.half[0];
     if constexpr (!KS) {
-      constexpr int PPR = BK / 8, RPC = 1024 / (BK * 2), RPL = 256 / (BK * 2);
       const bool upper = wave >= WAVES / 2;                    // uniform
-      const int valid = upper ? op.valid[1] : op.valid[0];
-      if (!GATHER && upper) b = op.half[1];
+      valid = upper ? op.valid[1] : op.valid[0];
+      if constexpr (GATHER) {
+        constexpr int PPR = BK / 8, RPC = 1024 / (BK * 2);
+        RowList r = reinterpret_cast<RowList>(reinterpret_cast<uintptr_t>(op.gather + op.grow + wave * (N * RPC)));
 #pragma unroll
-      for (int i = 0; i < N; ++i) {
-        const int row = (wave * N + i) * RPC + lane / PPR;
-        const int piece = (lane % PPR) ^ ((row / RPL) & (PPR - 1));
-        const int rh = row - (upper ? ROWS / 2 : 0);
-        const bool exists = rh < valid;
-        if constexpr (GATHER) {
-          const int mrow = op.gather[op.grow + (exists ? row : 0)];
-          voff[i] = exists ? static_cast<uint32_t>(mrow) * static_cast<uint32_t>(op.ld * 2) + piece * 16 : kOffNone;
-        } else {
-          voff[i] = exists ? static_cast<uint32_t>(static_cast<long>(rh) * op.ld * 2 + piece * 16) : kOffNone;
+        for (int i = 0; i < N; ++i) {
+          int row, piece, mrow = r[i * RPC];
+          place_of(i, wave, lane, row, piece);
+#pragma unroll
+          for (int q = 1; q < RPC; ++q) mrow = lane / PPR == q ? r[i * RPC + q] : mrow;   // entries past the tile's rows exist (padding) and are not used
+          voff[i] = off_if(row - (upper ? ROWS / 2 : 0) < valid, static_cast<uint32_t>(mrow) * ld2 + piece * 16, kOffNone);
         }
+      } else {
+        if (upper) b = op.half[1];
+        place_rows(wave, lane);
       }
     } else {
       constexpr int PPK = ROWS / 8;
@@ -236,12 +276,11 @@ template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false, bool TWO_SE
         const int col = piece * 8;
         const bool exists = col < op.valid[0] + op.valid[1];   // k-strided operands are never dual
         // (gathered: a column that does not exist reads the row's first one, so that row offset + column offset cannot wrap)
-        if constexpr (GATHER) voff[i] = static_cast<uint32_t>((exists ? col : 0) * 2);
-        else voff[i] = exists ? static_cast<uint32_t>((static_cast<long>(k) * op.ld + col) * 2) : kOffNone;
+        if constexpr (GATHER) voff[i] = off_if(exists, col * 2, 0);
+        else voff[i] = off_if(exists, static_cast<uint32_t>(k) * ld2 + col * 2, kOffNone);
       }
     }
     step = (KS ? (GATHER ? 0L : static_cast<long>(BK) * op.ld) : BK) * 2;
-    ld2 = static_cast<uint32_t>(op.ld * 2);
     // the base is the same in every lane: say so
     const uint64_t b64 = reinterpret_cast<uint64_t>(b);
     const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(b64));
@@ -254,6 +293,17 @@ template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false, bool TWO_SE
       fetch_rows(0);
     }
   }
+  // the partial last slab of a segment of a k-contiguous operand: pieces whose reduction index (k0: that of the slab) is >= K read zeros
+  __device__ __forceinline__ void mask_beyond(int k0, int wave, int lane) {
+    if constexpr (!KS) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        int row, piece;
+        place_of(i, wave, lane, row, piece);
+        voff[i] = k0 + piece * 8 < K ? voff[i] : kOffNone;
+      }
+    }
+  }
   // descriptor of slab `slab`; every part of it scalar (a clamp on the vector unit would make the loads a loop over lanes)
   __device__ __forceinline__ void point(int slab) {
     long off = slab * step;
@@ -262,8 +312,7 @@ template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false, bool TWO_SE
     if constexpr (KS && !GATHER) {
       int first = slab * BK;
       if constexpr (TWO_SEG) first -= slab >= seg_slabs ? seg_slabs * BK : 0;
-      int left = min(BK, K - first);
-      asm("" : "+s"(left));
+      int left = scalar_min(BK, K - first);
       left = max(left, 0);
       if constexpr (TWO_SEG) left = slab < nslabs ? left : 0;
       range = static_cast<uint32_t>(left) * ld2;
@@ -297,22 +346,6 @@ template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false, bool TWO_SE
 #pragma unroll
     for (int i = 0; i < N; ++i) issue_one(i, tile, wave);
     fetch_rows(slab + 1);
-  }
-  // the partial last slab of a k-contiguous operand: pieces whose reduction index is >= K read zeros
-  __device__ __forceinline__ void issue_tail(int slab, char* tile, int wave, int lane) {
-    nslabs = slab + 1;
-    point(slab);
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-      if constexpr (KS) {
-        issue_one(i, tile, wave);
-      } else {
-        constexpr int PPR = BK / 8, RPC = 1024 / (BK * 2), RPL = 256 / (BK * 2);
-        const int row = (wave * N + i) * RPC + lane / PPR;
-        const int piece = (lane % PPR) ^ ((row / RPL) & (PPR - 1));
-        issue_at(i, slab * BK + piece * 8 < K ? voff[i] : kOffNone, tile, wave);
-      }
-    }
   }
 };
 
@@ -364,21 +397,19 @@ __device__ __forceinline__ void zero_acc(Acc<T>& acc) {
 // advanced once per slab (4 to 12 vector additions against 64 MFMAs).
 template <class T, bool A_KS, bool B_KS, bool A_GATHER = false, bool B_GATHER = false, int B_HALF = T::WN / 2, bool TWO_SEG = false>
 struct MainLoop {
-  typedef Dma<A_KS, T::BM, T::BK, T::kWaves, A_GATHER> DmaA;
+  typedef Dma<A_KS, T::BM, T::BK, T::kWaves, A_GATHER, TWO_SEG> DmaA;
   typedef Dma<B_KS, T::BN, T::BK, T::kWaves, B_GATHER, TWO_SEG> DmaB;
   static constexpr int NA = DmaA::N, NB = DmaB::N;     // loads per thread per slab and side
   static constexpr int SA = T::SA, SB = T::SB;
   static constexpr int FM = T::FM, FN = T::FN;
-  static_assert(SA >= 2 && SB >= 3, "one slab being multiplied, at least one in flight");
+  static_assert(SA == 2 && SB == 3, "slab kt+2 is enqueued while slab kt is multiplied, on the row side after its barrier");
+  static constexpr int kAhead = 2;                     // slabs in the rings when one is begun
   static constexpr int STEPS = T::BK / 32;
   static_assert(STEPS == 2, "a slab is two reduction steps");
   static constexpr int R0 = FM >= 8 ? 2 : 1;           // rows of S1 before the barrier
   static_assert(FM > R0, "rows of S1 after the barrier");
-  static constexpr int kMaxAhead = (SA - 1) * NA + (SB - 2) * NB;   // loads in flight behind those of slab 0 when the stream starts
-  static constexpr int kBeyond = (SA - 2) * NA + (SB - 2) * NB;     // loads enqueued after those of slab kt+1 at the end of slab kt
   static_assert((SA - 1) * NA + (SB - 1) * NB < 64, "vmcnt is a 6-bit counter");
   static constexpr int RA = A_KS ? 2 : 1, RB = B_KS ? 2 : 1;   // LDS instructions per fragment
-  static constexpr bool KS_ONLY = A_KS && B_KS;        // a partial last slab needs no pass of its own
 
   DmaA da;
   DmaB db;
@@ -399,7 +430,8 @@ struct MainLoop {
   char* lds;
   uint32_t lds32;                                      // the ring's start as an LDS address
   int stage_a, stage_b;                                // ring positions of the slab being multiplied
-  int nslabs, K, wave;
+  int wave;
+  int ls;                                              // slab that is enqueued next, of the tile the loads point at
 
   // tile rows between the wave's first fragment of a side and fragment i (the second half of the column side may lie apart)
   static constexpr int a_frag_row(int i) { return 16 * i; }
@@ -528,27 +560,28 @@ struct MainLoop {
       step1_tail<I + 1>(acc);
     }
   }
-  // A slab of a wave with rows.  On entry the reads of its S0 are in flight, on exit those of the next slab's -- after the
-  // last one, of a buffer that holds nothing: a body of its own for the last slab costs registers across the loop.
-  __device__ __forceinline__ void slab(int kt, Acc<T>& acc) {
+  // A slab of a wave with rows.  On entry the reads of its S0 are in flight, on exit those of the slab that follows in the
+  // rings -- after a tile's last one, of the next tile, which reads them again: a body of its own for the last slab costs
+  // registers across the loop.
+  __device__ __forceinline__ void slab(Acc<T>& acc) {
     const int na = next_stage(stage_a, SA), nb = next_stage(stage_b, SB);
     const int adv_a = (na - stage_a) * T::kABytes, adv_b = (nb - stage_b) * T::kBBytes;
-    db.point(kt + SB - 1);
+    db.point(ls);
     step0<0>(buf_b(stage_b == 0 ? SB - 1 : stage_b - 1), adv_a, adv_b, acc);
-    db.fetch_rows(kt + SB);
+    db.fetch_rows(ls + 1);
     step1_head<0>(acc);
     all_arrived();                                     // this wave no longer needs the buffers of slab kt
-    wait_vmcnt<kBeyond>();                             // slab kt+1 has landed
+    wait_vmcnt<NB>();                                  // slab kt+1 has landed
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    da.point(kt + SA);
+    da.point(ls);
     if constexpr (!B_ROLL) read_range_b<0, 0, FN>();
     read_range_a<0, 0, R0>();
     __builtin_amdgcn_sched_barrier(0);
     refill_a<0, NA>(buf_a(stage_a));
     __builtin_amdgcn_sched_barrier(0);
     step1_tail<R0>(acc);
-    da.fetch_rows(kt + SA + 1);
+    da.fetch_rows(ls + 1);
     if constexpr (!A_KS) {
       aa[0] += (next_stage(na, SA) - na) * T::kABytes;
       aa[1] += adv_a;
@@ -557,11 +590,18 @@ struct MainLoop {
       ab[0] += (next_stage(nb, SB) - nb) * T::kBBytes;
       ab[1] += adv_b;
     }
-    stage_a = na; stage_b = nb;
     __builtin_amdgcn_sched_barrier(0);
   }
+  // the same of a wave without rows
+  __device__ __forceinline__ void idle_slab() {
+    db.issue(ls, buf_b(stage_b == 0 ? SB - 1 : stage_b - 1), wave);
+    wait_vmcnt<NB>();
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    da.issue(ls, buf_a(stage_a), wave);
+  }
 
-  // first slab's S0 from the first buffers of the rings
+  // the first step of the slab at the rings' current positions
   __device__ __forceinline__ void read_first() {
     if constexpr (B_ROLL) {                            // in the order of the slab body
       read_range_a<0, 0, FM - 1>();
@@ -571,211 +611,189 @@ struct MainLoop {
       read_range_b<0, 0, FN>();
       read_range_a<0, 0, FM>();
     }
-    if constexpr (!A_KS) aa[0] += T::kABytes;          // from here on [0] addresses the buffer of the next slab
-    if constexpr (!B_KS) ab[0] += T::kBBytes;
+    if constexpr (!A_KS) aa[0] += (next_stage(stage_a, SA) - stage_a) * T::kABytes;   // from here on [0] addresses the buffer of the next slab
+    if constexpr (!B_KS) ab[0] += (next_stage(stage_b, SB) - stage_b) * T::kBBytes;
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  __device__ __forceinline__ void prepare(int K_, char* lds_) {
+  __device__ __forceinline__ void prepare(char* lds_) {
     wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform: LDS destinations stay scalar
-    lds = lds_; K = K_;
+    lds = lds_;
     lds32 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)lds_));
-    nslabs = K > 0 ? (KS_ONLY ? (K + T::BK - 1) / T::BK : K / T::BK) : 0;
+    stage_a = 0; stage_b = 0;
   }
-  // fragment addresses in the first buffers of the rings (first tile rows of this wave's sub-tile: a_row / b_row)
+  // fragment addresses at the rings' current positions (first tile rows of this wave's sub-tile: a_row / b_row)
   __device__ __forceinline__ void place(int a_row, int b_row, int lane) {
+    const uint32_t at_a = lds32 + stage_a * T::kABytes, at_b = lds32 + T::kBBase + stage_b * T::kBBytes;
 #pragma unroll
     for (int i = 0; i < NAA; ++i) {                    // k-strided: fragment i at step 0; k-contiguous: fragment 0 at step i
-      if constexpr (A_KS) aa[i] = lds32 + frag_off<true, T::BM, T::BK>(a_row + a_frag_row(i), 0, lane);
-      else aa[i] = lds32 + frag_off<false, T::BM, T::BK>(a_row, i, lane);
+      if constexpr (A_KS) aa[i] = at_a + frag_off<true, T::BM, T::BK>(a_row + a_frag_row(i), 0, lane);
+      else aa[i] = at_a + frag_off<false, T::BM, T::BK>(a_row, i, lane);
     }
 #pragma unroll
     for (int i = 0; i < NAB; ++i) {
-      if constexpr (B_KS) ab[i] = lds32 + T::kBBase + frag_off<true, T::BN, T::BK>(b_row + b_frag_row(i), 0, lane);
-      else ab[i] = lds32 + T::kBBase + frag_off<false, T::BN, T::BK>(b_row, i, lane);
+      if constexpr (B_KS) ab[i] = at_b + frag_off<true, T::BN, T::BK>(b_row + b_frag_row(i), 0, lane);
+      else ab[i] = at_b + frag_off<false, T::BN, T::BK>(b_row, i, lane);
     }
   }
-  // point the loads at the operands and fill both rings, slab by slab.  The rings must be idle.  The column side of a slab
-  // goes first: the row side of a gathered product waits for its row list.
-  __device__ __forceinline__ void start(const Operand& oa, const Operand& ob, int a_row, int b_row) {
-    const int lane = threadIdx.x & 63;
-    da.init(oa, K, nslabs, wave, lane);
-    db.init(ob, K, nslabs, wave, lane);
-    fill();
-    place(a_row, b_row, lane);
-  }
-  __device__ __forceinline__ void fill() {
-    stage_a = 0; stage_b = 0;
-    if (nslabs <= 0) return;
-#pragma unroll
-    for (int s0 = 0; s0 < (SA > SB - 1 ? SA : SB - 1); ++s0) {
-      if (s0 < SB - 1) db.issue(s0, buf_b(s0), wave);
-      if (s0 < SA) da.issue(s0, buf_a(s0), wave);
+
+  // ---- tiles ----
+  // Slabs of a tile: a reduction of K indices (TWO_SEG: twice), a partial last slab counted whole, at least kAhead (the rings
+  // hold slabs of at most two tiles).
+  static __device__ __forceinline__ int slabs_of(int K) { return (TWO_SEG ? 2 : 1) * ((K + T::BK - 1) / T::BK); }
+  static __device__ __forceinline__ int slabs_run(int K) { return max(slabs_of(K), kAhead); }
+  // Point the loads at a tile's operands.  K = 0: there is no such tile, and its slabs are empty.  TWO_SEG: two segments of K indices each, columns 0 .. K-1 and K .. 2K-1 of the
+  // A side, opB and then opB2.
+  __device__ __forceinline__ void load_tile(const Operand& opA, const Operand& opB, const bf16_t* b2, int K) {
+    const int lane = not_before_here(threadIdx.x & 63), n = slabs_of(K);
+    da.init(opA, K, n, wave, lane);
+    db.init(opB, K, n, wave, lane);
+    if constexpr (TWO_SEG) {
+      static_assert(!TWO_SEG || (!A_KS && B_KS && !A_GATHER), "");
+      da.seg_slabs = db.seg_slabs = n / 2;
+      da.seg_delta = 2L * K - (n / 2) * da.step;
+      db.seg_delta = reinterpret_cast<const char*>(b2) - reinterpret_cast<const char*>(opB.half[0]) - (n / 2) * db.step;
     }
+    ls = 0;
   }
-  // Slabs k0 .. k1-1, the first of which has landed in the first buffers of the rings and is visible to all.
-  // `active` is false for a wave whose sub-tile holds no row of the expert (the tile sticks out of the row segment): it
-  // only takes part in the loads and barriers; its SIMD time goes to the other waves.
-  __device__ __forceinline__ void multiply(int k0, int k1, bool active, Acc<T>& acc) {
-    if (active) {
-      read_first();
-#pragma nounroll
-      for (int kt = k0; kt < k1; ++kt) slab(kt, acc);
-      all_arrived();                                   // nothing is in flight into a register when the epilogue starts
-      arrived_with_b<0, 0>(a[0]);
-    } else {
-#pragma nounroll
-      for (int kt = k0; kt < k1; ++kt) {
-        db.issue(kt + SB - 1, buf_b(stage_b == 0 ? SB - 1 : stage_b - 1), wave);
-        wait_vmcnt<kBeyond>();
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        da.issue(kt + SA, buf_a(stage_a), wave);
-        stage_a = next_stage(stage_a, SA); stage_b = next_stage(stage_b, SB);
+  // before slab `ls` is enqueued: a partial slab of a k-contiguous side
+  __device__ __forceinline__ void before_slab() {
+    if constexpr (!(A_KS && B_KS)) {
+      if (da.K % T::BK != 0) {                         // (widths that are no multiple of 64)
+        const int lane = not_before_here(threadIdx.x & 63);
+        int s = ls;
+        if constexpr (TWO_SEG) {
+          if (s == da.seg_slabs) da.place_rows(wave, lane);
+          if (s >= da.seg_slabs) s -= da.seg_slabs;
+        }
+        if (s == da.K / T::BK) {
+          da.mask_beyond(s * T::BK, wave, lane);
+          db.mask_beyond(s * T::BK, wave, lane);
+        }
       }
     }
-    wait_vmcnt<0>();                                   // the loads for slabs beyond the end write (zeros) into the rings too
-    __syncthreads();                                   // all reads and loads done before anything else uses the rings
   }
-  // multiply the segment whose first slabs have been enqueued by start()
-  __device__ __forceinline__ void go(bool active, Acc<T>& acc) {
-    if (nslabs <= 0) return;
-    wait_vmcnt<kMaxAhead>();                           // slab 0 has landed
+  // the first kAhead slabs of the first tile into the idle rings; on return its first one has landed and is visible to all
+  __device__ __forceinline__ void fill() {
+#pragma unroll
+    for (int s0 = 0; s0 < kAhead; ++s0) {
+      before_slab();
+      db.issue(ls, buf_b(s0), wave);
+      da.issue(ls, buf_a(s0), wave);
+      ++ls;
+    }
+    wait_vmcnt<NA + NB>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    multiply(0, nslabs, active, acc);
   }
-  // the reduction indices that do not fill a slab, where a side is k-contiguous: one slab on its own
-  __device__ __forceinline__ void tail(int a_row, int b_row, bool active, Acc<T>& acc) {
-    if constexpr (!KS_ONLY) {
-      if (K <= 0 || K % T::BK == 0) return;
-      const int lane = threadIdx.x & 63;
-      stage_a = 0; stage_b = 0;
-      da.issue_tail(nslabs, buf_a(0), wave, lane);
-      db.issue_tail(nslabs, buf_b(0), wave, lane);
-      place(a_row, b_row, lane);
-      wait_vmcnt<0>();
-      __syncthreads();
-      multiply(nslabs, nslabs + 1, active, acc);
+  // Multiply the n slabs of a tile, the first of which has landed at the rings' current positions; `next` points the loads
+  // at the tile that follows, whose first kAhead slabs are enqueued behind this one's.
+  // `active` is false for a wave whose sub-tile holds no row of the expert (the tile sticks out of the row segment): it
+  // only takes part in the loads and barriers; its SIMD time goes to the other waves.
+  template <bool ALWAYS_ACTIVE, class Next>
+  __device__ __forceinline__ void tile(int n, int a_row, int b_row, bool active, Acc<T>& acc, const Next& next) {
+    if (ALWAYS_ACTIVE || active) {
+      place(a_row, b_row, not_before_here(threadIdx.x & 63));
+      read_first();
     }
-  }
-
-  __device__ __forceinline__ void run(const Operand& opA, const Operand& opB, int K_, char* lds_, int a_row, int b_row, bool active, Acc<T>& acc) {
-    prepare(K_, lds_);
-    start(opA, opB, a_row, b_row);
-    go(active, acc);
-    tail(a_row, b_row, active, acc);
-  }
-  // Two segments of K reduction indices each: columns 0 .. K-1 and K .. 2K-1 of the A side, opB and then opB2.  Whole
-  // slabs stream through as one reduction of 2K (the rings never drain); otherwise one segment follows the other.
-  __device__ __forceinline__ void run2(const Operand& opA, const Operand& opB, const Operand& opB2, int K_, char* lds_, int a_row, int b_row,
-                                       bool active, Acc<T>& acc) {
-    static_assert(TWO_SEG && !A_KS && B_KS && !A_GATHER, "");
-    const bool whole = K_ % T::BK == 0;
 #pragma nounroll
-    for (int seg = 0; seg < (whole ? 1 : 2); ++seg) {
-      Operand oa = opA, ob = opB;
-      if (seg) { oa.half[0] += K_; oa.half[1] += K_; ob.half[0] = opB2.half[0]; ob.half[1] = opB2.half[1]; }
-      prepare(whole ? 2 * K_ : K_, lds_);
-      const int lane = threadIdx.x & 63;
-      da.init(oa, K, nslabs, wave, lane);
-      db.init(ob, K_, nslabs, wave, lane);
-      db.seg_slabs = whole ? K_ / T::BK : 0x7FFFFFFF;
-      db.seg_delta = whole ? reinterpret_cast<const char*>(opB2.half[0]) - reinterpret_cast<const char*>(opB.half[0]) - db.seg_slabs * db.step : 0L;
-      fill();
-      place(a_row, b_row, lane);
-      go(active, acc);
-      tail(a_row, b_row, active, acc);
+    for (int kt = 0; kt < n; ++kt) {
+      if (kt == n - kAhead) next();
+      before_slab();
+      if (ALWAYS_ACTIVE || active) slab(acc);
+      else idle_slab();
+      ++ls;
+      stage_a = next_stage(stage_a, SA); stage_b = next_stage(stage_b, SB);
+    }
+    if (ALWAYS_ACTIVE || active) {
+      all_arrived();                                   // nothing is in flight into a register when the epilogue starts
+      arrived_with_b<0, 0>(a[0]);
+    }
+  }
+  // After a tile: the part of the free column-side buffer that this wave's loads fill next (see the epilogue)
+  static constexpr int kScratch = NB * 1024;
+  __device__ __forceinline__ uint32_t scratch() const {
+    return lds32 + T::kBBase + (stage_b == 0 ? SB - 1 : stage_b - 1) * T::kBBytes + wave * kScratch;
+  }
+  // the empty slabs behind the last tile write zeros into the LDS: they are awaited before the workgroup gives it back
+  static __device__ __forceinline__ void finish() { wait_vmcnt<0>(); }
+};
+
+// ---- epilogue: accumulators -> LDS -> 16-byte row-contiguous global accesses -----------------------------
+// The products are accumulated transposed (the MFMA is handed the weight-side fragment as its first operand): of the
+// 16x16 tile (i, j) a lane then holds tile row lane%16 and the four consecutive columns 4*(lane/16) .. +3.  The memory
+// pipeline joins the 16-byte accesses of four neighbouring lanes, so results pass through the LDS to give neighbouring lanes
+// neighbouring columns (exchanged between lanes in registers, which gives them neighbouring rows, the stores of a
+// 256 x 256 tile took 10k clocks instead of 5k).
+//
+// The rings hold the next tile's first two slabs by then, but one column-side buffer is free: the one that the next tile's
+// slab 2 goes to.  A wave parks its results in the part of that buffer that its own loads will fill (kScratch bytes), so no
+// other wave has to be waited for.  Parking writes and reads are assembly statements for the reason given at lds_read_frag;
+// a wave's LDS accesses are executed in order, and every read is awaited inside its statement.
+__device__ __forceinline__ void lds_park8(uint32_t addr, u32x2 v) { asm volatile("ds_write_b64 %0, %1" :: "v"(addr), "v"(v)); }
+__device__ __forceinline__ void lds_park16(uint32_t addr, u32x4 v) { asm volatile("ds_write_b128 %0, %1" :: "v"(addr), "v"(v)); }
+__device__ __forceinline__ void lds_fetch(uint32_t a0, uint32_t a1, u32x4& v0, u32x4& v1) {
+  asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(v0), "=&v"(v1) : "v"(a0), "v"(a1));
+}
+__device__ __forceinline__ void lds_fetch(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x4& v0, u32x4& v1, u32x4& v2, u32x4& v3) {
+  asm volatile("ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+               : "=&v"(v0), "=&v"(v1), "=&v"(v2), "=&v"(v3) : "v"(a0), "v"(a1), "v"(a2), "v"(a3));
+}
+__device__ __forceinline__ u32x2 pack4(const f32x4& v) { return u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])}; }
+
+// 16 rows x 64 columns as bf16, 128 bytes per row; the 16-byte pieces of a row are XORed with the row.  fetch: lane l gets the
+// columns 8 (l%8) .. +7 of row l/8 and of row 8 + l/8.
+struct StripBf16 {
+  uint32_t at_w, at_r;
+  __device__ __forceinline__ StripBf16(uint32_t base, int lane) {
+    const int r = lane & 15, q = lane >> 4, l3 = lane >> 3;
+    at_w = base + r * 128 + (((q >> 1) ^ (r & 7)) << 4) + 8 * (q & 1);
+    at_r = base + l3 * 128 + (((lane & 7) ^ l3) << 4);
+  }
+  __device__ __forceinline__ void park(int j, const f32x4& v) const { lds_park8(at_w ^ (j * 32), pack4(v)); }
+  __device__ __forceinline__ void fetch(u32x4& lo, u32x4& hi) const { lds_fetch(at_r, at_r + 1024, lo, hi); }
+};
+// 16 rows x 64 columns of fp32, 256 bytes per row, swizzled likewise; fetch: as above, v[h] for row 8 h + l/8
+struct StripF32 {
+  uint32_t at_w, at_r;
+  __device__ __forceinline__ StripF32(uint32_t base, int lane) {
+    const int r = lane & 15, q = lane >> 4, l3 = lane >> 3;
+    at_w = base + r * 256 + ((q ^ r) << 4);
+    at_r = base + l3 * 256 + (((2 * (lane & 7)) ^ l3) << 4);
+  }
+  // (element by element: the compiler keeps vectors that are only used whole in one piece across the slab loop, and copies
+  // of the accumulators in scratch memory)
+  __device__ __forceinline__ void park(int j, const f32x4& v) const {
+    u32x4 w;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      float x = v[t];
+      asm("" : "+v"(x));
+      w[t] = __float_as_uint(x);
+    }
+    lds_park16(at_w ^ (j * 64), w);
+  }
+  __device__ __forceinline__ void fetch(float (&v)[2][8]) const {
+    const uint32_t hi = (at_r ^ 128) + 2048;
+    u32x4 a, b, c, d;
+    lds_fetch(at_r, at_r ^ 16, hi, hi ^ 16, a, b, c, d);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v[0][q] = __uint_as_float(a[q]); v[0][4 + q] = __uint_as_float(b[q]);
+      v[1][q] = __uint_as_float(c[q]); v[1][4 + q] = __uint_as_float(d[q]);
     }
   }
 };
 
-// ---- epilogue: accumulators -> LDS (fp32) -> 16-byte row-contiguous global accesses -----------------
-// The products are accumulated transposed (the MFMA is handed the weight-side fragment as its first operand): of the
-// 16x16 tile (i, j) a lane then holds tile row lane%16 and the four consecutive columns 4*(lane/16) .. +3.  Each wave
-// parks a 32-row strip of its sub-tile in its own part of the (now idle) LDS ring with 16-byte writes and reads it
-// back row-major, 8 consecutive columns per lane.  (The 8-bit products use 32x32 tiles: a lane holds row lane%32 and,
-// for g = 0..3, the four consecutive columns 8g + 4*(lane/32) .. +3 in elements 4g .. 4g+3.)
-template <class T> struct Strip {
-  static constexpr int LD = T::WN + 4;                 // floats per staged row: consecutive rows shift the banks by 4, so the 16 lanes
-                                                       // the LDS serves per cycle (16 rows, 16 bytes each) cover all 64 banks
-  static constexpr int kBytes = T::kStripBytes;
-  static_assert(kBytes == 32 * LD * 4 && T::kStripBase + T::kWaves * kBytes <= T::kLdsAlloc, "staging strips must fit in the LDS allocation");
-  static_assert(LD % 64 == 4, "bank rotation of the parked rows");
-};
-
-// strip number `mi`: rows 32 mi .. +31 of the wave's sub-tile
-template <class T>
-__device__ __forceinline__ void park_strip(const Acc<T>& acc, int mi, float* strip, int lane) {
-  float* row = strip + (lane & 15) * Strip<T>::LD + 4 * (lane >> 4);
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int j = 0; j < T::FN; ++j) {
-      const f32x4 v = acc[2 * mi + h][j];
-      *reinterpret_cast<float4*>(row + h * 16 * Strip<T>::LD + j * 16) = make_float4(v[0], v[1], v[2], v[3]);
-    }
-}
-template <class T>
-__device__ __forceinline__ void park_strip(const f32x16 (&acc_mi)[T::NI], float* strip, int lane) {
-  float* row = strip + (lane & 31) * Strip<T>::LD + 4 * (lane >> 5);
-#pragma unroll
-  for (int ni = 0; ni < T::NI; ++ni)
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      *reinterpret_cast<float4*>(row + ni * 32 + 8 * g) =
-          make_float4(acc_mi[ni][4 * g], acc_mi[ni][4 * g + 1], acc_mi[ni][4 * g + 2], acc_mi[ni][4 * g + 3]);
-}
-
-// The same for results that leave as bf16 with no further arithmetic: rounded before they are parked, so the strip
-// holds 2 instead of 4 bytes per element and the LDS moves half the bytes both ways.  Rows are WN * 2 bytes with
-// no padding; the 16-byte pieces of a row are XORed with the row index, which keeps the row-major 16-byte reads
-// free of bank conflicts (16 lanes = 256 consecutive bytes) and spreads the 32 rows of a parking write over
-// 16 different pieces.
-template <class T>
-__device__ __forceinline__ void park_strip_bf16(const Acc<T>& acc, int mi, char* strip, int lane) {
-  constexpr int PPR = T::WN / 8;                       // 16-byte pieces per staged row
-  const int r = lane & 15;                             // rows r and r + 16 have the same swizzle
-  char* row = strip + r * (T::WN * 2) + 8 * ((lane >> 4) & 1);
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int j = 0; j < T::FN; ++j) {
-      const f32x4 v = acc[2 * mi + h][j];
-      *reinterpret_cast<uint2*>(row + h * 16 * (T::WN * 2) + (((2 * j + (lane >> 5)) ^ (r & (PPR - 1))) << 4)) =
-          make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
-    }
-}
-template <class T>
-__device__ __forceinline__ void park_strip_bf16(const f32x16 (&acc_mi)[T::NI], char* strip, int lane) {
-  constexpr int PPR = T::WN / 8;                       // 16-byte pieces per staged row
-  const int r = lane & 31;
-  char* row = strip + r * (T::WN * 2) + 8 * (lane >> 5);
-#pragma unroll
-  for (int ni = 0; ni < T::NI; ++ni)
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      *reinterpret_cast<uint2*>(row + (((ni * 4 + g) ^ (r & (PPR - 1))) << 4)) =
-          make_uint2(pack_bf16x2(acc_mi[ni][4 * g], acc_mi[ni][4 * g + 1]), pack_bf16x2(acc_mi[ni][4 * g + 2], acc_mi[ni][4 * g + 3]));
-}
-// 8 consecutive columns (piece `piece` of staged row `row`) of a strip parked by park_strip_bf16
-template <class T>
-__device__ __forceinline__ uint4 read_strip_bf16(const char* strip, int row, int piece) {
-  return *reinterpret_cast<const uint4*>(strip + row * (T::WN * 2) + ((piece ^ (row & (T::WN / 8 - 1))) << 4));
-}
-
-// sum over each aligned group of LANES (8 or 16) consecutive lanes, left in every lane of the group; data-parallel
-// primitives (register moves between lanes), fixed order of additions
-template <int LANES>
-__device__ __forceinline__ float row_group_sum(float v) {
-  static_assert(LANES == 8 || LANES == 16, "groups of 8 or 16 lanes");
+// sum over each aligned group of 8 consecutive lanes, left in every lane of the group; data-parallel primitives (register moves
+// between lanes), fixed order of additions
+__device__ __forceinline__ float sum_of_8_lanes(float v) {
   auto dpp = [](float x, auto ctrl) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF, 0xF, true));
   };
   v += dpp(v, std::integral_constant<int, 0xB1>{});          // quad_perm [1,0,3,2]
   v += dpp(v, std::integral_constant<int, 0x4E>{});          // quad_perm [2,3,0,1]
   v += dpp(v, std::integral_constant<int, 0x141>{});         // row_half_mirror: the other quad of the 8 lanes
-  if constexpr (LANES == 16) v += dpp(v, std::integral_constant<int, 0x140>{});   // row_mirror: the other 8 lanes
   return v;
 }
 
@@ -783,50 +801,41 @@ __device__ __forceinline__ void read8(const float* p, float (&v)[8]) {
   const float4 x = *reinterpret_cast<const float4*>(p), y = *reinterpret_cast<const float4*>(p + 4);
   v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w; v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
 }
-__device__ __forceinline__ uint4 pack8(const float (&v)[8]) {
-  return make_uint4(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
+__device__ __forceinline__ u32x4 pack8(const float (&v)[8]) {
+  return u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
 }
-__device__ __forceinline__ void unpack8(const uint4& w, float (&v)[8]) {
-  v[0] = bf16_lo(w.x); v[1] = bf16_hi(w.x); v[2] = bf16_lo(w.y); v[3] = bf16_hi(w.y);
-  v[4] = bf16_lo(w.z); v[5] = bf16_hi(w.z); v[6] = bf16_lo(w.w); v[7] = bf16_hi(w.w);
+__device__ __forceinline__ void unpack8(const u32x4& w, float (&v)[8]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) { v[2 * q] = bf16_lo(w[q]); v[2 * q + 1] = bf16_hi(w[q]); }
 }
 
 // Results are written once and read by a later kernel: a non-temporal store keeps them from displacing the
 // operand panels that concurrently running tiles share through the L2 (measured: 2 % of the step).
-__device__ __forceinline__ void store16(void* p, const uint4& v) {
-  typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-  const u32x4_t w = {v.x, v.y, v.z, v.w};
-  __builtin_nontemporal_store(w, reinterpret_cast<u32x4_t*>(p));
-}
-__device__ __forceinline__ void store16(void* p, float a, float b, float c, float d) {
-  typedef float f32x4_t __attribute__((ext_vector_type(4)));
-  const f32x4_t w = {a, b, c, d};
-  __builtin_nontemporal_store(w, reinterpret_cast<f32x4_t*>(p));
-}
+__device__ __forceinline__ void store16(void* p, const u32x4& v) { __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p)); }
 
-// A 32-row strip (or fewer rows) of a row-major matrix as a buffer: a load of a row or column that does not exist returns
+// A few rows (of a strip or a tile) of a row-major matrix as a buffer: a load of a row or column that does not exist returns
 // zeros and a store to it does nothing, so the epilogues need no branches and no 64-bit address arithmetic per access.
-//   first: the strip's first row at the tile's first column (uniform); rows: how many of its rows exist (any integer);
-//   ld2: bytes per row; skip2: bytes between the start of a row and the tile's first column
+//   first: the first row at the tile's first column (uniform); rows: how many rows exist (any integer up to 256);
+//   pitch: bytes per row; skip: bytes between the start of a row and the tile's first column
 struct StripRows {
   __amdgpu_buffer_rsrc_t rsrc;
   static constexpr uint32_t kNone = 0x80000000u;       // offset of a column that does not exist (a strip is shorter than 2 GiB)
-  __device__ __forceinline__ void at(const void* first, int rows, uint32_t ld2, uint32_t skip2) {
-    int n = min(rows, 32);
-    asm("" : "+s"(n));                                 // (as two scalar instructions: a vector clamp would make this per lane)
+  __device__ __forceinline__ void at(const void* first, int rows, uint32_t pitch, uint32_t skip) {
+    int n = scalar(min(rows, 256));
     n = max(n, 0);
-    const uint32_t range = n > 0 ? static_cast<uint32_t>(n) * ld2 - skip2 : 0u;
+    const uint32_t range = n > 0 ? static_cast<uint32_t>(n) * pitch - skip : 0u;
     rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(first), 0, static_cast<int>(range), 0x00020000);
   }
-  typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-  __device__ __forceinline__ void store(uint32_t off, const uint4& v) const {          // non-temporal, as store16
-    const u32x4_t w = {v.x, v.y, v.z, v.w};
-    __builtin_amdgcn_raw_buffer_store_b128(w, rsrc, static_cast<int>(off), 0, 2);
+  __device__ __forceinline__ void store(uint32_t off, const u32x4& v) const {          // non-temporal, as store16
+    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, static_cast<int>(off), 0, 2);
   }
-  __device__ __forceinline__ uint4 load(uint32_t off) const {
-    const u32x4_t w = __builtin_amdgcn_raw_buffer_load_b128(rsrc, static_cast<int>(off), 0, 0);
-    return make_uint4(w.x, w.y, w.z, w.w);
+  __device__ __forceinline__ void store_half_line(uint32_t off, const u32x4& v) const {   // through the L2, which joins two waves' halves
+    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, static_cast<int>(off), 0, 0);
   }
+  __device__ __forceinline__ void store(uint32_t off, float v) const {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), rsrc, static_cast<int>(off), 0, 0);
+  }
+  __device__ __forceinline__ u32x4 load(uint32_t off) const { return __builtin_amdgcn_raw_buffer_load_b128(rsrc, static_cast<int>(off), 0, 0); }
 };
 
 // ---- device-built schedule of (expert, row tile) for row-grouped products -----------------
@@ -877,6 +886,10 @@ __global__ __launch_bounds__(1024) void build_row_tiles_kernel(const int32_t* __
   build_row_tiles(offsets, E, P, bm, rt);
 }
 
+// Lists that a launch only reads, as constant memory: uniform loads from them are scalar whatever the kernel has stored before.
+typedef __attribute__((address_space(4))) const int32_t* ConstList;
+__device__ __forceinline__ ConstList const_list(const int32_t* p) { return reinterpret_cast<ConstList>(reinterpret_cast<uintptr_t>(p)); }
+
 // workgroup id -> virtual tile id such that consecutive virtual ids share an XCD
 __device__ __forceinline__ int xcd_remap(int b, int total) {
   const int per = (total + kXcds - 1) / kXcds;
@@ -887,9 +900,6 @@ __device__ __forceinline__ int xcd_remap(int b, int total) {
 // ============================================================================================
 // Row-grouped kernels
 // ============================================================================================
-// Hands back its argument through an empty asm: values derived from the result cannot be computed before
-// this point, so the epilogue's per-lane indices do not occupy registers during the main loop.
-__device__ __forceinline__ int not_before_here(int v) { asm volatile("" : "+v"(v)); return v; }
 
 enum { kGateUp = 0, kDown = 1, kDAct = 2, kDX = 3, kRouterFwd = 4, kRouterDx = 5 };
 
@@ -928,272 +938,294 @@ struct RowArgs {
 //   dA = w_r * (dy[token(r)] Wd)              the combine weight scales the product's rows
 //   d w_r = <dy[token(r)], yp[r]> = <dy[token(r)] Wd, act[r]>    reduced over the columns of the tile
 //   act_w[r] = w_r * act[r]                   the operand with which dWd = dy[token]^T act_w needs no dyp
-template <int KIND, class T, bool FUSED = false>
+// ACT_W (kDAct): act_w is written; else the forward left it.
+template <int KIND, class T, bool FUSED = false, bool ACT_W = false>
 __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::kWavesPerSimd, T::kWavesPerSimd))) void row_grouped_kernel(RowArgs p) {
   static_assert(!FUSED || KIND == kGateUp || KIND == kDAct, "only the two products that read activations by token are fused");
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  constexpr int BM = T::BM, BN = T::BN, WM = T::WM, WN = T::WN, MI = T::MI;
-  const int n_row_tiles = p.rt.count[0];
-  const int v = xcd_remap(blockIdx.x, n_row_tiles * p.n_tiles_n);
-  if (v < 0) return;
-  const int mt = v / p.n_tiles_n, nt = v % p.n_tiles_n;
-  const int e = p.rt.expert[mt];
-  const int row0 = p.rt.row0[mt];
-  const int row_end = p.offsets ? min(p.offsets[e + 1], p.P) : p.P;
-  const int rows = min(BM, row_end - row0);
+  constexpr int BM = T::BM, BN = T::BN, WM = T::WM, WN = T::WN, MI = T::MI, FN = T::FN;
+  static_assert(FN == 4, "the epilogues take the fragments of a row in two pairs");
+  constexpr bool B_STRIDED = KIND == kDAct || KIND == kRouterDx || KIND == kDX, TWO_SEG = KIND == kDX;
+  // kGateUp: tile columns are BN/2 gate columns n0.. and the matching BN/2 up columns; each wave gets the same gate and up
+  // columns (the up fragments lie BN/2 tile rows further), so a lane holds the gate and the up value of an output
+  constexpr int HN = BN / 2, HW = WN / 2, OUT_N = KIND == kGateUp ? HN : BN;
+  typedef MainLoop<T, false, B_STRIDED, FUSED, false, KIND == kGateUp ? HN : WN / 2, TWO_SEG> Loop;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / T::WGN, wn = wave % T::WGN;
+  const int a_row = wm * WM, b_row = wn * (KIND == kGateUp ? HW : WN);   // first tile rows of this wave on either side
 
-  Acc<T> acc;
-  zero_acc<T>(acc);
-
-  const int a_row = wm * WM;                           // first tile row of this wave
-  // 32-row strips of this wave that hold rows of the expert (wave-uniform); a wave without any
-  // skips the arithmetic, and the epilogue skips strips without rows (opaque: a compiler that knows where it comes from
-  // splits the paths behind the main loop by its value and spills the accumulators on them)
-  const int mi_n = __builtin_amdgcn_readfirstlane(not_before_here(min(MI, max(0, (rows - wm * WM + 31) / 32))));
-  Operand opA, opB;
-  opA.ld = p.lda;
-  opA.valid[0] = min(rows, BM / 2);
-  opA.valid[1] = max(rows - BM / 2, 0);
-  opA.half[0] = FUSED ? p.a : p.a + static_cast<long>(row0) * p.lda;
-  opA.half[1] = FUSED ? p.a : opA.half[0] + (BM / 2) * p.lda;
-  opA.gather = FUSED ? p.row_token : nullptr;
-  opA.grow = row0;
-  opB.ld = p.ldw;
-  opB.gather = nullptr;
-  opB.grow = 0;
-
-  if constexpr (KIND == kGateUp) {
-    // tile columns: BN/2 gate columns n0.. and the matching BN/2 up columns; each wave gets the
-    // same gate and up columns so the SwiGLU product needs no exchange between lanes
-    constexpr int HN = BN / 2, HW = WN / 2;
-    const int n0 = nt * HN;
-    const int ncols = min(HN, p.N - n0);
-    const int b_row = wn * HW;                         // the up fragments lie HN tile rows further
-    opB.half[0] = p.w0 + e * p.w_expert_stride + static_cast<long>(n0) * p.ldw;
-    opB.half[1] = p.w1 + e * p.w_expert_stride + static_cast<long>(n0) * p.ldw;
-    opB.valid[0] = opB.valid[1] = ncols;
-    { MainLoop<T, false, false, FUSED, false, HN> ml; ml.run(opA, opB, p.K, lds, a_row, b_row, mi_n > 0, acc); }
-    // strip columns: [0, HW) gate, [WN/2 + 0, ...) up -- both halves hold the same output columns
-    float* strip = reinterpret_cast<float*>(lds + T::kStripBase + wave * Strip<T>::kBytes);
-    const int el = not_before_here(lane);             // this lane, for the epilogue
-    constexpr int LPR = HW / 8;                        // lanes per output row (8 columns each)
-    constexpr int RPP = 64 / LPR;                      // rows per pass
-    const int cl = wn * HW + (el % LPR) * 8;         // first of this lane's 8 columns inside the tile
-    // All LDS reads of a strip are issued before the first is used: one LDS latency per strip, not per pass.
-    constexpr int NP = 32 / RPP;                       // passes per strip
-    const uint32_t ld2 = static_cast<uint32_t>(p.ldo) * 2u, skip2 = static_cast<uint32_t>(n0) * 2u;
-    uint32_t off[NP];
-#pragma unroll
-    for (int pass = 0; pass < NP; ++pass) off[pass] = cl < ncols ? (pass * RPP + el / LPR) * ld2 + cl * 2u : StripRows::kNone;
-    float wr[MI][NP];                                  // the rows' combine weights, if the activation is to carry them
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-      for (int pass = 0; pass < NP; ++pass) {
-        const int r = wm * WM + mi * 32 + pass * RPP + el / LPR;
-        wr[mi][pass] = p.row_w ? p.row_w[row0 + (r < rows ? r : 0)] : 1.0f;
-      }
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi) {
-      if (mi >= mi_n) break;
-      park_strip<T>(acc, mi, strip, el);
-      float g[NP][8], u[NP][8];
-#pragma unroll
-      for (int pass = 0; pass < NP; ++pass) {
-        const int rs = pass * RPP + el / LPR;
-        read8(strip + rs * Strip<T>::LD + (el % LPR) * 8, g[pass]);
-        read8(strip + rs * Strip<T>::LD + WN / 2 + (el % LPR) * 8, u[pass]);
-      }
-      const int rs0 = wm * WM + mi * 32;               // first row of the strip inside the tile
-      const long o = static_cast<long>(row0 + rs0) * p.ldo + n0;
-      StripRows sg, su, sa;
-      sg.at(p.out0 + o, p.out0 ? rows - rs0 : 0, ld2, skip2);
-      su.at(p.out1 + o, p.out1 ? rows - rs0 : 0, ld2, skip2);
-      sa.at(p.out2 + o, p.out2 ? rows - rs0 : 0, ld2, skip2);
-#pragma unroll
-      for (int pass = 0; pass < NP; ++pass) {
-        float a[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) a[q] = wr[mi][pass] * (g[pass][q] * sigmoid_fast(g[pass][q]) * u[pass][q]);
-        sg.store(off[pass], pack8(g[pass]));
-        su.store(off[pass], pack8(u[pass]));
-        sa.store(off[pass], pack8(a));
-      }
+  // This workgroup's tiles: every gridDim.x-th of the list (see xcd_remap), the next one located while one is multiplied.
+  const int total = const_list(p.rt.count)[0] * p.n_tiles_n;
+  // (`exists` is a number of unknown origin: a truth value carried around the loop would be a lane mask, and the parts of the
+  // descriptors that are selected by it vectors, which makes every load of the slab loop a loop over lanes)
+  struct At { int row0, rows, e, n0, exists; };
+  auto locate = [&](int block) {
+    At t{};
+    const int v = xcd_remap(block, total);
+    t.exists = scalar(v >= 0 ? 1 : 0);
+    if (v >= 0) {
+      const int mt = scalar(v / p.n_tiles_n);
+      t.n0 = (v - mt * p.n_tiles_n) * OUT_N;
+      t.e = const_list(p.rt.expert)[mt];
+      t.row0 = const_list(p.rt.row0)[mt];
+      const int row_end = p.offsets ? min(const_list(p.offsets)[t.e + 1], p.P) : p.P;
+      t.rows = scalar(min(BM, row_end - t.row0));
     }
-    return;
-  } else {
-    const int n0 = nt * BN;
-    const int ncols = min(BN, p.N - n0);
-    const int b_row = wn * WN;
-    opB.valid[0] = min(ncols, BN / 2);
-    opB.valid[1] = max(ncols - BN / 2, 0);
-    if constexpr (KIND == kDown || KIND == kRouterFwd) {
-      // yp = act * Wd[e]^T (logits = x * Wr^T): weight rows are output columns, reduction contiguous
-      opB.half[0] = p.w0 + e * p.w_expert_stride + static_cast<long>(n0) * p.ldw;
-      opB.half[1] = opB.half[0] + (BN / 2) * p.ldw;
-      { MainLoop<T, false, false> ml; ml.run(opA, opB, p.K, lds, a_row, b_row, mi_n > 0, acc); }
-    } else if constexpr (KIND == kDAct || KIND == kRouterDx) {
-      // dA = dyp * Wd[e] (dx = dz * Wr): weight is [K, N], reduction strided
-      opB.half[0] = p.w0 + e * p.w_expert_stride + n0;
-      opB.half[1] = opB.half[0] + BN / 2;
-      { MainLoop<T, false, true, FUSED, false> ml; ml.run(opA, opB, p.K, lds, a_row, b_row, mi_n > 0, acc); }
+    return t;
+  };
+  int block = blockIdx.x;
+  At cur = locate(block);
+  if (cur.exists == 0) return;
+
+  Loop ml;
+  auto load = [&](const At& t) {
+    Operand opA, opB;
+    opA.ld = p.lda;
+    opA.valid[0] = min(t.rows, BM / 2);
+    opA.valid[1] = max(t.rows - BM / 2, 0);
+    opA.half[0] = FUSED ? p.a : p.a + static_cast<long>(t.row0) * p.lda;
+    opA.half[1] = FUSED ? p.a : opA.half[0] + (BM / 2) * p.lda;
+    opA.gather = FUSED ? p.row_token : nullptr;
+    opA.grow = t.row0;
+    opB.ld = p.ldw;
+    opB.gather = nullptr;
+    opB.grow = 0;
+    const int ncols = scalar(min(OUT_N, p.N - t.n0));
+    const bf16_t* w0 = p.w0 + t.e * p.w_expert_stride;
+    const bf16_t* w1 = nullptr;
+    if constexpr (KIND == kGateUp) {
+      opB.half[0] = w0 + static_cast<long>(t.n0) * p.ldw;
+      opB.half[1] = p.w1 + t.e * p.w_expert_stride + static_cast<long>(t.n0) * p.ldw;
+      opB.valid[0] = opB.valid[1] = ncols;
     } else {
-      // dxp = dG * Wg[e] + dU * Wu[e] : two reduction segments over the columns of [dG | dU]
-      opB.half[0] = p.w0 + e * p.w_expert_stride + n0;
-      opB.half[1] = opB.half[0] + BN / 2;
-      Operand opB2 = opB;
-      opB2.half[0] = p.w1 + e * p.w_expert_stride + n0;
-      opB2.half[1] = opB2.half[0] + BN / 2;
-      { MainLoop<T, false, true, false, false, T::WN / 2, true> ml; ml.run2(opA, opB, opB2, p.K, lds, a_row, b_row, mi_n > 0, acc); }
+      opB.valid[0] = min(ncols, BN / 2);
+      opB.valid[1] = max(ncols - BN / 2, 0);
+      // yp = act * Wd[e]^T (logits = x * Wr^T): weight rows are output columns, reduction contiguous
+      // dA = dyp * Wd[e] (dx = dz * Wr), dxp = dG * Wg[e] + dU * Wu[e]: weight is [K, N], reduction strided
+      opB.half[0] = B_STRIDED ? w0 + t.n0 : w0 + static_cast<long>(t.n0) * p.ldw;
+      opB.half[1] = B_STRIDED ? opB.half[0] + BN / 2 : opB.half[0] + (BN / 2) * p.ldw;
+      if constexpr (TWO_SEG) w1 = p.w1 + t.e * p.w_expert_stride + t.n0;
     }
+    ml.load_tile(opA, opB, w1, p.K * t.exists);
+  };
+  ml.prepare(lds);
+  load(cur);
+  ml.fill();
+  const int n_slabs = Loop::slabs_run(p.K);
 
-    float* strip = reinterpret_cast<float*>(lds + T::kStripBase + wave * Strip<T>::kBytes);
-    const int el = not_before_here(lane);             // this lane, for the epilogue
-    constexpr int LPR = WN / 8;                        // lanes per output row (8 columns each)
-    constexpr int RPP = 64 / LPR;                      // rows per pass
-    const int cl = wn * WN + (el % LPR) * 8;         // first of this lane's 8 columns inside the tile
-    // All LDS reads of a strip are issued before the first is used: one latency per strip, not one per pass.
-    constexpr int NP = 32 / RPP;                       // passes per strip
+  for (;;) {
+    block += gridDim.x;
+    const At nxt = locate(block);
+    const int rows = cur.rows, row0 = cur.row0, n0 = cur.n0;
+    const int ncols = min(OUT_N, p.N - n0);
+    // 32-row strips of this wave that hold rows of the expert (wave-uniform); a wave without any
+    // skips the arithmetic, and the epilogue skips strips without rows (its origin hidden: a compiler that knows where it comes
+    // from splits the paths behind the main loop by its value and spills the accumulators on them)
+    const int mi_n = scalar(min(MI, max(0, (rows - a_row + 31) / 32)));
+    // the combine weights of the wave's rows: lane l holds those of rows l, l + 64, ...
+    constexpr int NW = (KIND == kGateUp || KIND == kDAct) ? (WM + 63) / 64 : 1;
+    float row_w[NW];
+    if constexpr (KIND == kGateUp || (KIND == kDAct && FUSED)) {
+#pragma unroll
+      for (int c = 0; c < NW; ++c) {
+        const int r = a_row + c * 64 + lane;
+        row_w[c] = p.row_w ? p.row_w[row0 + (r < rows ? r : 0)] : 1.0f;
+      }
+    }
+    Acc<T> acc;
+    zero_acc<T>(acc);
+    ml.template tile<false>(n_slabs, a_row, b_row, mi_n > 0, acc, [&] { load(nxt); });
+
+    const int el = not_before_here(lane);              // this lane, for the epilogue
+    const uint32_t scratch = ml.scratch();
+    static_assert(Loop::kScratch >= (KIND == kDown || KIND == kDX ? 2048 : KIND == kGateUp ? 3072 : 4096), "strips of 16 rows");
+    auto weight_of = [&](int r) {                      // combine weight of the wave's row r (per lane, r - r%16 uniform)
+      return __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((r & 63) * 4, __builtin_bit_cast(int, r < 64 ? row_w[0] : row_w[NW - 1])));
+    };
     const uint32_t ld2 = static_cast<uint32_t>(p.ldo) * 2u, skip2 = static_cast<uint32_t>(n0) * 2u;
-    uint32_t off[NP];
+    const int cl = b_row + 8 * (el & 7), rl = el >> 3; // row-major: this lane's 8 columns, and its row in each 8 rows
+    auto off8 = [&](uint32_t pitch) { return off_if(cl < ncols, rl * pitch + cl * 2u, StripRows::kNone); };
+    if constexpr (KIND == kGateUp) {
+      // 16 rows x (32 gate + 32 up columns) parked as they are, 16 x 32 activations behind them; 4 lanes per row of 64 bytes
+      const int r = el & 15, q = el >> 4, r4 = el >> 2, c4 = el & 3;
+      const StripBf16 gu(scratch, el);
+      const uint32_t gu_r = scratch + r4 * 128 + ((c4 ^ (r4 & 7)) << 4);
+      const uint32_t act_w = scratch + 2048 + r * 64 + (((q >> 1) ^ ((r >> 1) & 3)) << 4) + 8 * (q & 1), act_r = scratch + 2048 + r4 * 64 + ((c4 ^ ((r4 >> 1) & 3)) << 4);
+      const int col = b_row + 8 * c4;
+      const uint32_t off = off_if(col < ncols, r4 * ld2 + col * 2u, StripRows::kNone);
 #pragma unroll
-    for (int pass = 0; pass < NP; ++pass) off[pass] = cl < ncols ? (pass * RPP + el / LPR) * ld2 + cl * 2u : StripRows::kNone;
-    if constexpr (KIND == kDAct) {
-      // The saved G and U of a strip are requested one strip ahead (the fragment registers are free now).  This epilogue is
+      for (int mi = 0; mi < MI; ++mi) {
+        if (mi >= mi_n) break;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int i = 2 * mi + h, rs0 = a_row + i * 16;   // first row of the strip inside the tile
+          const float w = weight_of(i * 16 + r);
+#pragma unroll
+          for (int j = 0; j < FN; ++j) gu.park(j, acc[i][j]);
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            f32x4 a;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) a[t] = w * (acc[i][j][t] * sigmoid_fast(acc[i][j][t]) * acc[i][j + 2][t]);
+            lds_park8(act_w ^ (j * 32), pack4(a));
+          }
+          u32x4 vg, vu, va, unused;
+          lds_fetch(gu_r, gu_r ^ 64, act_r, act_r, vg, vu, va, unused);
+          const long o = static_cast<long>(row0 + rs0) * p.ldo + n0;
+          StripRows sg, su, sa;
+          sg.at(p.out0 + o, p.out0 ? rows - rs0 : 0, ld2, skip2);
+          su.at(p.out1 + o, p.out1 ? rows - rs0 : 0, ld2, skip2);
+          sa.at(p.out2 + o, p.out2 ? rows - rs0 : 0, ld2, skip2);
+          sg.store_half_line(off, vg);
+          su.store_half_line(off, vu);
+          sa.store_half_line(off, va);
+        }
+      }
+    } else if constexpr (KIND == kDown || KIND == kDX) {
+      const StripBf16 strip(scratch, el);
+      const uint32_t off = off8(ld2);
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi) {
+        if (mi >= mi_n) break;
+        const int rs0 = a_row + mi * 32;
+        StripRows so;
+        so.at(p.out0 + static_cast<long>(row0 + rs0) * p.ldo + n0, rows - rs0, ld2, skip2);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+          for (int j = 0; j < FN; ++j) strip.park(j, acc[2 * mi + h][j]);
+          u32x4 v[2];
+          strip.fetch(v[0], v[1]);
+#pragma unroll
+          for (int c = 0; c < 2; ++c) so.store(off + (16 * h + 8 * c) * ld2, v[c]);
+        }
+      }
+    } else if constexpr (KIND == kDAct) {
+      // The saved G and U of 16 rows are requested 16 rows ahead (the fragment registers are free now).  This epilogue is
       // bound by the vector unit: 128 derivatives per lane, about 25 issue slots each, two waves per SIMD; it takes 24k of
-      // the 111k clocks of a tile (2560 rows per expert).  With compiled divisions, branches per access and the loads of a
-      // strip awaited on the spot, dA took 1145 us against 1065 there, 274 against 260 at 512 rows per expert.
+      // the 111k clocks of a tile (2560 rows per expert).
+      const StripF32 strip(scratch, el);
       const uint32_t n2 = static_cast<uint32_t>(p.N) * 2u;
-      uint32_t goff[NP];
-#pragma unroll
-      for (int pass = 0; pass < NP; ++pass) goff[pass] = cl < ncols ? (pass * RPP + el / LPR) * n2 + cl * 2u : StripRows::kNone;
-      uint4 gq[2][NP], uq[2][NP];
-      float wr[2][NP];
-      auto request = [&](int mi) {
-        const int rs0 = wm * WM + mi * 32;
+      const uint32_t off = off8(ld2), goff = off8(n2);
+      u32x4 gq[2][2], uq[2][2];                        // [fragment & 1][rows 0..7, 8..15]
+      auto request = [&](int i) {
+        const int rs0 = a_row + i * 16;
         const long gi = static_cast<long>(row0 + rs0) * p.N + n0;
         StripRows sg, su;
         sg.at(p.g + gi, rows - rs0, n2, skip2);
         su.at(p.u + gi, rows - rs0, n2, skip2);
 #pragma unroll
-        for (int c = 0; c < NP; ++c) {
-          gq[mi & 1][c] = sg.load(goff[c]);
-          uq[mi & 1][c] = su.load(goff[c]);
-          if constexpr (FUSED) {
-            const int r = rs0 + c * RPP + el / LPR;
-            wr[mi & 1][c] = p.row_w[row0 + (r < rows ? r : 0)];
-          }
+        for (int c = 0; c < 2; ++c) {
+          gq[i & 1][c] = sg.load(goff + 8 * c * n2);
+          uq[i & 1][c] = su.load(goff + 8 * c * n2);
         }
       };
       request(0);
 #pragma unroll
       for (int mi = 0; mi < MI; ++mi) {
         if (mi >= mi_n) break;
-        if (mi + 1 < MI) request(mi + 1);
-        park_strip<T>(acc, mi, strip, el);
-        float v[NP][8];
-#pragma unroll
-        for (int c = 0; c < NP; ++c)
-          read8(strip + (c * RPP + el / LPR) * Strip<T>::LD + (el % LPR) * 8, v[c]);
-        const int rs0 = wm * WM + mi * 32;
-        StripRows sdg, sdu, saw;
+        const int rs0 = a_row + mi * 32;
+        StripRows sdg, sdu, saw, sdw;
         const long o = static_cast<long>(row0 + rs0) * p.ldo + n0;
         sdg.at(p.out0 + o, rows - rs0, ld2, skip2);
         sdu.at(p.out0 + o + p.N, rows - rs0, ld2, skip2 + n2);
-        if constexpr (FUSED) saw.at(p.act_w + (static_cast<long>(row0 + rs0) * p.N + n0), p.act_w ? rows - rs0 : 0, n2, skip2);
+        if constexpr (FUSED) {
+          if constexpr (ACT_W) saw.at(p.act_w + (static_cast<long>(row0 + rs0) * p.N + n0), rows - rs0, n2, skip2);
+          sdw.at(p.dw_partial + static_cast<long>(n0 / BN * T::WGN + wn) * p.P + row0 + rs0, min(rows - rs0, 32), 4, 0);
+        }
 #pragma unroll
-        for (int c = 0; c < NP; ++c) {
-          float g[8], u[8], dg[8], du[8];
-          unpack8(gq[mi & 1][c], g);
-          unpack8(uq[mi & 1][c], u);
-          // silu'(g) = sg (1 + g (1 - sg)) = sg + t (1 - sg) with t = g sg = silu(g); 1 - sg is formed first: where it is zero
-          // the result is sg however large t is (sg + t - t sg would lose sg)
-          if constexpr (FUSED) {
-            const int r = rs0 + c * RPP + el / LPR;
-            const float w = wr[mi & 1][c];
-            float part = 0.0f, act[8];
+        for (int h = 0; h < 2; ++h) {
+          const int i = 2 * mi + h;
+          if (i + 1 < T::FM) request(i + 1);
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              const float sg = sigmoid_fast(g[q]), t = g[q] * sg, da = w * v[c][q];
-              act[q] = t * u[q];
-              part = fmaf(act[q], v[c][q], part);
-              dg[q] = (da * u[q]) * fmaf(t, 1.0f - sg, sg);
-              du[q] = da * t;
+          for (int j = 0; j < FN; ++j) strip.park(j, acc[i][j]);
+          float v[2][8];
+          strip.fetch(v);
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            float g[8], u[8], dg[8], du[8];
+            unpack8(gq[i & 1][c], g);
+            unpack8(uq[i & 1][c], u);
+            const uint32_t down = (16 * h + 8 * c);      // rows below the strip's first
+            // silu'(g) = sg (1 + g (1 - sg)) = sg + t (1 - sg) with t = g sg = silu(g); 1 - sg is formed first: where it is zero
+            // the result is sg however large t is (sg + t - t sg would lose sg)
+            if constexpr (FUSED) {
+              const float w = weight_of(i * 16 + 8 * c + rl);
+              float part = 0.0f, act[8];
+#pragma unroll
+              for (int q = 0; q < 8; ++q) {
+                const float sg = sigmoid_fast(g[q]), t = g[q] * sg, da = w * v[c][q];
+                act[q] = t * u[q];
+                part = fmaf(act[q], v[c][q], part);
+                dg[q] = (da * u[q]) * fmaf(t, 1.0f - sg, sg);
+                du[q] = da * t;
+              }
+              sdg.store(off + down * ld2, pack8(dg));
+              sdu.store(off + down * ld2, pack8(du));
+              if constexpr (ACT_W) {
+#pragma unroll
+                for (int q = 0; q < 8; ++q) act[q] *= w;
+                saw.store(goff + down * n2, pack8(act));
+              }
+              // the 8 lanes of a row add up their columns (one that does not exist holds NaN if the row of dy has an
+              // infinity); every (column slot, row) is written exactly once
+              part = sum_of_8_lanes(cl < ncols ? part : 0.0f);
+              sdw.store(off_if((el & 7) == 0, (down + rl) * 4u, StripRows::kNone), part);
+            } else {
+#pragma unroll
+              for (int q = 0; q < 8; ++q) {
+                const float sg = sigmoid_fast(g[q]), t = g[q] * sg;
+                dg[q] = (v[c][q] * u[q]) * fmaf(t, 1.0f - sg, sg);
+                du[q] = v[c][q] * t;
+              }
+              sdg.store(off + down * ld2, pack8(dg));
+              sdu.store(off + down * ld2, pack8(du));
             }
-            sdg.store(off[c], pack8(dg));
-            sdu.store(off[c], pack8(du));
-            if (p.act_w) {
-#pragma unroll
-              for (int q = 0; q < 8; ++q) act[q] *= w;
-              saw.store(goff[c], pack8(act));
-            }
-            // the LPR lanes of a row add up their columns (one that does not exist holds NaN if the row of dy has an
-            // infinity); every (column slot, row) is written exactly once
-            part = row_group_sum<LPR>(cl < ncols ? part : 0.0f);
-            if (r < rows && el % LPR == 0) p.dw_partial[static_cast<long>(nt * T::WGN + wn) * p.P + row0 + r] = part;
-          } else {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-              const float sg = sigmoid_fast(g[q]), t = g[q] * sg;
-              dg[q] = (v[c][q] * u[q]) * fmaf(t, 1.0f - sg, sg);
-              du[q] = v[c][q] * t;
-            }
-            sdg.store(off[c], pack8(dg));
-            sdu.store(off[c], pack8(du));
           }
         }
       }
-      return;
-    }
-    if constexpr (KIND == kDown || KIND == kDX) {      // rounded and stored as they are: staged as bf16
+    } else {                                           // the router's
+      const StripF32 strip(scratch, el);
 #pragma unroll
-      for (int mi = 0; mi < MI; ++mi) {
-        if (mi >= mi_n) break;
-        park_strip_bf16<T>(acc, mi, reinterpret_cast<char*>(strip), el);
-        uint4 v[NP];
+      for (int i = 0; i < T::FM; ++i) {
+        if (i >= 2 * mi_n) break;
+        const int rs0 = a_row + i * 16;
 #pragma unroll
-        for (int pass = 0; pass < NP; ++pass)
-          v[pass] = read_strip_bf16<T>(reinterpret_cast<const char*>(strip), pass * RPP + el / LPR, el % LPR);
-        const int rs0 = wm * WM + mi * 32;
+        for (int j = 0; j < FN; ++j) strip.park(j, acc[i][j]);
+        float v[2][8];
+        strip.fetch(v);
         StripRows so;
-        so.at(p.out0 + static_cast<long>(row0 + rs0) * p.ldo + n0, rows - rs0, ld2, skip2);
+        if constexpr (KIND == kRouterFwd) {
+          const uint32_t ld4 = static_cast<uint32_t>(p.ldo) * 4u;
+          so.at(p.out_f32 + static_cast<long>(row0 + rs0) * p.ldo + n0, rows - rs0, ld4, n0 * 4u);
+          const uint32_t off = off_if(cl < ncols, rl * ld4 + cl * 4u, StripRows::kNone);
 #pragma unroll
-        for (int pass = 0; pass < NP; ++pass) so.store(off[pass], v[pass]);
-      }
-      return;
-    }
+          for (int c = 0; c < 2; ++c)
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) {
-      if (mi >= mi_n) break;
-      park_strip<T>(acc, mi, strip, el);
-      float v[NP][8];
+            for (int t = 0; t < 2; ++t) {
+              u32x4 o;
 #pragma unroll
-      for (int pass = 0; pass < NP; ++pass)
-        read8(strip + (pass * RPP + el / LPR) * Strip<T>::LD + (el % LPR) * 8, v[pass]);
-#pragma unroll
-      for (int pass = 0; pass < NP; ++pass) {
-        const int r = wm * WM + mi * 32 + pass * RPP + el / LPR;
-        if (cl < ncols && r < rows) {
-          if constexpr (KIND == kRouterFwd) {
-            float* o = p.out_f32 + static_cast<long>(row0 + r) * p.ldo + n0 + cl;
-            store16(o, v[pass][0], v[pass][1], v[pass][2], v[pass][3]);
-            store16(o + 4, v[pass][4], v[pass][5], v[pass][6], v[pass][7]);
-          } else {                                     // kRouterDx
-            bf16_t* o = p.out0 + static_cast<long>(row0 + r) * p.ldo + n0 + cl;
-            if (p.accumulate) {
-              float old[8];
-              unpack8(*reinterpret_cast<const uint4*>(o), old);
-#pragma unroll
-              for (int q = 0; q < 8; ++q) v[pass][q] += old[q];
+              for (int q = 0; q < 4; ++q) o[q] = __float_as_uint(v[c][4 * t + q]);
+              so.store(off + 8 * c * ld4 + 16 * t, o);
             }
-            store16(o, pack8(v[pass]));
+        } else {                                       // kRouterDx
+          so.at(p.out0 + static_cast<long>(row0 + rs0) * p.ldo + n0, rows - rs0, ld2, skip2);
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            const uint32_t off = off8(ld2) + 8 * c * ld2;
+            float old[8];
+            unpack8(so.load(off), old);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[c][q] = p.accumulate ? v[c][q] + old[q] : v[c][q];
+            so.store(off, pack8(v[c]));
           }
         }
       }
     }
+    if (nxt.exists == 0) break;
+    cur = nxt;
   }
+  Loop::finish();
 }
 
 // ============================================================================================
@@ -1340,9 +1372,11 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   static_assert(!GATHER || WHICH < 2, "the router's operands are token-major already");
   constexpr bool GA = GATHER && WHICH == 0, GB = GATHER && WHICH == 1;
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  constexpr int BM = T::BM, BN = T::BN, WM = T::WM, WN = T::WN, MI = T::MI;
+  constexpr int BM = T::BM, BN = T::BN, WM = T::WM, WN = T::WN, FN = T::FN;
+  static_assert(FN == 4, "the epilogue takes the fragments of a row in two pairs");
+  typedef MainLoop<T, true, true, GA, GB> Loop;
   const int per_e = p.tiles_m * p.tiles_n;
-  const int n_items = p.items.count[0];
+  const int n_items = const_list(p.items.count)[0];
   // order of a work item's tiles: row tile fastest for [dW_gate; dW_up] (neighbouring workgroups share the rhs panel;
   // measured 6 % faster at 512 rows per expert), column tile fastest for the others
   constexpr bool MT_FASTEST = WHICH == 1;
@@ -1353,88 +1387,123 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   const int slow = MT_FASTEST ? p.tiles_n : p.tiles_m;
   int g = 1;
   while (g < slow && (n_items * g < 8 * kXcds || slow % g != 0)) ++g;
-  const int per_u = per_e / g;                          // g divides slow, so it divides per_e
-  const int unit = (blockIdx.x / kXcds) / per_u * kXcds + blockIdx.x % kXcds;
-  if (unit >= n_items * g) return;
-  const int item = unit / g;
-  const int vi = (unit % g) * per_u + (blockIdx.x / kXcds) % per_u;   // position among the item's tiles
-  const int mt = MT_FASTEST ? vi % p.tiles_m : vi / p.tiles_n;
-  const int nt = MT_FASTEST ? vi / p.tiles_m : vi % p.tiles_n;
-  const int e = p.items.expert[item];
-  const int slot = p.items.slot[item];
-  if (slot == -2) return;
-  const int begin = p.items.k0[item], end = p.items.k1[item];
-  const int m0 = mt * BM;
-  const int mrows = min(BM, p.M - m0);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  g = scalar(g);
+  const int per_u = scalar(per_e / g);                  // g divides slow, so it divides per_e
+  // This workgroup's tiles: every gridDim.x-th of that order, the next one located while one is multiplied.
+  struct At { int e, slot, begin, end, m0, n0, exists; };   // (`exists` is a number: see the row-grouped kernel)
+  auto locate = [&](int& block) {
+    At t{};
+    for (;; block += gridDim.x) {
+      const int q = block / kXcds, u = scalar(q / per_u);
+      const int unit = u * kXcds + block % kXcds;
+      t.exists = scalar(unit < n_items * g ? 1 : 0);
+      if (unit >= n_items * g) return t;
+      const int item = scalar(unit / g);
+      const int vi = (unit - item * g) * per_u + (q - u * per_u);      // position among the item's tiles
+      const int fast = MT_FASTEST ? p.tiles_m : p.tiles_n, slow_i = scalar(vi / fast), fast_i = vi - slow_i * fast;
+      t.m0 = (MT_FASTEST ? fast_i : slow_i) * BM;
+      t.n0 = (MT_FASTEST ? slow_i : fast_i) * BN;
+      t.slot = const_list(p.items.slot)[item];
+      if (t.slot == -2) continue;
+      t.e = const_list(p.items.expert)[item];
+      t.begin = const_list(p.items.k0)[item];
+      t.end = const_list(p.items.k1)[item];
+      return t;
+    }
+  };
+  int block = blockIdx.x;
+  At cur = locate(block);
+  if (cur.exists == 0) return;
+
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / T::WGN, wn = wave % T::WGN;
-
-  Acc<T> acc;
   const int a_row = wm * WM, b_row = wn * WN;
-  Operand opA, opB;
-  opA.ld = p.ld_lhs;
-  opA.half[0] = p.lhs + (GA ? 0L : static_cast<long>(begin) * p.ld_lhs) + m0;
-  opA.half[1] = opA.half[0] + BM / 2;
-  opA.valid[0] = min(mrows, BM / 2);
-  opA.valid[1] = max(mrows - BM / 2, 0);
-  opA.gather = GA ? p.row_token : nullptr;
-  opA.grow = begin;
-  opB.ld = p.ld_rhs;
-  opB.gather = GB ? p.row_token : nullptr;
-  opB.grow = begin;
-  const int n0 = nt * BN, ncols = min(BN, p.N - n0);
-  opB.half[0] = p.rhs + (GB ? 0L : static_cast<long>(begin) * p.ld_rhs) + n0;
-  opB.half[1] = opB.half[0] + BN / 2;
-  opB.valid[0] = min(ncols, BN / 2);
-  opB.valid[1] = max(ncols - BN / 2, 0);
-  zero_acc<T>(acc);
-  { MainLoop<T, true, true, GA, GB> ml; ml.run(opA, opB, end - begin, lds, a_row, b_row, true, acc); }
+  Loop ml;
+  auto load = [&](const At& t) {
+    Operand opA, opB;
+    const int mrows = scalar(min(BM, p.M - t.m0)), ncols = scalar(min(BN, p.N - t.n0));
+    opA.ld = p.ld_lhs;
+    opA.half[0] = p.lhs + (GA ? 0L : static_cast<long>(t.begin) * p.ld_lhs) + t.m0;
+    opA.half[1] = opA.half[0] + BM / 2;
+    opA.valid[0] = min(mrows, BM / 2);
+    opA.valid[1] = max(mrows - BM / 2, 0);
+    opA.gather = GA ? p.row_token : nullptr;
+    opA.grow = t.begin;
+    opB.ld = p.ld_rhs;
+    opB.gather = GB ? p.row_token : nullptr;
+    opB.grow = t.begin;
+    opB.half[0] = p.rhs + (GB ? 0L : static_cast<long>(t.begin) * p.ld_rhs) + t.n0;
+    opB.half[1] = opB.half[0] + BN / 2;
+    opB.valid[0] = min(ncols, BN / 2);
+    opB.valid[1] = max(ncols - BN / 2, 0);
+    ml.load_tile(opA, opB, nullptr, t.end - t.begin);
+  };
+  ml.prepare(lds);
+  load(cur);
+  ml.fill();
 
-  float* strip = reinterpret_cast<float*>(lds + T::kStripBase + wave * Strip<T>::kBytes);
-  constexpr int LPR = WN / 8;
-  constexpr int RPP = 64 / LPR;
-  constexpr int NP = 32 / RPP;                         // passes per strip; all their LDS reads are issued before the first is used
-  float* part = slot >= 0 ? p.partial + static_cast<long>(slot) * p.M * p.N : nullptr;
-  const int el = not_before_here(lane);                // this lane, for the epilogue
-  const int cl = wn * WN + (el % LPR) * 8;
-  if (part) {                                        // chunk of a split expert: fp32 partial tile
+  for (;;) {
+    block += gridDim.x;
+    const At nxt = locate(block);
+    Acc<T> acc;
+    zero_acc<T>(acc);
+    ml.template tile<true>(Loop::slabs_run(cur.end - cur.begin), a_row, b_row, true, acc, [&] { load(nxt); });
+
+    const int el = not_before_here(lane);              // this lane, for the epilogue
+    const uint32_t scratch = ml.scratch();
+    static_assert(Loop::kScratch >= 2048, "strips of 16 rows");
+    const int mrows = scalar(min(BM, p.M - cur.m0)), ncols = scalar(min(BN, p.N - cur.n0));
+    const uint32_t skip = static_cast<uint32_t>(cur.n0);
+    const int l3 = el >> 3, l7 = el & 7;
+    if (cur.slot >= 0) {                               // chunk of a split expert: fp32 partial tile, 16 rows x 32 columns at a time
+      const uint32_t ld4 = static_cast<uint32_t>(p.N) * 4u;
+      const uint32_t at_w = scratch + (el & 15) * 128 + (((el >> 4) ^ (el & 7)) << 4), at_r = scratch + l3 * 128 + ((l7 ^ l3) << 4);
+      StripRows so;
+      so.at(p.partial + (static_cast<long>(cur.slot) * p.M + cur.m0) * p.N + cur.n0, mrows, ld4, skip * 4u);
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) {
-      park_strip<T>(acc, mi, strip, el);
-      float v[NP][8];
+      for (int i = 0; i < T::FM; ++i)
 #pragma unroll
-      for (int pass = 0; pass < NP; ++pass)
-        read8(strip + (pass * RPP + el / LPR) * Strip<T>::LD + (el % LPR) * 8, v[pass]);
+        for (int q = 0; q < 2; ++q) {
+          lds_park16(at_w, __builtin_bit_cast(u32x4, acc[i][2 * q]));
+          lds_park16(at_w ^ 64, __builtin_bit_cast(u32x4, acc[i][2 * q + 1]));
+          u32x4 v[2];
+          lds_fetch(at_r, at_r + 1024, v[0], v[1]);
+          const int c = b_row + 32 * q + 4 * l7;
 #pragma unroll
-      for (int pass = 0; pass < NP; ++pass) {
-        const int rl = wm * WM + mi * 32 + pass * RPP + el / LPR;
-        if (cl < ncols && rl < mrows) {
-          float* o = part + static_cast<long>(m0 + rl) * p.N + n0 + cl;
-          store16(o, v[pass][0], v[pass][1], v[pass][2], v[pass][3]);
-          store16(o + 4, v[pass][4], v[pass][5], v[pass][6], v[pass][7]);
+          for (int h = 0; h < 2; ++h) so.store(off_if(c < ncols, (a_row + 16 * i + 8 * h + l3) * ld4 + c * 4u, StripRows::kNone), v[h]);
+        }
+    } else {                                           // whole expert: rounded once
+      const uint32_t ld2 = static_cast<uint32_t>(p.N) * 2u;
+      const StripBf16 strip(scratch, el);
+      const int c = b_row + 8 * l7;
+      // the tile's rows below m_split belong to out0, the others to out1
+      const int below = min(max(p.m_split - cur.m0, 0), mrows);
+#pragma nounroll
+      for (int half = 0; half < 2; ++half) {
+        const int lo = half == 0 ? 0 : below, hi = half == 0 ? below : mrows;
+        if (lo >= hi) continue;
+        bf16_t* out = half == 0 ? p.out0 + (static_cast<long>(cur.e) * p.m_split + cur.m0) * p.N
+                                : p.out1 + (static_cast<long>(cur.e) * (p.M - p.m_split) + (cur.m0 + lo - p.m_split)) * p.N;
+        StripRows so;
+        so.at(out + cur.n0, hi - lo, ld2, skip * 2u);
+#pragma unroll
+        for (int i = 0; i < T::FM; ++i) {
+#pragma unroll
+          for (int j = 0; j < FN; ++j) strip.park(j, acc[i][j]);
+          u32x4 v[2];
+          strip.fetch(v[0], v[1]);
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const int r = a_row + 16 * i + 8 * h + l3 - lo;
+            so.store(off_if(c < ncols && r >= 0, r * ld2 + c * 2u, StripRows::kNone), v[h]);
+          }
         }
       }
     }
-  } else {                                           // whole expert: rounded once, staged as bf16
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi) {
-      park_strip_bf16<T>(acc, mi, reinterpret_cast<char*>(strip), el);
-      uint4 v[NP];
-#pragma unroll
-      for (int pass = 0; pass < NP; ++pass)
-        v[pass] = read_strip_bf16<T>(reinterpret_cast<const char*>(strip), pass * RPP + el / LPR, el % LPR);
-#pragma unroll
-      for (int pass = 0; pass < NP; ++pass) {
-        const int rl = wm * WM + mi * 32 + pass * RPP + el / LPR;
-        if (cl < ncols && rl < mrows) {
-          const int m = m0 + rl;
-          bf16_t* out = m < p.m_split ? p.out0 + (static_cast<long>(e) * p.m_split + m) * p.N
-                                      : p.out1 + (static_cast<long>(e) * (p.M - p.m_split) + (m - p.m_split)) * p.N;
-          store16(out + n0 + cl, v[pass]);
-        }
-      }
-    }
+    if (nxt.exists == 0) break;
+    cur = nxt;
   }
+  Loop::finish();
 }
 
 // out[e] = bf16( sum over the chunks of a split expert, in chunk order, of its fp32 partial tiles )
@@ -1489,7 +1558,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradArgs p) {
 //   TileRouter: 64 x 128 x 64 for the skinny products with N = E, two workgroups per CU.
 typedef Tile<256, 256, 64, 2, 4, 2, 3> TileBig;
 typedef Tile<256, 256, 64, 4, 4, 2, 3> TileBigW16;
-typedef Tile<64, 128, 64, 2, 2, 3, 3> TileRouter;
+typedef Tile<64, 128, 64, 2, 2, 2, 3> TileRouter;
 
 // Row-grouped products of experts with few rows: a quarter of the tile, two workgroups of four waves per CU.  These products
 // stream the weights once; what they lack with the large tile is workgroups (a row tile per expert) and something to run
@@ -1610,35 +1679,39 @@ static bool allow_lds(LdsGrant& g, const void* kernel, int bytes, const char* na
   return err == hipSuccess;
 }
 
+// The products' workgroups stay on their CU and take tile after tile: as many as run at once, or fewer if there are fewer tiles.
+constexpr int kCus = 256;
 static unsigned padded_grid(int tiles) { return static_cast<unsigned>(ceil_div(tiles < 1 ? 1 : tiles, kXcds) * kXcds); }
 
-template <int KIND, class T, bool FUSED = false>
+static unsigned resident_grid(int tiles, int blocks_per_cu) { return std::min(padded_grid(tiles), static_cast<unsigned>(kCus * blocks_per_cu)); }
+
+template <int KIND, class T, bool FUSED = false, bool ACT_W = false>
 static void launch_row_t(RowArgs p, int P, int E, hipStream_t s) {
   static const char* const names[6] = {"ffn_gate_up", "ffn_down", "ffn_dact", "ffn_dx", "router_logits", "router_dx"};
   static LdsGrant grant;
-  if (!allow_lds(grant, reinterpret_cast<const void*>(&row_grouped_kernel<KIND, T, FUSED>), T::kLdsAlloc, names[KIND])) return;
+  if (!allow_lds(grant, reinterpret_cast<const void*>(&row_grouped_kernel<KIND, T, FUSED, ACT_W>), T::kLdsBytes, names[KIND])) return;
   p.n_tiles_n = ceil_div(p.N, KIND == kGateUp ? T::BN / 2 : T::BN);
-  const unsigned grid = padded_grid((ceil_div(P, T::BM) + E) * p.n_tiles_n);
-  MOE_LAUNCH(names[KIND], (row_grouped_kernel<KIND, T, FUSED>), dim3(grid), dim3(T::kThreads), T::kLdsAlloc, s, p);
+  const unsigned grid = resident_grid((ceil_div(P, T::BM) + E) * p.n_tiles_n, T::kBlocksPerCu);
+  MOE_LAUNCH(names[KIND], (row_grouped_kernel<KIND, T, FUSED, ACT_W>), dim3(grid), dim3(T::kThreads), T::kLdsBytes, s, p);
 }
 
-template <int KIND, bool FUSED = false>
+template <int KIND, bool FUSED = false, bool ACT_W = false>
 static void launch_row(const RowArgs& p, int P, int E, hipStream_t s) {
-  if (p.rt.bm == TileFew::BM) launch_row_t<KIND, TileFew, FUSED>(p, P, E, s);
-  else launch_row_t<KIND, TileBig, FUSED>(p, P, E, s);
+  if (p.rt.bm == TileFew::BM) launch_row_t<KIND, TileFew, FUSED, ACT_W>(p, P, E, s);
+  else launch_row_t<KIND, TileBig, FUSED, ACT_W>(p, P, E, s);
 }
 
 template <int WHICH, bool GATHER = false>
 static void launch_wgrad(WgradArgs p, hipStream_t s) {
   typedef TileBigW16 T;
   static LdsGrant grant;
-  if (!allow_lds(grant, reinterpret_cast<const void*>(&wgrad_kernel<WHICH, T, GATHER>), T::kLdsAlloc, "wgrad")) return;
+  if (!allow_lds(grant, reinterpret_cast<const void*>(&wgrad_kernel<WHICH, T, GATHER>), T::kLdsBytes, "wgrad")) return;
   p.tiles_m = ceil_div(p.M, T::BM);
   p.tiles_n = ceil_div(p.N, T::BN);
   // units are dealt to the XCDs in groups of 8, the last group may be partial: up to 8 more units than items
-  const unsigned grid = padded_grid(p.tiles_m * p.tiles_n * (p.items.max_items + kXcds));
+  const unsigned grid = resident_grid(p.tiles_m * p.tiles_n * (p.items.max_items + kXcds), T::kBlocksPerCu);
   MOE_LAUNCH(WHICH == 0 ? "wgrad_down" : WHICH == 1 ? "wgrad_gate_up" : "wgrad_router", (wgrad_kernel<WHICH, T, GATHER>), dim3(grid),
-             dim3(T::kThreads), T::kLdsAlloc, s, p);
+             dim3(T::kThreads), T::kLdsBytes, s, p);
   // the reduction loops are grid-strided: a launch with nothing to reduce (balanced routing) should cost as little as a launch can
   // (room for two split experts per pass of the loop; more only repeat it)
   const long rblocks = std::max(2 * ((static_cast<long>(p.M) * p.N + 2047) / 2048), p.dw_partial ? (static_cast<long>(p.P) + 255) / 256 : 1L);
@@ -1831,7 +1904,8 @@ void ffn_bwd_gather_bf16(const FfnBwdGatherArgs& a) {
     p.K = a.d; p.N = a.f; p.offsets = a.offsets; p.P = a.P; p.rt = rt;
     p.out0 = dgu; p.ldo = 2L * a.f; p.g = G; p.u = U;
     p.row_token = row_token; p.row_w = row_w; p.act_w = a.act_w ? nullptr : act_w_ws; p.dw_partial = dw_partial;
-    launch_row<kDAct, true>(p, a.P, a.E, a.stream);
+    if (p.act_w) launch_row<kDAct, true, true>(p, a.P, a.E, a.stream);
+    else launch_row<kDAct, true, false>(p, a.P, a.E, a.stream);
   }
   launch_dx(dgu, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, a.offsets, rt, a.dxp, a.stream);
   float* partial = reinterpret_cast<float*>(base + w.partial);
