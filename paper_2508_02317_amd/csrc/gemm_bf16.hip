@@ -829,8 +829,8 @@ struct StripRows {
   __device__ __forceinline__ void store(uint32_t off, const u32x4& v) const {          // non-temporal, as store16
     __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, static_cast<int>(off), 0, 2);
   }
-  __device__ __forceinline__ void store_half_line(uint32_t off, const u32x4& v) const {   // through the L2, which joins two waves' halves
-    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, static_cast<int>(off), 0, 0);
+  template <bool CACHED> __device__ __forceinline__ void store_as(uint32_t off, const u32x4& v) const {
+    __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, static_cast<int>(off), 0, CACHED ? 0 : 2);
   }
   __device__ __forceinline__ void store(uint32_t off, float v) const {
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), rsrc, static_cast<int>(off), 0, 0);
@@ -938,8 +938,8 @@ struct RowArgs {
 //   dA = w_r * (dy[token(r)] Wd)              the combine weight scales the product's rows
 //   d w_r = <dy[token(r)], yp[r]> = <dy[token(r)] Wd, act[r]>    reduced over the columns of the tile
 //   act_w[r] = w_r * act[r]                   the operand with which dWd = dy[token]^T act_w needs no dyp
-// ACT_W (kDAct): act_w is written; else the forward left it.
-template <int KIND, class T, bool FUSED = false, bool ACT_W = false>
+// OPTION, kDAct: act_w is written (else the forward left it); kGateUp: its half-line stores go through the L2 (see launch_gate_up).
+template <int KIND, class T, bool FUSED = false, bool OPTION = false>
 __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::kWavesPerSimd, T::kWavesPerSimd))) void row_grouped_kernel(RowArgs p) {
   static_assert(!FUSED || KIND == kGateUp || KIND == kDAct, "only the two products that read activations by token are fused");
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -1076,9 +1076,9 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
           sg.at(p.out0 + o, p.out0 ? rows - rs0 : 0, ld2, skip2);
           su.at(p.out1 + o, p.out1 ? rows - rs0 : 0, ld2, skip2);
           sa.at(p.out2 + o, p.out2 ? rows - rs0 : 0, ld2, skip2);
-          sg.store_half_line(off, vg);
-          su.store_half_line(off, vu);
-          sa.store_half_line(off, va);
+          sg.template store_as<OPTION>(off, vg);
+          su.template store_as<OPTION>(off, vu);
+          sa.template store_as<OPTION>(off, va);
         }
       }
     } else if constexpr (KIND == kDown || KIND == kDX) {
@@ -1130,7 +1130,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
         sdg.at(p.out0 + o, rows - rs0, ld2, skip2);
         sdu.at(p.out0 + o + p.N, rows - rs0, ld2, skip2 + n2);
         if constexpr (FUSED) {
-          if constexpr (ACT_W) saw.at(p.act_w + (static_cast<long>(row0 + rs0) * p.N + n0), rows - rs0, n2, skip2);
+          if constexpr (OPTION) saw.at(p.act_w + (static_cast<long>(row0 + rs0) * p.N + n0), rows - rs0, n2, skip2);
           sdw.at(p.dw_partial + static_cast<long>(n0 / BN * T::WGN + wn) * p.P + row0 + rs0, min(rows - rs0, 32), 4, 0);
         }
 #pragma unroll
@@ -1162,7 +1162,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
               }
               sdg.store(off + down * ld2, pack8(dg));
               sdu.store(off + down * ld2, pack8(du));
-              if constexpr (ACT_W) {
+              if constexpr (OPTION) {
 #pragma unroll
                 for (int q = 0; q < 8; ++q) act[q] *= w;
                 saw.store(goff + down * n2, pack8(act));
@@ -1685,20 +1685,20 @@ static unsigned padded_grid(int tiles) { return static_cast<unsigned>(ceil_div(t
 
 static unsigned resident_grid(int tiles, int blocks_per_cu) { return std::min(padded_grid(tiles), static_cast<unsigned>(kCus * blocks_per_cu)); }
 
-template <int KIND, class T, bool FUSED = false, bool ACT_W = false>
+template <int KIND, class T, bool FUSED = false, bool OPTION = false>
 static void launch_row_t(RowArgs p, int P, int E, hipStream_t s) {
   static const char* const names[6] = {"ffn_gate_up", "ffn_down", "ffn_dact", "ffn_dx", "router_logits", "router_dx"};
   static LdsGrant grant;
-  if (!allow_lds(grant, reinterpret_cast<const void*>(&row_grouped_kernel<KIND, T, FUSED, ACT_W>), T::kLdsBytes, names[KIND])) return;
+  if (!allow_lds(grant, reinterpret_cast<const void*>(&row_grouped_kernel<KIND, T, FUSED, OPTION>), T::kLdsBytes, names[KIND])) return;
   p.n_tiles_n = ceil_div(p.N, KIND == kGateUp ? T::BN / 2 : T::BN);
   const unsigned grid = resident_grid((ceil_div(P, T::BM) + E) * p.n_tiles_n, T::kBlocksPerCu);
-  MOE_LAUNCH(names[KIND], (row_grouped_kernel<KIND, T, FUSED, ACT_W>), dim3(grid), dim3(T::kThreads), T::kLdsBytes, s, p);
+  MOE_LAUNCH(names[KIND], (row_grouped_kernel<KIND, T, FUSED, OPTION>), dim3(grid), dim3(T::kThreads), T::kLdsBytes, s, p);
 }
 
-template <int KIND, bool FUSED = false, bool ACT_W = false>
+template <int KIND, bool FUSED = false, bool OPTION = false>
 static void launch_row(const RowArgs& p, int P, int E, hipStream_t s) {
-  if (p.rt.bm == TileFew::BM) launch_row_t<KIND, TileFew, FUSED, ACT_W>(p, P, E, s);
-  else launch_row_t<KIND, TileBig, FUSED, ACT_W>(p, P, E, s);
+  if (p.rt.bm == TileFew::BM) launch_row_t<KIND, TileFew, FUSED, OPTION>(p, P, E, s);
+  else launch_row_t<KIND, TileBig, FUSED, OPTION>(p, P, E, s);
 }
 
 template <int WHICH, bool GATHER = false>
@@ -1732,8 +1732,21 @@ static void launch_gate_up(const void* xp, const void* wg, const void* wu, int P
   p.w_expert_stride = static_cast<long>(f) * d; p.ldw = d;
   p.K = d; p.N = f; p.offsets = offsets; p.P = P; p.rt = rt;
   p.out0 = static_cast<bf16_t*>(G); p.out1 = static_cast<bf16_t*>(U); p.out2 = static_cast<bf16_t*>(act); p.ldo = f;
-  if (row_token) launch_row<kGateUp, true>(p, P, E, s);
-  else launch_row<kGateUp>(p, P, E, s);
+  // A wave's G, U and activation fill half a line per row.  Written around the L2 (non-temporal), both halves go to memory on
+  // their own; written through it, another wave's half joins them, but they displace weights and are still being written back
+  // when the next launch starts.  Joining them pays where all three are written by experts with many rows -- 40960 tokens,
+  // d = 2048, E = 128, k = 8, f = 768: 1760 -> 1681 us, 8192 tokens 424 -> 411 (step 2092 -> 2082), 16384 rows on 16 experts
+  // 106 -> 102 (594 -> 589) -- and costs with few rows (1531 tokens, 96 rows per expert: gate/up 155 -> 161, down 89 -> 96) or
+  // with the activation alone (8192 tokens forward: 709 -> 709; 2047 tokens: 313 -> 317).  256 rows per expert: step 1349 and 1350.
+  const bool through_l2 = G && act && P >= 256L * E;
+  if (through_l2) {
+    if (row_token) launch_row_t<kGateUp, TileBig, true, true>(p, P, E, s);
+    else launch_row_t<kGateUp, TileBig, false, true>(p, P, E, s);
+  } else if (row_token) {
+    launch_row<kGateUp, true>(p, P, E, s);
+  } else {
+    launch_row<kGateUp>(p, P, E, s);
+  }
 }
 
 static void launch_down(const void* act, const void* wd, int P, int d, int f, int E, const int32_t* offsets,
