@@ -62,7 +62,7 @@ def kernel_work(cfg, P, gather, save_gu, late_weight=False):
         pre + "dx": (mm, 4 * dff, 2 * Pf + 2 * Edf + Pd),
         "wgrad_down": (mm, 2 * dff, xin + Pf + Edf),
         "wgrad_gate_up": (mm, 4 * dff, 2 * Pf + xin + 2 * Edf),
-        "f32_wgrad": (mm, 6 * dff, None),   # the three weight gradients in one launch
+        "f32_dx_wgrad": (mm, 10 * dff, None),   # the data gradient and the three weight gradients in one launch
         "route_topk": ("hbm", T * E * 4 + P * 8, None),
         "route_bwd": ("hbm", T * E * 4 + P * 12, None),
         "permute_gather": ("hbm", (T + P) * d * s + 2 * P * 4, None),

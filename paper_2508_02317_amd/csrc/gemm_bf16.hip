@@ -1359,7 +1359,7 @@ struct WgradArgs {
   bf16_t* out0; bf16_t* out1; int m_split;     // out1 rows are (m - m_split)
   float* partial;                              // [max_slots][M][N]
   const int32_t* row_token;    // GATHER kernels: [P + padding], token of each expert-ordered row
-  // a side job of the reduction launch that follows dW_down in the gathered backward (null: none): the partial dot
+  // a side job of the reduction launch of the gathered backward, taken from dW_down's arguments (null: none): the partial dot
   // products of the combine-weight gradient, one per (column slot, row), are added in slot order and scattered to [T, k]
   const float* dw_partial; int dw_slots; const int32_t* pair_of_row; float* dtopk_w;
 };
@@ -1506,41 +1506,54 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   Loop::finish();
 }
 
-// out[e] = bf16( sum over the chunks of a split expert, in chunk order, of its fp32 partial tiles )
+// out[e] = bf16( sum over the chunks of a split expert, in chunk order, of its fp32 partial tiles ), for one weight gradient
+// or for both of the experts' (which share their work items) in one launch
 // (with balanced routing there are no split experts, and the launch is blocks that read one counter and leave)
-__global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradArgs p) {
+struct WgradReduceArgs { WgradArgs a, b; };            // b.partial == null: a alone
+__global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradReduceArgs args) {
+  const WgradArgs& p = args.a;
   if (p.dw_partial) {                                  // dtopk_w[pair_of_row[r]] = sum over the column slots, in slot order
     for (int r = blockIdx.x * 256 + threadIdx.x; r < p.P; r += gridDim.x * 256) {
+      // 16 slots requested together (one after the other, 32 slots of 8192 rows took 18 us), added in order
       float s = 0.0f;
-      for (int j = 0; j < p.dw_slots; ++j) s += p.dw_partial[static_cast<long>(j) * p.P + r];
+      for (int j = 0; j < p.dw_slots; j += 16) {
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = p.dw_partial[static_cast<long>(min(j + u, p.dw_slots - 1)) * p.P + r];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) s = j + u < p.dw_slots ? s + v[u] : s;
+      }
       p.dtopk_w[min(max(p.pair_of_row[r], 0), p.P - 1)] = s;
     }
   }
   // every (split expert, 8 outputs) pair is one unit of a single grid-strided loop: the launch is latency-bound (a unit is
   // one round of loads and one store), so the split experts are reduced side by side, not one after the other
   const int n_split = p.items.count[1];
-  const long mn = static_cast<long>(p.M) * p.N, per = mn / 8;          // N is a multiple of 8: a unit lies in one row
+  const long per_a = static_cast<long>(p.M) * p.N / 8;                 // N is a multiple of 8: a unit lies in one row
+  const long per = per_a + (args.b.partial ? static_cast<long>(args.b.M) * args.b.N / 8 : 0L);
   for (long unit = static_cast<long>(blockIdx.x) * 256 + threadIdx.x; unit < n_split * per; unit += static_cast<long>(gridDim.x) * 256) {
     const int s = static_cast<int>(unit / per);
-    const long i = (unit - s * per) * 8;
+    const long u = unit - s * per;
+    const WgradArgs& q = u < per_a ? args.a : args.b;
+    const long i = (u < per_a ? u : u - per_a) * 8, mn = static_cast<long>(q.M) * q.N;
     const int e = p.items.split_expert[s], n = p.items.split_n[s];
-    const float* part = p.partial + static_cast<long>(p.items.split_slot0[s]) * mn;
+    const float* part = q.partial + static_cast<long>(p.items.split_slot0[s]) * mn;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int j = 0; j < n; j += 4) {                       // four partial tiles requested together, added in slot order
       float v[4][8];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) read8(part + min(j + u, n - 1) * mn + i, v[u]);   // past the last slot: re-read it, not added
+      for (int t = 0; t < 4; ++t) read8(part + min(j + t, n - 1) * mn + i, v[t]);   // past the last slot: re-read it, not added
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (j + u < n) {
+      for (int t = 0; t < 4; ++t) {
+        if (j + t < n) {
 #pragma unroll
-          for (int q = 0; q < 8; ++q) acc[q] += v[u][q];
+          for (int c = 0; c < 8; ++c) acc[c] += v[t][c];
         }
       }
     }
-    const int m = static_cast<int>(i / p.N), col = static_cast<int>(i % p.N);
-    bf16_t* out = m < p.m_split ? p.out0 + (static_cast<long>(e) * p.m_split + m) * p.N
-                                : p.out1 + (static_cast<long>(e) * (p.M - p.m_split) + (m - p.m_split)) * p.N;
+    const int m = static_cast<int>(i / q.N), col = static_cast<int>(i % q.N);
+    bf16_t* out = m < q.m_split ? q.out0 + (static_cast<long>(e) * q.m_split + m) * q.N
+                                : q.out1 + (static_cast<long>(e) * (q.M - q.m_split) + (m - q.m_split)) * q.N;
     store16(out + col, pack8(acc));
   }
 }
@@ -1621,7 +1634,7 @@ static WsLayout ws_layout(int P, int d, int f, int E, bool need_dgu, bool need_g
     const size_t sp = align_up(static_cast<size_t>(wgrad_max_split(P, E)) * sizeof(int32_t), 256);
     off += 256 + 4 * it + 3 * sp;
     w.partial = off;
-    off += align_up(static_cast<size_t>(wgrad_max_slots(P)) * 2 * f * d * sizeof(float), 256);
+    off += align_up(static_cast<size_t>(wgrad_max_slots(P)) * 3 * f * d * sizeof(float), 256);   // dW_down's, then [dW_gate; dW_up]'s
   }
   w.total = off + 256;
   return w;
@@ -1712,12 +1725,16 @@ static void launch_wgrad(WgradArgs p, hipStream_t s) {
   const unsigned grid = resident_grid(p.tiles_m * p.tiles_n * (p.items.max_items + kXcds), T::kBlocksPerCu);
   MOE_LAUNCH(WHICH == 0 ? "wgrad_down" : WHICH == 1 ? "wgrad_gate_up" : "wgrad_router", (wgrad_kernel<WHICH, T, GATHER>), dim3(grid),
              dim3(T::kThreads), T::kLdsBytes, s, p);
+}
+// the partial tiles of one weight gradient, or (b given) of both of the experts' in one launch behind the two products
+static void launch_wgrad_reduce(const char* name, const WgradArgs& a, const WgradArgs* b, hipStream_t s) {
+  WgradReduceArgs r{a, {}};
+  if (b) r.b = *b;
   // the reduction loops are grid-strided: a launch with nothing to reduce (balanced routing) should cost as little as a launch can
   // (room for two split experts per pass of the loop; more only repeat it)
-  const long rblocks = std::max(2 * ((static_cast<long>(p.M) * p.N + 2047) / 2048), p.dw_partial ? (static_cast<long>(p.P) + 255) / 256 : 1L);
-  const dim3 rgrid(static_cast<unsigned>(std::min(rblocks, 2048L)));
-  MOE_LAUNCH(WHICH == 0 ? "wgrad_down_reduce" : WHICH == 1 ? "wgrad_gate_up_reduce" : "wgrad_router_reduce", wgrad_reduce_kernel, rgrid,
-             dim3(256), 0, s, p);
+  const long outputs = static_cast<long>(a.M) * a.N + (b ? static_cast<long>(b->M) * b->N : 0L);
+  const long blocks = std::max(2 * ((outputs + 2047) / 2048), a.dw_partial ? (static_cast<long>(a.P) + 255) / 256 : 1L);
+  MOE_LAUNCH(name, wgrad_reduce_kernel, dim3(static_cast<unsigned>(std::min(blocks, 2048L))), dim3(256), 0, s, r);
 }
 
 // row_token == null: xp is in expert order; else xp is the token-major input and rows are gathered from it
@@ -1809,8 +1826,9 @@ void ffn_bwd_bf16(const FfnBwdArgs& a) {
   }
   launch_dx(dgu, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, a.offsets, rt, a.dxp, a.stream);   // dxp = dG Wg + dU Wu
   float* partial = reinterpret_cast<float*>(base + w.partial);
+  WgradArgs down{}, gate_up{};
   {  // dWd[e] = dyp^T act
-    WgradArgs p{};
+    WgradArgs& p = down;
     p.lhs = static_cast<const bf16_t*>(a.dyp); p.ld_lhs = a.d; p.M = a.d;
     p.rhs = static_cast<const bf16_t*>(a.act); p.ld_rhs = a.f; p.N = a.f;
     p.E = a.E; p.P = a.P; p.items = items; p.partial = partial;
@@ -1818,13 +1836,14 @@ void ffn_bwd_bf16(const FfnBwdArgs& a) {
     launch_wgrad<0>(p, a.stream);
   }
   {  // [dWg[e]; dWu[e]] = [dG | dU]^T xp
-    WgradArgs p{};
+    WgradArgs& p = gate_up;
     p.lhs = dgu; p.ld_lhs = 2L * a.f; p.M = 2 * a.f;
     p.rhs = static_cast<const bf16_t*>(a.xp); p.ld_rhs = a.d; p.N = a.d;
-    p.E = a.E; p.P = a.P; p.items = items; p.partial = partial;
+    p.E = a.E; p.P = a.P; p.items = items; p.partial = partial + static_cast<size_t>(items.max_slots) * a.f * a.d;
     p.out0 = static_cast<bf16_t*>(a.dw_gate); p.out1 = static_cast<bf16_t*>(a.dw_up); p.m_split = a.f;
     launch_wgrad<1>(p, a.stream);
   }
+  launch_wgrad_reduce("wgrad_reduce", down, &gate_up, a.stream);
 }
 
 // ============================================================================================
@@ -1922,8 +1941,9 @@ void ffn_bwd_gather_bf16(const FfnBwdGatherArgs& a) {
   }
   launch_dx(dgu, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, a.offsets, rt, a.dxp, a.stream);
   float* partial = reinterpret_cast<float*>(base + w.partial);
+  WgradArgs down{}, gate_up{};
   {  // dWd[e] = dy[token]^T (w act)
-    WgradArgs p{};
+    WgradArgs& p = down;
     p.lhs = static_cast<const bf16_t*>(a.dy); p.ld_lhs = a.d; p.M = a.d;
     p.rhs = act_w; p.ld_rhs = a.f; p.N = a.f;
     p.E = a.E; p.P = a.P; p.items = items; p.partial = partial;
@@ -1933,14 +1953,15 @@ void ffn_bwd_gather_bf16(const FfnBwdGatherArgs& a) {
     launch_wgrad<0, true>(p, a.stream);
   }
   {  // [dWg[e]; dWu[e]] = [dG | dU]^T x[token]
-    WgradArgs p{};
+    WgradArgs& p = gate_up;
     p.lhs = dgu; p.ld_lhs = 2L * a.f; p.M = 2 * a.f;
     p.rhs = static_cast<const bf16_t*>(a.x); p.ld_rhs = a.d; p.N = a.d;
-    p.E = a.E; p.P = a.P; p.items = items; p.partial = partial;
+    p.E = a.E; p.P = a.P; p.items = items; p.partial = partial + static_cast<size_t>(items.max_slots) * a.f * a.d;
     p.out0 = static_cast<bf16_t*>(a.dw_gate); p.out1 = static_cast<bf16_t*>(a.dw_up); p.m_split = a.f;
     p.row_token = row_token;
     launch_wgrad<1, true>(p, a.stream);
   }
+  launch_wgrad_reduce("wgrad_reduce", down, &gate_up, a.stream);
 }
 
 // ============================================================================================
@@ -2051,6 +2072,7 @@ void router_bwd_bf16(const RouterBwdArgs& a) {
     p.E = 1; p.P = a.T; p.items = items; p.partial = reinterpret_cast<float*>(base + w.partial);
     p.out0 = static_cast<bf16_t*>(a.dw_router); p.out1 = p.out0; p.m_split = a.E;
     launch_wgrad<2>(p, a.stream);
+    launch_wgrad_reduce("wgrad_router_reduce", p, nullptr, a.stream);
   }
 }
 
