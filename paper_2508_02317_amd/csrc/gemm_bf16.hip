@@ -852,9 +852,9 @@ __device__ __forceinline__ void build_row_tiles(const int32_t* __restrict__ offs
   __shared__ int32_t first_row[kMaxExperts];
   const int e = threadIdx.x;
   int begin = 0, end = 0, nt = 0;
-  if (e < E) {                                       // offsets == null: one segment holding all P rows
-    begin = offsets ? min(max(offsets[e], 0), P) : 0;
-    end = offsets ? min(max(offsets[e + 1], begin), P) : P;
+  if (e < E) {
+    begin = min(max(offsets[e], 0), P);
+    end = min(max(offsets[e + 1], begin), P);
     nt = (end - begin + bm - 1) / bm;
   }
   scan[e] = nt;
@@ -955,7 +955,9 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   const int a_row = wm * WM, b_row = wn * (KIND == kGateUp ? HW : WN);   // first tile rows of this wave on either side
 
   // This workgroup's tiles: every gridDim.x-th of the list (see xcd_remap), the next one located while one is multiplied.
-  const int total = const_list(p.rt.count)[0] * p.n_tiles_n;
+  // The router's products have one segment of all rows: its row tiles follow from their number.
+  constexpr bool ONE_SEGMENT = KIND == kRouterFwd || KIND == kRouterDx;
+  const int total = (ONE_SEGMENT ? (p.P + BM - 1) / BM : const_list(p.rt.count)[0]) * p.n_tiles_n;
   // (`exists` is a number of unknown origin: a truth value carried around the loop would be a lane mask, and the parts of the
   // descriptors that are selected by it vectors, which makes every load of the slab loop a loop over lanes)
   struct At { int row0, rows, e, n0, exists; };
@@ -966,9 +968,9 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
     if (v >= 0) {
       const int mt = scalar(v / p.n_tiles_n);
       t.n0 = (v - mt * p.n_tiles_n) * OUT_N;
-      t.e = const_list(p.rt.expert)[mt];
-      t.row0 = const_list(p.rt.row0)[mt];
-      const int row_end = p.offsets ? min(const_list(p.offsets)[t.e + 1], p.P) : p.P;
+      t.e = ONE_SEGMENT ? 0 : const_list(p.rt.expert)[mt];
+      t.row0 = ONE_SEGMENT ? mt * BM : const_list(p.rt.row0)[mt];
+      const int row_end = ONE_SEGMENT ? p.P : min(const_list(p.offsets)[t.e + 1], p.P);
       t.rows = scalar(min(BM, row_end - t.row0));
     }
     return t;
@@ -1259,9 +1261,9 @@ __device__ __forceinline__ void build_wgrad_items(const int32_t* __restrict__ of
   __shared__ int32_t scan_split[kMaxExperts];
   const int e = threadIdx.x;
   int begin = 0, c = -1;
-  if (e < E) {                                       // offsets == null: one segment holding all P rows
-    begin = offsets ? min(max(offsets[e], 0), P) : 0;
-    c = (offsets ? min(max(offsets[e + 1], begin), P) : P) - begin;
+  if (e < E) {
+    begin = min(max(offsets[e], 0), P);
+    c = min(max(offsets[e + 1], begin), P) - begin;
   }
   cnt[e] = c;
   __syncthreads();
@@ -1291,7 +1293,7 @@ __device__ __forceinline__ void build_wgrad_items(const int32_t* __restrict__ of
   }
   if (e < E) {
     const int first = scan_items[e] - my_n, slot0 = scan_slots[e] - (split ? my_n : 0), sidx = scan_split[e] - split;
-    const int row0 = offsets ? min(max(offsets[my_e], 0), P) : 0;
+    const int row0 = min(max(offsets[my_e], 0), P);
     // the host sizes the lists for the worst case; offsets that are not a monotone scan ending at P cannot overflow them
     const bool fits = slot0 + my_n <= it.max_slots && sidx < it.max_split;
     for (int j = 0; j < my_n && first + j < it.max_items; ++j) {
@@ -1310,10 +1312,6 @@ __device__ __forceinline__ void build_wgrad_items(const int32_t* __restrict__ of
     it.count[0] = min(scan_items[1023], it.max_items);
     it.count[1] = min(scan_split[1023], it.max_split);
   }
-}
-__global__ __launch_bounds__(1024) void build_wgrad_items_kernel(const int32_t* __restrict__ offsets, int E, int P,
-                                                                  int chunk_rows, WgradItems it) {
-  build_wgrad_items(offsets, E, P, chunk_rows, it);
 }
 
 // entries of padding behind the list of row tokens: its scalar loads run up to SA + 1 = SB = 3 slabs past the last whole slab, that
@@ -1355,6 +1353,7 @@ struct WgradArgs {
   const bf16_t* rhs; long ld_rhs; int N;
   int E; int P;
   WgradItems items;
+  int one_segment_items, chunk_rows;           // the router's (items is not used): chunks of chunk_rows rows, at least one
   int tiles_m, tiles_n;
   bf16_t* out0; bf16_t* out1; int m_split;     // out1 rows are (m - m_split)
   float* partial;                              // [max_slots][M][N]
@@ -1376,7 +1375,8 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   static_assert(FN == 4, "the epilogue takes the fragments of a row in two pairs");
   typedef MainLoop<T, true, true, GA, GB> Loop;
   const int per_e = p.tiles_m * p.tiles_n;
-  const int n_items = const_list(p.items.count)[0];
+  constexpr bool ONE_SEGMENT = WHICH == 2;              // the router's: one segment of all rows, its chunks follow from their number
+  const int n_items = ONE_SEGMENT ? p.one_segment_items : const_list(p.items.count)[0];
   // order of a work item's tiles: row tile fastest for [dW_gate; dW_up] (neighbouring workgroups share the rhs panel;
   // measured 6 % faster at 512 rows per expert), column tile fastest for the others
   constexpr bool MT_FASTEST = WHICH == 1;
@@ -1403,6 +1403,12 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
       const int fast = MT_FASTEST ? p.tiles_m : p.tiles_n, slow_i = scalar(vi / fast), fast_i = vi - slow_i * fast;
       t.m0 = (MT_FASTEST ? fast_i : slow_i) * BM;
       t.n0 = (MT_FASTEST ? slow_i : fast_i) * BN;
+      if constexpr (ONE_SEGMENT) {
+        t.slot = n_items > 1 ? item : -1;
+        t.begin = item * p.chunk_rows;
+        t.end = min(p.P, t.begin + p.chunk_rows);
+        return t;
+      }
       t.slot = const_list(p.items.slot)[item];
       if (t.slot == -2) continue;
       t.e = const_list(p.items.expert)[item];
@@ -1528,7 +1534,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradReduceArgs args)
   }
   // every (split expert, 8 outputs) pair is one unit of a single grid-strided loop: the launch is latency-bound (a unit is
   // one round of loads and one store), so the split experts are reduced side by side, not one after the other
-  const int n_split = p.items.count[1];
+  const int n_split = p.one_segment_items ? (p.one_segment_items > 1 ? 1 : 0) : p.items.count[1];
   const long per_a = static_cast<long>(p.M) * p.N / 8;                 // N is a multiple of 8: a unit lies in one row
   const long per = per_a + (args.b.partial ? static_cast<long>(args.b.M) * args.b.N / 8 : 0L);
   for (long unit = static_cast<long>(blockIdx.x) * 256 + threadIdx.x; unit < n_split * per; unit += static_cast<long>(gridDim.x) * 256) {
@@ -1536,8 +1542,8 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradReduceArgs args)
     const long u = unit - s * per;
     const WgradArgs& q = u < per_a ? args.a : args.b;
     const long i = (u < per_a ? u : u - per_a) * 8, mn = static_cast<long>(q.M) * q.N;
-    const int e = p.items.split_expert[s], n = p.items.split_n[s];
-    const float* part = q.partial + static_cast<long>(p.items.split_slot0[s]) * mn;
+    const int e = p.one_segment_items ? 0 : p.items.split_expert[s], n = p.one_segment_items ? p.one_segment_items : p.items.split_n[s];
+    const float* part = q.partial + (p.one_segment_items ? 0L : static_cast<long>(p.items.split_slot0[s])) * mn;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int j = 0; j < n; j += 4) {                       // four partial tiles requested together, added in slot order
       float v[4][8];
@@ -1604,12 +1610,9 @@ static int max_row_tiles(int P, int E) { return ceil_div(P, 128) + E; }
 // 2048 rows is the measured optimum when 16 experts share 16K rows with two thirds of them on one expert
 // (1024: a third more partial traffic; 3072: too few work items per XCD).
 static int wgrad_chunk_rows(int P) { return std::max(2048, static_cast<int>(align_up(static_cast<size_t>(ceil_div(P, 32)), 256))); }
-static int wgrad_max_items(int P, int E, int chunk) { return E + ceil_div(P, chunk); }
-static int wgrad_max_split(int P, int E, int chunk) { return std::max(1, std::min(E, ceil_div(P, chunk))); }
-static int wgrad_max_slots(int P, int chunk) { return 2 * ceil_div(P, chunk); }
-static int wgrad_max_items(int P, int E) { return wgrad_max_items(P, E, wgrad_chunk_rows(P)); }
-static int wgrad_max_split(int P, int E) { return wgrad_max_split(P, E, wgrad_chunk_rows(P)); }
-static int wgrad_max_slots(int P) { return wgrad_max_slots(P, wgrad_chunk_rows(P)); }
+static int wgrad_max_items(int P, int E) { return E + ceil_div(P, wgrad_chunk_rows(P)); }
+static int wgrad_max_split(int P, int E) { return std::max(1, std::min(E, ceil_div(P, wgrad_chunk_rows(P)))); }
+static int wgrad_max_slots(int P) { return 2 * ceil_div(P, wgrad_chunk_rows(P)); }
 // The router's weight gradient has a single "expert" of all T rows and only E x d outputs: shorter chunks
 // (at least 64 of them) so that the launch fills the chip.
 static int router_chunk_rows(int T) { return std::max(256, static_cast<int>(align_up(static_cast<size_t>(ceil_div(T, 64)), 256))); }
@@ -1722,7 +1725,8 @@ static void launch_wgrad(WgradArgs p, hipStream_t s) {
   p.tiles_m = ceil_div(p.M, T::BM);
   p.tiles_n = ceil_div(p.N, T::BN);
   // units are dealt to the XCDs in groups of 8, the last group may be partial: up to 8 more units than items
-  const unsigned grid = resident_grid(p.tiles_m * p.tiles_n * (p.items.max_items + kXcds), T::kBlocksPerCu);
+  const int max_items = WHICH == 2 ? p.one_segment_items : p.items.max_items;
+  const unsigned grid = resident_grid(p.tiles_m * p.tiles_n * (max_items + kXcds), T::kBlocksPerCu);
   MOE_LAUNCH(WHICH == 0 ? "wgrad_down" : WHICH == 1 ? "wgrad_gate_up" : "wgrad_router", (wgrad_kernel<WHICH, T, GATHER>), dim3(grid),
              dim3(T::kThreads), T::kLdsBytes, s, p);
 }
@@ -1980,24 +1984,16 @@ __global__ __launch_bounds__(256) void cast_f32_bf16_kernel(const float* __restr
   store16(out + i * 8, pack8(v));
 }
 
-struct RouterWs { size_t tiles_count, tiles_expert, tiles_row0, dz, items, partial, total; };
+struct RouterWs { size_t dz, partial, total; };
+static int router_items(int T) { return std::max(1, ceil_div(T, router_chunk_rows(T))); }
 static RouterWs router_ws(int T, int d, int E, bool bwd) {
   RouterWs w{};
   size_t off = 0;
-  w.tiles_count = off; off += 256;
-  const size_t t = align_up(static_cast<size_t>(ceil_div(T, 64) + 1) * sizeof(int32_t), 256);   // row tiles of 64 or 256 rows
-  w.tiles_expert = off; off += t;
-  w.tiles_row0 = off; off += t;
-  w.dz = off; w.items = off; w.partial = off;
+  w.dz = off; w.partial = off;
   if (bwd) {
     off += align_up(static_cast<size_t>(T) * E * 2, 256);
-    w.items = off;
-    const int chunk = router_chunk_rows(T);
-    const size_t it = align_up(static_cast<size_t>(wgrad_max_items(T, 1, chunk)) * sizeof(int32_t), 256);
-    const size_t sp = align_up(static_cast<size_t>(wgrad_max_split(T, 1, chunk)) * sizeof(int32_t), 256);
-    off += 256 + 4 * it + 3 * sp;
     w.partial = off;
-    off += align_up(static_cast<size_t>(wgrad_max_slots(T, chunk)) * E * d * sizeof(float), 256);
+    off += align_up(static_cast<size_t>(router_items(T)) * E * d * sizeof(float), 256);
   }
   w.total = off + 256;
   return w;
@@ -2005,71 +2001,35 @@ static RouterWs router_ws(int T, int d, int E, bool bwd) {
 size_t router_fwd_ws_bytes_bf16(int T, int d, int E) { return router_ws(T, d, E, false).total; }
 size_t router_bwd_ws_bytes_bf16(int T, int d, int E) { return router_ws(T, d, E, true).total; }
 
-static RowTiles router_tiles_at(void* ws, const RouterWs& w, int T, int bm) {
-  char* b = static_cast<char*>(ws);
-  RowTiles rt;
-  rt.max_tiles = ceil_div(T, 64) + 1;
-  rt.bm = bm;
-  rt.count = reinterpret_cast<int32_t*>(b + w.tiles_count);
-  rt.expert = reinterpret_cast<int32_t*>(b + w.tiles_expert);
-  rt.row0 = reinterpret_cast<int32_t*>(b + w.tiles_row0);
-  return rt;
-}
-
 void router_fwd_bf16(const RouterFwdArgs& a) {
-  const RouterWs w = router_ws(a.T, a.d, a.E, false);
-  const RowTiles rt = router_tiles_at(a.ws, w, a.T, TileRouter::BM);
-  MOE_LAUNCH("build_row_tiles", build_row_tiles_kernel, dim3(1), dim3(1024), 0, a.stream, static_cast<const int32_t*>(nullptr), 1, a.T,
-             rt.bm, rt);
   RowArgs p{};
   p.a = static_cast<const bf16_t*>(a.x); p.lda = a.d;
   p.w0 = static_cast<const bf16_t*>(a.w_router); p.w_expert_stride = 0; p.ldw = a.d;
-  p.K = a.d; p.N = a.E; p.offsets = nullptr; p.P = a.T; p.rt = rt;
+  p.K = a.d; p.N = a.E; p.P = a.T;
   p.out_f32 = a.logits; p.ldo = a.E;
   launch_row_t<kRouterFwd, TileRouter>(p, a.T, 1, a.stream);
 }
 
 void router_bwd_bf16(const RouterBwdArgs& a) {
   const RouterWs w = router_ws(a.T, a.d, a.E, true);
-  const RowTiles rt = router_tiles_at(a.ws, w, a.T, TileBig::BM);
   char* base = static_cast<char*>(a.ws);
   bf16_t* dz = reinterpret_cast<bf16_t*>(base + w.dz);
   const long n8 = static_cast<long>(a.T) * a.E / 8;
   MOE_LAUNCH("router_cast_dz", cast_f32_bf16_kernel, dim3(static_cast<unsigned>((n8 + 255) / 256)), dim3(256), 0, a.stream, a.dlogits, dz, n8);
-  MOE_LAUNCH("build_row_tiles", build_row_tiles_kernel, dim3(1), dim3(1024), 0, a.stream, static_cast<const int32_t*>(nullptr), 1, a.T,
-             rt.bm, rt);
   {  // dx (+)= dz * Wr
     RowArgs p{};
     p.a = dz; p.lda = a.E;
     p.w0 = static_cast<const bf16_t*>(a.w_router); p.w_expert_stride = 0; p.ldw = a.d;
-    p.K = a.E; p.N = a.d; p.offsets = nullptr; p.P = a.T; p.rt = rt;
+    p.K = a.E; p.N = a.d; p.P = a.T;
     p.out0 = static_cast<bf16_t*>(a.dx); p.ldo = a.d; p.accumulate = a.accumulate;
     launch_row_t<kRouterDx, TileBig>(p, a.T, 1, a.stream);
   }
   {  // dWr = dz^T x
-    WgradItems items;
-    {
-      char* b = base + w.items;
-      items.max_items = wgrad_max_items(a.T, 1, router_chunk_rows(a.T));
-      items.max_split = wgrad_max_split(a.T, 1, router_chunk_rows(a.T));
-      items.max_slots = wgrad_max_slots(a.T, router_chunk_rows(a.T));
-      const size_t li = align_up(static_cast<size_t>(items.max_items) * sizeof(int32_t), 256);
-      const size_t ls = align_up(static_cast<size_t>(items.max_split) * sizeof(int32_t), 256);
-      items.count = reinterpret_cast<int32_t*>(b); b += 256;
-      items.expert = reinterpret_cast<int32_t*>(b); b += li;
-      items.k0 = reinterpret_cast<int32_t*>(b); b += li;
-      items.k1 = reinterpret_cast<int32_t*>(b); b += li;
-      items.slot = reinterpret_cast<int32_t*>(b); b += li;
-      items.split_expert = reinterpret_cast<int32_t*>(b); b += ls;
-      items.split_slot0 = reinterpret_cast<int32_t*>(b); b += ls;
-      items.split_n = reinterpret_cast<int32_t*>(b);
-    }
-    MOE_LAUNCH("build_wgrad_items", build_wgrad_items_kernel, dim3(1), dim3(1024), 0, a.stream, static_cast<const int32_t*>(nullptr), 1, a.T,
-               router_chunk_rows(a.T), items);
     WgradArgs p{};
     p.lhs = dz; p.ld_lhs = a.E; p.M = a.E;
     p.rhs = static_cast<const bf16_t*>(a.x); p.ld_rhs = a.d; p.N = a.d;
-    p.E = 1; p.P = a.T; p.items = items; p.partial = reinterpret_cast<float*>(base + w.partial);
+    p.E = 1; p.P = a.T; p.partial = reinterpret_cast<float*>(base + w.partial);
+    p.one_segment_items = router_items(a.T); p.chunk_rows = router_chunk_rows(a.T);
     p.out0 = static_cast<bf16_t*>(a.dw_router); p.out1 = p.out0; p.m_split = a.E;
     launch_wgrad<2>(p, a.stream);
     launch_wgrad_reduce("wgrad_router_reduce", p, nullptr, a.stream);
