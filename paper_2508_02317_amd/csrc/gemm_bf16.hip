@@ -1516,6 +1516,9 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
 // or for both of the experts' (which share their work items) in one launch
 // (with balanced routing there are no split experts, and the launch is blocks that read one counter and leave)
 struct WgradReduceArgs { WgradArgs a, b; };            // b.partial == null: a alone
+// AT_ONCE: partial tiles requested together.  Few chunks (the experts'): 4; 8 is 6 % slower at 151 MB of partial tiles.  Many (the
+// router's, 32 and 64): 8, 16.3 -> 13.6 and 24.6 -> 20.4 us.
+template <int AT_ONCE>
 __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradReduceArgs args) {
   const WgradArgs& p = args.a;
   if (p.dw_partial) {                                  // dtopk_w[pair_of_row[r]] = sum over the column slots, in slot order
@@ -1545,12 +1548,12 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(WgradReduceArgs args)
     const int e = p.one_segment_items ? 0 : p.items.split_expert[s], n = p.one_segment_items ? p.one_segment_items : p.items.split_n[s];
     const float* part = q.partial + (p.one_segment_items ? 0L : static_cast<long>(p.items.split_slot0[s])) * mn;
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int j = 0; j < n; j += 4) {                       // four partial tiles requested together, added in slot order
-      float v[4][8];
+    for (int j = 0; j < n; j += AT_ONCE) {                 // requested together, added in slot order
+      float v[AT_ONCE][8];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) read8(part + min(j + t, n - 1) * mn + i, v[t]);   // past the last slot: re-read it, not added
+      for (int t = 0; t < AT_ONCE; ++t) read8(part + min(j + t, n - 1) * mn + i, v[t]);   // past the last slot: re-read it, not added
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
+      for (int t = 0; t < AT_ONCE; ++t) {
         if (j + t < n) {
 #pragma unroll
           for (int c = 0; c < 8; ++c) acc[c] += v[t][c];
@@ -1738,7 +1741,9 @@ static void launch_wgrad_reduce(const char* name, const WgradArgs& a, const Wgra
   // (room for two split experts per pass of the loop; more only repeat it)
   const long outputs = static_cast<long>(a.M) * a.N + (b ? static_cast<long>(b->M) * b->N : 0L);
   const long blocks = std::max(2 * ((outputs + 2047) / 2048), a.dw_partial ? (static_cast<long>(a.P) + 255) / 256 : 1L);
-  MOE_LAUNCH(name, wgrad_reduce_kernel, dim3(static_cast<unsigned>(std::min(blocks, 2048L))), dim3(256), 0, s, r);
+  const dim3 grid(static_cast<unsigned>(std::min(blocks, 2048L)));
+  if (a.one_segment_items) MOE_LAUNCH(name, wgrad_reduce_kernel<8>, grid, dim3(256), 0, s, r);
+  else MOE_LAUNCH(name, wgrad_reduce_kernel<4>, grid, dim3(256), 0, s, r);
 }
 
 // row_token == null: xp is in expert order; else xp is the token-major input and rows are gathered from it
@@ -2022,7 +2027,10 @@ void router_bwd_bf16(const RouterBwdArgs& a) {
     p.w0 = static_cast<const bf16_t*>(a.w_router); p.w_expert_stride = 0; p.ldw = a.d;
     p.K = a.E; p.N = a.d; p.P = a.T;
     p.out0 = static_cast<bf16_t*>(a.dx); p.ldo = a.d; p.accumulate = a.accumulate;
-    launch_row_t<kRouterDx, TileBig>(p, a.T, 1, a.stream);
+    // A tile here is two slabs and an epilogue: while all tiles of 128 x 128 run at once they take 13-14 us where the few large
+    // ones took 20-22 (300 and 1531 tokens, d = 2048; 4096, d = 1024); 8192 tokens, d = 2048, twice as many: 27.1 and 26.8.
+    if (static_cast<long>(ceil_div(a.T, TileFew::BM)) * ceil_div(a.d, TileFew::BN) <= 2 * kCus) launch_row_t<kRouterDx, TileFew>(p, a.T, 1, a.stream);
+    else launch_row_t<kRouterDx, TileBig>(p, a.T, 1, a.stream);
   }
   {  // dWr = dz^T x
     WgradArgs p{};
