@@ -835,6 +835,9 @@ struct StripRows {
   __device__ __forceinline__ void store(uint32_t off, float v) const {
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), rsrc, static_cast<int>(off), 0, 0);
   }
+  __device__ __forceinline__ void store_byte(uint32_t off, uint32_t v) const {
+    __builtin_amdgcn_raw_buffer_store_b8(static_cast<uint8_t>(v), rsrc, static_cast<int>(off), 0, 0);
+  }
   __device__ __forceinline__ u32x4 load(uint32_t off) const { return __builtin_amdgcn_raw_buffer_load_b128(rsrc, static_cast<int>(off), 0, 0); }
 };
 
@@ -2045,7 +2048,7 @@ void router_bwd_bf16(const RouterBwdArgs& a) {
 }
 
 // ============================================================================================
-// Forward products with 8-bit block-scaled operands (same tiles, loaders and staging strips)
+// Forward products with 8-bit block-scaled operands (same tiles, loaders, rings and way of walking the tiles)
 // ============================================================================================
 #include "gemm_mx8.inc"
 
