@@ -105,6 +105,21 @@ def test_expert_offsets(L):
         assert np.array_equal(to_np(counts), rc) and np.array_equal(to_np(offsets), ro)
 
 
+@pytest.mark.parametrize("T,E,k,renorm", [(1, 1024, 4, 1), (31, 128, 8, 0), (32, 6, 3, 1), (32, 1024, 64, 1), (33, 128, 8, 1)])
+def test_one_workgroup_writes_the_offsets_itself(L, T, E, k, renorm):
+    """32 tokens and fewer, 4096 given pairs and fewer: no second launch for counts and offsets."""
+    z = _route_logits(T, E, "normal", seed=T * E)
+    idx, w, counts, offsets = L.moe_route_topk(to_dev(z), k, renorm)
+    ridx, rw, rcounts, roffsets = O.route_topk(z, k, renorm)
+    assert np.array_equal(to_np(idx), ridx) and np.array_equal(to_np(counts), rcounts) and np.array_equal(to_np(offsets), roffsets)
+    assert_close(to_np(w), rw, "f32", "topk_w")
+    for n in (4096, 4097):
+        pairs = np.random.default_rng(n).integers(0, E, size=n).astype(np.int32)
+        counts, offsets = L.moe_expert_offsets(to_dev(pairs), E)
+        rc, ro = O.counts_offsets(pairs, E)
+        assert np.array_equal(to_np(counts), rc) and np.array_equal(to_np(offsets), ro)
+
+
 # --------------------------------------------------------------------------------- permute
 
 @pytest.mark.parametrize("T,d,E,k,dt", [(256, 128, 8, 2, "f32"), (1000, 512, 128, 8, "bf16"), (777, 264, 16, 2, "bf16"),
