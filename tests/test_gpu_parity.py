@@ -105,9 +105,17 @@ def test_expert_offsets(L):
         assert np.array_equal(to_np(counts), rc) and np.array_equal(to_np(offsets), ro)
 
 
-@pytest.mark.parametrize("T,E,k,renorm", [(1, 1024, 4, 1), (31, 128, 8, 0), (32, 6, 3, 1), (32, 1024, 64, 1), (33, 128, 8, 1)])
+@pytest.mark.parametrize("E,k", [(1, 1), (16, 16), (17, 17), (17, 5), (32, 16), (33, 2), (64, 8), (65, 16), (128, 16), (128, 17), (129, 8)])
+@pytest.mark.parametrize("T,renorm,kind", [(3, 1, "normal"), (67, 0, "ties"), (1029, 1, "equal")])
+def test_route_topk_of_a_row_of_lanes(L, T, renorm, kind, E, k):
+    """A token per row of 16 lanes up to 128 experts and 16 selected, per wave beyond: logits per lane, ties, a last partial wave."""
+    test_route_topk(L, T, E, k, renorm, kind)
+
+
+@pytest.mark.parametrize("T,E,k,renorm", [(1, 1024, 4, 1), (32, 1024, 64, 1), (33, 300, 8, 1), (31, 128, 8, 0), (64, 6, 3, 1),
+                                          (65, 128, 8, 1)])
 def test_one_workgroup_writes_the_offsets_itself(L, T, E, k, renorm):
-    """32 tokens and fewer, 4096 given pairs and fewer: no second launch for counts and offsets."""
+    """32 tokens and fewer (64 up to 128 experts), 4096 given pairs and fewer: no second launch for counts and offsets."""
     z = _route_logits(T, E, "normal", seed=T * E)
     idx, w, counts, offsets = L.moe_route_topk(to_dev(z), k, renorm)
     ridx, rw, rcounts, roffsets = O.route_topk(z, k, renorm)
