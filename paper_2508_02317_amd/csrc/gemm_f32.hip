@@ -290,11 +290,16 @@ __device__ __forceinline__ void f32_wgrad_block(const F32Rows& R, const F32Wgrad
     return;
   }
   const int e = static_cast<int>(block / tiles - which * R.E), tile = static_cast<int>(block % tiles);
-  const int M = which == 0 ? p.d : p.f, N = which == 0 ? p.f : p.d, tiles_n = which == 0 ? p.tiles_f : p.tiles_d;
+  // The fields are read before one of them is chosen: chosen first, the whole struct is copied to scratch memory to have
+  // addresses to choose from (24 experts, d = 328, f = 208: a step of 95 us took 112).
+  const int d = p.d, f = p.f, tiles_d = p.tiles_d, tiles_f = p.tiles_f;
+  const float *const dy = p.dy, *const act = p.act, *const dG = p.dG, *const dU = p.dU, *const x = p.x;
+  float *const dw_down = p.dw_down, *const dw_gate = p.dw_gate, *const dw_up = p.dw_up;
+  const int M = which == 0 ? d : f, N = which == 0 ? f : d, tiles_n = which == 0 ? tiles_f : tiles_d;
   const int m0 = tile / tiles_n * kF32Tile, n0 = tile % tiles_n * kF32Tile;
   // both operands are strided: the fragments of a side hold its entries 2 i and 2 i + 1
-  const float* lhs = (which == 0 ? p.dy : which == 1 ? p.dG : p.dU) + min(m0 + 2 * (lane & 15), M - 2);
-  const float* rhs = (which == 0 ? p.act : p.x) + min(n0 + 2 * (lane & 15), N - 2);
+  const float* lhs = (which == 0 ? dy : which == 1 ? dG : dU) + min(m0 + 2 * (lane & 15), M - 2);
+  const float* rhs = (which == 0 ? act : x) + min(n0 + 2 * (lane & 15), N - 2);
   const int begin = min(max(R.offsets[e], 0), R.P), end = min(R.offsets[e + 1], R.P);
   F32Acc acc = f32_zero();
   for (int r0 = begin + wave * kF32Piece; r0 < end; r0 += kF32Batch * kF32Stride) {
@@ -318,7 +323,7 @@ __device__ __forceinline__ void f32_wgrad_block(const F32Rows& R, const F32Wgrad
   }
   const f32x4 v = f32_reduce<true, true>(acc, red, wave, lane);
   const int m = m0 + (threadIdx.x >> 3), n = n0 + 4 * (threadIdx.x & 7);
-  float* out = which == 0 ? p.dw_down : which == 1 ? p.dw_gate : p.dw_up;
+  float* out = which == 0 ? dw_down : which == 1 ? dw_gate : dw_up;
   if (m < M && n < N) store4(out + (static_cast<size_t>(e) * M + m) * N + n, v);
 }
 
