@@ -1369,7 +1369,8 @@ struct WgradArgs {
 // WHICH 0: dW_down, 1: [dW_gate; dW_up], 2: router (separate symbols so profiles tell them apart).
 // GATHER: the operand that holds one row per token -- lhs for WHICH 0 (the output gradient), rhs for WHICH 1
 // (the layer input) -- is the token-major matrix itself, and reduction row r reads its row row_token[r].
-template <int WHICH, class T, bool GATHER = false>
+// THROUGH_L2: result stores that stay in the L2 until the kernel ends (see launch_wgrad).
+template <int WHICH, class T, bool GATHER, bool THROUGH_L2>
 __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::kWavesPerSimd, T::kWavesPerSimd))) void wgrad_kernel(WgradArgs p) {
   static_assert(!GATHER || WHICH < 2, "the router's operands are token-major already");
   constexpr bool GA = GATHER && WHICH == 0, GB = GATHER && WHICH == 1;
@@ -1392,13 +1393,18 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   while (g < slow && (n_items * g < 8 * kXcds || slow % g != 0)) ++g;
   g = scalar(g);
   const int per_u = scalar(per_e / g);                  // g divides slow, so it divides per_e
-  // This workgroup's tiles: every gridDim.x-th of that order, the next one located while one is multiplied.
+  // This workgroup's tiles: every gridDim.x-th of that order, the next one located while one is multiplied.  The last round goes
+  // the other way round: where it is not full, the tiles left over go to the workgroups whose tiles were the shortest.
+  const int total = scalar(((n_items * g + kXcds - 1) / kXcds) * per_u * kXcds), grid = static_cast<int>(gridDim.x);
+  const int last = scalar(total > grid ? (total - 1) / grid * grid : total);
   struct At { int e, slot, begin, end, m0, n0, exists; };   // (`exists` is a number: see the row-grouped kernel)
   auto locate = [&](int& block) {
     At t{};
     for (;; block += gridDim.x) {
-      const int q = block / kXcds, u = scalar(q / per_u);
-      const int unit = u * kXcds + block % kXcds;
+      const int turned = block < last ? block : 2 * last + grid - kXcds - block + 2 * (block % kXcds);
+      const int at = block < last + grid ? turned : total;   // (there is no tile at `total` and beyond)
+      const int q = at / kXcds, u = scalar(q / per_u);
+      const int unit = u * kXcds + at % kXcds;
       t.exists = scalar(unit < n_items * g ? 1 : 0);
       if (unit >= n_items * g) return t;
       const int item = scalar(unit / g);
@@ -1504,7 +1510,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
             const int r = a_row + 16 * i + 8 * h + l3 - lo;
-            so.store(off_if(c < ncols && r >= 0, r * ld2 + c * 2u, StripRows::kNone), v[h]);
+            so.store_as<THROUGH_L2>(off_if(c < ncols && r >= 0, r * ld2 + c * 2u, StripRows::kNone), v[h]);
           }
         }
       }
@@ -1723,18 +1729,26 @@ static void launch_row(const RowArgs& p, int P, int E, hipStream_t s) {
   else launch_row_t<KIND, TileBig, FUSED, OPTION>(p, P, E, s);
 }
 
-template <int WHICH, bool GATHER = false>
-static void launch_wgrad(WgradArgs p, hipStream_t s) {
+template <int WHICH, bool GATHER, bool THROUGH_L2>
+static void launch_wgrad_as(WgradArgs p, hipStream_t s) {
   typedef TileBigW16 T;
   static LdsGrant grant;
-  if (!allow_lds(grant, reinterpret_cast<const void*>(&wgrad_kernel<WHICH, T, GATHER>), T::kLdsBytes, "wgrad")) return;
+  if (!allow_lds(grant, reinterpret_cast<const void*>(&wgrad_kernel<WHICH, T, GATHER, THROUGH_L2>), T::kLdsBytes, "wgrad")) return;
   p.tiles_m = ceil_div(p.M, T::BM);
   p.tiles_n = ceil_div(p.N, T::BN);
   // units are dealt to the XCDs in groups of 8, the last group may be partial: up to 8 more units than items
   const int max_items = WHICH == 2 ? p.one_segment_items : p.items.max_items;
   const unsigned grid = resident_grid(p.tiles_m * p.tiles_n * (max_items + kXcds), T::kBlocksPerCu);
-  MOE_LAUNCH(WHICH == 0 ? "wgrad_down" : WHICH == 1 ? "wgrad_gate_up" : "wgrad_router", (wgrad_kernel<WHICH, T, GATHER>), dim3(grid),
+  MOE_LAUNCH(WHICH == 0 ? "wgrad_down" : WHICH == 1 ? "wgrad_gate_up" : "wgrad_router", (wgrad_kernel<WHICH, T, GATHER, THROUGH_L2>), dim3(grid),
              dim3(T::kThreads), T::kLdsBytes, s, p);
+}
+// Result rows that are no whole number of lines go through the L2, where the pieces of a line meet: past it they reach memory one
+// by one, and the next tile waits for their acknowledgements (E = 128, 45 rows, d = 568, f = 1216: gate/up 209 -> 101 us, step 593
+// -> 530).  Whole lines go past it: through it 8 rows of d = 2048, f = 768 take 156 instead of 145 us, the step 774 instead of 701.
+template <int WHICH, bool GATHER = false>
+static void launch_wgrad(const WgradArgs& p, hipStream_t s) {
+  if (p.N * 2 % 128 != 0) launch_wgrad_as<WHICH, GATHER, true>(p, s);
+  else launch_wgrad_as<WHICH, GATHER, false>(p, s);
 }
 // the partial tiles of one weight gradient, or (b given) of both of the experts' in one launch behind the two products
 static void launch_wgrad_reduce(const char* name, const WgradArgs& a, const WgradArgs* b, hipStream_t s) {
