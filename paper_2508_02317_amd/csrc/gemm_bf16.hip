@@ -374,7 +374,7 @@ __device__ __forceinline__ void zero_acc(Acc<T>& acc) {
 // 32 x 32 x 16 one (256 CUs, operands in registers: 1974-2128 against 1713-1880 TFLOP/s; with the LDS reads of a
 // 128 x 64 sub-tile 1768-1851 against 1680-1694: in both the clock falls below its 2.4 GHz).
 //
-// What bounds the loop: a slab of the gate/up product at 2560 rows per expert takes 2.62 k clocks at 1.86 GHz = 1.41 us
+// What bounds the loop (stamps of a build with one tile per workgroup): a slab of the gate/up product at 2560 rows per expert takes 2.62 k clocks at 1.86 GHz = 1.41 us
 // (64 MFMAs per wave, two waves per SIMD: 2.05 k clocks).  The loads and barriers alone take 1.36 us (at 2.39 GHz), the
 // MFMAs and LDS reads alone 1.10 us (at 2.06 GHz): the row products run at the rate the slabs arrive, 64 KiB per CU.  The
 // weight gradients' loads alone take 1.12-1.21 us, their MFMAs and LDS reads 1.25 us, together 1.60 us at 1.70-1.76 GHz.
@@ -388,10 +388,15 @@ __device__ __forceinline__ void zero_acc(Acc<T>& acc) {
 //         wait: own LDS reads of slab kt complete, own loads of slab kt+1 landed (later slabs stay in flight)
 //         barrier: slab kt+1 is visible to all, and nobody reads the buffers of slab kt any more
 //         read b, a_0 .. a_R0-1 of S0 of slab kt+1
-//         rows R0 .. | read a_i of S0 of slab kt+1 | (spread) refill A of slab kt+SA
+//         refill A of slab kt+SA, at once
+//         rows R0 .. | read a_i of S0 of slab kt+1
 // LDS reads of a wave complete in order, so "fragment X has arrived" is a wait for all but the reads issued after it;
 // loads complete in the order they were enqueued, so "slab kt+1 has landed" is a wait for all but the loads enqueued
-// after it -- immediates, both: slabs beyond the end of the reduction are enqueued too (see Dma) and touch no memory.
+// after it -- immediates, both.
+// The rings do not drain between the tiles of a workgroup: behind the last slabs of a tile come the first of its next
+// one, or empty slabs if there is none.  With one tile per workgroup 5.4-6.8 k clocks passed from a workgroup's entry to its first
+// slab, and 3.4 us from the last store of a workgroup to the entry of the next: at T = 8192, E = 128, k = 8, d = 2048, f = 768 the
+// six products took 2111 us and take 1851.
 // The loop is a plain loop over one slab body with run-time ring positions, a single path: with a body chosen per slab
 // the compiler keeps fragments and accumulators in scratch memory.  The address registers of the fragments are
 // advanced once per slab (4 to 12 vector additions against 64 MFMAs).
@@ -642,8 +647,8 @@ struct MainLoop {
   // hold slabs of at most two tiles).
   static __device__ __forceinline__ int slabs_of(int K) { return (TWO_SEG ? 2 : 1) * ((K + T::BK - 1) / T::BK); }
   static __device__ __forceinline__ int slabs_run(int K) { return max(slabs_of(K), kAhead); }
-  // Point the loads at a tile's operands.  K = 0: there is no such tile, and its slabs are empty.  TWO_SEG: two segments of K indices each, columns 0 .. K-1 and K .. 2K-1 of the
-  // A side, opB and then opB2.
+  // Point the loads at a tile's operands.  K = 0: there is no such tile, and its slabs are empty.  TWO_SEG: two segments of K
+  // indices each, columns 0 .. K-1 and K .. 2K-1 of the A side, opB and then opB2.
   __device__ __forceinline__ void load_tile(const Operand& opA, const Operand& opB, const bf16_t* b2, int K) {
     const int lane = not_before_here(threadIdx.x & 63), n = slabs_of(K);
     da.init(opA, K, n, wave, lane);
@@ -1394,7 +1399,8 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   g = scalar(g);
   const int per_u = scalar(per_e / g);                  // g divides slow, so it divides per_e
   // This workgroup's tiles: every gridDim.x-th of that order, the next one located while one is multiplied.  The last round goes
-  // the other way round: where it is not full, the tiles left over go to the workgroups whose tiles were the shortest.
+  // the other way round: where it is not full, the tiles left over go to the workgroups whose tiles were the shortest (4096
+  // skewed rows on 16 experts: 51 -> 48 and 64 -> 61 us; 16384 rows: dW_down 70 -> 66 us; full rounds: equal).
   const int total = scalar(((n_items * g + kXcds - 1) / kXcds) * per_u * kXcds), grid = static_cast<int>(gridDim.x);
   const int last = scalar(total > grid ? (total - 1) / grid * grid : total);
   struct At { int e, slot, begin, end, m0, n0, exists; };   // (`exists` is a number: see the row-grouped kernel)
