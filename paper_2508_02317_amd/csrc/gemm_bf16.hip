@@ -78,6 +78,12 @@ __device__ __forceinline__ int not_before_here(int v) { asm volatile("" : "+v"(v
 // A wave-uniform value in a scalar register (integer divisions and clamps are done on the vector unit, and everything derived
 // from their results would stay there).
 __device__ __forceinline__ int scalar(int v) { return __builtin_amdgcn_readfirstlane(not_before_here(v)); }
+// This lane of the wave, worked out where it is wanted: threadIdx.x kept for it would occupy a register during the main loop.
+__device__ __forceinline__ int lane_id() {
+  unsigned all = ~0u;
+  asm volatile("" : "+s"(all));
+  return static_cast<int>(__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u)));
+}
 // min of two wave-uniform values, as a scalar instruction (a minimum and a maximum in a row would become one vector instruction)
 __device__ __forceinline__ int scalar_min(int a, int b) {
   int v = min(a, b);
@@ -1250,8 +1256,8 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
 // run, unlike atomic accumulation.  Items are ordered by descending expert size so the long ones start first.
 // ============================================================================================
 struct WgradItems {
-  int32_t* count;        // [2]: number of items, number of split experts
-  int32_t* expert;       // [max_items]
+  int32_t* count;        // [5]: number of items, of split experts and of experts without rows; the next piece of zeros of each product
+  int32_t* expert;       // [max_items]; the experts without rows follow those of the items
   int32_t* k0;           // [max_items] first row of the chunk
   int32_t* k1;           // [max_items] one past its last row
   int32_t* slot;         // [max_items] partial-tile slot, or -1: write the result directly
@@ -1316,9 +1322,20 @@ __device__ __forceinline__ void build_wgrad_items(const int32_t* __restrict__ of
       it.split_n[sidx] = my_n;
     }
   }
+  // An expert without rows has no item: a tile of zeros would run two empty slabs and hold up the rings of a workgroup that
+  // has rows to multiply.  They are the last ones of the order; workgroups store their zeros behind their last tile (pre-routed
+  // steps of 32 experts, most of them empty: 144 rows, d = 512, f = 704 107 -> 100 us, 1500 rows, d = 1024, f = 1408 230 -> 214).
+  if (e < E && my_c == 0 && (e == 0 || cnt[order[e - 1]] > 0)) {
+    it.count[0] = min(scan_items[e] - 1, it.max_items);
+    it.count[2] = min(E - e, it.max_items - it.count[0]);
+  }
+  if (e == E - 1 && my_c > 0) {
+    it.count[0] = min(scan_items[e], it.max_items);
+    it.count[2] = 0;
+  }
   if (e == 1023) {
-    it.count[0] = min(scan_items[1023], it.max_items);
     it.count[1] = min(scan_split[1023], it.max_split);
+    it.count[3] = it.count[4] = 0;
   }
 }
 
@@ -1432,11 +1449,55 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
       return t;
     }
   };
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // The zeros of the experts without rows, 128 KiB at a time.  Workgroups without a tile store them while the others multiply, if
+  // at least half of those launched have none; else whoever has no tile left takes the next piece, by a counter: a fixed share
+  // for each leaves the workgroups of the longest experts theirs (1500 rows: the two products 83 us, by the counter 74).  With few
+  // tiles the counter's round trip to memory is what a workgroup with a tile ends on (144 rows: 25 us, without it 22).
+  auto store_zeros = [&] {
+    if constexpr (!ONE_SEGMENT) {
+      constexpr int kPer = 8, kPieces = kPer * T::kThreads;                   // 16-byte pieces
+      int M = p.M, N = p.N;
+      int32_t* count = p.items.count;
+      asm volatile("" : "+s"(M), "+s"(N), "+s"(count));  // (nothing of this is worked out ahead of the tiles and kept)
+      const long of_out0 = static_cast<long>(p.m_split) * N / 8, of_expert = static_cast<long>(M) * N / 8;
+      const int per_e = static_cast<int>((of_expert + kPieces - 1) / kPieces), n = const_list(count)[2] * per_e;
+      const int idle = max(grid - total, 0);
+      const bool only_idle = 2 * idle >= grid;
+      int c = static_cast<int>(blockIdx.x) - total, next = 0;
+      if (n == 0 || (only_idle && c < 0)) return;
+      const int tid = wave * 64 + lane_id();
+      int32_t* const word = reinterpret_cast<int32_t*>(lds);
+      __syncthreads();                                  // (the rings are done with)
+      while (c < n) {
+        if (!only_idle && tid == 0) next = idle + atomicAdd(count + 3 + WHICH, 1);
+        if (c >= 0) {
+          const int j = scalar(c / per_e);
+          const long e = const_list(p.items.expert)[n_items + j], first = static_cast<long>(c - j * per_e) * kPieces;
+#pragma unroll
+          for (int q = 0; q < kPer; ++q) {
+            const long i = first + q * T::kThreads + tid;
+            if (i < of_expert) store16(i < of_out0 ? p.out0 + (e * of_out0 + i) * 8 : p.out1 + (e * (of_expert - of_out0) + i - of_out0) * 8, u32x4{0, 0, 0, 0});
+          }
+        }
+        c += idle;
+        if (!only_idle) {
+          if (tid == 0) *word = next;
+          __syncthreads();
+          c = scalar(*word);
+          __syncthreads();
+        }
+      }
+    }
+  };
   int block = blockIdx.x;
   At cur = locate(block);
-  if (cur.exists == 0) return;
+  if (cur.exists == 0) {
+    store_zeros();
+    return;
+  }
 
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
   const int wm = wave / T::WGN, wn = wave % T::WGN;
   const int a_row = wm * WM, b_row = wn * WN;
   Loop ml;
@@ -1525,6 +1586,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
     cur = nxt;
   }
   Loop::finish();
+  store_zeros();
 }
 
 // out[e] = bf16( sum over the chunks of a split expert, in chunk order, of its fp32 partial tiles ), for one weight gradient
