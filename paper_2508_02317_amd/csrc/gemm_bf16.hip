@@ -849,6 +849,9 @@ struct StripRows {
   __device__ __forceinline__ void store_byte(uint32_t off, uint32_t v) const {
     __builtin_amdgcn_raw_buffer_store_b8(static_cast<uint8_t>(v), rsrc, static_cast<int>(off), 0, 0);
   }
+  __device__ __forceinline__ float load_float(uint32_t off) const {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, static_cast<int>(off), 0, 0));
+  }
   __device__ __forceinline__ u32x4 load(uint32_t off) const { return __builtin_amdgcn_raw_buffer_load_b128(rsrc, static_cast<int>(off), 0, 0); }
 };
 
@@ -1039,9 +1042,9 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
     // from splits the paths behind the main loop by its value and spills the accumulators on them)
     const int mi_n = scalar(min(MI, max(0, (rows - a_row + 31) / 32)));
     // the combine weights of the wave's rows: lane l holds those of rows l, l + 64, ...
-    constexpr int NW = (KIND == kGateUp || KIND == kDAct) ? (WM + 63) / 64 : 1;
+    constexpr int NW = KIND == kGateUp ? (WM + 63) / 64 : 1;
     float row_w[NW];
-    if constexpr (KIND == kGateUp || (KIND == kDAct && FUSED)) {
+    if constexpr (KIND == kGateUp) {
 #pragma unroll
       for (int c = 0; c < NW; ++c) {
         const int r = a_row + c * 64 + lane;
@@ -1117,13 +1120,16 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
         }
       }
     } else if constexpr (KIND == kDAct) {
-      // The saved G and U of 16 rows are requested 16 rows ahead (the fragment registers are free now).  This epilogue is
+      // The saved G and U of 16 rows are requested 16 rows ahead (the fragment registers are free now), and with them the rows'
+      // combine weights: held across the slab loop, those made the 256 x 256 tile reload registers from scratch memory for every
+      // tile (4096 tokens on 16 experts 81 -> 80 us, 8192 on 128 270 -> 268, 1531 107 -> 105).  This epilogue is
       // bound by the vector unit: 128 derivatives per lane, about 25 issue slots each, two waves per SIMD; it takes 24k of
       // the 111k clocks of a tile (2560 rows per expert).
       const StripF32 strip(scratch, el);
       const uint32_t n2 = static_cast<uint32_t>(p.N) * 2u;
       const uint32_t off = off8(ld2), goff = off8(n2);
       u32x4 gq[2][2], uq[2][2];                        // [fragment & 1][rows 0..7, 8..15]
+      float wq[2][2];
       auto request = [&](int i) {
         const int rs0 = a_row + i * 16;
         const long gi = static_cast<long>(row0 + rs0) * p.N + n0;
@@ -1135,16 +1141,20 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
           gq[i & 1][c] = sg.load(goff + 8 * c * n2);
           uq[i & 1][c] = su.load(goff + 8 * c * n2);
         }
+        if constexpr (FUSED) {
+          StripRows sw;
+          sw.at(p.row_w + row0 + rs0, rows - rs0, 4, 0);
+#pragma unroll
+          for (int c = 0; c < 2; ++c) wq[i & 1][c] = sw.load_float((8 * c + rl) * 4u);
+        }
       };
       request(0);
 #pragma unroll
       for (int mi = 0; mi < MI; ++mi) {
         if (mi >= mi_n) break;
         const int rs0 = a_row + mi * 32;
-        StripRows sdg, sdu, saw, sdw;
-        const long o = static_cast<long>(row0 + rs0) * p.ldo + n0;
-        sdg.at(p.out0 + o, rows - rs0, ld2, skip2);
-        sdu.at(p.out0 + o + p.N, rows - rs0, ld2, skip2 + n2);
+        StripRows sd, saw, sdw;                          // (a row of [dG | dU] is one: dU lies n2 bytes further in it)
+        sd.at(p.out0 + static_cast<long>(row0 + rs0) * p.ldo + n0, rows - rs0, ld2, skip2);
         if constexpr (FUSED) {
           if constexpr (OPTION) saw.at(p.act_w + (static_cast<long>(row0 + rs0) * p.N + n0), rows - rs0, n2, skip2);
           sdw.at(p.dw_partial + static_cast<long>(n0 / BN * T::WGN + wn) * p.P + row0 + rs0, min(rows - rs0, 32), 4, 0);
@@ -1166,7 +1176,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
             // silu'(g) = sg (1 + g (1 - sg)) = sg + t (1 - sg) with t = g sg = silu(g); 1 - sg is formed first: where it is zero
             // the result is sg however large t is (sg + t - t sg would lose sg)
             if constexpr (FUSED) {
-              const float w = weight_of(i * 16 + 8 * c + rl);
+              const float w = wq[i & 1][c];
               float part = 0.0f, act[8];
 #pragma unroll
               for (int q = 0; q < 8; ++q) {
@@ -1176,8 +1186,8 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
                 dg[q] = (da * u[q]) * fmaf(t, 1.0f - sg, sg);
                 du[q] = da * t;
               }
-              sdg.store(off + down * ld2, pack8(dg));
-              sdu.store(off + down * ld2, pack8(du));
+              sd.store(off + down * ld2, pack8(dg));
+              sd.store(off + down * ld2 + n2, pack8(du));
               if constexpr (OPTION) {
 #pragma unroll
                 for (int q = 0; q < 8; ++q) act[q] *= w;
@@ -1194,8 +1204,8 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
                 dg[q] = (v[c][q] * u[q]) * fmaf(t, 1.0f - sg, sg);
                 du[q] = v[c][q] * t;
               }
-              sdg.store(off + down * ld2, pack8(dg));
-              sdu.store(off + down * ld2, pack8(du));
+              sd.store(off + down * ld2, pack8(dg));
+              sd.store(off + down * ld2 + n2, pack8(du));
             }
           }
         }

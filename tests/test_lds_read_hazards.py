@@ -104,27 +104,49 @@ def test_scanner_sees_a_planted_hazard():
     assert len(scan_kernel(word + ["\ts_waitcnt vmcnt(3)", "\tv_lshrrev_b32_e32 v8, v9, v7"])) == 1
 
 
-def test_no_instruction_touches_a_pending_lds_read(tmp_path):
+@pytest.fixture(scope="module")
+def assembly(tmp_path_factory):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):
         pytest.skip("hipcc not available")
     from paper_2508_02317_amd.build import HIPCC_FLAGS
-    out = str(tmp_path / "gemm_bf16.s")
+    out = str(tmp_path_factory.mktemp("asm") / "gemm_bf16.s")
     flags = [f for f in HIPCC_FLAGS if f != "-fPIC"]
     res = subprocess.run([hipcc, *flags, "--cuda-device-only", "-S", os.path.join(CSRC, "gemm_bf16.hip"), "-o", out],
                          capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-2000:]
-    text = open(out).read()
-    kernels = re.split(r"\n(?=_ZN3moe[^\n]*:\s*;\s*@)", text)
+    return open(out).read()
+
+
+def _is_product(name):
+    return any(k in name for k in ("row_grouped_kernel", "wgrad_kernel", "mx8_row_kernel"))
+
+
+def test_no_instruction_touches_a_pending_lds_read(assembly):
+    kernels = re.split(r"\n(?=_ZN3moe[^\n]*:\s*;\s*@)", assembly)
     checked = 0
     for k in kernels:
         name = k.split(":")[0]
-        if "row_grouped_kernel" not in name and "wgrad_kernel" not in name and "mx8_row_kernel" not in name:
+        if not _is_product(name):
             continue
         lines = k.split("\n")
         n_reads = sum(1 for l in lines if re.match(r"\s*ds_read_b(?:64_tr_b16|128) ", l))
         assert n_reads > 0, name
         bad = scan_kernel(lines)
         assert not bad, "%s: %s" % (name, bad[:5])
+        checked += 1
+    assert checked >= 13
+
+
+def test_products_keep_nothing_in_scratch_memory(assembly):
+    """Accumulators, fragments and addresses fill the register file; a value that does not fit is reloaded for every tile or slab,
+    behind a wait for all outstanding loads, which drains the rings."""
+    checked = 0
+    for k in re.split(r"\n  - ", assembly[assembly.index("amdhsa.kernels"):]):
+        name = re.search(r"\.name:\s*(\S+)", k)
+        if name is None or not _is_product(name[1]):
+            continue
+        for field in ("private_segment_fixed_size", "vgpr_spill_count"):
+            assert int(re.search(r"\.%s:\s*(\d+)" % field, k)[1]) == 0, (field, name[1])
         checked += 1
     assert checked >= 13
