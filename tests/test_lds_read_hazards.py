@@ -150,3 +150,14 @@ def test_products_keep_nothing_in_scratch_memory(assembly):
             assert int(re.search(r"\.%s:\s*(\d+)" % field, k)[1]) == 0, (field, name[1])
         checked += 1
     assert checked >= 13
+
+
+def test_much_8_bit_activation_is_stored_through_the_l2(assembly):
+    """A wave stores 32 bytes of a line of activation codes: with non-temporal stores each piece is a write to memory of its own.  The
+    variants for many codes must not have them (the last template argument), the others do."""
+    kernels = [k for k in re.split(r"\n(?=_ZN3moe[^\n]*:\s*;\s*@)", assembly) if re.match(r"\S*mx8_row_kernelILi0E", k)]
+    assert len(kernels) == 4
+    for k in kernels:
+        stores = re.findall(r"buffer_store_dwordx4 [^\n]*", k)
+        through_l2 = re.match(r"\S*mx8_row_kernelILi0E\S*Lb1EEEvNS", k) is not None
+        assert stores and all((re.search(r"\bnt\b", st) is None) == through_l2 for st in stores), k.split(":")[0]
