@@ -826,13 +826,15 @@ __device__ __forceinline__ void store16(void* p, const u32x4& v) { __builtin_non
 
 // A few rows (of a strip or a tile) of a row-major matrix as a buffer: a load of a row or column that does not exist returns
 // zeros and a store to it does nothing, so the epilogues need no branches and no 64-bit address arithmetic per access.
-//   first: the first row at the tile's first column (uniform); rows: how many rows exist (any integer up to 256);
+//   first: the first row at the tile's first column (uniform); rows: how many rows exist (any integer);
 //   pitch: bytes per row; skip: bytes between the start of a row and the tile's first column
+// Ranges and offsets have 32 bits, so a buffer spans no more rows than one wave takes: MAX = 32, and rows of up to 64 MiB lie
+// below kNone; MAX = 64 (weight gradients), and rows below 64 MiB lie below kOffNone.
 struct StripRows {
   __amdgpu_buffer_rsrc_t rsrc;
-  static constexpr uint32_t kNone = 0x80000000u;       // offset of a column that does not exist (a strip is shorter than 2 GiB)
-  __device__ __forceinline__ void at(const void* first, int rows, uint32_t pitch, uint32_t skip) {
-    int n = scalar(min(rows, 256));
+  static constexpr uint32_t kNone = 0x80000000u;       // offset of a column that does not exist (to which rows may be added)
+  template <int MAX = 32> __device__ __forceinline__ void at(const void* first, int rows, uint32_t pitch, uint32_t skip) {
+    int n = scalar(min(rows, MAX));
     n = max(n, 0);
     const uint32_t range = n > 0 ? static_cast<uint32_t>(n) * pitch - skip : 0u;
     rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(first), 0, static_cast<int>(range), 0x00020000);
@@ -1551,7 +1553,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
       const uint32_t ld4 = static_cast<uint32_t>(p.N) * 4u;
       const uint32_t at_w = scratch + (el & 15) * 128 + (((el >> 4) ^ (el & 7)) << 4), at_r = scratch + l3 * 128 + ((l7 ^ l3) << 4);
       StripRows so;
-      so.at(p.partial + (static_cast<long>(cur.slot) * p.M + cur.m0) * p.N + cur.n0, mrows, ld4, skip * 4u);
+      so.at<WM>(p.partial + (static_cast<long>(cur.slot) * p.M + cur.m0 + a_row) * p.N + cur.n0, mrows - a_row, ld4, skip * 4u);
 #pragma unroll
       for (int i = 0; i < T::FM; ++i)
 #pragma unroll
@@ -1562,7 +1564,7 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
           lds_fetch(at_r, at_r + 1024, v[0], v[1]);
           const int c = b_row + 32 * q + 4 * l7;
 #pragma unroll
-          for (int h = 0; h < 2; ++h) so.store(off_if(c < ncols, (a_row + 16 * i + 8 * h + l3) * ld4 + c * 4u, StripRows::kNone), v[h]);
+          for (int h = 0; h < 2; ++h) so.store(off_if(c < ncols, (16 * i + 8 * h + l3) * ld4 + c * 4u, kOffNone), v[h]);
         }
     } else {                                           // whole expert: rounded once
       const uint32_t ld2 = static_cast<uint32_t>(p.N) * 2u;
@@ -1574,10 +1576,11 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
       for (int half = 0; half < 2; ++half) {
         const int lo = half == 0 ? 0 : below, hi = half == 0 ? below : mrows;
         if (lo >= hi) continue;
-        bf16_t* out = half == 0 ? p.out0 + (static_cast<long>(cur.e) * p.m_split + cur.m0) * p.N
-                                : p.out1 + (static_cast<long>(cur.e) * (p.M - p.m_split) + (cur.m0 + lo - p.m_split)) * p.N;
+        const int first = max(lo, a_row);                // of this wave's rows
+        bf16_t* out = half == 0 ? p.out0 + (static_cast<long>(cur.e) * p.m_split + cur.m0 + first) * p.N
+                                : p.out1 + (static_cast<long>(cur.e) * (p.M - p.m_split) + (cur.m0 + first - p.m_split)) * p.N;
         StripRows so;
-        so.at(out + cur.n0, hi - lo, ld2, skip * 2u);
+        so.at<WM>(out + cur.n0, min(hi, a_row + WM) - first, ld2, skip * 2u);
 #pragma unroll
         for (int i = 0; i < T::FM; ++i) {
 #pragma unroll
@@ -1586,8 +1589,8 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
           strip.fetch(v[0], v[1]);
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
-            const int r = a_row + 16 * i + 8 * h + l3 - lo;
-            so.store_as<THROUGH_L2>(off_if(c < ncols && r >= 0, r * ld2 + c * 2u, StripRows::kNone), v[h]);
+            const int r = a_row + 16 * i + 8 * h + l3 - first;
+            so.store_as<THROUGH_L2>(off_if(c < ncols && r >= 0, r * ld2 + c * 2u, kOffNone), v[h]);
           }
         }
       }
