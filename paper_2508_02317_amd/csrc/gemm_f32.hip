@@ -13,6 +13,7 @@
 // At 512 rows, d = 128, f = 256, 8 experts the former one-thread-per-output kernels with sequential sums took 130 (gate/up),
 // 39 (down), 18 (dA), 74 (dX) and 3 x 37 us (weight gradients), with two and three further launches per pass; these take
 // 8.5, 5.8, 6.4, 9.3 and 10 us (all three weight gradients), and the training step of 256 tokens 72 us instead of 396.
+#include "launch_plan.h"
 #include "moe_common.h"
 
 namespace moe {
@@ -364,8 +365,16 @@ static F32Dx f32_dx(const F32Rows& R, const float* dG, const float* dU, const vo
 static void f32_dx_wgrad(const F32Dx& x, const F32Rows& R, F32Wgrad w, hipStream_t s) {
   w.tiles_d = ceil_div(w.d, kF32Tile); w.tiles_f = ceil_div(w.f, kF32Tile);
   const unsigned dx_blocks = R.P > 0 ? row_grid(x.rows, x.n_tiles) : 0u;
-  const size_t grid = dx_blocks + 3 * static_cast<size_t>(w.tiles_d) * w.tiles_f * R.E + (w.dw_partial ? blocks_for(R.P) : 0);
-  MOE_LAUNCH("f32_dx_wgrad", f32_dx_wgrad_kernel, dim3(static_cast<unsigned>(grid)), dim3(kF32Threads), 0, s, x, dx_blocks, R, w);
+  const size_t wgrad_blocks = 3 * static_cast<size_t>(w.tiles_d) * w.tiles_f * R.E + (w.dw_partial ? blocks_for(R.P) : 0);
+  auto launch = [&](size_t dx, size_t wgrad) {
+    MOE_LAUNCH("f32_dx_wgrad", f32_dx_wgrad_kernel, dim3(static_cast<unsigned>(dx + wgrad)), dim3(kF32Threads), 0, s, x, static_cast<unsigned>(dx), R, w);
+  };
+  if (fits_one_launch(dx_blocks + wgrad_blocks, kF32Threads)) {
+    launch(dx_blocks, wgrad_blocks);
+  } else {                                             // together they are too many (half a billion rows)
+    launch(dx_blocks, 0);
+    launch(0, wgrad_blocks);
+  }
 }
 
 size_t ffn_fwd_ws_bytes_f32(int, int, int, int) { return 256; }
