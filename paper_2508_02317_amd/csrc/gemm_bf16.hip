@@ -35,6 +35,7 @@
 #include <mutex>
 #include <type_traits>
 #include <utility>
+#include "launch_plan.h"
 #include "moe_common.h"
 
 namespace moe {
@@ -45,8 +46,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-constexpr int kXcds = 8;
 
 // ---- tile shapes ------------------------------------------------------------------------------
 template <int BM_, int BN_, int BK_, int WGM_, int WGN_, int STAGES_A_, int STAGES_B_>
@@ -909,13 +908,6 @@ __global__ __launch_bounds__(1024) void build_row_tiles_kernel(const int32_t* __
 typedef __attribute__((address_space(4))) const int32_t* ConstList;
 __device__ __forceinline__ ConstList const_list(const int32_t* p) { return reinterpret_cast<ConstList>(reinterpret_cast<uintptr_t>(p)); }
 
-// workgroup id -> virtual tile id such that consecutive virtual ids share an XCD
-__device__ __forceinline__ int xcd_remap(int b, int total) {
-  const int per = (total + kXcds - 1) / kXcds;
-  const int v = (b % kXcds) * per + b / kXcds;
-  return (b / kXcds < per && v < total) ? v : -1;
-}
-
 // ============================================================================================
 // Row-grouped kernels
 // ============================================================================================
@@ -1412,38 +1404,22 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
   constexpr int BM = T::BM, BN = T::BN, WM = T::WM, WN = T::WN, FN = T::FN;
   static_assert(FN == 4, "the epilogue takes the fragments of a row in two pairs");
   typedef MainLoop<T, true, true, GA, GB> Loop;
-  const int per_e = p.tiles_m * p.tiles_n;
   constexpr bool ONE_SEGMENT = WHICH == 2;              // the router's: one segment of all rows, its chunks follow from their number
   const int n_items = ONE_SEGMENT ? p.one_segment_items : const_list(p.items.count)[0];
   // order of a work item's tiles: row tile fastest for [dW_gate; dW_up] (neighbouring workgroups share the rhs panel;
   // measured 6 % faster at 512 rows per expert), column tile fastest for the others
   constexpr bool MT_FASTEST = WHICH == 1;
-  // Work items come sorted by length, so consecutive stretches of the list differ in work: they are dealt to the
-  // XCDs (workgroup b runs on XCD b % 8) in turn, in units of 1/g of an item's tiles -- whole items while there
-  // are at least 8 per XCD, otherwise g runs of the slow tile index, so that under skewed routing every XCD still
-  // gets several units of the few long items.  A unit's workgroups are consecutive on their XCD (shared panels).
-  const int slow = MT_FASTEST ? p.tiles_n : p.tiles_m;
-  int g = 1;
-  while (g < slow && (n_items * g < 8 * kXcds || slow % g != 0)) ++g;
-  g = scalar(g);
-  const int per_u = scalar(per_e / g);                  // g divides slow, so it divides per_e
-  // This workgroup's tiles: every gridDim.x-th of that order, the next one located while one is multiplied.  The last round goes
-  // the other way round: where it is not full, the tiles left over go to the workgroups whose tiles were the shortest (4096
-  // skewed rows on 16 experts: 51 -> 48 and 64 -> 61 us; 16384 rows: dW_down 70 -> 66 us; full rounds: equal).
-  const int total = scalar(((n_items * g + kXcds - 1) / kXcds) * per_u * kXcds), grid = static_cast<int>(gridDim.x);
-  const int last = scalar(total > grid ? (total - 1) / grid * grid : total);
+  auto sc = [](int v) { return scalar(v); };
+  const WgradWalk walk = wgrad_walk(n_items, MT_FASTEST ? p.tiles_n : p.tiles_m, p.tiles_m * p.tiles_n, static_cast<int>(gridDim.x), sc);
+  // This workgroup's tiles, the next one located while one is multiplied
   struct At { int e, slot, begin, end, m0, n0, exists; };   // (`exists` is a number: see the row-grouped kernel)
   auto locate = [&](int& block) {
     At t{};
     for (;; block += gridDim.x) {
-      const int turned = block < last ? block : 2 * last + grid - kXcds - block + 2 * (block % kXcds);
-      const int at = block < last + grid ? turned : total;   // (there is no tile at `total` and beyond)
-      const int q = at / kXcds, u = scalar(q / per_u);
-      const int unit = u * kXcds + at % kXcds;
-      t.exists = scalar(unit < n_items * g ? 1 : 0);
-      if (unit >= n_items * g) return t;
-      const int item = scalar(unit / g);
-      const int vi = (unit - item * g) * per_u + (q - u * per_u);      // position among the item's tiles
+      const WgradTile at = wgrad_tile(walk, block, sc);
+      t.exists = scalar(at.exists ? 1 : 0);
+      if (!at.exists) return t;
+      const int item = at.item, vi = at.tile;
       const int fast = MT_FASTEST ? p.tiles_m : p.tiles_n, slow_i = scalar(vi / fast), fast_i = vi - slow_i * fast;
       t.m0 = (MT_FASTEST ? fast_i : slow_i) * BM;
       t.n0 = (MT_FASTEST ? slow_i : fast_i) * BN;
@@ -1474,9 +1450,9 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
       asm volatile("" : "+s"(M), "+s"(N), "+s"(count));  // (nothing of this is worked out ahead of the tiles and kept)
       const long of_out0 = static_cast<long>(p.m_split) * N / 8, of_expert = static_cast<long>(M) * N / 8;
       const int per_e = static_cast<int>((of_expert + kPieces - 1) / kPieces), n = const_list(count)[2] * per_e;
-      const int idle = max(grid - total, 0);
-      const bool only_idle = 2 * idle >= grid;
-      int c = static_cast<int>(blockIdx.x) - total, next = 0;
+      const int idle = max(walk.grid - walk.total, 0);
+      const bool only_idle = 2 * idle >= walk.grid;
+      int c = static_cast<int>(blockIdx.x) - walk.total, next = 0;
       if (n == 0 || (only_idle && c < 0)) return;
       const int tid = wave * 64 + lane_id();
       int32_t* const word = reinterpret_cast<int32_t*>(lds);

@@ -9,4 +9,47 @@ namespace moe {
 // A launch has at most 2^32 - 1 threads.
 constexpr bool fits_one_launch(size_t blocks, int threads) { return blocks <= 0xFFFFFFFFu / static_cast<unsigned>(threads); }
 
+constexpr int kXcds = 8;                               // workgroup b runs on XCD b % 8
+
+// workgroup id -> virtual tile id such that consecutive virtual ids share an XCD; -1: none
+constexpr int xcd_remap(int b, int total) {
+  const int per = (total + kXcds - 1) / kXcds;
+  const int v = (b % kXcds) * per + b / kXcds;
+  return (b / kXcds < per && v < total) ? v : -1;
+}
+
+// The weight gradients' tiles.  Work items come sorted by length, so consecutive stretches of the list differ in work: they are
+// dealt to the XCDs in turn, in units of 1/g of an item's tiles -- whole items while there are at least 8 per XCD, otherwise g runs
+// of the slow tile index, so that under skewed routing every XCD still gets several units of the few long items.  A unit's
+// workgroups are consecutive on their XCD (shared panels).
+// A workgroup takes every `grid`-th position of that order.  The last round goes the other way round: where it is not full, the
+// tiles left over go to the workgroups whose tiles were the shortest (4096 skewed rows on 16 experts: 51 -> 48 and 64 -> 61 us;
+// 16384 rows: dW_down 70 -> 66 us; full rounds: equal).
+struct WgradWalk {
+  int units, g, per_u;                                 // units in all; units and their tiles of an item
+  int total, grid, last;                               // positions, workgroups (a multiple of 8), first position of the last round
+};
+struct WgradTile { int item, tile; bool exists; };     // tile: position among the item's tiles
+
+// scalar: the kernel's way of saying that a value is the same in every lane
+template <class Scalar> constexpr WgradWalk wgrad_walk(int n_items, int slow, int tiles, int grid, Scalar scalar) {
+  int g = 1;
+  while (g < slow && (n_items * g < 8 * kXcds || slow % g != 0)) ++g;
+  g = scalar(g);
+  const int per_u = scalar(tiles / g);                 // g divides slow, so it divides tiles
+  const int total = scalar(((n_items * g + kXcds - 1) / kXcds) * per_u * kXcds);
+  const int last = scalar(total > grid ? (total - 1) / grid * grid : total);
+  return WgradWalk{n_items * g, g, per_u, total, grid, last};
+}
+// the tile at position `block` (any number >= 0: a workgroup's id plus multiples of the grid)
+template <class Scalar> constexpr WgradTile wgrad_tile(const WgradWalk& w, int block, Scalar scalar) {
+  const int turned = block < w.last ? block : 2 * w.last + w.grid - kXcds - block + 2 * (block % kXcds);
+  const int at = block < w.last + w.grid ? turned : w.total;   // (there is no tile at `total` and beyond)
+  const int q = at / kXcds, u = scalar(q / w.per_u);
+  const int unit = u * kXcds + at % kXcds;
+  if (unit >= w.units) return WgradTile{0, 0, false};
+  const int item = scalar(unit / w.g);
+  return WgradTile{item, (unit - item * w.g) * w.per_u + (q - u * w.per_u), true};
+}
+
 }  // namespace moe

@@ -31,3 +31,60 @@ def test_a_launch_has_fewer_than_2_to_the_32_threads(tmp_path):
                       fits_one_launch(16777215, 256) && !fits_one_launch(16777216, 256) && fits_one_launch(4194303, 1024) && !fits_one_launch(4194304, 1024);
       return ok ? 0 : 1;
     }""")
+
+
+def test_every_tile_of_the_weight_gradients_is_taken_once(tmp_path):
+    """Workgroups walk the tiles of sorted work items in rounds, the last one from its other end: over lists of any length, tiles per
+    item and grids (fewer workgroups than positions, as many, and more), every (item, tile) comes up exactly once, in range, and a
+    workgroup past its last tile finds none however far it goes on."""
+    out = _run(tmp_path, """int main() {
+      std::mt19937 r(1);
+      auto same = [](int v) { return v; };
+      long cases = 0;
+      for (int n = 0; n < 6000; ++n) {
+        const int few[] = {0, 1, 2, 3, 7, 8, 9, 16, 17, 33, 64, 65, 130, 1024}, grids[] = {8, 16, 64, 128, 256};
+        const int items = few[r() % 14], slow = 1 + r() % (items > 100 ? 4 : 20), fast = 1 + r() % (items > 100 ? 3 : 12), tiles = slow * fast, grid = grids[r() % 5];
+        const WgradWalk w = wgrad_walk(items, slow, tiles, grid, same);
+        if (slow % w.g || w.per_u * w.g != tiles || w.total % kXcds) { printf("walk %d %d %d\\n", items, slow, fast); return 1; }
+        std::vector<char> seen(static_cast<size_t>(items) * tiles, 0);
+        size_t taken = 0;
+        for (int b = 0; b < grid; ++b) {
+          int block = b, past = 0;
+          for (; past < 4; block += grid) {
+            const WgradTile t = wgrad_tile(w, block, same);
+            if (!t.exists) { ++past; continue; }
+            // a workgroup ends at the first position without a tile, so no tile may follow one
+            if (past || t.item < 0 || t.item >= items || t.tile < 0 || t.tile >= tiles || seen[static_cast<size_t>(t.item) * tiles + t.tile]++) {
+              printf("items %d slow %d fast %d grid %d block %d\\n", items, slow, fast, grid, block);
+              return 1;
+            }
+            ++taken;
+          }
+        }
+        if (taken != seen.size()) { printf("missing: items %d slow %d fast %d grid %d\\n", items, slow, fast, grid); return 1; }
+        ++cases;
+      }
+      printf("%ld\\n", cases);
+      return 0;
+    }""")
+    assert out.strip() == "6000"
+
+
+def test_every_tile_of_the_row_products_is_taken_once(tmp_path):
+    """The same for the row products, whose consecutive tiles share an XCD."""
+    _run(tmp_path, """int main() {
+      for (int total = 0; total < 1200; ++total)
+        for (int grid : {8, 64, 256, 512}) {
+          std::vector<int> seen(total, 0);
+          for (int b = 0; b < grid; ++b) {
+            bool past = false;
+            for (int block = b; block < total + 4 * grid; block += grid) {
+              const int v = xcd_remap(block, total);
+              if (v < 0) { past = true; continue; }
+              if (past || v >= total || seen[v]++) { printf("total %d grid %d block %d\\n", total, grid, block); return 1; }
+            }
+          }
+          if (std::count(seen.begin(), seen.end(), 1) != total) { printf("missing: total %d grid %d\\n", total, grid); return 1; }
+        }
+      return 0;
+    }""")
