@@ -198,7 +198,7 @@ int32_t moe_grouped_gemm_swiglu_fwd(const void* xp, const void* w_gate, const vo
  * The backward workspace holds [dG | dU] (2 P f elements), the recomputed G and U when nothing was
  * saved, the device-built schedules, and room for fp32 partial weight-gradient tiles of experts
  * whose rows are cut into several reduction chunks under skewed routing: at most 2 ceil(P / C)
- * slots of 2 f d floats with C = max(2048, ceil(P / 32) rounded up to 256) rows (64 slots at most;
+ * slots of 3 f d floats with C = max(2048, ceil(P / 32) rounded up to 256) rows (64 slots at most;
  * with balanced routing none is touched).
  */
 size_t moe_grouped_gemm_swiglu_bwd_workspace_bytes(int dtype, int P, int d, int f, int E, int have_saved);

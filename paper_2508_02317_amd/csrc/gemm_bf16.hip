@@ -10,8 +10,8 @@
 //     one being multiplied, every MFMA operand is read from LDS most of a reduction step before its use,
 //     and one barrier per slab separates writers from readers; what does not exist (rows, columns, the end
 //     of a partial last slab) is out of the loads' range and reads as zero;
-//   * a workgroup stays on its CU and takes tile after tile; the rings never drain: the first two slabs of the
-//     next tile are enqueued behind the last of this one and land while the epilogue runs;
+//   * a workgroup stays on its CU and takes tile after tile: the first two slabs of the next tile are enqueued
+//     behind the last of this one and land while the epilogue runs;
 //   * results leave through LDS as well -- 16 rows of a wave at a time, in the one ring buffer that is free
 //     between two tiles -- so that all global stores (and the loads of the saved pre-activations in the fused
 //     SwiGLU derivative) are 16 bytes per lane and contiguous along rows;
@@ -214,9 +214,10 @@ template <bool KS, int ROWS, int BK, int WAVES, bool GATHER = false, bool TWO_SE
   long seg_delta;            // ... whose bytes lie this much further
   int valid;                 // k-contiguous: rows of this wave's half of the tile that exist
   __amdgpu_buffer_rsrc_t rsrc;   // the slab being enqueued
-  // The row list of a gathered operand is read with scalar loads: they do not touch the vector-memory counter that orders
-  // the ring.  k-strided: the memory rows of the wave's NR reduction rows of the next slab to be issued, fetched one slab
-  // ahead.  k-contiguous: the memory rows of the wave's tile rows, once per tile.
+  // The row list of a gathered operand.  k-strided: the memory rows of the wave's NR reduction rows of the next slab to be issued,
+  // fetched one slab ahead with scalar loads, which do not touch the vector-memory counter that orders the ring.  k-contiguous: the
+  // memory rows of the wave's tile rows, once per tile; every lane wants its own, so these are vector loads, and the wait for
+  // them is one for everything in flight (as scalar loads, eight rows at a time: gate/up 394 -> 399 us).
   typedef __attribute__((address_space(4))) const int32_t* RowList;
   typedef int32_t RowVec __attribute__((ext_vector_type(KS && GATHER ? NR : 1)));   // a value, not an array: stays in scalar registers
   RowList rows;              // wave-uniform: gather + grow + wave * NR
@@ -398,10 +399,14 @@ __device__ __forceinline__ void zero_acc(Acc<T>& acc) {
 // LDS reads of a wave complete in order, so "fragment X has arrived" is a wait for all but the reads issued after it;
 // loads complete in the order they were enqueued, so "slab kt+1 has landed" is a wait for all but the loads enqueued
 // after it -- immediates, both.
-// The rings do not drain between the tiles of a workgroup: behind the last slabs of a tile come the first of its next
-// one, or empty slabs if there is none.  With one tile per workgroup 5.4-6.8 k clocks passed from a workgroup's entry to its first
-// slab, and 3.4 us from the last store of a workgroup to the entry of the next: at T = 8192, E = 128, k = 8, d = 2048, f = 768 the
-// six products took 2111 us and take 1851.
+// Behind the last slabs of a tile come the first of the workgroup's next one, or empty slabs if there is none.  With one tile per
+// workgroup 5.4-6.8 k clocks passed from a workgroup's entry to its first slab, and 3.4 us from the last store of a workgroup to the
+// entry of the next.  Down, dX and the weight gradients keep slabs in flight from tile to tile.  Loads into registers are
+// awaited with everything older, so where a product reads data of its rows the rings drain for a moment: for the gathered row list two slabs
+// before a tile's end, for gate/up's combine weights at a tile's first slab and in its epilogue, for dA's G and U in the epilogue.
+// At T = 8192, E = 128, k = 8, d = 2048, f = 768, one tile per workgroup -> several, timed in turn: weight gradients 747 -> 671 us, down 242 ->
+// 229, gate/up 433 -> 434, dA 263 -> 268, dX 407 -> 421, the six products 2091 -> 2022.  (dA's epilogue takes 16 rows at a time in one
+// buffer where it had 32 in the whole LDS; the row products' reads from memory grew, dX's by 11 %.)
 // The loop is a plain loop over one slab body with run-time ring positions, a single path: with a body chosen per slab
 // the compiler keeps fragments and accumulators in scratch memory.  The address registers of the fragments are
 // advanced once per slab (4 to 12 vector additions against 64 MFMAs).
@@ -1343,8 +1348,8 @@ __device__ __forceinline__ void build_wgrad_items(const int32_t* __restrict__ of
   }
 }
 
-// entries of padding behind the list of row tokens: its scalar loads run up to SA + 1 = SB = 3 slabs past the last whole slab, that
-// is 63 + 2 * 64 + 64 entries past the last row, and never leave it
+// entries of padding behind the list of row tokens: a tile of 256 rows begins at most at the last row, and the weight gradients'
+// scalar loads run one slab ahead and over at least two slabs, up to 3 * 64 entries past a chunk's first row or 2 * 64 past its last
 constexpr int kRowTokenPad = 256;
 
 // Everything a pass needs before its first product, in one launch: block 0 builds the (expert, row tile)
@@ -1706,7 +1711,9 @@ static WsLayout ws_layout(int P, int d, int f, int E, bool need_dgu, bool need_g
     const size_t sp = align_up(static_cast<size_t>(wgrad_max_split(P, E)) * sizeof(int32_t), 256);
     off += 256 + 4 * it + 3 * sp;
     w.partial = off;
-    off += align_up(static_cast<size_t>(wgrad_max_slots(P)) * 3 * f * d * sizeof(float), 256);   // dW_down's, then [dW_gate; dW_up]'s
+    // dW_down's, then [dW_gate; dW_up]'s: one reduction launch for both, 5 us less of each step, for a third of this memory (64 slots,
+    // d = 2048, f = 768: 1208 MB, with two launches 805)
+    off += align_up(static_cast<size_t>(wgrad_max_slots(P)) * 3 * f * d * sizeof(float), 256);
   }
   w.total = off + 256;
   return w;

@@ -151,8 +151,8 @@ __global__ __launch_bounds__(kRouteThreads) void route_topk_kernel(
 // lane first sorts its own keys (19 exchanges at V = 8), and a round compares only the lanes' first ones, four steps inside the
 // row, and moves up the winner's: about 80 instructions per token and 8 rounds instead of 240.  The weights come out of the same
 // sums in the same order.
-// The whole call, one token per wave -> per row of lanes: E = 128, k = 8: T = 16 5.0 -> 3.4 us, T = 2047 10.6 -> 6.9 us, T = 8192
-// 12.7 -> 8.7 us, T = 16384 about 16 -> 8 us; E = 8, k = 2: T = 256 6.2 -> 4.5 us.
+// The whole call in a graph, one token per wave and always two launches -> as it is: E = 128, k = 8: T = 16 7.3 -> 3.2 us, T = 64
+// 10.4 -> 5.1, T = 2047 11.2 -> 6.7, T = 8192 13.0 -> 8.4, T = 16384 19.6 -> 11.9, T = 40960 36.9 -> 20.6; E = 8, k = 2: T = 256 6.8 -> 4.4.
 constexpr int kRowLanes = 16, kRowTokensPerWave = 64 / kRowLanes;
 template <int N> __device__ __forceinline__ uint32_t row_ror(uint32_t v) {                 // lane l of a row gets lane (l + N) % 16's or (l - N) % 16's
   return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x120 + N, 0xF, 0xF, true));
