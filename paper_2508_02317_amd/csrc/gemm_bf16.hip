@@ -862,17 +862,28 @@ struct StripRows {
 };
 
 // ---- device-built schedule of (expert, row tile) for row-grouped products -----------------
+// An expert of up to kGroup row tiles has its tiles in the order that keeps those of the same columns together: they share a weight
+// panel, which comes from memory, and a stretch of the list that runs at one time ends between two panels, not between two row
+// tiles that share them all.  Beyond, an expert's row panels are as many as an XCD's workgroups take at once, and the columns of a row
+// tile come first.  Read from memory at T = 8192, E = 128, k = 8, d = 2048, f = 768 (512 rows per expert), columns first -> as it
+// is: gate/up 2040 -> 1840 MB, down 718 -> 564, 8-bit gate/up 1034 -> 861 (a product's time is hardly bound by them: down 225 -> 220 us,
+// 8-bit down 144 -> 140, dA 264 -> 261, the others equal).
+constexpr int kGroup = 4;
+struct TileEntry {                                     // of a row tile: one aligned scalar load finds everything
+  int32_t expert, first, n;                            // its group: the list's row tiles first .. first + n - 1
+  int32_t row0, row_end;                               // first row of the group; one past the expert's last
+  int32_t unused[3];
+};
 struct RowTiles {
   int32_t* count;        // [1] number of row tiles
-  int32_t* expert;       // [max_tiles]
-  int32_t* row0;         // [max_tiles]
+  TileEntry* entry;      // [max_tiles]
   int max_tiles;
   int bm;                // rows of a tile: which of the tile shapes the list is for
 };
 
 __device__ __forceinline__ void build_row_tiles(const int32_t* __restrict__ offsets, int E, int P, int bm, RowTiles rt) {
   __shared__ int32_t scan[kMaxExperts];     // inclusive scan of the row tiles per expert
-  __shared__ int32_t first_row[kMaxExperts];
+  __shared__ int32_t first_row[kMaxExperts], end_row[kMaxExperts];
   const int e = threadIdx.x;
   int begin = 0, end = 0, nt = 0;
   if (e < E) {
@@ -882,6 +893,7 @@ __device__ __forceinline__ void build_row_tiles(const int32_t* __restrict__ offs
   }
   scan[e] = nt;
   first_row[e] = begin;
+  end_row[e] = end;
   __syncthreads();
   for (int o = 1; o < 1024; o <<= 1) {
     int v = e >= o ? scan[e - o] : 0;
@@ -898,9 +910,11 @@ __device__ __forceinline__ void build_row_tiles(const int32_t* __restrict__ offs
       const int mid = (lo + hi) >> 1;
       if (scan[mid] > t) hi = mid; else lo = mid + 1;
     }
-    const int before = lo > 0 ? scan[lo - 1] : 0;
-    rt.expert[t] = lo;
-    rt.row0[t] = first_row[lo] + (t - before) * bm;
+    const int before = lo > 0 ? scan[lo - 1] : 0, tiles = min(scan[lo], total) - before;
+    const bool grouped = tiles <= kGroup;
+    int4* const out = reinterpret_cast<int4*>(rt.entry + t);
+    out[0] = int4{lo, grouped ? before : t, grouped ? tiles : 1, first_row[lo] + (grouped ? 0 : t - before) * bm};
+    out[1] = int4{end_row[lo], 0, 0, 0};
   }
   if (e == 1023) rt.count[0] = total;
 }
@@ -912,6 +926,17 @@ __global__ __launch_bounds__(1024) void build_row_tiles_kernel(const int32_t* __
 // Lists that a launch only reads, as constant memory: uniform loads from them are scalar whatever the kernel has stored before.
 typedef __attribute__((address_space(4))) const int32_t* ConstList;
 __device__ __forceinline__ ConstList const_list(const int32_t* p) { return reinterpret_cast<ConstList>(reinterpret_cast<uintptr_t>(p)); }
+
+// Tile v of a row-grouped product with n_tiles_n column tiles: its expert, rows and column tile n.
+struct TileAt { int e, row0, rows, n; };
+__device__ __forceinline__ TileAt tile_at(const RowTiles& rt, int v, int n_tiles_n, int bm) {
+  typedef int32_t Words __attribute__((ext_vector_type(8)));
+  static_assert(sizeof(TileEntry) == sizeof(Words), "");
+  const int mt = scalar(v / n_tiles_n);
+  const Words w = *reinterpret_cast<__attribute__((address_space(4))) const Words*>(reinterpret_cast<uintptr_t>(rt.entry + mt));
+  const int l = v - w[1] * n_tiles_n, n = scalar(l / w[2]), row0 = w[3] + (l - n * w[2]) * bm;
+  return TileAt{w[0], row0, scalar(min(bm, w[4] - row0)), n};
+}
 
 // ============================================================================================
 // Row-grouped kernels
@@ -928,7 +953,6 @@ struct RowArgs {
   long ldw;                // row pitch of one expert's weight matrix
   int K;                   // reduction length per segment
   int N;                   // output columns
-  const int32_t* offsets;
   int P;
   RowTiles rt;
   int n_tiles_n;
@@ -982,12 +1006,16 @@ __global__ __launch_bounds__(T::kThreads) __attribute__((amdgpu_waves_per_eu(T::
     const int v = xcd_remap(block, total);
     t.exists = scalar(v >= 0 ? 1 : 0);
     if (v >= 0) {
-      const int mt = scalar(v / p.n_tiles_n);
-      t.n0 = (v - mt * p.n_tiles_n) * OUT_N;
-      t.e = ONE_SEGMENT ? 0 : const_list(p.rt.expert)[mt];
-      t.row0 = ONE_SEGMENT ? mt * BM : const_list(p.rt.row0)[mt];
-      const int row_end = ONE_SEGMENT ? p.P : min(const_list(p.offsets)[t.e + 1], p.P);
-      t.rows = scalar(min(BM, row_end - t.row0));
+      if constexpr (ONE_SEGMENT) {
+        const int mt = scalar(v / p.n_tiles_n);
+        t.n0 = (v - mt * p.n_tiles_n) * OUT_N;
+        t.row0 = mt * BM;
+        t.rows = scalar(min(BM, p.P - t.row0));
+      } else {
+        const TileAt at = tile_at(p.rt, v, p.n_tiles_n, BM);
+        t.e = at.e; t.row0 = at.row0; t.rows = at.rows;
+        t.n0 = at.n * OUT_N;
+      }
     }
     return t;
   };
@@ -1692,15 +1720,13 @@ static int wgrad_max_slots(int P) { return 2 * ceil_div(P, wgrad_chunk_rows(P));
 static int router_chunk_rows(int T) { return std::max(256, static_cast<int>(align_up(static_cast<size_t>(ceil_div(T, 64)), 256))); }
 
 struct WsLayout {
-  size_t tiles_count, tiles_expert, tiles_row0, dgu, g, u, items, partial, total;
+  size_t tiles_count, tiles_entry, dgu, g, u, items, partial, total;
 };
 static WsLayout ws_layout(int P, int d, int f, int E, bool need_dgu, bool need_gu) {
   WsLayout w{};
   size_t off = 0;
   w.tiles_count = off; off += 256;
-  const size_t t = align_up(static_cast<size_t>(max_row_tiles(P, E)) * sizeof(int32_t), 256);
-  w.tiles_expert = off; off += t;
-  w.tiles_row0 = off; off += t;
+  w.tiles_entry = off; off += align_up(static_cast<size_t>(max_row_tiles(P, E)) * sizeof(TileEntry), 256);
   const size_t pf = align_up(static_cast<size_t>(P) * f * 2, 256);
   w.dgu = off; if (need_dgu) off += 2 * pf;
   w.g = off; if (need_gu) off += pf;
@@ -1730,8 +1756,7 @@ static RowTiles row_tiles_at(void* ws, const WsLayout& w, int P, int E, int bm) 
   rt.max_tiles = max_row_tiles(P, E);
   rt.bm = bm;
   rt.count = reinterpret_cast<int32_t*>(b + w.tiles_count);
-  rt.expert = reinterpret_cast<int32_t*>(b + w.tiles_expert);
-  rt.row0 = reinterpret_cast<int32_t*>(b + w.tiles_row0);
+  rt.entry = reinterpret_cast<TileEntry*>(b + w.tiles_entry);
   return rt;
 }
 
@@ -1829,7 +1854,7 @@ static void launch_wgrad_reduce(const char* name, const WgradArgs& a, const Wgra
 
 // row_token == null: xp is in expert order; else xp is the token-major input and rows are gathered from it
 static void launch_gate_up(const void* xp, const void* wg, const void* wu, int P, int d, int f, int E,
-                           const int32_t* offsets, const RowTiles& rt, void* G, void* U, void* act, hipStream_t s,
+                           const RowTiles& rt, void* G, void* U, void* act, hipStream_t s,
                            const int32_t* row_token = nullptr, const float* row_w = nullptr) {
   RowArgs p{};
   p.row_token = row_token;
@@ -1837,7 +1862,7 @@ static void launch_gate_up(const void* xp, const void* wg, const void* wu, int P
   p.a = static_cast<const bf16_t*>(xp); p.lda = d;
   p.w0 = static_cast<const bf16_t*>(wg); p.w1 = static_cast<const bf16_t*>(wu);
   p.w_expert_stride = static_cast<long>(f) * d; p.ldw = d;
-  p.K = d; p.N = f; p.offsets = offsets; p.P = P; p.rt = rt;
+  p.K = d; p.N = f; p.P = P; p.rt = rt;
   p.out0 = static_cast<bf16_t*>(G); p.out1 = static_cast<bf16_t*>(U); p.out2 = static_cast<bf16_t*>(act); p.ldo = f;
   // A wave's G, U and activation fill half a line per row.  Written around the L2 (non-temporal), both halves go to memory on
   // their own; written through it, another wave's half joins them, but they displace weights and are still being written back
@@ -1856,23 +1881,23 @@ static void launch_gate_up(const void* xp, const void* wg, const void* wu, int P
   }
 }
 
-static void launch_down(const void* act, const void* wd, int P, int d, int f, int E, const int32_t* offsets,
+static void launch_down(const void* act, const void* wd, int P, int d, int f, int E,
                         const RowTiles& rt, void* yp, hipStream_t s) {
   RowArgs p{};
   p.a = static_cast<const bf16_t*>(act); p.lda = f;
   p.w0 = static_cast<const bf16_t*>(wd); p.w_expert_stride = static_cast<long>(d) * f; p.ldw = f;
-  p.K = f; p.N = d; p.offsets = offsets; p.P = P; p.rt = rt;
+  p.K = f; p.N = d; p.P = P; p.rt = rt;
   p.out0 = static_cast<bf16_t*>(yp); p.ldo = d;
   launch_row<kDown>(p, P, E, s);
 }
 
-static void launch_dx(const bf16_t* dgu, const void* wg, const void* wu, int P, int d, int f, int E, const int32_t* offsets,
+static void launch_dx(const bf16_t* dgu, const void* wg, const void* wu, int P, int d, int f, int E,
                       const RowTiles& rt, void* dxp, hipStream_t s) {
   RowArgs p{};
   p.a = dgu; p.lda = 2L * f;
   p.w0 = static_cast<const bf16_t*>(wg); p.w1 = static_cast<const bf16_t*>(wu);
   p.w_expert_stride = static_cast<long>(f) * d; p.ldw = d;
-  p.K = f; p.N = d; p.offsets = offsets; p.P = P; p.rt = rt;
+  p.K = f; p.N = d; p.P = P; p.rt = rt;
   p.out0 = static_cast<bf16_t*>(dxp); p.ldo = d;
   launch_row<kDX>(p, P, E, s);
 }
@@ -1881,8 +1906,8 @@ void ffn_fwd_bf16(const FfnFwdArgs& a) {
   const WsLayout w = ws_layout(a.P, a.d, a.f, a.E, false, false);
   const RowTiles rt = row_tiles_at(a.ws, w, a.P, a.E, row_bm(a.P, a.E, a.d, false));
   MOE_LAUNCH("build_row_tiles", build_row_tiles_kernel, dim3(1), dim3(1024), 0, a.stream, a.offsets, a.E, a.P, rt.bm, rt);
-  launch_gate_up(a.xp, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, a.offsets, rt, a.g_save, a.u_save, a.act, a.stream);
-  launch_down(a.act, a.w_down, a.P, a.d, a.f, a.E, a.offsets, rt, a.yp, a.stream);
+  launch_gate_up(a.xp, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, rt, a.g_save, a.u_save, a.act, a.stream);
+  launch_down(a.act, a.w_down, a.P, a.d, a.f, a.E, rt, a.yp, a.stream);
 }
 
 void ffn_bwd_bf16(const FfnBwdArgs& a) {
@@ -1903,18 +1928,18 @@ void ffn_bwd_bf16(const FfnBwdArgs& a) {
   if (recompute) {
     bf16_t* Gr = reinterpret_cast<bf16_t*>(base + w.g);
     bf16_t* Ur = reinterpret_cast<bf16_t*>(base + w.u);
-    launch_gate_up(a.xp, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, a.offsets, rt, Gr, Ur, nullptr, a.stream);
+    launch_gate_up(a.xp, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, rt, Gr, Ur, nullptr, a.stream);
     G = Gr; U = Ur;
   }
   {  // dA = dyp Wd, fused with the SwiGLU derivative -> [dG | dU]
     RowArgs p{};
     p.a = static_cast<const bf16_t*>(a.dyp); p.lda = a.d;
     p.w0 = static_cast<const bf16_t*>(a.w_down); p.w_expert_stride = static_cast<long>(a.d) * a.f; p.ldw = a.f;
-    p.K = a.d; p.N = a.f; p.offsets = a.offsets; p.P = a.P; p.rt = rt;
+    p.K = a.d; p.N = a.f; p.P = a.P; p.rt = rt;
     p.out0 = dgu; p.ldo = 2L * a.f; p.g = G; p.u = U;
     launch_row<kDAct>(p, a.P, a.E, a.stream);
   }
-  launch_dx(dgu, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, a.offsets, rt, a.dxp, a.stream);   // dxp = dG Wg + dU Wu
+  launch_dx(dgu, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, rt, a.dxp, a.stream);   // dxp = dG Wg + dU Wu
   float* partial = reinterpret_cast<float*>(base + w.partial);
   WgradArgs down{}, gate_up{};
   {  // dWd[e] = dyp^T act
@@ -1986,9 +2011,9 @@ void ffn_fwd_gather_bf16(const FfnFwdGatherArgs& a) {
     if (a.topk_w) { sa.topk_w = a.topk_w; sa.row_w = row_w; }
     launch_schedules(sa, a.stream);
   }
-  launch_gate_up(a.x, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, a.offsets, rt, a.g_save, a.u_save, a.act, a.stream, row_token,
+  launch_gate_up(a.x, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, rt, a.g_save, a.u_save, a.act, a.stream, row_token,
                  a.topk_w ? row_w : nullptr);
-  launch_down(a.act, a.w_down, a.P, a.d, a.f, a.E, a.offsets, rt, a.yp, a.stream);
+  launch_down(a.act, a.w_down, a.P, a.d, a.f, a.E, rt, a.yp, a.stream);
 }
 
 void ffn_bwd_gather_bf16(const FfnBwdGatherArgs& a) {
@@ -2016,20 +2041,20 @@ void ffn_bwd_gather_bf16(const FfnBwdGatherArgs& a) {
   if (recompute) {
     bf16_t* Gr = reinterpret_cast<bf16_t*>(base + w.g);
     bf16_t* Ur = reinterpret_cast<bf16_t*>(base + w.u);
-    launch_gate_up(a.x, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, a.offsets, rt, Gr, Ur, nullptr, a.stream, row_token);
+    launch_gate_up(a.x, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, rt, Gr, Ur, nullptr, a.stream, row_token);
     G = Gr; U = Ur;
   }
   {  // dA = w (dy[token] Wd) with the SwiGLU derivative, the weight gradient's dot products and w * act
     RowArgs p{};
     p.a = static_cast<const bf16_t*>(a.dy); p.lda = a.d;
     p.w0 = static_cast<const bf16_t*>(a.w_down); p.w_expert_stride = static_cast<long>(a.d) * a.f; p.ldw = a.f;
-    p.K = a.d; p.N = a.f; p.offsets = a.offsets; p.P = a.P; p.rt = rt;
+    p.K = a.d; p.N = a.f; p.P = a.P; p.rt = rt;
     p.out0 = dgu; p.ldo = 2L * a.f; p.g = G; p.u = U;
     p.row_token = row_token; p.row_w = row_w; p.act_w = a.act_w ? nullptr : act_w_ws; p.dw_partial = dw_partial;
     if (p.act_w) launch_row<kDAct, true, true>(p, a.P, a.E, a.stream);
     else launch_row<kDAct, true, false>(p, a.P, a.E, a.stream);
   }
-  launch_dx(dgu, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, a.offsets, rt, a.dxp, a.stream);
+  launch_dx(dgu, a.w_gate, a.w_up, a.P, a.d, a.f, a.E, rt, a.dxp, a.stream);
   float* partial = reinterpret_cast<float*>(base + w.partial);
   WgradArgs down{}, gate_up{};
   {  // dWd[e] = dy[token]^T (w act)
