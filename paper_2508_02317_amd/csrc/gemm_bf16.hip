@@ -871,7 +871,7 @@ struct StripRows {
 // is: gate/up 2040 -> 1840 MB, down 718 -> 564, 8-bit gate/up 1034 -> 861 (a product's time is hardly bound by them: down 225 -> 220 us,
 // 8-bit down 144 -> 140, dA 264 -> 261, the others equal).
 constexpr int kGroup = 4;
-struct TileEntry {                                     // of a row tile: one aligned scalar load finds everything
+struct TileEntry {                                     // of a row tile: one scalar load finds everything
   int32_t expert, first, n;                            // its group: the list's row tiles first .. first + n - 1
   int32_t row0, row_end;                               // first row of the group; one past the expert's last
   int32_t unused[3];
@@ -932,7 +932,7 @@ __device__ __forceinline__ ConstList const_list(const int32_t* p) { return reint
 // Tile v of a row-grouped product with n_tiles_n column tiles: its expert, rows and column tile n.
 struct TileAt { int e, row0, rows, n; };
 __device__ __forceinline__ TileAt tile_at(const RowTiles& rt, int v, int n_tiles_n, int bm) {
-  typedef int32_t Words __attribute__((ext_vector_type(8)));
+  typedef int32_t Words __attribute__((ext_vector_type(8), aligned(16)));   // (a workspace starts at a multiple of 16 bytes, not of 32)
   static_assert(sizeof(TileEntry) == sizeof(Words), "");
   const int mt = scalar(v / n_tiles_n);
   const Words w = *reinterpret_cast<__attribute__((address_space(4))) const Words*>(reinterpret_cast<uintptr_t>(rt.entry + mt));
