@@ -117,7 +117,7 @@ def _load():
 
 
 lib = _load()
-_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)     # a shortcut: not public, absent from a torch without devices
 
 
 def moe_version():
@@ -163,8 +163,10 @@ def _need(t, dtype=None, name="tensor"):
 
 
 def _stream():
-    """The current stream of the current device (torch.cuda.current_stream() would make an object of it, 1 us)."""
-    return _raw_stream(_current_device())
+    """The current stream of the current device (torch.cuda.current_stream() makes an object of it, 1 us)."""
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ws(query, args, ws, device):

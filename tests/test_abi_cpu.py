@@ -137,3 +137,17 @@ def test_binding_refuses_to_load_without_library(L, monkeypatch, tmp_path):
     mod = importlib.util.module_from_spec(spec)
     with pytest.raises(ImportError):
         spec.loader.exec_module(mod)      # no .so next to the copy -> loud failure, no fallback
+
+
+def test_binding_needs_no_private_name_of_torch():
+    """The binding loads, and its host functions and the stream handle work, with a torch that lacks the shortcut to the raw stream."""
+    import subprocess
+    import sys
+    code = ("import torch\n"
+            "del torch._C._cuda_getCurrentRawStream\n"
+            "from paper_2508_02317_amd import libmoe as L\n"
+            "assert L.moe_version() and L.lib.moe_route_topk_workspace_bytes(8, 8, 2) > 0\n"
+            "torch.cuda.current_stream = lambda: type('Stream', (), {'cuda_stream': 77})\n"
+            "assert L._stream() == 77\n")
+    res = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr[-2000:]
