@@ -864,18 +864,6 @@ struct StripRows {
 };
 
 // ---- device-built schedule of (expert, row tile) for row-grouped products -----------------
-// An expert of up to kGroup row tiles has its tiles in the order that keeps those of the same columns together: they share a weight
-// panel, which comes from memory, and a stretch of the list that runs at one time ends between two panels, not between two row
-// tiles that share them all.  Beyond, an expert's row panels are as many as an XCD's workgroups take at once, and the columns of a row
-// tile come first.  Read from memory at T = 8192, E = 128, k = 8, d = 2048, f = 768 (512 rows per expert), columns first -> as it
-// is: gate/up 2040 -> 1840 MB, down 718 -> 564, 8-bit gate/up 1034 -> 861 (a product's time is hardly bound by them: down 225 -> 220 us,
-// 8-bit down 144 -> 140, dA 264 -> 261, the others equal).
-constexpr int kGroup = 4;
-struct TileEntry {                                     // of a row tile: one scalar load finds everything
-  int32_t expert, first, n;                            // its group: the list's row tiles first .. first + n - 1
-  int32_t row0, row_end;                               // first row of the group; one past the expert's last
-  int32_t unused[3];
-};
 struct RowTiles {
   int32_t* count;        // [1] number of row tiles
   TileEntry* entry;      // [max_tiles]
@@ -905,18 +893,13 @@ __device__ __forceinline__ void build_row_tiles(const int32_t* __restrict__ offs
   }
   // offsets that are not a monotone scan ending at P cannot overflow the lists
   const int total = min(scan[1023], rt.max_tiles);
-  // every thread writes the tiles t, t + 1024, ...: the expert of tile t is the first whose inclusive scan exceeds t
+  // every thread writes the tiles t, t + 1024, ...
   for (int t = threadIdx.x; t < total; t += 1024) {
-    int lo = 0, hi = E - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (scan[mid] > t) hi = mid; else lo = mid + 1;
-    }
-    const int before = lo > 0 ? scan[lo - 1] : 0, tiles = min(scan[lo], total) - before;
-    const bool grouped = tiles <= kGroup;
+    const int x = expert_of_row_tile(scan, E, t);
+    const TileEntry w = row_tile_entry(scan, x, t, total, first_row[x], end_row[x], bm);
     int4* const out = reinterpret_cast<int4*>(rt.entry + t);
-    out[0] = int4{lo, grouped ? before : t, grouped ? tiles : 1, first_row[lo] + (grouped ? 0 : t - before) * bm};
-    out[1] = int4{end_row[lo], 0, 0, 0};
+    out[0] = int4{w.expert, w.first, w.n, w.row0};
+    out[1] = int4{w.row_end, 0, 0, 0};
   }
   if (e == 1023) rt.count[0] = total;
 }
@@ -930,14 +913,12 @@ typedef __attribute__((address_space(4))) const int32_t* ConstList;
 __device__ __forceinline__ ConstList const_list(const int32_t* p) { return reinterpret_cast<ConstList>(reinterpret_cast<uintptr_t>(p)); }
 
 // Tile v of a row-grouped product with n_tiles_n column tiles: its expert, rows and column tile n.
-struct TileAt { int e, row0, rows, n; };
 __device__ __forceinline__ TileAt tile_at(const RowTiles& rt, int v, int n_tiles_n, int bm) {
   typedef int32_t Words __attribute__((ext_vector_type(8), aligned(16)));   // (a workspace starts at a multiple of 16 bytes, not of 32)
   static_assert(sizeof(TileEntry) == sizeof(Words), "");
   const int mt = scalar(v / n_tiles_n);
   const Words w = *reinterpret_cast<__attribute__((address_space(4))) const Words*>(reinterpret_cast<uintptr_t>(rt.entry + mt));
-  const int l = v - w[1] * n_tiles_n, n = scalar(l / w[2]), row0 = w[3] + (l - n * w[2]) * bm;
-  return TileAt{w[0], row0, scalar(min(bm, w[4] - row0)), n};
+  return tile_of_entry(TileEntry{w[0], w[1], w[2], w[3], w[4], {}}, v, n_tiles_n, bm, [](int x) { return scalar(x); });
 }
 
 // ============================================================================================

@@ -18,6 +18,42 @@ constexpr int xcd_remap(int b, int total) {
   return (b / kXcds < per && v < total) ? v : -1;
 }
 
+// The row-grouped products' list of row tiles: the experts in order, the rows of each cut into tiles of bm rows (`scan`: inclusive scan of
+// the experts' numbers of tiles).  Virtual tile v of a product with n_tiles_n column tiles is found through entry v / n_tiles_n.
+//
+// An expert of up to kGroup row tiles has its tiles in the order that keeps those of the same columns together: they share a weight
+// panel, which comes from memory, and a stretch of the list that runs at one time ends between two panels, not between two row
+// tiles that share them all.  Beyond, an expert's row panels are as many as an XCD's workgroups take at once, and the columns of a row
+// tile come first.  Read from memory at T = 8192, E = 128, k = 8, d = 2048, f = 768 (512 rows per expert), columns first -> as it
+// is: gate/up 2040 -> 1840 MB, down 718 -> 564, 8-bit gate/up 1034 -> 861 (a product's time is hardly bound by them: down 225 -> 220 us,
+// 8-bit down 144 -> 140, dA 264 -> 261, the others equal).
+constexpr int kGroup = 4;
+struct TileEntry {                                     // of a row tile: one scalar load finds everything
+  int32_t expert, first, n;                            // its group: the list's row tiles first .. first + n - 1
+  int32_t row0, row_end;                               // first row of the group; one past the expert's last
+  int32_t unused[3];
+};
+// the expert of row tile t: the first whose inclusive scan exceeds t (the last one if none does)
+constexpr int expert_of_row_tile(const int32_t* scan, int E, int t) {
+  int lo = 0, hi = E - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (scan[mid] > t) hi = mid; else lo = mid + 1;
+  }
+  return lo;
+}
+// its entry in a list that is cut off at `total` row tiles
+constexpr TileEntry row_tile_entry(const int32_t* scan, int expert, int t, int total, int first_row, int row_end, int bm) {
+  const int before = expert > 0 ? scan[expert - 1] : 0, tiles = (scan[expert] < total ? scan[expert] : total) - before;
+  const bool grouped = tiles <= kGroup;
+  return TileEntry{expert, grouped ? before : t, grouped ? tiles : 1, first_row + (grouped ? 0 : t - before) * bm, row_end, {0, 0, 0}};
+}
+struct TileAt { int e, row0, rows, n; };               // expert, first row, rows, column tile
+template <class Scalar> constexpr TileAt tile_of_entry(const TileEntry& w, int v, int n_tiles_n, int bm, Scalar scalar) {
+  const int l = v - w.first * n_tiles_n, n = scalar(l / w.n), row0 = w.row0 + (l - n * w.n) * bm, left = w.row_end - row0;
+  return TileAt{w.expert, row0, scalar(bm < left ? bm : left), n};
+}
+
 // The weight gradients' tiles.  Work items come sorted by length, so consecutive stretches of the list differ in work: they are
 // dealt to the XCDs in turn, in units of 1/g of an item's tiles -- whole items while there are at least 8 per XCD, otherwise g runs
 // of the slow tile index, so that under skewed routing every XCD still gets several units of the few long items.  A unit's

@@ -88,3 +88,57 @@ def test_every_tile_of_the_row_products_is_taken_once(tmp_path):
         }
       return 0;
     }""")
+
+
+def test_every_row_tile_of_the_list_is_found_with_every_column_once(tmp_path):
+    """The list of row tiles and the tile at a position of it: over experts of any number of rows (none, one, a row to either side of
+    one to six tiles, thousands), both heights of a tile, any number of column tiles and lists that are cut off, every (row tile, column
+    tile) comes up exactly once with its expert and rows; experts of up to four row tiles have those of a column next to each
+    other, larger ones the columns of a row tile."""
+    out = _run(tmp_path, """int main() {
+      std::mt19937 r(2);
+      auto same = [](int v) { return v; };
+      long grouped = 0, single = 0;
+      for (int c = 0; c < 4000; ++c) {
+        const int E = 1 + r() % 24, bm = r() % 2 ? 128 : 256, cols = 1 + r() % 13;
+        std::vector<int> scan(E), first(E), end(E), expert, row0, rows;   // the list as it should be: expert and rows of every row tile
+        int at = 0, tiles = 0;
+        for (int e = 0; e < E; ++e) {
+          const int kind = r() % 8;
+          const int n = kind < 2 ? 0 : kind == 2 ? 1 : kind < 6 ? static_cast<int>(1 + r() % 6) * bm + static_cast<int>(r() % 3) - 1 : static_cast<int>(r() % 5000);
+          first[e] = at; at += n; end[e] = at;
+          for (int q = first[e]; q < end[e]; q += bm) { expert.push_back(e); row0.push_back(q); rows.push_back(std::min(bm, end[e] - q)); }
+          scan[e] = tiles += (n + bm - 1) / bm;
+        }
+        const int total = r() % 4 ? tiles : static_cast<int>(r() % (tiles + 1));
+        std::vector<TileEntry> list(total);
+        for (int t = 0; t < total; ++t) {
+          const int e = expert_of_row_tile(scan.data(), E, t);
+          if (e != expert[t]) { printf("case %d: tile %d is expert %d's, not %d's\\n", c, t, expert[t], e); return 1; }
+          list[t] = row_tile_entry(scan.data(), e, t, total, first[e], end[e], bm);
+        }
+        std::vector<int> seen(static_cast<size_t>(total) * cols, 0);
+        int last_t = -1, last_n = -1;
+        for (int v = 0; v < total * cols; ++v) {
+          const TileAt a = tile_of_entry(list[v / cols], v, cols, bm, same);
+          int t = 0;
+          while (t < total && row0[t] != a.row0) ++t;
+          if (t == total || a.e != expert[t] || a.rows != rows[t] || a.n < 0 || a.n >= cols || seen[static_cast<size_t>(t) * cols + a.n]++) {
+            printf("case %d: position %d gives expert %d, rows %d + %d, column %d\\n", c, v, a.e, a.row0, a.rows, a.n);
+            return 1;
+          }
+          const int before = a.e ? scan[a.e - 1] : 0, of_expert = std::min(scan[a.e], total) - before;
+          if (last_t >= 0 && expert[last_t] == a.e) {     // the next tile of the same expert
+            const bool together = of_expert <= 4;
+            const int in_row = last_t + 1 - before, next_t = together ? before + in_row % of_expert : last_t + (last_n + 1 == cols),
+                      next_n = together ? last_n + in_row / of_expert : (last_n + 1) % cols;
+            if (t != next_t || a.n != next_n) { printf("case %d: order at %d\\n", c, v); return 1; }
+            ++(together ? grouped : single);
+          }
+          last_t = t; last_n = a.n;
+        }
+        if (std::count(seen.begin(), seen.end(), 1) != static_cast<long>(seen.size())) { printf("case %d: missing\\n", c); return 1; }
+      }
+      return grouped > 100000 && single > 100000 ? 0 : 2;
+    }""")
+    assert out == ""
