@@ -117,7 +117,7 @@ def _load():
 
 
 lib = _load()
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)     # a shortcut: not public, absent from a torch without devices
+_raw_stream, _current_device = getattr(torch._C, "_cuda_getCurrentRawStream", None), torch.cuda.current_device
 
 
 def moe_version():
@@ -162,11 +162,13 @@ def _need(t, dtype=None, name="tensor"):
     return t
 
 
-def _stream():
-    """The current stream of the current device (torch.cuda.current_stream() makes an object of it, 1 us)."""
-    if _raw_stream is None:
+if _raw_stream is not None:
+    def _stream():
+        """The current stream of the current device (torch.cuda.current_stream() makes an object of it, 1 us)."""
+        return _raw_stream(_current_device())
+else:                                     # the shortcut is not public, and absent from a torch without devices
+    def _stream():
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(torch.cuda.current_device())
 
 
 def _ws(query, args, ws, device):
