@@ -383,8 +383,9 @@ __device__ __forceinline__ void zero_acc(Acc<T>& acc) {
 // What bounds the loop (stamps of a build with one tile per workgroup): a slab of the gate/up product at 2560 rows per expert takes 2.62 k clocks at 1.86 GHz = 1.41 us
 // (64 MFMAs per wave, two waves per SIMD: 2.05 k clocks).  The loads and barriers alone take 1.36 us (at 2.39 GHz), the
 // MFMAs and LDS reads alone 1.10 us (at 2.06 GHz): the row products run at the rate the slabs arrive, 64 KiB per CU, which is a
-// matter of latency (the same loads without barriers, 32 KiB per CU in flight: 0.5-0.65 us).  Four waves of 128 x 128 per tile, with two thirds
-// of the LDS reads, take the same time a slab and twice as long in the epilogues: 0.97 of the speed.  The
+// matter of latency (the same loads without barriers, 32 KiB per CU in flight: 0.5-0.65 us) and hardly of the clock, which falls with the load.
+// So what leaves the slabs' arrival as it is leaves the time as it is: four waves of 128 x 128 per tile, with two thirds of the LDS reads, take the
+// same time a slab (and twice as long in the epilogues: 0.97 of the speed), and a tenth less read from memory changes little (see kGroup).  The
 // weight gradients' loads alone take 1.12-1.21 us, their MFMAs and LDS reads 1.25 us, together 1.60 us at 1.70-1.76 GHz.
 //
 // Slabs stream through the two LDS rings (SA buffers for the A side, SB for the B side) filled by direct

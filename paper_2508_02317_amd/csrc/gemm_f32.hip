@@ -12,7 +12,8 @@
 //     so no schedule or row list is built by a launch of its own; the data gradient and the three weight gradients share one launch.
 // At 512 rows, d = 128, f = 256, 8 experts the former one-thread-per-output kernels with sequential sums took 130 (gate/up),
 // 39 (down), 18 (dA), 74 (dX) and 3 x 37 us (weight gradients), with two and three further launches per pass; these take
-// 8.5, 5.8, 6.4, 9.3 and 10 us (all three weight gradients), and the training step of 256 tokens 72 us instead of 396.
+// 8.5, 5.8, 6.4, 9.3 and 10 us (all three weight gradients), and the training step of 256 tokens 72 us instead of 396
+// (its kernels alone 45 us, replayed from a graph; the rest is the host's share of ten calls, which has come down since).
 #include "launch_plan.h"
 #include "moe_common.h"
 

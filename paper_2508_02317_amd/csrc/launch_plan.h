@@ -23,10 +23,14 @@ constexpr int xcd_remap(int b, int total) {
 //
 // An expert of up to kGroup row tiles has its tiles in the order that keeps those of the same columns together: they share a weight
 // panel, which comes from memory, and a stretch of the list that runs at one time ends between two panels, not between two row
-// tiles that share them all.  Beyond, an expert's row panels are as many as an XCD's workgroups take at once, and the columns of a row
-// tile come first.  Read from memory at T = 8192, E = 128, k = 8, d = 2048, f = 768 (512 rows per expert), columns first -> as it
-// is: gate/up 2040 -> 1840 MB, down 718 -> 564, 8-bit gate/up 1034 -> 861 (a product's time is hardly bound by them: down 225 -> 220 us,
-// 8-bit down 144 -> 140, dA 264 -> 261, the others equal).
+// tiles that share them all.  Beyond, the columns of a row tile come first.  Read from memory at T = 8192, E = 128, k = 8, d = 2048, f = 768
+// (512 rows per expert), columns first -> as it is: gate/up 2040 -> 1809 MB, down 718 -> 564, dX 1791 -> 1631, 8-bit gate/up 1034 -> 848.
+// The time hardly follows.  Both sides of the line, whole steps in turn (two runs of one build differ by up to 0.4 %, with E = 16 by 1.6 %):
+//   no groups -> 4:  E = 8, d = 4096, f = 3072, 900 rows per expert 1619 -> 1550 us; the layer above 2104 -> 2091, and at 900 to 1800 rows per
+//                    expert equal; E = 16, d = 1024, f = 2048, 512 to 1800 rows 0.993-1.005; 8-bit forward at 900 rows 0.996
+//   4 -> 8 and more: the layer above at 512 and 900 rows equal, at 1150, 1400 and 1800 (5 to 8 row tiles) 4142 -> 4090, 4954 -> 4913 and
+//                    6254 -> 6228; E = 16 at 1400 rows 971 -> 964, else as far apart as its runs; 8-bit equal
+// So the line is not too high; up to 8 row tiles it could be higher.
 constexpr int kGroup = 4;
 struct TileEntry {                                     // of a row tile: one scalar load finds everything
   int32_t expert, first, n;                            // its group: the list's row tiles first .. first + n - 1
